@@ -54,6 +54,20 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
                  const void *bias, const float *res, const void *aux, int32_t aux_wrap, float scale,
                  int32_t beta, int32_t tile, void *stream);
 
+/*
+ * Kernel-level test hook: the library's causal attention by itself.
+ * qkv: dtype [batch*seq, 3*heads*width] (Q | K | V, heads contiguous); o: dtype [batch*seq, heads*width]; lse: fp32
+ * [batch, heads, seq] (in the unit the backward of the same dtype and width wants).  The forward always runs;
+ * the backward follows if d_o (dtype [streams*batch*seq, heads*width]) is given, into dqkv (dtype
+ * [streams*batch*seq, 3*heads*width]).  dsum: fp32 [streams*batch*seq * max(heads, heads*width/32)], scratch -
+ * except where il_attention_wants_dsum() is 1: there the caller provides the row sums of d_o * o over 32 columns
+ * each, [heads*width/32][streams*batch*seq], as the GEMM that makes d_o leaves them (with o of an earlier call).
+ * IL_E_SHAPE: the widths and extents il_init refuses, or streams outside [1, 16].
+ */
+int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq, int32_t heads, int32_t width,
+                      void *o, float *lse, const void *d_o, int32_t streams, void *dqkv, float *dsum, void *stream);
+int il_attention_wants_dsum(int32_t dtype, int32_t width);
+
 /* ---- measured peaks of the board (reported beside the nominal 2.5 PFLOP/s and 8 TB/s) ------------- */
 
 /*

@@ -25,7 +25,7 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_routing_plan", "il_profile_read", "il_status_string", "il_test_gemm", "il_lr_schedule",
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
-           "il_head_xent_static")
+           "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum")
 
 
 class il_config(C.Structure):
@@ -67,6 +67,8 @@ def load():
                                     C.POINTER(C.c_double)]
     lib.il_test_gemm.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, i32, i32, i32, vp, vp, i32, vp, vp, vp,
                                  i32, C.c_float, i32, i32, vp]
+    lib.il_test_attention.argtypes = [i32, vp, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp]
+    lib.il_attention_wants_dsum.argtypes = [i32, i32]
     lib.il_lr_schedule.argtypes = [C.c_int64, i32, i32]
     lib.il_lr_schedule.restype = C.c_double
     lib.il_adam_step.argtypes = [i32, vp, vp, vp, vp, vp, C.c_size_t, C.c_int64, C.c_float, C.c_float, C.c_float,
@@ -174,6 +176,16 @@ def il_test_gemm(dtype, A, B, M, N, K, lda, ldb, a_kmajor, b_kmajor, epi, Cout, 
                              ldc if ldc is not None else N, p(bias), p(res), p(aux), aux_wrap, scale, beta,
                              tile, stream)
     _check(rc, "il_test_gemm")
+
+
+def il_test_attention(dtype, qkv, batch, seq, heads, width, o, lse, d_o=None, streams=1, dqkv=None, dsum=None, stream=None):
+    """The library's attention kernels by themselves on torch device tensors (test hook)."""
+    _check(load().il_test_attention(dtype, _ptr(qkv), batch, seq, heads, width, _ptr(o), _ptr(lse), _ptr(d_o), streams,
+                                    _ptr(dqkv), _ptr(dsum), stream), "il_test_attention")
+
+
+def il_attention_wants_dsum(dtype, width) -> bool:
+    return bool(load().il_attention_wants_dsum(dtype, width))
 
 
 def il_profile_read(ctx) -> Dict[str, dict]:

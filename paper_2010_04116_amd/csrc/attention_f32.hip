@@ -13,6 +13,13 @@
 // owns one query (key) and its four registers are four consecutive streamed rows: k step r of the second
 // product takes register r as its B operand and streamed row 4 (l >> 4) + r as its A operand, and
 // probabilities never leave the registers.
+//
+// A query sees the keys up to its own and nothing else: 16-row blocks without a visible pair are not computed,
+// and a masked score is -inf, never a finite number that a visible score can lie below.  In the one 16x16 block
+// on the diagonal a matrix product multiplies every streamed row into every owned column, so there a row that is
+// not finite reaches columns it is masked for (0 x NaN).  A wavefront whose sums come out other than finite
+// therefore adds them up again pair by pair, over the visible pairs only: nothing in the loop pays for it (a
+// check of that block's operands cost 5 % at widths up to 64 and 25 % at 128, by its registers).
 #include "common.h"
 
 namespace il {
@@ -22,7 +29,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f4;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kNegBig = -1.0e30f;
 constexpr int kOwn = 64;  // queries / keys per workgroup, 16 per wavefront
 
 __device__ inline f4 get4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
@@ -93,6 +99,45 @@ __device__ inline void store_own(T *row, const f4 (&f)[DH / 16], float scale, in
   for (int s = 0; s < DH / 16; ++s) put4(row + 16 * s + 4 * (lane >> 4), f[s] * scale);
 }
 
+// What exponentials are taken relative to while the maximum so far is m: scores of -inf weigh nothing.
+__device__ inline float base_of(float m) { return m == -INFINITY ? 0.f : m; }
+
+// acc[dh][column] += sum over the 16 streamed rows of w[row][column] X[row][dh], in the layout above (w[r]: row
+// 4 (lane >> 4) + r).
+template <typename TL, int DH>
+__device__ inline void add_block(f4 (&acc)[DH / 16], const float *lds, int r0, const f4 &w, int lane) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) acc[dt] = mma(TL::cols(lds, r0, r, dt, lane), w[r], acc[dt]);
+}
+// ... and pair by pair, for the wavefronts that redo their sums: own . X of a streamed row, acc += w X.
+template <typename T, int DH>
+__device__ inline float dot_row(const f4 (&own)[DH / 16], const T *X, int lane) {
+  float s = 0.f;
+#pragma unroll
+  for (int e4 = 0; e4 < DH / 16; ++e4) {
+    const f4 x = get4(X + 16 * e4 + 4 * (lane >> 4));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(own[e4][e], x[e], s);
+  }
+  return sum_groups(s);
+}
+template <typename T, int DH>
+__device__ inline void add_row(f4 (&acc)[DH / 16], float w, const T *X, int lane) {
+#pragma unroll
+  for (int dt = 0; dt < DH / 16; ++dt) acc[dt] += get4(X + 16 * dt + 4 * (lane >> 4)) * w;
+}
+template <int DH>
+__device__ inline bool all_finite(const f4 (&acc)[DH / 16]) {  // (uniform over the wavefront)
+  bool ok = true;
+#pragma unroll
+  for (int dt = 0; dt < DH / 16; ++dt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ok = ok && __builtin_isfinite(acc[dt][e]);
+  return __ballot(!ok) == 0;
+}
+
 // Streamed rows per LDS tile: two stages of two tiles stay within 64 KB.
 constexpr int tile_rows(int dh) { return dh >= 128 ? 32 : 64; }
 
@@ -112,7 +157,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const T *__restrict__ qkv, i
   f4 qf[DH / 16], acc[DH / 16];
   load_own<T, DH>(qf, base + (size_t)q * ld, q < Tn, lane);
   zero<DH>(acc);
-  float m = kNegBig, l = 0.f;
+  float m = -INFINITY, l = 0.f;
   const float sc = rsqrtf((float)DH) * kLog2e;
   TL tk, tv;
   tk.fetch(base + d, ld, 0, Tn, t);
@@ -128,10 +173,12 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const T *__restrict__ qkv, i
     }
     const int kv0 = it * R;
     if (kv0 > qw + 15) continue;
+    const int live = min(NB, (qw + 15 - kv0) / 16 + 1);  // blocks that some query of the wavefront sees (uniform)
     f4 s[NB];
-    float mx = kNegBig;
+    float mx = -INFINITY;
 #pragma unroll
     for (int a = 0; a < NB; ++a) {
+      if (a >= live) break;
       s[a] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e4 = 0; e4 < DH / 16; ++e4) {
@@ -142,26 +189,35 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const T *__restrict__ qkv, i
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int kv = kv0 + 16 * a + 4 * kk + r;
-        s[a][r] = kv > q || kv >= Tn ? kNegBig : s[a][r] * sc;
+        s[a][r] = kv > q || kv >= Tn ? -INFINITY : s[a][r] * sc;
         mx = fmaxf(mx, s[a][r]);
       }
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - mn);
+    const float mn = fmaxf(m, mx), at = base_of(mn), alpha = __builtin_amdgcn_exp2f(m - at);
     m = mn;
     l *= alpha;
 #pragma unroll
     for (int i = 0; i < DH / 16; ++i) acc[i] *= alpha;
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+    for (int a = 0; a < NB; ++a) {
+      if (a >= live) break;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = __builtin_amdgcn_exp2f(s[a][r] - m);
-        l += p;
-#pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) acc[dt] = mma(TL::cols(sv, 16 * a, r, dt, lane), p, acc[dt]);
+        s[a][r] = __builtin_amdgcn_exp2f(s[a][r] - at);
+        l += s[a][r];
       }
+      add_block<TL, DH>(acc, sv, 16 * a, s[a], lane);
+    }
+  }
+  if (!all_finite<DH>(acc)) {
+    zero<DH>(acc);
+    for (int u = 0; u < min(Tn, qw + 16); ++u) {
+      const T *row = base + u * ld;
+      const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(qf, row + d, lane) * sc - base_of(m));
+      if (u <= q) add_row<T, DH>(acc, p, row + 2 * d, lane);
+    }
   }
   l = sum_groups(l);
   if (q < Tn) {
@@ -228,11 +284,19 @@ __global__ __launch_bounds__(256) void attn_dq_f32(const T *__restrict__ qkv, co
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int kv = kv0 + 4 * kk + r;
-        const float p = kv > q || kv >= Tn ? 0.f : __builtin_amdgcn_exp2f(s[r] * sc2 - L2);
-        const float ds = p * (dp[r] - D);
-#pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) dq[dt] = mma(TL::cols(sk, 16 * a, r, dt, lane), ds, dq[dt]);
+        const float ds = __builtin_amdgcn_exp2f(s[r] * sc2 - L2) * (dp[r] - D);
+        s[r] = kv > q || kv >= Tn ? 0.f : ds;
       }
+      add_block<TL, DH>(dq, sk, 16 * a, s, lane);
+    }
+  }
+  if (!all_finite<DH>(dq)) {
+    zero<DH>(dq);
+    for (int u = 0; u < min(Tn, qw + 16); ++u) {
+      const T *row = base + u * ld;
+      const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(qf, row + d, lane) * sc2 - L2);
+      const float ds = p * (dot_row<T, DH>(gf, row + 2 * d, lane) - D);
+      if (u <= q) add_row<T, DH>(dq, ds, row + d, lane);
     }
   }
   if (q < Tn) store_own<T, DH>(dqkv + (sidx * N + tok) * ld + h * DH, dq, sc, lane);
@@ -295,14 +359,25 @@ __global__ __launch_bounds__(256) void attn_dkv_f32(const T *__restrict__ qkv, c
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int q = q0 + 4 * kk + r;
-        const float p = kv > q || q >= Tn ? 0.f : __builtin_amdgcn_exp2f(s[r] * sc2 - l4[r]);
-        const float ds = p * (dp[r] - d4[r]);
-#pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) {
-          dv[dt] = mma(TL::cols(sg, 16 * a, r, dt, lane), p, dv[dt]);
-          dk[dt] = mma(TL::cols(sq, 16 * a, r, dt, lane), ds, dk[dt]);
-        }
+        const bool seen = kv <= q && q < Tn;
+        const float p = seen ? __builtin_amdgcn_exp2f(s[r] * sc2 - l4[r]) : 0.f;
+        dp[r] = seen ? p * (dp[r] - d4[r]) : 0.f;
+        s[r] = p;
       }
+      add_block<TL, DH>(dv, sg, 16 * a, s, lane);
+      add_block<TL, DH>(dk, sq, 16 * a, dp, lane);
+    }
+  }
+  if (!all_finite<DH>(dv) || !all_finite<DH>(dk)) {
+    zero<DH>(dv);
+    zero<DH>(dk);
+    for (int u = kw; u < Tn; ++u) {
+      const T *qr = base + u * ld, *gr = gbase + (size_t)u * d;
+      const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(kf, qr, lane) * sc2 - lrow[u] * kLog2e);
+      const float ds = p * (dot_row<T, DH>(vf, gr, lane) - drow[u]);
+      if (u < kv) continue;
+      add_row<T, DH>(dv, p, gr, lane);
+      add_row<T, DH>(dk, ds, qr, lane);
     }
   }
   if (kv < Tn) {

@@ -625,6 +625,10 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
   return IL_OK;
 }
 
+bool head_width_ok(int dtype, int dh) {
+  return dh == 16 || dh == 32 || dh == 64 || dh == 128 || (dh == 256 && dtype == IL_BF16);
+}
+
 int validate(const il_config *cfg) {
   if (cfg->K < 1 || cfg->blocks_per_component < 1 || cfg->d_model < 1 || cfg->n_heads < 1 || cfg->d_mlp < 1 ||
       cfg->vocab < 2 || cfg->batch < 1 || cfg->seq < 1)
@@ -636,8 +640,7 @@ int validate(const il_config *cfg) {
   if (cfg->profile < 0 || cfg->profile > 2) return IL_E_ARG;
   if (cfg->head_chunk < 0 || cfg->head_blocks < 0 || cfg->head_blocks > 64 || cfg->reserved != 0) return IL_E_ARG;
   if (cfg->d_model % cfg->n_heads) return IL_E_SHAPE;
-  const int dh = cfg->d_model / cfg->n_heads;
-  if (dh != 16 && dh != 32 && dh != 64 && dh != 128 && !(dh == 256 && cfg->dtype == IL_BF16)) return IL_E_SHAPE;
+  if (!head_width_ok(cfg->dtype, cfg->d_model / cfg->n_heads)) return IL_E_SHAPE;
   if (cfg->d_model > 2048) return IL_E_SHAPE;
   const long long N = (long long)cfg->batch * cfg->seq;
   if (N > (1 << 24) || (long long)cfg->vocab > (1 << 24)) return IL_E_SHAPE;
@@ -1081,6 +1084,23 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
   }
   const hipError_t e = dtype == IL_F32 ? gemm_f32(g, (hipStream_t)stream) : gemm_bf16(g, (hipStream_t)stream);
   return e == hipSuccess ? IL_OK : (e == hipErrorInvalidValue ? IL_E_SHAPE : IL_E_HIP);
+}
+
+int il_attention_wants_dsum(int32_t dtype, int32_t width) { return attention_dsum_given(dtype, width) ? 1 : 0; }
+
+int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq, int32_t heads, int32_t width,
+                      void *o, float *lse, const void *d_o, int32_t streams, void *dqkv, float *dsum, void *stream) {
+  if (!qkv || !o || !lse || batch < 1 || seq < 1 || heads < 1 || width < 1) return IL_E_ARG;
+  if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
+  if (d_o && (!dqkv || !dsum)) return IL_E_ARG;
+  const long long N = (long long)batch * seq, rows = N * (d_o ? streams : 1);
+  if (!head_width_ok(dtype, width) || (long long)heads * width > 2048 || (long long)batch * heads > 65535 || N > (1 << 24) ||
+      (d_o && (streams < 1 || streams > kMaxStreams)) || rows * 3 * heads * width * (dtype == IL_F32 ? 4 : 2) >= 0x7FFFFFFFll)
+    return IL_E_SHAPE;
+  hipStream_t s = (hipStream_t)stream;
+  IL_TRY(attention_forward(dtype, qkv, batch, seq, heads, width, o, lse, s));
+  if (d_o) IL_TRY(attention_backward(dtype, qkv, o, d_o, lse, streams, batch, seq, heads, width, dqkv, dsum, s));
+  return IL_OK;
 }
 
 int il_set_accumulation(il_ctx *c, int32_t accumulate, float grad_scale) {

@@ -1,0 +1,139 @@
+"""The library's causal attention by itself (il_test_attention) against float64 sums over the visible keys only."""
+import numpy as np
+import pytest
+
+from paper_2010_04116_amd import binding as b
+
+pytestmark = pytest.mark.gpu
+IL = {"f32": b.IL_F32, "bf16": b.IL_BF16}
+
+
+def reference(qkv, g, B, T, H, dh):
+    """float64: row q of the result is made of keys 0..q and of nothing else, so what is not finite in a token
+    reaches exactly the rows that see it."""
+    d = H * dh
+    x = qkv.astype(np.float64).reshape(B, T, 3, H, dh).transpose(2, 0, 3, 1, 4)
+    q, k, v = x[0], x[1], x[2]
+    go = g.astype(np.float64).reshape(B, T, H, dh).transpose(0, 2, 1, 3)
+    sc = dh ** -0.5
+    o = np.zeros((B, H, T, dh))
+    dq, dk, dv = np.zeros_like(o), np.zeros_like(o), np.zeros_like(o)
+    with np.errstate(all="ignore"):
+        for t in range(T):
+            s = np.einsum("bhi,bhui->bhu", q[:, :, t], k[:, :, :t + 1]) * sc
+            m = np.where(np.isneginf(s.max(axis=2, keepdims=True)), 0, s.max(axis=2, keepdims=True))
+            p = np.exp(s - m)
+            p = p / p.sum(axis=2, keepdims=True)
+            o[:, :, t] = np.einsum("bhu,bhui->bhi", p, v[:, :, :t + 1])
+            D = (o[:, :, t] * go[:, :, t]).sum(axis=2, keepdims=True)
+            ds = p * (np.einsum("bhi,bhui->bhu", go[:, :, t], v[:, :, :t + 1]) - D)
+            dq[:, :, t] = np.einsum("bhu,bhui->bhi", ds, k[:, :, :t + 1]) * sc
+            dk[:, :, :t + 1] += ds[..., None] * q[:, :, t][:, :, None] * sc
+            dv[:, :, :t + 1] += p[..., None] * go[:, :, t][:, :, None]
+    rows = lambda a: a.transpose(0, 2, 1, 3).reshape(B * T, d)  # noqa: E731
+    return rows(o), np.concatenate([rows(dq), rows(dk), rows(dv)], axis=1)
+
+
+def run(dtype, qkv, g, B, T, H, dh):
+    import torch
+    dev, tt = torch.device("cuda:0"), torch.float32 if dtype == "f32" else torch.bfloat16
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(tt).to(dev)  # noqa: E731
+    d, N = H * dh, B * T
+    dqkv_in, dg = to(qkv), to(g)
+    o = torch.full((N, d), 7.0, dtype=tt, device=dev)
+    lse = torch.full((B, H, T), 7.0, device=dev)
+    out = torch.full((N, 3 * d), 7.0, dtype=tt, device=dev)
+    dsum = torch.zeros(N * max(H, (d + 31) // 32), device=dev)
+    args = (IL[dtype], dqkv_in, B, T, H, dh, o, lse)
+    stream = torch.cuda.current_stream().cuda_stream
+    if b.il_attention_wants_dsum(IL[dtype], dh):
+        b.il_test_attention(*args, stream=stream)
+        dsum = (dg.float() * o.float()).reshape(N, d // 32, 32).sum(dim=2).t().contiguous()
+    b.il_test_attention(*args, dg, 1, out, dsum, stream=stream)
+    torch.cuda.synchronize()
+    return o.float().cpu().numpy(), out.float().cpu().numpy()
+
+
+def bf16(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(torch.bfloat16).float().numpy()
+
+
+def draw(seed, B, T, H, dh):
+    rng = np.random.default_rng(seed)
+    return bf16(rng.standard_normal((B * T, 3 * H * dh))), bf16(rng.standard_normal((B * T, H * dh)))
+
+
+def held(got, want, dtype, what):
+    """fp32 sums of a few hundred terms, and for bf16 one rounding to eight bits of the final value."""
+    assert np.array_equal(np.isnan(got), np.isnan(want)), what + ": NaN in other places"
+    fin = np.isfinite(want)
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)]), what
+    scale = np.sqrt(np.mean(want[fin] ** 2)) if fin.any() else 1.0
+    tol = 2e-5 * (scale + np.abs(want[fin])) + (2 ** -8 * np.abs(want[fin]) if dtype == "bf16" else 0)
+    bad = np.abs(got[fin] - want[fin]) - tol
+    assert bad.size == 0 or bad.max() <= 0, f"{what}: off by {np.abs(got[fin] - want[fin]).max():.3e}"
+
+
+FP32_PRODUCTS = [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16)]
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("T", [1, 17, 64, 150])
+def test_forward_and_backward(dtype, dh, T):
+    B, H = 2, 2
+    qkv, g = draw(T, B, T, H, dh)
+    print("case", dtype, dh, T, flush=True)
+    o, dqkv = run(dtype, qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh)
+    held(o, wo, dtype, "o")
+    if dtype == "f32":      # (in bf16 the backward takes the row sums from the rounded o)
+        held(dqkv, wd, dtype, "dqkv")
+    else:
+        assert np.linalg.norm(dqkv - wd) <= 4e-3 * np.linalg.norm(wd)
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("T,token", [(17, 5), (64, 40), (90, 16), (90, 31), (90, 89)])
+@pytest.mark.parametrize("part,value", [("q", np.nan), ("k", np.nan), ("v", np.nan), ("v", np.inf), ("g", np.nan), ("g", -np.inf)])
+def test_what_is_not_finite_stays_with_the_rows_that_see_it(dtype, dh, T, token, part, value):
+    B, H = 1, 2
+    qkv, g = draw(T + token, B, T, H, dh)
+    d = H * dh
+    if part == "g":
+        g[token, 3] = value
+    else:
+        qkv[token, {"q": 0, "k": d, "v": 2 * d}[part] + 3] = value
+    print("case", dtype, dh, T, token, part, value, flush=True)
+    o, dqkv = run(dtype, qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh)
+    held(o, wo, dtype, "o")
+    for i, what in enumerate(("dq", "dk", "dv")):
+        got, want = dqkv[:, i * d:(i + 1) * d], wd[:, i * d:(i + 1) * d]
+        assert np.array_equal(np.isfinite(got), np.isfinite(want)), what
+        if dtype == "f32":
+            held(np.where(np.isfinite(got), got, 0), np.where(np.isfinite(want), want, 0), dtype, what)
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("low", [-1e31, -1e37, -np.inf])
+def test_scores_below_any_mask_value(dtype, dh, low):
+    """The first tokens' scores are all equal and lie far below -1e30; a later block's are -inf for every other key.
+    Masked keys hold another value of V and must not show."""
+    B, T, H = 1, 90, 2
+    qkv, g = draw(3, B, T, H, dh)
+    x = qkv.reshape(T, 3, H, dh)
+    x[:, 0] = 0
+    x[:, 0, :, 0] = 1e19                       # q . k = 1e19 k_0
+    x[:, 1] = 0
+    if np.isinf(low):
+        x[1::2, 1, :, 0] = -3e38               # -inf in fp32: weighs nothing; the others score 0
+    else:
+        x[:, 1, :, 0] = low * dh ** 0.5 / 1e19
+    x[:, 2] = np.arange(T)[:, None, None]
+    qkv = bf16(qkv)
+    print("case", dtype, dh, low, flush=True)
+    o, _ = run(dtype, qkv, g, B, T, H, dh)
+    t = np.arange(T)
+    want = t / 2 if not np.isinf(low) else np.floor(t / 2)   # the mean of 0..t, of the even ones among them
+    held(o, np.repeat(want[:, None], H * dh, axis=1), dtype, "o")
