@@ -1,5 +1,5 @@
-// Causal attention with fp32 products: the path of fp32 runs, and of bf16 runs with narrow heads (16),
-// whose tiles are too small for the bf16 kernels' loads.  v_mfma_f32_16x16x4_f32 on fp32 values staged in
+// Causal attention with fp32 products: the path of fp32 runs, and of bf16 runs with narrow heads (16 and 32),
+// where probabilities and their gradients stay fp32.  v_mfma_f32_16x16x4_f32 on fp32 values staged in
 // LDS (bf16 inputs are widened on the way in), fp32 softmax; nothing is rounded below the inputs' and
 // outputs' own type.
 //
@@ -411,12 +411,13 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
 hipError_t attention_backward_mfma(const void *qkv, const void *d_o, const float *lse, const float *dsum, int ns,
                                    int B, int T, int H, int dh, void *dqkv, hipStream_t s);
 
-// Front ends used by the step: bf16 with head widths 32 to 256 runs on the bf16 matrix instructions, fp32
-// and bf16 with head width 16 on the kernels above.
+// Front ends used by the step: bf16 with head widths 64 to 256 runs on the bf16 matrix instructions, fp32
+// and bf16 with head widths 16 and 32 on the kernels above.
 hipError_t attention_forward(int dtype, const void *qkv, int B, int T, int H, int dh, void *o, float *lse,
                              hipStream_t s) {
   if (dtype == 1) {
     if (dh == 16) return fwd_t<bf16_t, 16>(qkv, B, T, H, o, lse, s);
+    if (dh == 32) return fwd_t<bf16_t, 32>(qkv, B, T, H, o, lse, s);
     return attention_forward_mfma(qkv, B, T, H, dh, o, lse, s);
   }
   switch (dh) {
@@ -431,6 +432,7 @@ hipError_t attention_backward(int dtype, const void *qkv, const void *o, const v
                               int ns, int B, int T, int H, int dh, void *dqkv, float *dsum, hipStream_t s) {
   if (dtype == 1) {
     if (dh == 16) return bwd_t<bf16_t, 16>(qkv, o, d_o, lse, ns, B, T, H, dqkv, dsum, s);
+    if (dh == 32) return bwd_t<bf16_t, 32>(qkv, o, d_o, lse, ns, B, T, H, dqkv, dsum, s);
     return attention_backward_mfma(qkv, d_o, lse, dsum, ns, B, T, H, dh, dqkv, s);
   }
   switch (dh) {

@@ -1,5 +1,5 @@
 // Causal attention forward / backward on the gfx950 matrix cores for bf16 and head
-// widths 32, 64, 128 and 256.  K/V (forward, dQ) or Q/dO (dK, dV) tiles are LDS-resident, double
+// widths 64, 128 and 256.  K/V (forward, dQ) or Q/dO (dK, dV) tiles are LDS-resident, double
 // buffered and filled by direct HBM -> LDS loads; scores are never written to memory.
 //
 // Orientation.  Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16:
@@ -52,8 +52,7 @@ union Frag {
 // send 16 consecutive rows to 16 different 16-byte positions of the 256-byte bank span and 4
 // consecutive rows to 4 different 64-byte quarters of it.  Rows of 256 bytes or more all start at
 // bank 0: h(r) = (r & 3) << 2 | (r >> 2) & 3.  Rows of 128 bytes alternate between the two halves
-// of the span by themselves (bit 0 of r): h(r) = bit 1 of r << 2 | bit 2 << 1 | bit 3; rows of 64 bytes over
-// its quarters: h(r) = (r >> 2) & 3.  (With the
+// of the span by themselves (bit 0 of r): h(r) = bit 1 of r << 2 | bit 2 << 1 | bit 3.  (With the
 // earlier three-bit h(r) = (r & 3) << 1 | (r >> 2) & 1 the LDS counters showed every second cycle
 // of these kernels' LDS activity as a bank conflict.)
 template <int ROWS, int DH, int NT = 256>
@@ -65,7 +64,6 @@ struct TokTile {
   uint32_t rstride;
   __device__ static inline int h(int r) {
     if constexpr (DH >= 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-    if constexpr (DH == 32) return (r >> 2) & 3;
     return (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
   }
   // col0: first element column of this head; ld: elements per token row
@@ -640,7 +638,6 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
                                   hipStream_t s) {
   const bf16_t *x = (const bf16_t *)qkv;
   switch (dh) {
-    case 32: return fwd<32>(x, B, T, H, (bf16_t *)o, lse, s);
     case 64: return fwd<64>(x, B, T, H, (bf16_t *)o, lse, s);
     case 128: return fwd<128>(x, B, T, H, (bf16_t *)o, lse, s);
     case 256: return fwd<256>(x, B, T, H, (bf16_t *)o, lse, s);
@@ -654,7 +651,6 @@ hipError_t attention_backward_mfma(const void *qkv, const void *d_o, const float
   hipLaunchKernelGGL(attn_bwd_mfma<DH>, dim3((T + 127) / 128, B * H, bwd_roles(DH) * ns), dim3(256), 0, s,       \
                      (const bf16_t *)qkv, (const bf16_t *)d_o, lse, dsum, ns, B, T, H, (bf16_t *)dqkv)
   switch (dh) {
-    case 32: IL_ATTN_BWD(32); break;
     case 64: IL_ATTN_BWD(64); break;
     case 128: IL_ATTN_BWD(128); break;
     case 256: IL_ATTN_BWD(256); break;

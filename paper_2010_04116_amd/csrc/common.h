@@ -195,7 +195,7 @@ hipError_t attention_forward(int dtype, const void *qkv, int B, int T, int H, in
 // d_o: T [nstreams*N, d]; dqkv: T [nstreams*N, 3d]; dsum: where attention_dsum_given(), the row sums of
 // dO * O per 32 columns, fp32 [d / 32][nstreams*N], left by EPI_STORE_DOT; else fp32 scratch [nstreams*N*H].
 // lse is what attention_forward of the same type and head width wrote (its unit is theirs).
-inline bool attention_dsum_given(int dtype, int dh) { return dtype == 1 && dh >= 32; }
+inline bool attention_dsum_given(int dtype, int dh) { return dtype == 1 && dh >= 64; }
 hipError_t attention_backward(int dtype, const void *qkv, const void *o, const void *d_o, const float *lse,
                               int nstreams, int B, int T, int H, int dh, void *dqkv, float *dsum,
                               hipStream_t s);
