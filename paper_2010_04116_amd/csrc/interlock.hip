@@ -4,9 +4,8 @@
 // route) live in fp32 "slots" ordered by the lowest component they reach.  Under the
 // window-sum and far-head routings the streams live at any component occupy adjacent
 // slots, i.e. one contiguous stack [cnt*N, d], and every backward GEMM processes all of
-// them in a single launch; where the live slots are not adjacent the component's data
-// gradients run once per contiguous range, and the ranges meet again in the weighted sum of
-// streams that every parameter gradient is taken of.
+// them in a single launch; where the live slots are not adjacent the component's backward
+// runs once per contiguous range, and the ranges' parameter gradients add up in fp32.
 #include "../../include/interlock.h"
 #include "../../include/interlock_test.h"
 
@@ -168,12 +167,20 @@ struct RingEntry {
   char *DU, *DQKV;    // [live streams][N, m] and [N, 3d]: gradients at the MLP's hidden layer and at Q|K|V
   float *ln[2];       // LayerNorm 2's and 1's first-stage column sums
 };
-struct Tail {         // one queued tail (or, beyond kMaxStreams weighted streams, one part of it)
+struct Tail {         // one queued tail
   const BlockOff *b; const BlockSave *s; const RingEntry *r;
-  SumTable by_slot, by_stack;  // the weighted streams, as slots of Ga / Gb and as positions in DU / DQKV
-  int ln_blocks;               // partial sums per LayerNorm, 0: none queued with this part
-  int acc;                     // adds to what an earlier part wrote
+  const std::vector<Run> *runs;  // (outlives the launch)
+  int ln_blocks;                 // partial sums per LayerNorm
 };
+// the part-th range that carries weighted streams, nullptr beyond the last
+const Run *weighted_run(const std::vector<Run> &runs, int part) {
+  for (const Run &r : runs) {
+    bool any = false;
+    for (int i = 0; i < r.cnt; ++i) any = any || r.wt[i] != 0.f;
+    if (any && part-- == 0) return &r;
+  }
+  return nullptr;
+}
 
 }  // namespace
 
@@ -501,56 +508,70 @@ int launch_tails(il_ctx *c) {
     IL_TRY(hipStreamWaitEvent(c->side, c->ev_ready, 0));
     c->stream = c->side;
   }
-  SumColsumJobs sums;
-  ColsumJobs finals;
-  GemmArgs wg[4 * kGroup];
-  int nw = 0;
-  double sum_bytes = 0;
-  memset(&sums, 0, sizeof(sums));
-  sums.N = c->N;
-  finals.count = 0;
-  for (int i = 0; i < c->ntails; ++i) {
-    const Tail &t = c->tails[i];
-    const BlockOff &b = *t.b;
-    sums.table[2 * i] = t.by_slot;
-    sums.table[2 * i + 1] = t.by_stack;
-    const int ns = t.by_slot.ns;
-    const bool plain = ns == 1 && t.by_slot.w[0] == 1.f;
-    const char *dy[4] = {t.r->Ga, t.r->DU, t.r->Gb, t.r->DQKV};
-    const char *x[4] = {t.s->gl, t.s->h2, t.s->o, t.s->h1};
-    const size_t w_off[4] = {b.w_fc2, b.w_fc1, b.w_o, b.w_qkv}, b_off[4] = {b.b_fc2, b.b_fc1, b.b_o, b.b_qkv};
-    const int in[4] = {c->m, c->d, c->d, c->d};
-    for (int j = 0; j < 4; ++j) {
-      SumColsumJob &q = sums.job[sums.count++];
-      q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j & 1);
-      q.ysum = plain ? nullptr : c->YS[i][j];
-      q.partials = c->partials[i][j];
-      sum_bytes += (double)(plain ? 1 : ns + 1) * c->N * wide[j] * c->eb;
-      finals.job[finals.count++] = ColsumJob{q.partials, 0, q.cols, Gr(c, b_off[j]), t.acc};
-      GemmArgs g = base_args();
-      g.A = x[j]; g.lda = in[j]; g.a_kmajor = 1;
-      g.B = plain ? dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb : c->YS[i][j];
-      g.ldb = (int)wide[j]; g.b_kmajor = 1;
-      g.M = in[j]; g.N = (int)wide[j]; g.K = c->N;
-      g.epi = EPI_WGRAD; g.C = Gr(c, w_off[j]); g.ldc = (int)wide[j]; g.beta = t.acc;
-      wg[nw++] = g;
-    }
-  }
-  {
-    Scope sc(c, KC_COLSUM, 0, sum_bytes);
-    int nblk = 0;
-    IL_TRY(sum_colsum_multi(c->cfg.dtype, sums, &nblk, c->stream));
-    for (int i = 0; i < finals.count; ++i) finals.job[i].nblk = nblk;
+  // Ranges of slots one after the other, each for all queued tails: a range's sum of streams is stored in the
+  // operands' type, but what different ranges contribute only meets in the fp32 gradients.
+  for (int part = 0;; ++part) {
+    SumColsumJobs sums;
+    ColsumJobs finals;
+    GemmArgs wg[4 * kGroup];
+    int nw = 0;
+    double sum_bytes = 0;
+    memset(&sums, 0, sizeof(sums));
+    sums.N = c->N;
+    finals.count = 0;
     for (int i = 0; i < c->ntails; ++i) {
       const Tail &t = c->tails[i];
-      if (!t.ln_blocks) continue;
-      finals.job[finals.count++] = ColsumJob{t.r->ln[0], t.ln_blocks, 2 * c->d, Gr(c, t.b->ln2_g), c->accumulate};
-      finals.job[finals.count++] = ColsumJob{t.r->ln[1], t.ln_blocks, 2 * c->d, Gr(c, t.b->ln1_g), c->accumulate};
+      const Run *run = weighted_run(*t.runs, part);
+      if (!run) continue;
+      const BlockOff &b = *t.b;
+      // the weighted streams, as slots of Ga / Gb and as positions in DU / DQKV
+      SumTable &by_slot = sums.table[2 * i], &by_stack = sums.table[2 * i + 1];
+      for (int j = 0; j < run->cnt; ++j) {
+        if (run->wt[j] == 0.f) continue;
+        const int n = by_slot.ns++;
+        by_stack.ns = n + 1;
+        by_slot.row[n] = run->s0 + j;
+        by_stack.row[n] = run->off + j;
+        by_slot.w[n] = by_stack.w[n] = run->wt[j];
+      }
+      const int ns = by_slot.ns, acc = part > 0 || c->accumulate;
+      const bool plain = ns == 1 && by_slot.w[0] == 1.f;
+      const char *dy[4] = {t.r->Ga, t.r->DU, t.r->Gb, t.r->DQKV};
+      const char *x[4] = {t.s->gl, t.s->h2, t.s->o, t.s->h1};
+      const size_t w_off[4] = {b.w_fc2, b.w_fc1, b.w_o, b.w_qkv}, b_off[4] = {b.b_fc2, b.b_fc1, b.b_o, b.b_qkv};
+      const int in[4] = {c->m, c->d, c->d, c->d};
+      for (int j = 0; j < 4; ++j) {
+        SumColsumJob &q = sums.job[sums.count++];
+        q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j & 1);
+        q.ysum = plain ? nullptr : c->YS[i][j];
+        q.partials = c->partials[i][j];
+        sum_bytes += (double)(plain ? 1 : ns + 1) * c->N * wide[j] * c->eb;
+        finals.job[finals.count++] = ColsumJob{q.partials, 0, q.cols, Gr(c, b_off[j]), acc};
+        GemmArgs g = base_args();
+        g.A = x[j]; g.lda = in[j]; g.a_kmajor = 1;
+        g.B = plain ? dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb : c->YS[i][j];
+        g.ldb = (int)wide[j]; g.b_kmajor = 1;
+        g.M = in[j]; g.N = (int)wide[j]; g.K = c->N;
+        g.epi = EPI_WGRAD; g.C = Gr(c, w_off[j]); g.ldc = (int)wide[j]; g.beta = acc;
+        wg[nw++] = g;
+      }
     }
-    IL_TRY(colsum_final_multi(finals, c->stream));
+    if (nw == 0) break;
+    {
+      Scope sc(c, KC_COLSUM, 0, sum_bytes);
+      int nblk = 0;
+      IL_TRY(sum_colsum_multi(c->cfg.dtype, sums, &nblk, c->stream));
+      for (int i = 0; i < finals.count; ++i) finals.job[i].nblk = nblk;
+      for (int i = 0; part == 0 && i < c->ntails; ++i) {  // (every range's LayerNorm sums at once)
+        const Tail &t = c->tails[i];
+        finals.job[finals.count++] = ColsumJob{t.r->ln[0], t.ln_blocks, 2 * c->d, Gr(c, t.b->ln2_g), c->accumulate};
+        finals.job[finals.count++] = ColsumJob{t.r->ln[1], t.ln_blocks, 2 * c->d, Gr(c, t.b->ln1_g), c->accumulate};
+      }
+      IL_TRY(colsum_final_multi(finals, c->stream));
+    }
+    const int rc = launch_wgrads(c, wg, nw);
+    if (rc) return rc;
   }
-  const int rc = launch_wgrads(c, wg, nw);
-  if (rc) return rc;
   if (async) {
     const int half = (int)(c->tails[0].r - c->ring) / kGroup;
     IL_TRY(hipEventRecord(c->ev_tail[half], c->side));
@@ -594,31 +615,7 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
       return rc;
     ln_blocks += nblk;
   }
-  // queue the tail; more than kMaxStreams weighted streams go in several parts, each launched before the next
-  Tail t;
-  memset(&t, 0, sizeof(t));
-  t.b = &b; t.s = &s; t.r = &r; t.ln_blocks = ln_blocks; t.acc = c->accumulate;
-  auto queue = [&]() -> int {
-    c->tails[c->ntails++] = t;
-    t.by_slot.ns = t.by_stack.ns = 0;
-    t.ln_blocks = 0;
-    t.acc = 1;
-    return IL_OK;
-  };
-  for (const Run &run : runs)
-    for (int i = 0; i < run.cnt; ++i) {
-      if (run.wt[i] == 0.f) continue;
-      if (t.by_slot.ns == kMaxStreams) {
-        queue();
-        if ((rc = launch_tails(c))) return rc;
-      }
-      const int n = t.by_slot.ns++;
-      t.by_stack.ns = n + 1;
-      t.by_slot.row[n] = run.s0 + i;
-      t.by_stack.row[n] = run.off + i;
-      t.by_slot.w[n] = t.by_stack.w[n] = run.wt[i];
-    }
-  queue();
+  c->tails[c->ntails++] = Tail{&b, &s, &r, &runs, ln_blocks};
   if (c->tail_inline || next % kGroup == 0)
     if ((rc = launch_tails(c))) return rc;
   c->pos = next;
