@@ -280,8 +280,8 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *__restrict__ dy, c
 }
 
 // The number of column passes J a width needs: registers per lane, and so wavefronts per SIMD, follow it.
-// Widths that divide by 4 (and vectors that start on 16 / 8 bytes, which an odd d_mlp can prevent in fp32)
-// take four columns per lane.
+// Widths that divide by 4 take four columns per lane where every vector starts on 16 (bf16: 8) bytes, which an
+// odd d_mlp can prevent in fp32, and the caller's x in both types.
 template <typename F>
 void with_width(int d, bool vec, F &&f) {
 #define IL_W(V, J) return f(std::integral_constant<int, V>{}, std::integral_constant<int, J>{})
@@ -301,15 +301,17 @@ void with_width(int d, bool vec, F &&f) {
 #undef IL_W
 }
 
+// (x of the first block is the caller's, who is asked for no alignment; nullptr is aligned)
 template <typename T>
-bool vec4(int d, const void *gamma, const void *beta) {
-  return (d & 3) == 0 && (((uintptr_t)gamma | (uintptr_t)beta) & (4 * sizeof(T) - 1)) == 0;
+bool vec4(int d, const T *gamma, const T *beta, const float *x, const float *xcopy) {
+  return (d & 3) == 0 && (((uintptr_t)gamma | (uintptr_t)beta) & (4 * sizeof(T) - 1)) == 0 &&
+         (((uintptr_t)x | (uintptr_t)xcopy) & 15) == 0;
 }
 
 template <typename T>
 void launch_fwd(hipStream_t s, const float *x, const T *gamma, const T *beta, float eps, int rows, int d, T *y,
                 float *stats, float *xcopy) {
-  with_width(d, vec4<T>(d, gamma, beta), [&](auto v, auto j) {
+  with_width(d, vec4<T>(d, gamma, beta, x, xcopy), [&](auto v, auto j) {
     hipLaunchKernelGGL((ln_fwd_kernel<T, decltype(v)::value, decltype(j)::value>), dim3((rows + kWaves - 1) / kWaves),
                        dim3(256), 0, s, x, gamma, beta, eps, rows, d, y, stats, xcopy);
   });
@@ -320,7 +322,7 @@ void launch_bwd(int blocks, hipStream_t s, const T *dy, const float *x, const fl
   auto launch = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, dy, x, stats, gamma, rows, N, d, G, Gb, sw, partials);
   };
-  if (!vec4<T>(d, gamma, gamma)) {
+  if (!vec4<T>(d, gamma, gamma, x, G)) {
     if (d <= 256) launch(ln_bwd_kernel<T, 1, 4>, 256);
     else launch(ln_bwd_kernel<T, 1, 32>, 256);
   } else if (d <= 256) {
