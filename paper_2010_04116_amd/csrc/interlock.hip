@@ -163,7 +163,8 @@ struct ProfRec { int cls; bool kernel, bracket; hipEvent_t e0, e1; KernelTimer k
 // tails do.
 constexpr int kGroup = 2, kRing = 2 * kGroup;
 struct RingEntry {
-  char *Ga, *Gb;      // gradient stream as a GEMM operand, [nslots][N, d]: above the MLP / above the attention
+  char *Ga;           // gradient stream above the MLP as a GEMM operand, [nslots][N, d]
+  char *Gb;           // ... above the attention, [live streams][N, d]
   char *DU, *DQKV;    // [live streams][N, m] and [N, 3d]: gradients at the MLP's hidden layer and at Q|K|V
   float *ln[2];       // LayerNorm 2's and 1's first-stage column sums
 };
@@ -203,7 +204,7 @@ struct il_ctx {
   int pos = 0;                     // ring entry of the next block
   char *DH; float *dsum, *skws; size_t skws_floats;
   Tail tails[kGroup]; int ntails = 0;
-  char *YS[kGroup][4]; float *partials[kGroup][4];  // weighted stream sums and bias partials of the queued tails
+  float *partials[kGroup][4];      // bias partials of the queued tails
   hipEvent_t ev_ready = nullptr, ev_tail[2] = {nullptr, nullptr};
   char tail_pending[2] = {0, 0};   // half of the ring: its tails were launched and nobody has waited for them
   int tail_last = 0;               // the half launched last
@@ -297,7 +298,7 @@ size_t layout_workspace(il_ctx *c, void *base) {
   c->G = (float *)cv.take(ns * N * d * 4);
   for (RingEntry &r : c->ring) {
     r.Ga = (char *)cv.take(ns * N * d * eb);
-    r.Gb = (char *)cv.take(ns * N * d * eb);
+    r.Gb = (char *)cv.take(live * d * eb);
     r.DU = (char *)cv.take(live * m * eb);
     r.DQKV = (char *)cv.take(live * 3 * d * eb);
     for (float *&p : r.ln) p = (float *)cv.take((size_t)c->plan.maxruns * ln_backward_max_blocks() * 2 * d * 4);
@@ -306,10 +307,7 @@ size_t layout_workspace(il_ctx *c, void *base) {
   c->dsum = (float *)cv.take(S * std::max(H, d / 32) * 4);
   const size_t wide[4] = {d, m, d, 3 * d};  // outputs of FC2, FC1, the attention output projection, QKV
   for (int p = 0; p < kGroup; ++p)
-    for (int i = 0; i < 4; ++i) {
-      c->YS[p][i] = (char *)cv.take(N * wide[i] * eb);
-      c->partials[p][i] = (float *)cv.take((size_t)colsum_max_blocks() * wide[i] * 4);
-    }
+    for (int i = 0; i < 4; ++i) c->partials[p][i] = (float *)cv.take((size_t)colsum_max_blocks() * wide[i] * 4);
   c->skws_floats = head_split_floats(c, c->Nc, (size_t)-1);
   c->skws = (float *)cv.take(c->skws_floats * 4);
   c->xb = (char *)cv.take(N * d * eb);
@@ -457,15 +455,15 @@ int attention_bwd(il_ctx *c, const BlockSave &s, const void *d_o, int cnt, void 
   return IL_OK;
 }
 
+// Gout: the range's rows of the updated stream as a GEMM operand
 int ln_bwd(il_ctx *c, const Run &run, const void *dy, const float *x, const float *stats, size_t g_off, void *Gout,
            float *partials, int *nblk) {
   StreamWeights sw;
   memcpy(sw.w, run.wt, sizeof(sw.w));
   const int rows = run.cnt * c->N;
-  const size_t at = (size_t)run.s0 * c->N * c->d;
   Scope sc(c, KC_LN_BWD, 0, (double)rows * c->d * (c->eb + 8 + c->eb) + (double)c->N * c->d * 4);
-  IL_TRY(ln_backward_residual(c->cfg.dtype, dy, x, stats, P(c, g_off), rows, c->N, c->d, c->G + at,
-                              (char *)Gout + at * c->eb, sw, partials, nblk, c->stream));
+  IL_TRY(ln_backward_residual(c->cfg.dtype, dy, x, stats, P(c, g_off), rows, c->N, c->d,
+                              c->G + (size_t)run.s0 * c->N * c->d, Gout, sw, partials, nblk, c->stream));
   return IL_OK;
 }
 
@@ -492,7 +490,8 @@ int block_forward(il_ctx *c, const BlockOff &b, const BlockSave &s, const float 
 // Launch the queued tails: weighted sum over the gradient streams of each of a block's four linear outputs
 // (the weight gradient is linear in them, so one product over N rows serves any number of streams) with
 // their column sums, the second stage of the column sums, the weight gradients.  A single stream of weight
-// 1 is its own sum and is read where the data gradients left it.
+// 1 is its own sum and is read where the data gradients left it; a sum of several takes the place of the first of
+// them, which nothing else reads any more.
 int launch_tails(il_ctx *c) {
   if (c->ntails == 0) return IL_OK;
   const bool async = c->cfg.profile != 1 && !c->tail_inline;
@@ -524,7 +523,7 @@ int launch_tails(il_ctx *c) {
       const Run *run = weighted_run(*t.runs, part);
       if (!run) continue;
       const BlockOff &b = *t.b;
-      // the weighted streams, as slots of Ga / Gb and as positions in DU / DQKV
+      // the weighted streams, as slots of Ga and as positions in Gb, DU and DQKV
       SumTable &by_slot = sums.table[2 * i], &by_stack = sums.table[2 * i + 1];
       for (int j = 0; j < run->cnt; ++j) {
         if (run->wt[j] == 0.f) continue;
@@ -536,21 +535,21 @@ int launch_tails(il_ctx *c) {
       }
       const int ns = by_slot.ns, acc = part > 0 || c->accumulate;
       const bool plain = ns == 1 && by_slot.w[0] == 1.f;
-      const char *dy[4] = {t.r->Ga, t.r->DU, t.r->Gb, t.r->DQKV};
+      char *const dy[4] = {t.r->Ga, t.r->DU, t.r->Gb, t.r->DQKV};
       const char *x[4] = {t.s->gl, t.s->h2, t.s->o, t.s->h1};
       const size_t w_off[4] = {b.w_fc2, b.w_fc1, b.w_o, b.w_qkv}, b_off[4] = {b.b_fc2, b.b_fc1, b.b_o, b.b_qkv};
       const int in[4] = {c->m, c->d, c->d, c->d};
       for (int j = 0; j < 4; ++j) {
         SumColsumJob &q = sums.job[sums.count++];
-        q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j & 1);
-        q.ysum = plain ? nullptr : c->YS[i][j];
+        q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j > 0);
+        char *first = dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb;
+        q.ysum = plain ? nullptr : first;
         q.partials = c->partials[i][j];
         sum_bytes += (double)(plain ? 1 : ns + 1) * c->N * wide[j] * c->eb;
         finals.job[finals.count++] = ColsumJob{q.partials, 0, q.cols, Gr(c, b_off[j]), acc};
         GemmArgs g = base_args();
         g.A = x[j]; g.lda = in[j]; g.a_kmajor = 1;
-        g.B = plain ? dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb : c->YS[i][j];
-        g.ldb = (int)wide[j]; g.b_kmajor = 1;
+        g.B = first; g.ldb = (int)wide[j]; g.b_kmajor = 1;
         g.M = in[j]; g.N = (int)wide[j]; g.K = c->N;
         g.epi = EPI_WGRAD; g.C = Gr(c, w_off[j]); g.ldc = (int)wide[j]; g.beta = acc;
         wg[nw++] = g;
@@ -591,14 +590,15 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
   int rc, ln_blocks = 0;
   for (const Run &run : runs) {
     const int S = run.cnt * N;
-    const size_t at = (size_t)run.s0 * N * d * eb;
-    char *Ga = r.Ga + at, *Gb = r.Gb + at, *DU = r.DU + (size_t)run.off * N * m * eb;
-    char *DQKV = r.DQKV + (size_t)run.off * N * 3 * d * eb;
+    const size_t slot = (size_t)run.s0 * N, stack = (size_t)run.off * N;
+    char *Ga = r.Ga + slot * d * eb, *Gb = r.Gb + stack * d * eb, *DU = r.DU + stack * m * eb;
+    char *DQKV = r.DQKV + stack * 3 * d * eb;
+    float *ln[2] = {r.ln[0] + (size_t)ln_blocks * 2 * d, r.ln[1] + (size_t)ln_blocks * 2 * d};
     int nblk = 0;
     // MLP
     if ((rc = linear_dgrad(c, Ga, b.w_fc2, S, m, d, EPI_GELU_BWD, DU, s.u, N))) return rc;
     if ((rc = linear_dgrad(c, DU, b.w_fc1, S, d, m, EPI_STORE, c->DH, nullptr, 0))) return rc;
-    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, r.Gb, r.ln[0] + (size_t)ln_blocks * 2 * d, &nblk))) return rc;
+    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk))) return rc;
     // attention
     const bool dots = attention_dsum_given(c->cfg.dtype, c->dh);
     if ((rc = linear_dgrad(c, Gb, b.w_o, S, d, d, dots ? EPI_STORE_DOT : EPI_STORE, c->DH, dots ? s.o : nullptr, N,
@@ -611,8 +611,7 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
       IL_TRY(hipStreamWaitEvent(c->main_stream, c->ev_tail[next / kGroup], 0));
       c->tail_pending[next / kGroup] = 0;
     }
-    if ((rc = ln_bwd(c, run, c->DH, s.xs, s.st1, b.ln1_g, c->ring[next].Ga, r.ln[1] + (size_t)ln_blocks * 2 * d, &nblk)))
-      return rc;
+    if ((rc = ln_bwd(c, run, c->DH, s.xs, s.st1, b.ln1_g, c->ring[next].Ga + slot * d * eb, ln[1], &nblk))) return rc;
     ln_blocks += nblk;
   }
   c->tails[c->ntails++] = Tail{&b, &s, &r, &runs, ln_blocks};

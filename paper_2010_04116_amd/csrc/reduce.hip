@@ -46,7 +46,8 @@ __device__ inline void store_vec(T *p, const float (&v)[V]) {
 
 // First stage, fused with the weighted sum over gradient streams: for every token row the kernel
 // forms the job's weighted sum of streams in fp32, optionally stores it (rounded to T) for the
-// weight-gradient GEMM, and accumulates its column sums (the bias gradient).  Bound by the bytes it
+// weight-gradient GEMM, and accumulates its column sums (the bias gradient).  ysum may lie on one of the
+// streams: a thread has read its elements of all of them before it writes.  Bound by the bytes it
 // reads and writes.  Grid (column groups, row splits, jobs); block = 32 column groups of V x 8 row
 // lanes with 16-byte accesses (V = 1: 64 columns x 4 row lanes, for columns that do not divide).
 template <typename T, int V>
@@ -55,8 +56,8 @@ __global__ __launch_bounds__(256) void sum_colsum_kernel(SumColsumJobs jobs) {
   __shared__ float red[RL][CG * V];
   const SumColsumJob &jb = jobs.job[blockIdx.z];
   const SumTable &tab = jobs.table[jb.table];
-  const T *__restrict__ Y = (const T *)jb.Y;
-  T *__restrict__ ysum = (T *)jb.ysum;
+  const T *Y = (const T *)jb.Y;
+  T *ysum = (T *)jb.ysum;
   float *__restrict__ partials = jb.partials;
   const int N = jobs.N, cols = jb.cols, ns = tab.ns;
   if ((int)blockIdx.x * CG * V >= cols) return;  // uniform: this job is narrower than the widest one

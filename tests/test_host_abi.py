@@ -172,3 +172,18 @@ def test_timing_model_host_functions_match_the_oracle():
         binding.il_optimal_microbatches(4, 0)
     lib = binding.load()
     assert lib.il_set_accumulation(None, 1, 0.5) == binding.IL_E_ARG
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_workspace_grows_by_what_is_kept_and_nothing_twice(n, dtype):
+    """What one more column of the MLP and one more component add to the workspace, byte for byte: the operands of
+    four blocks' tails for every live stream, one more slot of the gradient streams, no copies of either."""
+    w = synth.Workload("x", dtype, K=6, L=2, d=256, H=4, m=512, V=512, B=4, T=64, n=n)
+    eb = 4 if dtype == "f32" else 2
+    size = lambda **kw: binding.query_sizes(binding.make_config(w.with_(**kw)))[2]  # noqa: E731
+    live = max(binding.il_routing_plan(w.K, n)[0])
+    N, d, m, blocks = w.N, w.d, w.m, w.K * w.L
+    assert size(m=m + 64) - size() == 64 * (blocks * 2 * N * eb + 4 * live * N * eb + 2 * 64 * 4)
+    saved = N * (2 * d * 4 + (6 * d + 2 * m) * eb + w.H * 4 + 2 * 2 * 4)   # a block's activations
+    assert size(K=w.K + 1) - size() == w.L * saved + N * d * 4 + 4 * N * d * eb + N * d * 4   # stream, operand, dx of the head
