@@ -603,7 +603,9 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
 // With at least two wavefronts per SIMD demanded, the register budget is the 256 architectural VGPRs and the
 // compiler keeps the MFMA accumulators there; without, it places them in the accumulation registers and
 // moves every score to a VGPR and back (a third of the vector instructions at head width 64).  Head width
-// 256 does not fit that budget.
+// 256 does not fit that budget (256 + 256 registers and 16 bytes of scratch, dK / dV's need, also for dQ, which
+// alone takes 232 + 160); two launches are slower all the same: 32 x 128 tokens, 4 heads 45.2 us against 26.8, two
+// streams 49.5 against 45.7, 4 x 512, 8 heads 100.6 against 60.4.
 constexpr int bwd_roles(int dh) { return dh == 128 ? 3 : 2; }
 template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 128 ? 1 : 2))) void attn_bwd_mfma(
@@ -622,16 +624,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 128 ? 
 
 }  // namespace
 
-// A workgroup of four wavefronts takes 128 queries; where that leaves CUs without a workgroup, two
-// wavefronts take 64 (8 x 256 tokens, 8 heads of 64: 7.7 -> 7.2 us) - unless sequences are long, where the
-// keys, read twice as often, cost more than the idle CUs (2 x 900, 8 heads of 32: 13.6 -> 14.2 us).
+// A workgroup of four wavefronts takes 128 queries; where that leaves CUs without a workgroup, two wavefronts take
+// 64, but each of them reads the keys for half as many queries and has more of them to load.  Forward in us, four /
+// two wavefronts:
+//   width 64   8 x 64 tokens, 8 heads 4.64 / 4.62;  4 x 128, 16: 5.65 / 5.08;  8 x 256, 8: 7.78 / 7.34;
+//              2 x 512, 16: 11.45 / 10.99;  longer sequences lose (2 x 900, 8 heads of 32, when that width ran here: 13.6 / 14.2)
+//   width 128  4 x 64, 16 heads 5.33 / 6.00;  8 x 256, 4: 10.72 / 11.13;  2 x 512, 16: 16.94 / 18.23  (the two-wavefront
+//              form gets 230 + 134 registers from the compiler, one wavefront per SIMD, where four get 256 + 0 and two)
+//   width 256  16 x 64, 4 heads 8.62 / 9.01;  8 x 128, 4: 14.39 / 13.33;  4 x 256, 4: 22.14 / 21.93;  2 x 512, 8: 39.0 / 40.0
 template <int DH>
 hipError_t fwd(const bf16_t *qkv, int B, int T, int H, bf16_t *o, float *lse, hipStream_t s) {
-  const int tiles = (T + 127) / 128 * B * H;
-  if (tiles < 256 && T <= 512)
-    hipLaunchKernelGGL((attn_fwd_mfma<DH, 2>), dim3((T + 63) / 64, B * H), dim3(128), 0, s, qkv, T, H, o, lse);
-  else
-    hipLaunchKernelGGL((attn_fwd_mfma<DH, 4>), dim3((T + 127) / 128, B * H), dim3(256), 0, s, qkv, T, H, o, lse);
+  if constexpr (DH != 128) {
+    const int tiles = (T + 127) / 128 * B * H;
+    if (tiles < 256 && (DH == 64 ? T <= 512 : T > 64 && T <= 256)) {
+      hipLaunchKernelGGL((attn_fwd_mfma<DH, 2>), dim3((T + 63) / 64, B * H), dim3(128), 0, s, qkv, T, H, o, lse);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((attn_fwd_mfma<DH, 4>), dim3((T + 127) / 128, B * H), dim3(256), 0, s, qkv, T, H, o, lse);
   return hipGetLastError();
 }
 hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, void *o, float *lse,

@@ -136,3 +136,25 @@ def test_scores_below_any_mask_value(dtype, dh, low):
     t = np.arange(T)
     want = t / 2 if not np.isinf(low) else np.floor(t / 2)   # the mean of 0..t, of the even ones among them
     held(o, np.repeat(want[:, None], H * dh, axis=1), dtype, "o")
+
+
+@pytest.mark.parametrize("dh,T,H", [(64, 64, 2), (64, 512, 2), (64, 513, 2), (64, 129, 130), (128, 100, 2), (128, 260, 1),
+                                    (256, 64, 1), (256, 65, 1), (256, 256, 1), (256, 257, 1)])
+def test_bf16_products(dh, T, H):
+    """The bf16 matrix kernels at both sides of every line of their choice of workgroup.  Probabilities and dS are
+    rounded to bf16, 2^-9 each at most and independently, as is the result: 2^-8 of the norm, and twice that for
+    dQ, dK through two such factors."""
+    B = 2 if H <= 2 else 1
+    if H * dh > 2048:
+        B, H = B * H // 13, 13                 # (many workgroups: several batches instead)
+    qkv, g = draw(dh + T, B, T, H, dh)
+    print("case bf16", dh, T, B, H, flush=True)
+    o, dqkv = run("bf16", qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh, stored_o=o)
+    assert np.linalg.norm(o - wo) <= 2 ** -8 * np.linalg.norm(wo)
+    assert np.abs(o - wo).max() <= 2 ** -7 * np.abs(wo).max()
+    for i in range(3):
+        got, want = (a[:, i * H * dh:(i + 1) * H * dh] for a in (dqkv, wd))
+        assert np.linalg.norm(got - want) <= 2 ** -7 * np.linalg.norm(want), "QKV"[i]
+        rows = np.sqrt(((got - want) ** 2).sum(axis=1) / np.maximum((want ** 2).sum(axis=1), (want ** 2).sum() / len(want)))
+        assert rows.max() <= 2 ** -5, ("QKV"[i], int(rows.argmax()))
