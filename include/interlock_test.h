@@ -42,7 +42,9 @@ int il_profile_read(il_ctx *ctx, int32_t cap, const char **names, int64_t *launc
  *      the 64x64 tiles): C = acc as IEEE half, clamped to the finite range; if C2 is given also the softmax
  *      statistics of the fp32 accumulators: C2 = fp32 [M][G][2], G = ceil(N / 64), (max, sum of exp(z - max)) of
  *      every group of 64 columns, followed by fp32 [M] target logits z[row, aux[row]] with aux = int32 [M]
- *      targets (rows whose target is outside [0, N) are left unwritten);
+ *      targets (rows whose target is outside [0, N) are left unwritten) |
+ *      8 store (T) and, in C2 = fp32 [N / 32][M], the sums over 32 columns each of C as stored times
+ *      aux[row % aux_wrap] (bf16 operands, N a multiple of 32, data-gradient layout only);
  * tile: 0 = library's choice, else (bf16 only; "+4" = four wavefronts that only load)
  *       1 = 256x256 / 8 wavefronts in two groups that take turns, 2 = 128x128 / 4+4, two K steps staged, 3 = 128x128 / 4+4, four staged,
  *       4 = 64x64 / 4 wavefronts, 5 = 64x64 / 4+4, four staged, 6 = 256x128 / 8+4, three staged,
@@ -53,6 +55,16 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
                  int32_t ldb, int32_t a_kmajor, int32_t b_kmajor, int32_t epi, void *C, void *C2, int32_t ldc,
                  const void *bias, const float *res, const void *aux, int32_t aux_wrap, float scale,
                  int32_t beta, int32_t tile, void *stream);
+
+/*
+ * Kernel-level test hook: C[M,N] (fp32, row pitch ldc) = A[M,K] B[N,K]^T with K in `splits` parts (fewer if a part
+ * would be empty), each a whole number of 64-deep steps, whose products go to ws (fp32 [splits][M][N]) and are added
+ * up in order; with the plan of a head's dx: il_gemm_split_plan returns the number of parts the library would choose
+ * within ws_floats, and the tile through *tile.  N and ldc multiples of 4; otherwise as il_test_gemm.
+ */
+int il_test_gemm_splitk(int32_t dtype, const void *A, const void *B, int32_t M, int32_t N, int32_t K, int32_t splits,
+                        int32_t tile, float *ws, float *C, int32_t ldc, void *stream);
+int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws_floats, int32_t *tile);
 
 /*
  * Kernel-level test hook: the library's causal attention by itself.

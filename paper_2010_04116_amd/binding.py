@@ -25,7 +25,8 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_routing_plan", "il_profile_read", "il_status_string", "il_test_gemm", "il_lr_schedule",
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
-           "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum")
+           "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum",
+           "il_test_gemm_splitk", "il_gemm_split_plan")
 
 
 class il_config(C.Structure):
@@ -68,6 +69,8 @@ def load():
     lib.il_test_gemm.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, i32, i32, i32, vp, vp, i32, vp, vp, vp,
                                  i32, C.c_float, i32, i32, vp]
     lib.il_test_attention.argtypes = [i32, vp, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp]
+    lib.il_test_gemm_splitk.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
+    lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
     lib.il_lr_schedule.argtypes = [C.c_int64, i32, i32]
     lib.il_lr_schedule.restype = C.c_double
@@ -176,6 +179,21 @@ def il_test_gemm(dtype, A, B, M, N, K, lda, ldb, a_kmajor, b_kmajor, epi, Cout, 
                              ldc if ldc is not None else N, p(bias), p(res), p(aux), aux_wrap, scale, beta,
                              tile, stream)
     _check(rc, "il_test_gemm")
+
+
+def il_test_gemm_splitk(dtype, A, B, M, N, K, splits, tile, ws, Cout, ldc, stream=None):
+    """One split-K product (fp32 result) of the library's kernels (test hook)."""
+    _check(load().il_test_gemm_splitk(dtype, _ptr(A), _ptr(B), M, N, K, splits, tile, _ptr(ws), _ptr(Cout), ldc, stream),
+           "il_test_gemm_splitk")
+
+
+def il_gemm_split_plan(dtype, M, N, K, ws_floats):
+    """(parts, tile) the library takes for the data gradient of a head."""
+    tile = C.c_int32()
+    parts = load().il_gemm_split_plan(dtype, M, N, K, ws_floats, C.byref(tile))
+    if parts < 0:
+        raise InterlockError(parts, "il_gemm_split_plan")
+    return parts, tile.value
 
 
 def il_test_attention(dtype, qkv, batch, seq, heads, width, o, lse, d_o=None, streams=1, dqkv=None, dsum=None, stream=None):

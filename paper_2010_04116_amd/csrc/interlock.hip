@@ -1062,7 +1062,8 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
                  int32_t beta, int32_t tile, void *stream) {
   if (!A || !B || !C || M < 1 || N < 1 || K < 1) return IL_E_ARG;
   if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
-  if (epi < EPI_STORE || epi > EPI_LOGITS || tile < 0 || tile > 8) return IL_E_ARG;
+  if (epi < EPI_STORE || epi > EPI_STORE_DOT || tile < 0 || tile > 8) return IL_E_ARG;
+  if (epi == EPI_STORE_DOT && (dtype != IL_BF16 || !aux || !C2 || aux_wrap < 1)) return IL_E_ARG;
   if (epi == EPI_LOGITS && (dtype != IL_BF16 || (C2 && !aux))) return IL_E_ARG;
   if ((epi == EPI_BIAS || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RES) && !bias) return IL_E_ARG;
   if ((epi == EPI_BIAS_RES && !res) || (epi == EPI_BIAS_GELU && !C2)) return IL_E_ARG;
@@ -1078,8 +1079,29 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
     g.C2 = nullptr;
     g.aux = nullptr;
   }
+  if (epi == EPI_STORE_DOT) {
+    g.row_stats = (float *)C2;
+    g.C2 = nullptr;
+  }
   const hipError_t e = dtype == IL_F32 ? gemm_f32(g, (hipStream_t)stream) : gemm_bf16(g, (hipStream_t)stream);
   return e == hipSuccess ? IL_OK : (e == hipErrorInvalidValue ? IL_E_SHAPE : IL_E_HIP);
+}
+
+int il_test_gemm_splitk(int32_t dtype, const void *A, const void *B, int32_t M, int32_t N, int32_t K, int32_t splits,
+                        int32_t tile, float *ws, float *C, int32_t ldc, void *stream) {
+  if (!A || !B || !C || !ws || M < 1 || N < 1 || K < 1 || splits < 1 || tile < 0 || tile > 8) return IL_E_ARG;
+  if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
+  GemmArgs g = base_args();
+  g.A = A; g.B = B; g.M = M; g.N = N; g.K = K; g.lda = K; g.ldb = K; g.epi = EPI_STORE_F32; g.C = C; g.ldc = ldc;
+  const hipError_t e = gemm_splitk(dtype, g, SplitPlan{splits, tile}, ws, (hipStream_t)stream);
+  return e == hipSuccess ? IL_OK : (e == hipErrorInvalidValue ? IL_E_SHAPE : IL_E_HIP);
+}
+
+int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws_floats, int32_t *tile) {
+  if ((dtype != IL_F32 && dtype != IL_BF16) || M < 1 || N < 1 || K < 1) return IL_E_ARG;
+  const SplitPlan p = gemm_split_plan(dtype, M, N, K, ws_floats);
+  if (tile) *tile = p.tile;
+  return p.splits;
 }
 
 int il_attention_wants_dsum(int32_t dtype, int32_t width) { return attention_dsum_given(dtype, width) ? 1 : 0; }

@@ -126,9 +126,8 @@ def test_library_choice_at_the_benchmark_shapes():
 
 @pytest.mark.parametrize("tile", [0, 8])
 def test_persistent_kernel_second_round_ragged(tile):
-    """More than 256 tiles of 256x256 with ragged M and N (18 x 17 = 306 tiles): workgroups of the
-    persistent kernel take a second tile, the loaders run ahead into it while the first tile's epilogue
-    is still draining.  Every (layout, epilogue) the step uses."""
+    """More than 256 tiles of 256x256 with ragged M and N (18 x 17 = 306 tiles), more than the chip has CUs: a
+    second, partial round of workgroups.  Every (layout, epilogue) the step uses."""
     for i, (akm, bkm, epi) in enumerate(_COMBOS):
         M, N = (4360, 4104) if not akm else (4360 - 8, 4104)
         run_case(M, N, 128, akm, bkm, epi, tile, seed=70 + i, beta=int(epi == 6))
@@ -233,3 +232,104 @@ def test_f32_gemm(M, N, K, akm, bkm):
     # K fused multiply-adds and two adds, each within 2^-24 of the running magnitude
     bound = (K + 2) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(y) + np.abs(bias) + np.abs(res))
     assert np.all(np.abs(C.cpu().numpy() - want) <= bound)
+
+
+@pytest.mark.parametrize("akm,bkm,epi,beta", [(0, 1, 0, 0), (0, 1, 1, 0), (0, 1, 2, 0), (0, 0, 4, 0), (0, 0, 5, 0),
+                                              (1, 1, 6, 0), (1, 1, 6, 1)])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 32), (37, 3, 5), (67, 132, 33), (300, 200, 260), (2816, 3000, 40)])
+def test_f32_epilogues(M, N, K, akm, bkm, epi, beta):
+    """Every epilogue the step has in fp32, over both tiles and both load widths, with rows that wrap."""
+    import torch
+    rng = np.random.default_rng(M + 7 * N + K + epi)
+    x, y = (rng.normal(size=s).astype(np.float32) for s in ((M, K), (K, N)))
+    bias, c0 = rng.normal(size=N).astype(np.float32), rng.normal(size=(M, N)).astype(np.float32)
+    wrap = max(1, M // 3)
+    aux = rng.normal(size=(wrap, N)).astype(np.float32)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")  # noqa: E731
+    A, B = dev(x.T if akm else x), dev(y if bkm else y.T)
+    C, C2 = dev(c0) if beta else torch.full((M, N), float("nan"), device="cuda:0"), torch.zeros((M, N), device="cuda:0")
+    print("case f32", M, N, K, akm, bkm, epi, beta, flush=True)
+    b.il_test_gemm(0, A, B, M, N, K, A.shape[1], B.shape[1], akm, bkm, epi, C, C2=C2, bias=dev(bias), aux=dev(aux),
+                   aux_wrap=wrap, scale=0.5, beta=beta)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy().astype(np.float64)
+    acc = x.astype(np.float64) @ y
+    mag = np.abs(x).astype(np.float64) @ np.abs(y)
+    bound = (K + 2) * 2.0 ** -24 * (mag + np.abs(bias) + np.abs(c0))     # K multiply-adds, two more operations
+    if epi == 4:
+        f = _gelu_grad(aux.astype(np.float64))[np.arange(M) % wrap]
+        # the hardware's exponential and reciprocal: some 1e-6 of the derivative's terms, which reach 1.2
+        assert np.all(np.abs(got - acc * f) <= bound * (1 + np.abs(f)) + 4e-6 * np.abs(acc))
+        return
+    want = acc + (bias if epi in (1, 2) else 0)
+    if epi == 6:
+        want = 0.5 * acc + (c0 if beta else 0)
+    assert np.all(np.abs(got - want) <= bound)
+    if epi == 2:
+        g2 = C2.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(g2 - _gelu(got)) <= 4e-6 * np.abs(got) + 1e-12)
+
+
+@pytest.mark.parametrize("tile", [0] + TILES)
+@pytest.mark.parametrize("M,N,K,wrap", [(8, 32, 64, 8), (72, 96, 72, 40), (200, 160, 200, 200), (520, 288, 128, 130),
+                                        (300, 1056, 64, 64)])
+def test_row_sums_epilogue(M, N, K, wrap, tile):
+    """The product of a data gradient with the sums over 32 of its columns, as stored, times another operand."""
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    x, y, aux = (_bf16(rng.standard_normal(s)) for s in ((M, K), (N, K), (wrap, N)))
+    to = lambda v: torch.from_numpy(v).to(torch.bfloat16).to("cuda:0")  # noqa: E731
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    S = torch.full((M * (N // 32) + 64,), -7.0, device="cuda:0")
+    print("case row sums", M, N, K, wrap, tile, flush=True)
+    b.il_test_gemm(b.IL_BF16, to(x), to(y), M, N, K, K, K, 0, 0, 8, C, C2=S, aux=to(aux), aux_wrap=wrap, tile=tile)
+    torch.cuda.synchronize()
+    c = C.float().cpu().numpy().astype(np.float64)
+    want = x.astype(np.float64) @ y.T.astype(np.float64)
+    # one rounding to bf16 of a sum of K fp32 additions
+    assert np.all(np.abs(c - want) <= 2.0 ** -8 * np.abs(want) + K * 2.0 ** -24 * (np.abs(x) @ np.abs(y).T))
+    s = S.cpu().numpy().astype(np.float64)
+    t = (c * aux[np.arange(M) % wrap]).reshape(M, N // 32, 32)
+    assert np.all(np.abs(s[:M * (N // 32)].reshape(N // 32, M).T - t.sum(axis=2)) <= 32 * 2.0 ** -24 * np.abs(t).sum(axis=2))
+    assert np.all(s[M * (N // 32):] == -7.0)
+
+
+def _split_case(dtype, M, N, K, splits, tile, ldc):
+    import torch
+    rng = np.random.default_rng(M + N + K + splits)
+    x, y = (_bf16(rng.standard_normal(s)) for s in ((M, K), (N, K)))
+    tt = torch.float32 if dtype == b.IL_F32 else torch.bfloat16
+    to = lambda v: torch.from_numpy(v).to(tt).to("cuda:0")  # noqa: E731
+    C = torch.full((M, ldc), -7.0, device="cuda:0")
+    ws = torch.full((splits * M * N + 64,), float("nan"), device="cuda:0")
+    print("case split", dtype, M, N, K, splits, tile, flush=True)
+    b.il_test_gemm_splitk(dtype, to(x), to(y), M, N, K, splits, tile, ws, C, ldc)
+    torch.cuda.synchronize()
+    c = C.cpu().numpy().astype(np.float64)
+    want = x.astype(np.float64) @ y.T.astype(np.float64)
+    bound = (K + splits) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(y).T)
+    assert np.all(np.abs(c[:, :N] - want) <= bound)
+    assert np.all(c[:, N:] == -7.0) and torch.isnan(ws[splits * M * N:]).all()
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("M,N,K,splits", [(64, 64, 192, 2), (72, 40, 328, 3), (264, 136, 648, 5), (8, 8, 1032, 16),
+                                          (64, 512, 4104, 9), (40, 24, 128, 7)])
+def test_split_k_bf16(M, N, K, splits, tile):
+    """Parts of whole 64-deep steps, a last part that is shorter, more parts than steps; result rows of another pitch."""
+    _split_case(b.IL_BF16, M, N, K, splits, tile, N + 8)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(64, 64, 192, 2), (70, 44, 333, 3), (65, 132, 260, 4), (3, 4, 1001, 16), (130, 8, 65, 2)])
+def test_split_k_f32(M, N, K, splits):
+    _split_case(b.IL_F32, M, N, K, splits, 0, N + 4)
+
+
+@pytest.mark.parametrize("dtype", [b.IL_F32, b.IL_BF16])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 50304), (512, 512, 8192), (832, 768, 31992), (64, 1024, 256)])
+def test_split_plan_as_the_head_takes_it(M, N, K, dtype):
+    for floats in (2 ** 40, 3 * M * N, M * N, 0):
+        parts, tile = b.il_gemm_split_plan(dtype, M, N, K, floats)
+        assert 1 <= parts <= 32 and (parts == 1 or parts * M * N <= floats)
+    parts, tile = b.il_gemm_split_plan(dtype, M, N, K, 2 ** 40)
+    _split_case(dtype, M, N, K, parts, tile, N)
