@@ -255,7 +255,7 @@ __device__ inline void epilogue_strips(const GemmArgs &g, floatx16 (&acc)[MI][NI
 // Direct loads write 16 bytes per lane at consecutive LDS addresses in lane order, so the
 // LDS image of a tile is fixed and the swizzle is applied on the global side: the thread that
 // fills LDS chunk position p fetches the logical chunk that belongs there.
-//   k-contiguous tile: [row][BKT] (BKT*2 bytes per row), chunk c of row r at c ^ g(r)
+//   k-contiguous tile: [row][64 k] (128 bytes per row), chunk c of row r at c ^ g(r)
 //   k-major tile:      [k][ROWS]  (ROWS*2 bytes per k),  chunk c of k-row k at c ^ KS(k & 3), KS = 4 for k-rows of
 //                      256 bytes or more (all start at bank 0 of the 64 four-byte banks: the four k-rows that one
 //                      cycle of a transposing read touches, 64 bytes each, go to the four quarters of the bank
@@ -265,25 +265,27 @@ __device__ inline void epilogue_strips(const GemmArgs &g, floatx16 (&acc)[MI][NI
 // lane j the four k values kb..kb+3 of row j - exactly the MFMA operand order.
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short short4v;
 
-template <int ROWS, int BKT, bool KMAJOR, int NT>
+constexpr int kBK = 64;  // K step
+
+template <int ROWS, bool KMAJOR, int NT>
 struct DmaTile {
-  static constexpr int BYTES = ROWS * BKT * 2;
+  static constexpr int BYTES = ROWS * kBK * 2;
   static constexpr int NLD = BYTES / (NT * 16);  // loads per thread per K step
   static_assert(BYTES % (NT * 16) == 0 && NLD >= 1, "tile must divide over the threads");
-  static constexpr int RB = KMAJOR ? ROWS * 2 : BKT * 2;  // LDS bytes per row
+  static constexpr int RB = KMAJOR ? ROWS * 2 : kBK * 2;  // LDS bytes per row
   static constexpr int KS = ROWS >= 128 ? 4 : 2;          // k-major swizzle step, in 16-byte chunks
   uint32_t voff[NLD];
   int kadd[NLD];
   uint32_t kstride;
 
-  __device__ static inline int g(int row) { return BKT == 64 ? ((row ^ (row >> 3)) & 7) : ((row >> 1) & 3); }
+  __device__ static inline int g(int row) { return (row ^ (row >> 3)) & 7; }
 
   __device__ inline void init(int row0, int rows, int ld, int t) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const int p = i * NT + t;
       if constexpr (!KMAJOR) {
-        constexpr int CPR = BKT / 8;
+        constexpr int CPR = kBK / 8;
         const int row = p / CPR, chunk = (p % CPR) ^ g(row);
         kadd[i] = chunk * 8;
         voff[i] = row0 + row < rows ? ((uint32_t)(row0 + row) * ld + chunk * 8) * 2u : kOob;
@@ -307,12 +309,12 @@ struct DmaTile {
       dma16(rs, base + i * (NT * 16), ok ? voff[i] + adv : kOob);
     }
   }
-  // K-contiguous tiles with a 64-deep K step: the swizzled address of fragment (row block i, k
+  // K-contiguous tiles: the swizzled address of fragment (row block i, k
   // slice ks) differs from that of (0, 0) in bits 5-6 only, by an exclusive-or with a constant
   // (32 rows toggle bit 2 of g, a k slice adds 2 to the chunk index).  One lane-dependent base per
   // operand plus a constant per read costs no registers for precomputed addresses, which the
   // multiply loop of the large tile needs for its accumulators.
-  static constexpr bool XOR_FORM = !KMAJOR && BKT == 64;
+  static constexpr bool XOR_FORM = !KMAJOR;
   __device__ static inline uint32_t lane_base(uint32_t lds_addr, int rbase0, int lane) {
     const int row = rbase0 + (lane & 31);
     return lds_addr + row * RB + ((((lane >> 5) ^ g(row)) & 7) << 4);
@@ -364,17 +366,15 @@ struct GemmBatch {
 // nothing but load, NSTAGE-1 tiles ahead, and the multiplying wavefronts never have a load in
 // their LDS queue; without, every wavefront loads its share and then multiplies (the cheaper
 // arrangement when many small workgroups share a CU and cover for each other).
-// LOADERS: 0 = every wavefront loads; 1 = loader wavefronts, multiply loop as the compiler
-// schedules it; 2 = loader wavefronts and the hand-pipelined multiply loop (what the library uses).
+// The multiply loop is hand-pipelined where it has the wavefront's LDS queue to itself.
 constexpr int kLoaderWaves = 4;
-template <int BM, int BN, int WGM, int WGN, int BKT, int NSTAGE, bool AKM, bool BKM, int EPI, int LOADERS = 0>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS>
 __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) void gemm_dma_kernel(GemmBatch batch) {
-  constexpr bool SPEC = LOADERS != 0, PIPE = LOADERS == 2;
   constexpr int NC = 64 * WGM * WGN;                // multiplying threads
-  constexpr int NL = SPEC ? 64 * kLoaderWaves : NC;  // threads that share the loading of one tile
+  constexpr int NL = LOADERS ? 64 * kLoaderWaves : NC;  // threads that share the loading of one tile
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int MI = WTM / 32, NI = WTN / 32;
-  constexpr int ABYTES = BM * BKT * 2, STAGE = (BM + BN) * BKT * 2;
+  constexpr int ABYTES = BM * kBK * 2, STAGE = (BM + BN) * kBK * 2;
   constexpr int EPIB = WGM * WGN * EpiStrip<WTN>::FLOATS * 4;  // epilogue staging reuses the operand buffers
   __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE > EPIB ? NSTAGE * STAGE : EPIB];
 
@@ -398,20 +398,20 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
   const int m0 = tm * BM, n0 = tn * BN;
 
   const BufRsrc ra = make_rsrc(g.A, g.a_bytes), rb = make_rsrc(g.B, g.b_bytes);
-  typedef DmaTile<BM, BKT, AKM, NL> TA;
-  typedef DmaTile<BN, BKT, BKM, NL> TB;
+  typedef DmaTile<BM, AKM, NL> TA;
+  typedef DmaTile<BN, BKM, NL> TB;
   TA la;
   TB lb;
   la.init(m0, g.M, g.lda, t % NL);
   lb.init(n0, g.N, g.ldb, t % NL);
   const int lwave = wave % (NL / 64);             // position of this wavefront among the loaders of a tile
-  const bool loader = SPEC && wave >= WGM * WGN;  // this wavefront only loads (uniform)
+  const bool loader = LOADERS && wave >= WGM * WGN;  // this wavefront only loads (uniform)
   constexpr int LPS = TA::NLD + TB::NLD;  // loads per thread per K step
-  const int nk = (ke - kb0 + BKT - 1) / BKT;
+  const int nk = (ke - kb0 + kBK - 1) / kBK;
   auto issue = [&](int kt) {
     char *st = smem + (kt % NSTAGE) * STAGE;
-    la.issue(ra, st, lwave, kb0 + kt * BKT, ke);
-    lb.issue(rb, st + ABYTES, lwave, kb0 + kt * BKT, ke);
+    la.issue(ra, st, lwave, kb0 + kt * kBK, ke);
+    lb.issue(rb, st + ABYTES, lwave, kb0 + kt * kBK, ke);
   };
 
   floatx16 acc[MI][NI];
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
   // K steps kt .. kt+NSTAGE-2 are in flight while step kt is multiplied; one barrier per step:
   // it publishes step kt (every loading thread waited for its own loads of it) and retires the
   // buffer of step kt-1, which the loads issued right after it overwrite.
-  if (!SPEC || loader) {
+  if (!LOADERS || loader) {
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
       if (s < nk) issue(s);
@@ -447,25 +447,25 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
   }
 
   for (int kt = 0; kt < nk; ++kt) {
-    if constexpr (!SPEC) {
+    if constexpr (!LOADERS) {
       if (nk - 1 - kt >= NSTAGE - 2)
         wait_vmcnt<(NSTAGE - 2) * LPS>();
       else
         wait_vmcnt<0>();
     }
     __syncthreads();
-    if constexpr (!SPEC) {
+    if constexpr (!LOADERS) {
       if (kt + NSTAGE - 1 < nk) issue(kt + NSTAGE - 1);
     }
     const char *sa = smem + (kt % NSTAGE) * STAGE;
     const char *sb = sa + ABYTES;
     const uint32_t soff = (uint32_t)(kt % NSTAGE) * STAGE;  // (added before the exclusive-or: no carry into bits 4-6)
-    if constexpr (PIPE) {
+    if constexpr (LOADERS) {
       // Software pipeline over the (k slice, row block) slots of the step: the A fragment of the next
       // slot and, two slots before a new k slice, its B fragments are requested before the MFMAs of
       // the current slot, and the scheduler is held to that order (one group of LDS reads, then the
       // slot's MFMAs), so a read's latency passes under the previous slot's matrix work.
-      constexpr int KS = BKT / 16, ARD = AKM ? 2 : 1, BRD = BKM ? 2 : 1;  // LDS instructions per fragment
+      constexpr int KS = kBK / 16, ARD = AKM ? 2 : 1, BRD = BKM ? 2 : 1;  // LDS instructions per fragment
       auto getA = [&](int ks, int i) {
         return TA::XOR_FORM ? TA::frag_x(xa + soff, i, ks) : TA::frag(sa, wm * WTM + i * 32, ks, lane);
       };
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
       continue;
     }
 #pragma unroll
-    for (int ks = 0; ks < BKT / 16; ++ks) {
+    for (int ks = 0; ks < kBK / 16; ++ks) {
       bf16x8 af[MI], bfr[NI];
 #pragma unroll
       for (int i = 0; i < MI; ++i)
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
 // group's products occupy the matrix units, the other reads its next fragments from LDS and issues direct
 // loads; a workgroup barrier hands over.  No wavefront both waits for LDS and feeds the matrix unit, and -
 // unlike with separate loader wavefronts, which leave 168 registers to each of twelve - a wavefront has the
-// registers for all fragments of 32 products (512 matrix cycles) besides its 128 accumulators.
+// registers for all fragments of 16 products (512 matrix cycles) besides its 128 accumulators.
 //
 // A wavefront (wm, wn) owns columns 64 wn .. 64 wn + 63 and rows 64 wm .. 64 wm + 63 of both 128-row halves.
 // Two K steps are staged, 2 x 64 KB, each operand as two tiles of 128 rows.  A K step is two phases,
@@ -539,12 +539,12 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
 // Every read of a phase has returned before the barrier that ends its reading part (lgkmcnt 0), and the
 // next phase's loads come after that barrier, so a load never meets a read of the slot it refills; and a
 // load is awaited (vmcnt: eight younger ones may be outstanding, each wavefront for its own, then the
-// barrier) three phases after it was issued - one and a half K steps, where a two-stage ring of whole tiles
-// gives one.
+// barrier) two phases after it was issued and read after three - one and a half K steps, where a two-stage
+// ring of whole tiles gives one.
 //
 // Bound: with every CU busy the part holds 1.6-1.7 GHz under its power limit on products of this kind, and
-// the kernel keeps the matrix units at 87 % of that clock (8192^3: 1.44 PFLOP/s; with loader wavefronts and
-// a persistent grid 1.39; data gradients 8192 x 2048 x 6144: 164 -> 150 us).  Two barriers more per K step
+// the kernel keeps the matrix units busy 81-86 % of its cycles (8192^3: 1.44 PFLOP/s; with loader wavefronts and
+// a persistent grid 1.39; data gradients 8192 x 2048 x 6144: 164 -> 150 us).  A K step has four barriers; four more
 // (a phase per quadrant) cost 9 %, 16x16x32 products 5 %.
 #define IL_FENCE()                         \
   do {                                     \
@@ -557,8 +557,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ __attribute__((aligned(1024))) char smem[8 * HB];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 2, wn = wave & 3;
-  typedef DmaTile<128, 64, AKM, 512> TA;
-  typedef DmaTile<128, 64, BKM, 512> TB;
+  typedef DmaTile<128, AKM, 512> TA;
+  typedef DmaTile<128, BKM, 512> TB;
   static_assert(TA::NLD == 2 && TB::NLD == 2, "the load counts below");
 
   int prob = 0, tile0 = 0;
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 thread_local const KernelTimer *tl_timer = nullptr;  // armed by gemm_time_next()
 
-template <int BM, int BN, int WGM, int WGN, int BKT, int NSTAGE, bool AKM, bool BKM, int EPI, int LOADERS = 0>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS>
 hipError_t launch_dma(GemmBatch &b, hipStream_t s) {
   int tiles = 0;
   for (int i = 0; i < b.count; ++i) {
@@ -687,10 +687,10 @@ hipError_t launch_dma(GemmBatch &b, hipStream_t s) {
   constexpr int nthreads = 64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0));
   if (const KernelTimer *t = tl_timer) {
     tl_timer = nullptr;
-    hipExtLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, BKT, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
+    hipExtLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
                           dim3(nthreads), 0, s, t->start, t->stop, 0, b);
   } else {
-    hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, BKT, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
+    hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
                        dim3(nthreads), 0, s, b);
   }
   return hipGetLastError();
@@ -730,12 +730,12 @@ hipError_t pick_tile(GemmBatch &b, hipStream_t s) {
   switch (b.p[0].tile) {
     case 1:
     case 8: return launch_pair<AKM, BKM, EPI>(b, s);
-    case 2: return launch_dma<128, 128, 2, 2, 64, 2, AKM, BKM, EPI, 2>(b, s);
-    case 3: return launch_dma<128, 128, 2, 2, 64, 4, AKM, BKM, EPI, 2>(b, s);
-    case 4: if constexpr (EPI != EPI_LOGITS) return launch_dma<64, 64, 2, 2, 64, 2, AKM, BKM, EPI>(b, s); else break;
-    case 5: if constexpr (EPI != EPI_LOGITS) return launch_dma<64, 64, 2, 2, 64, 4, AKM, BKM, EPI, 2>(b, s); else break;
-    case 6: return launch_dma<256, 128, 4, 2, 64, 3, AKM, BKM, EPI, 2>(b, s);
-    case 7: return launch_dma<128, 256, 2, 4, 64, 3, AKM, BKM, EPI, 2>(b, s);
+    case 2: return launch_dma<128, 128, 2, 2, 2, AKM, BKM, EPI, true>(b, s);
+    case 3: return launch_dma<128, 128, 2, 2, 4, AKM, BKM, EPI, true>(b, s);
+    case 4: if constexpr (EPI != EPI_LOGITS) return launch_dma<64, 64, 2, 2, 2, AKM, BKM, EPI, false>(b, s); else break;
+    case 5: if constexpr (EPI != EPI_LOGITS) return launch_dma<64, 64, 2, 2, 4, AKM, BKM, EPI, true>(b, s); else break;
+    case 6: return launch_dma<256, 128, 4, 2, 3, AKM, BKM, EPI, true>(b, s);
+    case 7: return launch_dma<128, 256, 2, 4, 3, AKM, BKM, EPI, true>(b, s);
     default: break;
   }
   // Measured on MI355X, with operands that are not already in cache (inside a training step a
@@ -747,18 +747,18 @@ hipError_t pick_tile(GemmBatch &b, hipStream_t s) {
   // most two workgroups land on a CU (the deeper ring covers the trip to HBM), beyond that up to five
   // plain small workgroups per CU that cover for each other.
   if (t256 >= 160) return launch_pair<AKM, BKM, EPI>(b, s);
-  if (t128 >= 192 && t128 <= 256) return launch_dma<128, 128, 2, 2, 64, 4, AKM, BKM, EPI, 2>(b, s);
+  if (t128 >= 192 && t128 <= 256) return launch_dma<128, 128, 2, 2, 4, AKM, BKM, EPI, true>(b, s);
   // about one 256x128 (or 128x256) tile per CU, three stages: as good as the 128x128 tile on cached
   // operands and 15-20 % better on operands from HBM (fewer bytes per flop, deeper ring)
   if (std::min(t256x128, t128x256) >= 192 && std::min(t256x128, t128x256) <= 256)
-    return t128x256 <= t256x128 ? launch_dma<128, 256, 2, 4, 64, 3, AKM, BKM, EPI, 2>(b, s)
-                                : launch_dma<256, 128, 4, 2, 64, 3, AKM, BKM, EPI, 2>(b, s);
-  if (t128 > 256) return launch_dma<128, 128, 2, 2, 64, 2, AKM, BKM, EPI, 2>(b, s);
+    return t128x256 <= t256x128 ? launch_dma<128, 256, 2, 4, 3, AKM, BKM, EPI, true>(b, s)
+                                : launch_dma<256, 128, 4, 2, 3, AKM, BKM, EPI, true>(b, s);
+  if (t128 > 256) return launch_dma<128, 128, 2, 2, 2, AKM, BKM, EPI, true>(b, s);
   if constexpr (EPI == EPI_LOGITS) {
-    return launch_dma<128, 128, 2, 2, 64, 4, AKM, BKM, EPI, 2>(b, s);  // (never the 32-wide wave tiles)
+    return launch_dma<128, 128, 2, 2, 4, AKM, BKM, EPI, true>(b, s);  // (never the 32-wide wave tiles)
   } else {
-    if (t64 <= 512) return launch_dma<64, 64, 2, 2, 64, 4, AKM, BKM, EPI, 2>(b, s);
-    return launch_dma<64, 64, 2, 2, 64, 2, AKM, BKM, EPI>(b, s);
+    if (t64 <= 512) return launch_dma<64, 64, 2, 2, 4, AKM, BKM, EPI, true>(b, s);
+    return launch_dma<64, 64, 2, 2, 2, AKM, BKM, EPI, false>(b, s);
   }
 }
 
