@@ -23,7 +23,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3
+PEAK_F32_TFLOPS = 157.3       # its fp32 matrix instructions
 PEAK_HBM_GBS = 8000.0
 
 # HBM-side bytes per GEMM kernel launch (average over the GEMM launches of one step), from two
@@ -32,10 +32,10 @@ PEAK_HBM_GBS = 8000.0
 # profiles/traffic_<workload>.md.  bench.py cannot run the profiler on itself, so the figures are
 # carried here for the workloads they were measured on and are null for any other.
 MEASURED_TRAFFIC = {
-    "small_bf16_n2": 41.98e6,   # 32.190 MB read + 9.788 MB written per launch, 1536 launches (1.85 x)
-    "large_bf16_n2": 478.98e6,  # 390.00 MB read + 88.97 MB written per launch, 4320 launches (2.15 x algorithmic)
-    "medium_bf16_n2": 179.40e6,  # 140.98 + 38.42 MB, 2880 launches (1.88 x)
-    "many_head_bf16_n3": 238.28e6,  # 190.65 + 47.63 MB, 2880 launches (1.99 x)
+    "small_bf16_n2": 37.89e6,   # 27.66 MB read + 10.23 MB written per launch, 1104 launches (1.58 x algorithmic)
+    "large_bf16_n2": 462.79e6,  # 369.64 + 93.15 MB, 4104 launches (1.95 x)
+    "medium_bf16_n2": 172.80e6,  # 132.79 + 40.02 MB, 2736 launches (1.69 x)
+    "many_head_bf16_n3": 209.19e6,  # 158.61 + 50.59 MB, 3072 launches (1.65 x)
 }
 
 # which roofline bounds a kernel class, and the peak its fraction is taken against
@@ -223,7 +223,7 @@ def measure(w, steps, warmup, peaks):
     achieved = g_fl / (g_ms * 1e-3) / 1e12 if g_ms > 0 else 0.0
     iso = g_fl / (iso_ms * 1e-3) / 1e12 if iso_ms > 0 else 0.0
     traffic = MEASURED_TRAFFIC.get(f"{w.name}_{w.dtype}_n{w.n}")
-    roof = {"bound": "mfma" if bf else "alu",
+    roof = {"bound": "mfma",
             "kernel": "gemm_dma_kernel / gemm_pair_kernel: every GEMM launch of one step (forward, dgrad, wgrad, head)"
             if bf else "gemm_f32_kernel: every GEMM launch of one step",
             "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
@@ -242,11 +242,9 @@ def measure(w, steps, warmup, peaks):
     kernels = {}
     for k, v in prof.items():
         bound = CLASS_BOUND.get(k, "hbm")
-        if not bf and bound == "mfma":
-            bound = "alu"
         t = v["ms_per_step"] * 1e-3
         e = {"ms_per_step": round(v["ms_per_step"], 4), "launches": v["launches_per_step"], "bound": bound}
-        if bound in ("mfma", "alu"):
+        if bound == "mfma":
             e["tflops"] = v["flops_per_step"] / t / 1e12 if t > 0 and v["flops_per_step"] else None
             e["frac"] = e["tflops"] / peak if e["tflops"] else None
             if bf and k in gemm:                       # the kernel alone, and inside the two-stream step
@@ -421,6 +419,44 @@ def config_of(w):
             "n": w.n, "route": "window_sum", "param_seed": synth.PARAM_SEED, "token_seed": synth.TOKEN_SEED}
 
 
+def short(x):
+    """Floats to six significant digits, all the way down."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: short(v) for k, v in x.items()}
+    return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def pick(d, *keys):
+    return {k: d[k] for k in keys if d.get(k) is not None}
+
+
+def summary_line(out):
+    """What goes to stdout: the metric, its roofline and one line per kernel class and further workload.  Everything
+    measured goes to --full; a reader of the last few kilobytes of a log still finds this line whole."""
+    line = {k: out[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                "scaling", "vs_baseline", "dtype", "data", "config")}
+    line["timed_as"] = out["launch"]["timed_as"]
+    line.update(pick(out, "mfma_utilisation_pct_of_bf16_peak", "algorithmic_tflop_per_step"))
+    r = out["roofline"]
+    line["roofline"] = dict(pick(r, "bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "launches_per_step",
+                                 "avg_launch_ms", "algorithmic_bytes_per_launch", "frac_is", "frac_of_measured_peak"),
+                            isolated_frac=r["isolated"]["frac"])
+    line["kernels"] = {k: pick(v, "ms_per_step", "bound", "frac") for k, v in out["kernels"].items()}
+    line["optimizer"] = pick(out["optimizer"], "parameters", "ms", "achieved", "unit", "frac")
+    line["embedding"] = pick(out["embedding"], "forward_ms", "backward_ms")
+    if "measured_peaks" in out:
+        line["measured_peaks"] = pick(out["measured_peaks"], "mfma_only_tflops", "stream_copy_gbs")
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = pick(out["cpu_baseline"], "value", "unit", "cores", "kind", "seconds", "extrapolated")
+    line["other_workloads"] = {
+        k: dict(pick(v, "ms_per_step", "tokens_per_s", "mfma_utilisation_pct_of_bf16_peak"),
+                gemm_frac=v["roofline"]["frac"], gemm_isolated_frac=v["roofline"]["isolated"]["frac"])
+        for k, v in out.get("other_workloads", {}).items()}
+    return short(line)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -432,6 +468,7 @@ def main():
                     help="comma-separated further workloads reported under other_workloads ('none' = none); "
                          "name:n overrides the window, e.g. large:6")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--full", metavar="FILE", help="write everything that was measured to this file, as JSON")
     ap.add_argument("--no-peaks", action="store_true", help="skip the MFMA-only / streaming-copy micro-benchmarks")
     ap.add_argument("--peaks-only", action="store_true",
                     help="run only the MFMA-only / streaming-copy micro-benchmarks and print their JSON line")
@@ -493,7 +530,10 @@ def main():
         others[f"{wo.name}_{wo.dtype}_n{wo.n}"] = ro
     if others:
         out["other_workloads"] = others
-    print(json.dumps(out))
+    if a.full:
+        with open(a.full, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(summary_line(out)))
 
 
 if __name__ == "__main__":

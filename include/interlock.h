@@ -93,8 +93,9 @@ typedef struct il_config {
   int32_t dtype;                /* il_dtype                                          */
   int32_t route;                /* il_route                                          */
   float ln_eps;                 /* e.g. 1e-5                                         */
-  int32_t head_chunk;           /* token rows per head chunk (0 = library default: half the
-                                   rows, at most 2048, halved until the tile is below 2 GiB);
+  int32_t head_chunk;           /* token rows per head chunk (0 = library default: the fewest equal
+                                   chunks, at least two, of at most 2048 rows and below 2 GiB of
+                                   logits, rounded up to multiples of 64 rows in bf16);
                                    only a [head_chunk, vocab] logits tile ever exists      */
   int32_t profile;              /* 0: off.  1: HIP event times per kernel class (read with
                                    il_profile_read, interlock_test.h); everything then runs on
@@ -166,7 +167,8 @@ int il_head_xent(il_ctx *ctx, int32_t k, const float *x_k, const int32_t *target
  * dL_k/dx_k into the context's gradient stream).
  * IL_E_WORKSPACE when batch*seq*d_model + head_chunk*vocab elements of `dtype` + batch*seq*4 bytes +
  * the split-K partials (up to 8 * head_chunk * d_model floats) + in bf16 the tile's softmax statistics
- * (head_chunk * (ceil(vocab/64) * 8 + 4) bytes) exceed the static array; IL_E_SHAPE when
+ * (head_chunk * (ceil(vocab/64) * 8 + 4) bytes) exceed the static array - with head_chunk = 0 also after chunks of
+ * min(batch*seq/2, 2048) rows, rounded down to a multiple of 64 in bf16, were tried; IL_E_SHAPE when
  * head_blocks > 0 (such heads keep activations in the workspace; use il_head_xent); IL_E_HIP when the
  * array's address on the current device cannot be resolved.  Nothing in the array has to start at
  * zero: every piece is written before it is read within the call.  All calls on one GPU share the one

@@ -543,9 +543,10 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
 // ring of whole tiles gives one.
 //
 // Bound: with every CU busy the part holds 1.6-1.7 GHz under its power limit on products of this kind, and
-// the kernel keeps the matrix units busy 81-86 % of its cycles (8192^3: 1.44 PFLOP/s; with loader wavefronts and
-// a persistent grid 1.39; data gradients 8192 x 2048 x 6144: 164 -> 150 us).  A K step has four barriers; four more
-// (a phase per quadrant) cost 9 %, 16x16x32 products 5 %.
+// 8192^3 at 1.44 PFLOP/s is 81-86 % of the matrix units' rate at that clock (with loader wavefronts and a
+// persistent grid 1.39; data gradients 8192 x 2048 x 6144: 164 -> 150 us); the counters say busy 86-90 % of the
+// CUs' busy cycles in a d = 2048 step's plain-store launches, 59-60 % where the epilogue is heavy.  A K step has
+// four barriers; four more (a phase per quadrant) cost 9 %, 16x16x32 products 5 %.
 #define IL_FENCE()                         \
   do {                                     \
     asm volatile("" ::: "memory");         \
