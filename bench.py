@@ -443,7 +443,7 @@ def summary_line(out):
     line["roofline"] = dict(pick(r, "bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "launches_per_step",
                                  "avg_launch_ms", "algorithmic_bytes_per_launch", "frac_is", "frac_of_measured_peak"),
                             isolated_frac=r["isolated"]["frac"])
-    line["kernels"] = {k: pick(v, "ms_per_step", "bound", "frac") for k, v in out["kernels"].items()}
+    line["kernels"] = {k: pick(v, "ms_per_step", "bound", "frac", "kernel_frac") for k, v in out["kernels"].items()}
     line["optimizer"] = pick(out["optimizer"], "parameters", "ms", "achieved", "unit", "frac")
     line["embedding"] = pick(out["embedding"], "forward_ms", "backward_ms")
     if "measured_peaks" in out:
@@ -512,7 +512,7 @@ def main():
     if w.dtype == "bf16" and not a.no_peaks:
         out["gemm_reference"] = gemm_reference(w)
     out["target"] = {"mfma_utilisation_pct": 50.0, "met": out["mfma_utilisation_pct_of_bf16_peak"] >= 50.0,
-                     "note": "north star: >= 50 % of bf16 MFMA peak on the GEMM-dominated configurations"}
+                     "note": "aim: >= 50 % of bf16 MFMA peak on the GEMM-dominated configurations"}
     if not a.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, params, x0.astype(np.float64), tgt)
     del params, x0, tgt

@@ -1,7 +1,7 @@
 """Shared helpers of the GPU parity tests: run the HIP path and the oracle on the same
 seeded inputs and compare element by element.
 
-Tolerances (the benchmark spec): fp32 - relative error <= 1e-4 on every loss and on every
+Tolerances: fp32 - relative error <= 1e-4 on every loss and on every
 gradient tensor; bf16 - <= 1e-3 on losses, <= 2e-2 on gradient tensors.  A loss is compared
 as |a-b|/|b|; a gradient tensor as ||a-b||_2/||b||_2 over the whole tensor.
 
@@ -19,8 +19,8 @@ tile, so every tensor is also held to three element-level bounds:
 A completely wrong row scores about 1 (or more) on `rows`, a zeroed tile 1 on both, a single
 garbage or dropped element 0.5 or more on `elem`; rounding noise scores a small multiple of the tensor
 tolerance (the bounds are ROW_FACTOR and ELEM_FACTOR times it).  Measured worst over all cases, the
-full-size runs included: bf16 tensor 8.5e-3, rows 1.4e-2, cols 4.8e-2, elem 5.3e-2; fp32 9e-7, 1e-6,
-2.4e-6, 3e-6.
+full-size runs included: bf16 tensor 9.3e-3, rows 1.4e-2, cols 6.4e-2, elem 0.11 (one column of a head matrix; 0.05 to
+0.11 as x_0 changes in its last bits); fp32 2e-6, 3e-6, 4e-6, 9e-6.
 """
 import json
 import os
