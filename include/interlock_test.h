@@ -45,7 +45,8 @@ int il_profile_read(il_ctx *ctx, int32_t cap, const char **names, int64_t *launc
  *      targets (rows whose target is outside [0, N) are left unwritten) |
  *      8 store (T) and, in C2 = fp32 [N / 32][M], the sums over 32 columns each of C as stored times
  *      aux[row % aux_wrap] (bf16 operands, N a multiple of 32, data-gradient layout only);
- * tile: 0 = library's choice, else (bf16 only; "+4" = four wavefronts that only load)
+ * tile: 0 = library's choice, else for fp32 2 = 128x128, 3 = 128x64, any other 64x64 (operands whose rows do not
+ *       divide by four always take the last), and for bf16 ("+4" = four wavefronts that only load)
  *       1 = 256x256 / 8 wavefronts in two groups that take turns, 2 = 128x128 / 4+4, two K steps staged, 3 = 128x128 / 4+4, four staged,
  *       4 = 64x64 / 4 wavefronts, 5 = 64x64 / 4+4, four staged, 6 = 256x128 / 8+4, three staged,
  *       7 = 128x256 / 8+4, three staged, 8 = the same as 1.

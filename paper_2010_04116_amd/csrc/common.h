@@ -120,7 +120,7 @@ struct GemmArgs {
   uint32_t a_bytes, b_bytes;  // operand extents in bytes (filled by the bf16 front end)
   int splits, k_per;  // split-K: part i of `splits` sums k in [i k_per, (i + 1) k_per) into C + i M N (fp32 outputs
                       // with ldc = N); 0 = one part
-  int tile;           // bf16: 0 = choose by shape, 1 = 256x256, 2 / 3 = 128x128 with 2 / 4 stages, 4 / 5 = 64x64 with 2 / 4,
+  int tile;           // 0 = choose by shape; fp32: 2 = 128x128, 3 = 128x64, 4 = 64x64; bf16: 1 = 256x256, 2 / 3 = 128x128 with 2 / 4 stages, 4 / 5 = 64x64 with 2 / 4,
                       // 6 = 256x128, 7 = 128x256 (three stages), 8 = 1
   int beta;           // EPI_WGRAD: accumulate into C
   // EPI_STORE_DOT: row_stats.  EPI_LOGITS, all optional together: row_stats [M][ceil(N / kStatGroup)][2] fp32, row_targets [M] int32,

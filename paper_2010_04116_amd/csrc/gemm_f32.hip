@@ -1,20 +1,22 @@
-// fp32 GEMM (il_config.dtype == IL_F32) on the matrix cores: v_mfma_f32_32x32x2_f32, fp32 operands,
-// fp32 multiply-add, no reduced-precision step anywhere.  Arbitrary M, N, K, both operand layouts,
-// the library's fused epilogues.
+// fp32 GEMM (il_config.dtype == IL_F32) on the bf16 matrix instructions: every fp32 operand element is the sum of
+// three bf16 and a product of two elements the sum of six bf16 products, accumulated in fp32.  Arbitrary M, N, K,
+// both operand layouts, the library's fused epilogues.
 //
-// Bound: the fp32 matrix rate (64 cycles per 32x32x2 product and SIMD, 256 flop per clock and CU -
-// twice what single fused multiply-adds reach, which is what the plain-FMA kernel that stood here was
-// limited by: it ran at 14 TFLOP/s over a step of d = 512, 2048 rows).  A product's operands are two
-// registers per lane, so a K step of 32 is 1024 matrix cycles per wavefront for a 64x64 tile against
-// 16 KB of operands: neither LDS nor L2 is near its limit, and what has to be arranged is only that
-// loads are far enough ahead and that every CU has a tile.  As in the bf16 kernels, four loader
-// wavefronts per workgroup issue direct HBM -> LDS loads several K steps ahead.
+// Precision.  hi + mid + lo holds all 24 bits; the three products left out are below 2^-26 of the largest.  What
+// remains are the roundings of the accumulation, and there are fewer of them than with the fp32 instruction
+// (v_mfma_f32_32x32x2_f32: two k at a time): against 64 bits the relative error (2-norm) at 2048 x 512 x 2048 is
+// 3.5e-7 where that instruction gave 8.1e-7, at 256 x 256 x 31992 1.6e-6 and 3.2e-6, at K = 16 3.3e-8 and 7.3e-8;
+// no shape, layout or distribution tried (normal, with an offset, over ten decades, probabilities) was worse.
+// What comes out not finite is computed again with the fp32 instruction: an infinity splits into NaN parts.
 //
-// The k index of a product is a summation label: lane half h of product e in k group g takes
-// k = 8 g + 4 h + e, so a k-contiguous operand is read as one 16-byte vector per lane for four
-// products; a k-major operand is read as four 4-byte values whose 32 lanes are consecutive.
+// Bound: 6 x 32 matrix cycles for 32 x 32 x 16, where the fp32 instruction takes 8 x 64: 2.7 times its rate at equal
+// clock.  4096 x 4096 x 2048 558 -> 328 us (210 TFLOP/s, 1.26 PFLOP/s of bf16 products: the clock the power limit
+// allows); 2048 x 2048 x 512 with GELU 47 -> 31, 4096 x 512 x 2048 74 -> 51, 2048 x 512 x 2048 45 -> 33 us: small
+// outputs are bound by what a CU is delivered (64 KB and four products of 64 x 64 x 64 every 0.9 us), not by the
+// matrix units.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm_tile.h"
@@ -23,12 +25,28 @@
 namespace il {
 namespace {
 
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short short4v;
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
-constexpr int kBK = 32;           // K step
-constexpr int kLoaders = 4;       // loader wavefronts per workgroup
-constexpr int NL = 64 * kLoaders;
+// Loading threads of a workgroup, beside the four wavefronts that multiply: eight wavefronts in two per SIMD, so that
+// one converts while the other waits (four: 33 -> 36 us at 2048 x 512 x 2048, 328 -> 345 at 4096 x 4096 x 2048).
+constexpr int NL = 512;
+constexpr int kAhead = 3;  // K steps in flight (four or five change nothing)
+
+// Loads to registers, which the compiler waits for; outside the descriptor's range they return 0.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ inline Rsrc rsrc(const void *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ inline floatx4 load_f32x4(Rsrc r, uint32_t off) {
+  return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+__device__ inline float load_f32(Rsrc r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 
 struct GemmBatch {
   int count;
@@ -36,116 +54,160 @@ struct GemmBatch {
   GemmArgs p[kMaxBatch];
 };
 
-// One operand tile in LDS.  Loads write VB bytes per lane in lane order, so the swizzle is applied to
-// the address each lane fetches.  16-byte chunk c of a row sits at
-//   k-contiguous [row][32 k]:  c ^ (row ^ row >> 3) & 7   (16 rows of a vector read: 16 different places)
-//   k-major      [k][rows]:    c ^ 8 (k >> 2 & 1)         (the lane halves read k and k + 4: different
-//                                                         128-byte halves of the 64 banks)
-// VB = 16 needs 16-byte aligned rows and an extent divisible by four along the contiguous axis; VB = 4
-// takes anything.
-template <int ROWS, bool KMAJOR, int VB>
+// One operand tile in LDS: three bf16 planes (hi, mid, lo), each in 16-byte chunks of eight elements that are
+// consecutive in memory.  Chunk c of a row sits at
+//   k-contiguous [row][BK]:  c ^ g(row): 16 consecutive rows of a vector read go to 16 different places of the banks
+//   k-major      [k][ROWS]:  c ^ KS (k & 3): the four k rows of a transposing read go to different quarters
+// LB = 4 elements per load needs 16-byte aligned rows and an extent divisible by four along the contiguous
+// axis; LB = 1 takes anything.
+template <int ROWS, bool KMAJOR, int BK, int LB>
 struct Tile {
-  static constexpr int BYTES = ROWS * kBK * 4, NLD = BYTES / (NL * VB), EPL = VB / 4;
-  static constexpr int RB = KMAJOR ? ROWS * 4 : kBK * 4;  // bytes per LDS row
-  uint32_t voff[NLD];
+  static constexpr int RB = KMAJOR ? ROWS * 2 : BK * 2, CPR = RB / 16, PLANE = ROWS * BK * 2;  // bytes, chunks, bytes
+  static constexpr int NCH = PLANE / 16 / NL, NLD = 8 / LB;  // chunks per loader thread, loads per chunk
+  static constexpr int KS = ROWS >= 128 ? 4 : 2;
+  static_assert(PLANE % (16 * NL) == 0, "a plane divides over the loading threads");
+  static_assert(BK == 32 || BK == 64, "g below");
+  uint32_t voff[NCH][NLD];
+  int kadd[NCH];
   uint32_t kstride;
-  int kadd[NLD];
-  __device__ static inline int g(int row) { return (row ^ (row >> 3)) & 7; }
+  struct Raw { float v[NCH][8]; };
+  __device__ static inline int g(int row) { return BK == 64 ? (row ^ (row >> 3)) & 7 : (row >> 2) & 3; }
   __device__ inline void init(int row0, int rows, int ld, int t) {
     kstride = KMAJOR ? (uint32_t)ld * 4u : 4u;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int el = (i * NL + t) * EPL;  // first element of this lane's piece of the LDS image
-      const int r = el / (RB / 4), c = (el % (RB / 4)) >> 2, e = el & 3;
-      int row, k;
-      if constexpr (!KMAJOR) {
-        row = r;
-        k = ((c ^ g(r)) << 2) + e;
-      } else {
-        k = r;
-        row = ((c ^ (8 * ((r >> 2) & 1))) << 2) + e;
-      }
+    for (int i = 0; i < NCH; ++i) {
+      const int p = i * NL + t, r = p / CPR, c = p % CPR;
+      const int row = KMAJOR ? 8 * (c ^ (KS * (r & 3))) : r, k = KMAJOR ? r : 8 * (c ^ g(r));
       kadd[i] = k;
-      voff[i] = row0 + row < rows ? (KMAJOR ? (uint32_t)k * ld + row0 + row : (uint32_t)(row0 + row) * ld + k) * 4u : kOob;
+#pragma unroll
+      for (int e = 0; e < NLD; ++e) {
+        const int re = row0 + row + (KMAJOR ? e * LB : 0);
+        voff[i][e] = re < rows ? (KMAJOR ? (uint32_t)k * ld + re : (uint32_t)re * ld + k + e * LB) * 4u : kOob;
+      }
     }
   }
-  __device__ inline void issue(BufRsrc rs, char *lds, int wave, int k0, int kend) const {
+  __device__ inline void load(Rsrc rs, int k0, int kend, Raw &raw) const {
     const uint32_t adv = (uint32_t)k0 * kstride;
-    const uint32_t base = lds_address(lds) + wave * 64 * VB;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const uint32_t off = k0 + kadd[i] < kend ? voff[i] + adv : kOob;
-      if constexpr (VB == 16) dma16(rs, base + i * NL * VB, off);
-      else dma4(rs, base + i * NL * VB, off);
-    }
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+      for (int e = 0; e < NLD; ++e) {
+        const bool in = k0 + kadd[i] + (KMAJOR ? 0 : e * LB) < kend;
+        const uint32_t off = in ? voff[i][e] + adv : kOob;
+        if constexpr (LB == 4) {
+          const floatx4 q = load_f32x4(rs, off);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) raw.v[i][4 * e + j] = q[j];
+        } else {
+          raw.v[i][e] = load_f32(rs, off);
+        }
+      }
   }
-  // rows rbase + (lane & 31), k = 8 ks + 4 (lane >> 5) + (0..3)
-  __device__ static inline floatx4 frag(const char *lds, int rbase, int ks, int lane) {
-    const int row = rbase + (lane & 31);
+  // 32 x 16 operand of rows [rbase, rbase + 32), k slice ks, of one plane
+  __device__ static inline bf16x8 frag(const char *lds, int rbase, int ks, int lane) {
     if constexpr (!KMAJOR) {
-      return *reinterpret_cast<const floatx4 *>(lds + row * RB + (((2 * ks + (lane >> 5)) ^ g(row)) << 4));
+      const int row = rbase + (lane & 31), c = 2 * ks + (lane >> 5);
+      return *reinterpret_cast<const bf16x8 *>(lds + row * RB + ((c ^ g(row)) << 4));
     } else {
-      const int k = 8 * ks + 4 * (lane >> 5);
-      const char *p = lds + k * RB + (((row >> 2) ^ (8 * (lane >> 5))) << 4) + (row & 3) * 4;
-      floatx4 f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) f[e] = *reinterpret_cast<const float *>(p + e * RB);
-      return f;
+      const int g16 = lane >> 4, i = lane & 15;
+      const int m = rbase + 16 * (g16 & 1) + 4 * (i & 3), k = 16 * ks + 8 * (g16 >> 1) + (i >> 2);
+      const int col = (((m >> 3) ^ (KS * (i >> 2))) << 4) + ((m >> 2) & 1) * 8;
+      union { short4v h[2]; bf16x8 v; } f;
+      f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v *)(lds + k * RB + col));
+      f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v *)(lds + (k + 4) * RB + col));
+      return f.v;
     }
   }
 };
 
-// A 32x32 block of the result.  A lane holds column lane & 31 and rows 8 (r / 4) + 4 (lane >> 5) + (r & 3):
-// every access covers two rows of 128 bytes.  What the epilogue reads is requested for all 16 rows first.
-template <int EPI>
-__device__ inline void emit_block(const GemmArgs &g, const floatx16 &acc, int row0, int col, float bias) {
-  const float *in = EPI == EPI_BIAS_RES ? g.res : (EPI == EPI_GELU_BWD ? (const float *)g.aux : (const float *)g.C);
-  constexpr bool READS = EPI == EPI_BIAS_RES || EPI == EPI_GELU_BWD || EPI == EPI_WGRAD;
-  const bool reads = READS && (EPI != EPI_WGRAD || g.beta);
-  float x[16];
+// A float as the sum of three bf16, hi + mid + lo, each the rounded rest of the one before: 8 + 8 + 8 bits and
+// two signs hold all 24 (operands below 2^-110, whose lo leaves bf16's range, keep fewer).  Eight values become
+// a chunk of each plane.
+__device__ inline void split8(const float (&x)[8], u32x4 (&f)[3]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = row0 + 8 * (r >> 2) + (r & 3);
-    x[r] = 0.f;
-    if (reads && row < g.M) x[r] = in[(size_t)(EPI == EPI_GELU_BWD ? row % g.aux_wrap : row) * g.ldc + col];
-  }
+  for (int i = 0; i < 4; ++i) {
+    float a = x[2 * i], b = x[2 * i + 1];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = row0 + 8 * (r >> 2) + (r & 3);
-    if (row >= g.M) continue;
-    const size_t o = (size_t)row * g.ldc + col;
-    float v = acc[r];
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) v += bias;
-    if constexpr (EPI == EPI_BIAS_RES) v = v + bias + x[r];
-    if constexpr (EPI == EPI_GELU_BWD) v *= gelu_grad_f(x[r]);
-    if constexpr (EPI == EPI_WGRAD) v = g.scale * v + x[r];
-    ((float *)g.C)[o] = v;
-    if constexpr (EPI == EPI_BIAS_GELU) ((float *)g.C2)[o] = gelu_f(v);
+    for (int k = 0; k < 3; ++k) {
+      uint32_t u = pack_bf16x2(a, b);
+      asm("" : "+v"(u));  // (or the low half is converted a second time for its own shift)
+      f[k][i] = u;
+      if (k < 2) {  // (exact: the rest has the remaining bits only)
+        a -= __builtin_bit_cast(float, u << 16);
+        b -= __builtin_bit_cast(float, u & 0xFFFF0000u);
+      }
+    }
   }
 }
-__device__ inline void emit(const GemmArgs &g, const floatx16 &acc, int row0, int col) {
-  if (col >= g.N) return;
-  const bool biased = g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS_RES;
-  const float bias = biased ? ((const float *)g.bias)[col] : 0.f;
-  switch (g.epi) {  // (uniform)
-    case EPI_BIAS: emit_block<EPI_BIAS>(g, acc, row0, col, bias); break;
-    case EPI_BIAS_GELU: emit_block<EPI_BIAS_GELU>(g, acc, row0, col, bias); break;
-    case EPI_BIAS_RES: emit_block<EPI_BIAS_RES>(g, acc, row0, col, bias); break;
-    case EPI_GELU_BWD: emit_block<EPI_GELU_BWD>(g, acc, row0, col, bias); break;
-    case EPI_WGRAD: emit_block<EPI_WGRAD>(g, acc, row0, col, bias); break;
-    default: emit_block<EPI_STORE>(g, acc, row0, col, bias); break;
+struct Split {
+  bf16x8 p[3];  // hi, mid, lo
+};
+// Four consecutive columns of one row: the epilogue operation and the store.  x is what it reads there
+// (residual, pre-activation, accumulated-into output).
+template <int EPI>
+constexpr bool kReads = EPI == EPI_BIAS_RES || EPI == EPI_GELU_BWD || EPI == EPI_WGRAD;
+__device__ inline float4 load4(const float *p, int n, bool wide) {  // n of the four columns exist
+  if (wide) return *reinterpret_cast<const float4 *>(p);
+  return make_float4(p[0], n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, n > 3 ? p[3] : 0.f);
+}
+__device__ inline void store4(float *p, const float4 v, int n, bool wide) {
+  if (wide) {
+    *reinterpret_cast<float4 *>(p) = v;
+    return;
   }
+  p[0] = v.x;
+  if (n > 1) p[1] = v.y;
+  if (n > 2) p[2] = v.z;
+  if (n > 3) p[3] = v.w;
+}
+template <int EPI>
+__device__ inline float4 load_extra(const GemmArgs &g, int row, int col, bool wide) {
+  const float *in = EPI == EPI_BIAS_RES ? g.res : (EPI == EPI_GELU_BWD ? (const float *)g.aux : (const float *)g.C);
+  if (!kReads<EPI> || (EPI == EPI_WGRAD && !g.beta) || row >= g.M || col >= g.N) return make_float4(0.f, 0.f, 0.f, 0.f);
+  return load4(in + (size_t)(EPI == EPI_GELU_BWD ? row % g.aux_wrap : row) * g.ldc + col, g.N - col, wide);
+}
+template <int EPI>
+__device__ inline void emit4(const GemmArgs &g, float4 v, const float4 x, const float4 bias, int row, int col, bool wide) {
+  if (row >= g.M || col >= g.N) return;
+  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RES) {
+    v.x += bias.x; v.y += bias.y; v.z += bias.z; v.w += bias.w;
+  }
+  if constexpr (EPI == EPI_BIAS_RES) {
+    v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+  }
+  if constexpr (EPI == EPI_GELU_BWD) {
+    v.x *= gelu_grad_f(x.x); v.y *= gelu_grad_f(x.y); v.z *= gelu_grad_f(x.z); v.w *= gelu_grad_f(x.w);
+  }
+  if constexpr (EPI == EPI_WGRAD) {
+    v.x = g.scale * v.x + x.x; v.y = g.scale * v.y + x.y; v.z = g.scale * v.z + x.z; v.w = g.scale * v.w + x.w;
+  }
+  const size_t o = (size_t)row * g.ldc + col;
+  store4((float *)g.C + o, v, g.N - col, wide);
+  if constexpr (EPI == EPI_BIAS_GELU)
+    store4((float *)g.C2 + o, make_float4(gelu_f(v.x), gelu_f(v.y), gelu_f(v.z), gelu_f(v.w)), g.N - col, wide);
 }
 
-// WG x WG multiplying wavefronts own a BT x BT tile.  K steps kt .. kt + NSTAGE - 2 are in flight while
-// step kt is multiplied; one barrier per step publishes it and retires the slot of step kt - 1.
-template <int BT, int NSTAGE, bool AKM, bool BKM, int VB>
-__global__ __launch_bounds__(256 + NL) void gemm_f32_kernel(GemmBatch batch) {
-  constexpr int WG = 2, WT = BT / WG, MI = WT / 32;
-  typedef Tile<BT, AKM, VB> TA;
-  typedef Tile<BT, BKM, VB> TB;
-  constexpr int STAGE = TA::BYTES + TB::BYTES, LPS = TA::NLD + TB::NLD;
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE];
+// Four multiplying wavefronts own a BM x BN tile in squares of 64 x 64: four squares of 128 x 128, two of 128 x 64, one
+// of 64 x 64.  Wavefronts that share a square share out a K step in slices of 16 (an operand read from LDS then
+// serves as many products as in the large tile), and their sums meet in LDS at the end.  Eight loader wavefronts fetch K
+// steps ahead into registers, split them - every element once - and write the planes of step kt + 1 while step kt
+// is multiplied; one barrier per step publishes them and retires the slot of step kt - 1.  A slice's operands are
+// read while the slice before it is multiplied.
+template <int BM, int BN>
+struct Shape {
+  static constexpr int WM = BM / 64, WN = BN / 64, KG = 4 / (WM * WN), BK = KG > 1 ? 64 : 32;
+  static constexpr int SL = BK / 16 / KG;  // slices per wavefront and step
+  static constexpr int STAGE = (BM + BN) * BK * 6, PITCH = BN + 8;
+  static constexpr int RING = 2 * STAGE, SUMS = KG * BM * PITCH * 4, LDS = RING > SUMS ? RING : SUMS;
+};
+template <int BM, int BN, bool AKM, bool BKM, int LB>
+__global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_f32_kernel(GemmBatch batch) {
+  typedef Shape<BM, BN> S;
+  constexpr int WM = S::WM, WN = S::WN, KG = S::KG, SL = S::SL, BK = S::BK;
+  typedef Tile<BM, AKM, BK, LB> TA;
+  typedef Tile<BN, BKM, BK, LB> TB;
+  static_assert(3 * (TA::PLANE + TB::PLANE) == S::STAGE, "stage");
+  __shared__ __attribute__((aligned(1024))) char smem[S::LDS];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
@@ -153,102 +215,231 @@ __global__ __launch_bounds__(256 + NL) void gemm_f32_kernel(GemmBatch batch) {
   for (int i = 0; i < batch.count - 1; ++i)
     if ((int)blockIdx.x >= batch.tile_end[i]) { prob = i + 1; tile0 = batch.tile_end[i]; }
   GemmArgs g = batch.p[prob];
-  const int tiles_m = (g.M + BT - 1) / BT, tiles_n = (g.N + BT - 1) / BT;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   int kb0, ke;
   const int pid = my_tile(g, blockIdx.x - tile0, tiles_m * tiles_n, kb0, ke);
   constexpr int GM = 8;
   const int per_group = GM * tiles_n, first_m = pid / per_group * GM, gsize = min(tiles_m - first_m, GM);
-  const int m0 = (first_m + (pid % per_group) % gsize) * BT, n0 = ((pid % per_group) / gsize) * BT;
-  const int nk = (ke - kb0 + kBK - 1) / kBK;
+  const int m0 = (first_m + (pid % per_group) % gsize) * BM, n0 = ((pid % per_group) / gsize) * BN;
+  const int nk = (ke - kb0 + BK - 1) / BK;
 
-  if (wave >= WG * WG) {  // loader wavefronts
-    const BufRsrc ra = make_rsrc(g.A, g.a_bytes), rb = make_rsrc(g.B, g.b_bytes);
+  float *sums = reinterpret_cast<float *>(smem);
+  if (wave >= 4) {  // loader wavefronts
+    const Rsrc ra = rsrc(g.A, g.a_bytes), rb = rsrc(g.B, g.b_bytes);
     TA la;
     TB lb;
-    la.init(m0, g.M, g.lda, t % NL);
-    lb.init(n0, g.N, g.ldb, t % NL);
-    auto issue = [&](int kt) {
-      char *st = smem + (kt % NSTAGE) * STAGE;
-      la.issue(ra, st, wave % kLoaders, kb0 + kt * kBK, ke);
-      lb.issue(rb, st + TA::BYTES, wave % kLoaders, kb0 + kt * kBK, ke);
+    la.init(m0, g.M, g.lda, t - 256);
+    lb.init(n0, g.N, g.ldb, t - 256);
+    constexpr int D = kAhead;  // steps
+    typename TA::Raw qa[D];
+    typename TB::Raw qb[D];
+    auto fetch = [&](int kt, int set) {  // (a step past the last reads as zero)
+      la.load(ra, kb0 + kt * BK, ke, qa[set]);
+      lb.load(rb, kb0 + kt * BK, ke, qb[set]);
     };
+    auto publish = [&](int kt, int set) {
+      char *st = smem + (kt & 1) * S::STAGE + (t - 256) * 16;
+      u32x4 f[3];
 #pragma unroll
-    for (int s = 0; s < NSTAGE - 1; ++s)
-      if (s < nk) issue(s);
-    for (int kt = 0; kt < nk; ++kt) {
-      if (nk - 1 - kt >= NSTAGE - 2)
-        wait_vmcnt<(NSTAGE - 2) * LPS>();
-      else
-        wait_vmcnt<0>();
-      __syncthreads();
-      if (kt + NSTAGE - 1 < nk) issue(kt + NSTAGE - 1);
-    }
-    return;
-  }
-
-  const int wm = wave / WG, wn = wave % WG;
-  floatx16 acc[MI][MI];
+      for (int i = 0; i < TA::NCH; ++i) {
+        split8(qa[set].v[i], f);
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < MI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  for (int kt = 0; kt < nk; ++kt) {
-    __syncthreads();
-    const char *sa = smem + (kt % NSTAGE) * STAGE, *sb = sa + TA::BYTES;
-    floatx4 a[2][MI], b[2][MI];  // the fragments of the next k group are requested before this one's products
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      a[0][i] = TA::frag(sa, wm * WT + 32 * i, 0, lane);
-      b[0][i] = TB::frag(sb, wn * WT + 32 * i, 0, lane);
-    }
-#pragma unroll
-    for (int ks = 0; ks < kBK / 8; ++ks) {
-      if (ks + 1 < kBK / 8) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          a[(ks + 1) & 1][i] = TA::frag(sa, wm * WT + 32 * i, ks + 1, lane);
-          b[(ks + 1) & 1][i] = TB::frag(sb, wn * WT + 32 * i, ks + 1, lane);
-        }
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4 *>(st + k * TA::PLANE + i * NL * 16) = f[k];
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int i = 0; i < TB::NCH; ++i) {
+        split8(qb[set].v[i], f);
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4 *>(st + 3 * TA::PLANE + k * TB::PLANE + i * NL * 16) = f[k];
+      }
+    };
 #pragma unroll
-          for (int j = 0; j < MI; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ks & 1][i][e], b[ks & 1][j][e], acc[i][j], 0, 0, 0);
+    for (int u = 0; u < D; ++u) fetch(u, u);
+    __builtin_amdgcn_sched_barrier(0);
+    publish(0, 0);
+    fetch(D, 0);
+    [&] {
+      for (int kt = 0;;) {
+#pragma unroll
+        for (int u = 1; u <= D; ++u) {
+          __syncthreads();
+          if (++kt >= nk) return;
+          publish(kt, u % D);
+          fetch(kt + D, u % D);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }();
+    __syncthreads();  // (every wavefront is done with the ring)
+  } else {
+    const int kg = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
+    floatx16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    struct Operands { Split a[2], b[2]; };
+    auto read = [&](int kt, int s) {
+      const char *sa = smem + (kt & 1) * S::STAGE, *sb = sa + 3 * TA::PLANE;
+      Operands o;
+#pragma unroll
+      for (int k = 2; k >= 0; --k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          o.a[i].p[k] = TA::frag(sa + k * TA::PLANE, wm * 64 + 32 * i, kg * SL + s, lane);
+          o.b[i].p[k] = TB::frag(sb + k * TB::PLANE, wn * 64 + 32 * i, kg * SL + s, lane);
+        }
+      return o;
+    };
+    auto products = [&](const Operands &o) {
+      // all but the products below 2^-26 of the largest, the small ones first
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a[i].p[PA[q]], o.b[j].p[PB[q]], acc[i][j], 0, 0, 0);
+    };
+    __syncthreads();
+    Operands cur = read(0, 0);
+    for (int kt = 0; kt < nk - 1; ++kt) {
+#pragma unroll
+      for (int s = 1; s < SL; ++s) {
+        const Operands nxt = read(kt, s);
+        products(cur);
+        cur = nxt;
+      }
+      __syncthreads();
+      const Operands nxt = read(kt + 1, 0);
+      products(cur);
+      cur = nxt;
     }
+#pragma unroll
+    for (int s = 1; s < SL; ++s) {
+      const Operands nxt = read(nk - 1, s);
+      products(cur);
+      cur = nxt;
+    }
+    products(cur);
+
+    // Infinities and values that round to one split into NaN parts, and parts of a product can overflow to both
+    // signs: what comes out not finite is done again in fp32 products, straight from memory.
+    float bad = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad = __builtin_fmaf(acc[i][j][r], 0.f, bad);
+    if (__any(!(bad == 0.f))) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int kt = 0; kt < nk; ++kt)
+#pragma unroll 1
+        for (int e = 0; e < 8 * SL; ++e) {
+          const int k = kb0 + kt * BK + kg * SL * 16 + 2 * e + (lane >> 5);
+          float a[2], b[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int m = m0 + wm * 64 + 32 * i + (lane & 31), n = n0 + wn * 64 + 32 * i + (lane & 31);
+            a[i] = k < ke && m < g.M ? ((const float *)g.A)[AKM ? (size_t)k * g.lda + m : (size_t)m * g.lda + k] : 0.f;
+            b[i] = k < ke && n < g.N ? ((const float *)g.B)[BKM ? (size_t)k * g.ldb + n : (size_t)n * g.ldb + k] : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+    __syncthreads();  // every wavefront is done with the ring
+    // a lane holds column lane & 31 and rows 8 (r / 4) + 4 (lane >> 5) + (r & 3) of each 32x32 block
+    float *mine = sums + (kg * BM + wm * 64 + 4 * (lane >> 5)) * S::PITCH + wn * 64 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[(32 * i + 8 * (r >> 2) + (r & 3)) * S::PITCH + 32 * j] = acc[i][j][r];
   }
 
+  // What the epilogue reads is requested for all of a thread's rows before the sums are there.
+  constexpr int QPR = BN / 4, RPP = (256 + NL) / QPR, NQ = (BM + RPP - 1) / RPP;  // quads per row, rows per pass, passes
+  const bool biased = g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS_RES;
+  const bool wide = !((g.ldc | g.N) & 3) && !(((uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.bias | (uintptr_t)g.res | (uintptr_t)g.aux) & 15);
+  const int row_l = t / QPR, col = n0 + t % QPR * 4;
+  const float4 bias = biased && col < g.N ? load4((const float *)g.bias + col, g.N - col, wide) : make_float4(0.f, 0.f, 0.f, 0.f);
+  auto finish = [&](auto epi) {
+    constexpr int EPI = decltype(epi)::value;
+    float4 x[NQ];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+    for (int q = 0; q < NQ; ++q) x[q] = load_extra<EPI>(g, row_l + q * RPP < BM ? m0 + row_l + q * RPP : g.M, col, wide);
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < MI; ++j)
-      emit(g, acc[i][j], m0 + wm * WT + 32 * i + 4 * (lane >> 5), n0 + wn * WT + 32 * j + (lane & 31));
+    for (int q = 0; q < NQ; ++q) {
+      const int row = row_l + q * RPP;
+      if (row >= BM) break;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < KG; ++k) {
+        const float4 p = *reinterpret_cast<const float4 *>(sums + (k * BM + row) * S::PITCH + t % QPR * 4);
+        v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+      }
+      emit4<EPI>(g, v, x[q], bias, m0 + row, col, wide);
+    }
+  };
+  switch (g.epi) {  // (uniform)
+    case EPI_BIAS: finish(std::integral_constant<int, EPI_BIAS>{}); break;
+    case EPI_BIAS_GELU: finish(std::integral_constant<int, EPI_BIAS_GELU>{}); break;
+    case EPI_BIAS_RES: finish(std::integral_constant<int, EPI_BIAS_RES>{}); break;
+    case EPI_GELU_BWD: finish(std::integral_constant<int, EPI_GELU_BWD>{}); break;
+    case EPI_WGRAD: finish(std::integral_constant<int, EPI_WGRAD>{}); break;
+    default: finish(std::integral_constant<int, EPI_STORE>{}); break;
+  }
 }
 
-template <int BT, int NSTAGE, bool AKM, bool BKM, int VB>
+template <int BM, int BN>
+long tiles_of(const GemmArgs &g) {
+  return (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * std::max(g.splits, 1);
+}
+template <int BM, int BN, bool AKM, bool BKM, int LB>
 hipError_t launch(GemmBatch &b, hipStream_t s) {
   int tiles = 0;
-  for (int i = 0; i < b.count; ++i) {
-    tiles += ((b.p[i].M + BT - 1) / BT) * ((b.p[i].N + BT - 1) / BT) * std::max(b.p[i].splits, 1);
-    b.tile_end[i] = tiles;
-  }
-  hipLaunchKernelGGL((gemm_f32_kernel<BT, NSTAGE, AKM, BKM, VB>), dim3(tiles), dim3(256 + NL), 0, s, b);
+  for (int i = 0; i < b.count; ++i) b.tile_end[i] = tiles += (int)tiles_of<BM, BN>(b.p[i]);
+  hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, AKM, BKM, LB>), dim3(tiles), dim3(256 + NL), 0, s, b);
   return hipGetLastError();
 }
 
-// A 64x64 tile is as fast per flop as a 128x128 one while its operands come at 16 bytes per clock and
-// CU, and it balances better; the larger tile halves the L2 traffic and is taken once it fills the chip
-// twice over.
+// Rounds of workgroups, times what one takes: microseconds per 64 of K with the chip full, and about five for start
+// and epilogue.  Measured (128x128 / 128x64 / 64x64): 2048x1536x512 24 / 30 / 31 us, 4096x512x2048 64 / 51 / 65,
+// 2048x512x2048 - / 43 / 33, 1600x768x3072 87 / 62 / 85, 4096x2048x512 57 / 71 / 91.
 template <bool AKM, bool BKM>
 hipError_t pick(GemmBatch &b, bool aligned, hipStream_t s) {
-  if (!aligned) return launch<64, 3, AKM, BKM, 4>(b, s);
-  long t128 = 0;
-  for (int i = 0; i < b.count; ++i) t128 += (long)((b.p[i].M + 127) / 128) * ((b.p[i].N + 127) / 128) * std::max(b.p[i].splits, 1);
-  return t128 >= 512 ? launch<128, 4, AKM, BKM, 16>(b, s) : launch<64, 4, AKM, BKM, 16>(b, s);
+  if (!aligned) return launch<64, 64, AKM, BKM, 1>(b, s);
+  long t64 = 0, t128x64 = 0, t128 = 0;
+  int k = 0;
+  for (int i = 0; i < b.count; ++i) {
+    t64 += tiles_of<64, 64>(b.p[i]);
+    t128x64 += tiles_of<128, 64>(b.p[i]);
+    t128 += tiles_of<128, 128>(b.p[i]);
+    k = std::max(k, b.p[i].splits > 1 ? b.p[i].k_per : b.p[i].K);
+  }
+  auto price = [&](long tiles, double step_us) { return (double)((tiles + 255) / 256) * (5.0 + (k + 63) / 64 * step_us); };
+  const double us64 = price(t64, 0.9), us128x64 = price(t128x64, 1.45), us128 = price(t128, 2.6);
+  int tile = b.p[0].tile;
+  if (!tile) tile = us128 <= std::min(us128x64, us64) ? 2 : us128x64 <= us64 ? 3 : 4;
+  switch (tile) {
+    case 2: return launch<128, 128, AKM, BKM, 4>(b, s);
+    case 3: return launch<128, 64, AKM, BKM, 4>(b, s);
+    default: return launch<64, 64, AKM, BKM, 4>(b, s);
+  }
 }
 
 }  // namespace

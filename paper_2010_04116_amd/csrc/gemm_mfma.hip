@@ -859,7 +859,7 @@ hipError_t gemm_bf16(const GemmArgs &g, hipStream_t s) { return gemm_bf16_batch(
 
 // Prices every number of parts with every tile (measured microseconds per 64-deep K step of a workgroup:
 // the 128x128 tile alone on its CU 0.47 with four stages, two of them with two stages 0.96; 256x256 1.35;
-// 64x64 up to two per CU 0.42; fp32, matrix-bound, 0.9 per 64x64 tile), the rounds its workgroups need, and
+// 64x64 up to two per CU 0.42; fp32 0.9 for 64x64, 1.45 for 128x64, 2.6 for 128x128), the rounds its workgroups need, and
 // the traffic of writing and adding up the parts at 4 bytes per picosecond.
 SplitPlan gemm_split_plan(int dtype, int M, int N, int K, size_t ws_floats) {
   const long steps = (K + 63) / 64, cap = std::min<long>({32, (long)(ws_floats / ((size_t)M * N)), steps / 4});
@@ -875,7 +875,9 @@ SplitPlan gemm_split_plan(int dtype, int M, int N, int K, size_t ws_floats) {
       if (us < best_us) { best_us = us; best = SplitPlan{(int)sp, tile}; }
     };
     if (dtype == 0) {
-      price(0, tiles(64) * sp, 256, 0.9);
+      price(4, tiles(64) * sp, 256, 0.9);
+      price(3, up(M, 128) * up(N, 64) * sp, 256, 1.45);
+      price(2, tiles(128) * sp, 256, 2.6);
     } else {
       price(3, tiles(128) * sp, 256, 0.47);
       price(2, tiles(128) * sp, 512, 0.96);

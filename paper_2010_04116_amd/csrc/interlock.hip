@@ -964,6 +964,10 @@ int il_head_xent_static(il_ctx *c, int32_t k, const float *x_k, const int32_t *t
       carve(rows, (size_t)8 * rows * c->d);
     }
   }
+  if (need > kStaticScratchBytes) {  // fewer parts, whatever is left for them
+    const size_t rest = need - ((skws_floats * 4 + 255) & ~(size_t)255);
+    carve(rows, rest < kStaticScratchBytes ? (kStaticScratchBytes - rest) / 4 : 0);
+  }
   if (need > kStaticScratchBytes) return IL_E_WORKSPACE;
   char *base = nullptr;
   { const int rc = static_scratch(&base); if (rc) return rc; }

@@ -234,6 +234,57 @@ def test_f32_gemm(M, N, K, akm, bkm):
     assert np.all(np.abs(C.cpu().numpy() - want) <= bound)
 
 
+@pytest.mark.parametrize("tile", [2, 3, 4])
+@pytest.mark.parametrize("akm,bkm,epi", [(0, 1, 3), (0, 0, 0), (1, 1, 6)])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 16), (128, 64, 64), (132, 68, 100), (260, 196, 292), (4, 4, 4)])
+def test_f32_tiles(M, N, K, akm, bkm, epi, tile):
+    """Each fp32 tile at its edges, with one K step, a part of one and several; values over twelve decades."""
+    import torch
+    rng = np.random.default_rng(M + 7 * N + K + tile)
+    x, y = ((rng.normal(size=s) * 10.0 ** rng.uniform(-6, 6, size=s)).astype(np.float32) for s in ((M, K), (K, N)))
+    res, bias = rng.normal(size=(M, N)).astype(np.float32), rng.normal(size=N).astype(np.float32)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")  # noqa: E731
+    A, B = dev(x.T if akm else x), dev(y if bkm else y.T)
+    C = torch.full((M, N), float("nan"), device="cuda:0")
+    print("case f32", M, N, K, akm, bkm, epi, tile, flush=True)
+    b.il_test_gemm(0, A, B, M, N, K, A.shape[1], B.shape[1], akm, bkm, epi, C, bias=dev(bias), res=dev(res), tile=tile)
+    torch.cuda.synchronize()
+    add = epi == 3
+    want = x.astype(np.float64) @ y + (bias + res.astype(np.float64) if add else 0)
+    mag = np.abs(x).astype(np.float64) @ np.abs(y) + (np.abs(bias) + np.abs(res) if add else 0)
+    assert np.all(np.abs(C.cpu().numpy() - want) <= (K + 2) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("tile,M,N,K", [(2, 130, 130, 40), (3, 130, 66, 72), (4, 68, 68, 136), (0, 67, 65, 33)])
+@pytest.mark.parametrize("akm,bkm", [(0, 1), (0, 0), (1, 1)])
+def test_f32_not_finite(tile, M, N, K, akm, bkm):
+    """Infinities, NaN and values that round to an infinity in eight bits give what fp32 products give: an infinity
+    stays one, beside rows and columns that are not touched."""
+    import torch
+    rng = np.random.default_rng(5)
+    M, N, K = (v if tile == 0 else v // 4 * 4 for v in (M, N, K))
+    x, y = (rng.normal(size=s).astype(np.float32) for s in ((M, K), (K, N)))
+    y[np.abs(y) < 1e-3] = 1.0
+    y[:, 0] = 1.0                                   # an operand whose rest is zero: inf * 0 must not appear
+    x[0, 1], x[1, K - 1], x[2, 0], x[M - 1, 3] = np.inf, -np.inf, np.nan, 3.402e38
+    y[2, N - 1], y[3, N - 1] = 0.25, 0.25           # (the large value stays finite in this column ...)
+    y[3, 1] = 2.0                                   # (... and overflows in this one)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")  # noqa: E731
+    A, B = dev(x.T if akm else x), dev(y if bkm else y.T)
+    C = torch.zeros((M, N), device="cuda:0")
+    print("case f32 not finite", tile, M, N, K, akm, bkm, flush=True)
+    b.il_test_gemm(0, A, B, M, N, K, A.shape[1], B.shape[1], akm, bkm, 6 if akm else 0, C, tile=tile)
+    torch.cuda.synchronize()
+    got = C.cpu().numpy()
+    with np.errstate(all="ignore"):
+        want = x.astype(np.float64) @ y
+        big = np.abs(want) > 3.4028235e38
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(np.isinf(got), np.isinf(want) | big) and np.all(np.sign(got[big]) == np.sign(want[big]))
+        ok = np.isfinite(want) & ~big
+        assert np.all(np.abs(got - want)[ok] <= ((K + 2) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(y)))[ok])
+
+
 @pytest.mark.parametrize("akm,bkm,epi,beta", [(0, 1, 0, 0), (0, 1, 1, 0), (0, 1, 2, 0), (0, 0, 4, 0), (0, 0, 5, 0),
                                               (1, 1, 6, 0), (1, 1, 6, 1)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 32), (37, 3, 5), (67, 132, 33), (300, 200, 260), (2816, 3000, 40)])
