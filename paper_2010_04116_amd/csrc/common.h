@@ -154,11 +154,13 @@ hipError_t gemm_splitk(int dtype, const GemmArgs &g, SplitPlan plan, float *ws, 
 // y = LN(x)*gamma+beta -> T; stats[row] = (mean, rstd); optional fp32 copy of x.
 hipError_t ln_forward(int dtype, const float *x, const void *gamma, const void *beta, float eps,
                       int rows, int d, void *y, float *stats, float *xcopy, hipStream_t s);
-// For each stacked row r (stream r / N, token r % N): G[r] += LN'(x)^T dy[r]; Gb[r] = T(G[r]);
-// partial column sums of w*dy*xhat and w*dy go to `partials` ([nblk][2*d]); returns nblk.
-hipError_t ln_backward_residual(int dtype, const void *dy, const float *x, const float *stats,
-                                const void *gamma, int rows, int N, int d, float *G, void *Gb,
-                                StreamWeights sw, float *partials, int *nblk, hipStream_t s);
+// For each row r of ns streams stacked over N tokens (stream r / N, token r % N): G[r] += LN'(x)^T dy[r]; Gb[r] = T(G[r]);
+// partial column sums of w*dy*xhat and w*dy go to `partials` ([nblk][2*d]); returns nblk.  If ypart is given (and
+// *summed returns true, which takes vectors of four): partial column sums [nblk][d] of the streams' weighted sum
+// sum_s w[s] Gb[s], and the sum itself to ysum [N][d] unless that is NULL.
+hipError_t ln_backward_residual(int dtype, const void *dy, const float *x, const float *stats, const void *gamma,
+                                int ns, int N, int d, float *G, void *Gb, const StreamWeights &sw, float *partials,
+                                int *nblk, void *ysum, float *ypart, bool *summed, hipStream_t s);
 int ln_backward_max_blocks();
 
 // ---- reductions / elementwise (reduce.hip) --------------------------------------------

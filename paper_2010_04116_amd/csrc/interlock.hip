@@ -167,19 +167,32 @@ struct RingEntry {
   char *Gb;           // ... above the attention, [live streams][N, d]
   char *DU, *DQKV;    // [live streams][N, m] and [N, 3d]: gradients at the MLP's hidden layer and at Q|K|V
   float *ln[2];       // LayerNorm 2's and 1's first-stage column sums
+  // What the LayerNorm that makes Ga (Gb) leaves with it: the weighted sum over the streams [N, d] (where there
+  // are several) and the first stage of its column sums.
+  char *sum[2]; float *sum_cols[2];
 };
+// A block's linear outputs in the order FC2, FC1, attention output projection, QKV: the streams' weighted sum as
+// an operand, and its column sums' first stage, where the kernel that made the streams has left them.
+struct Summed { const void *y; const float *cols; int nblk; };
 struct Tail {         // one queued tail
   const BlockOff *b; const BlockSave *s; const RingEntry *r;
   const std::vector<Run> *runs;  // (outlives the launch)
   int ln_blocks;                 // partial sums per LayerNorm
+  Summed done[4];                // cols == nullptr: not summed yet
 };
+// The streams of a range that carry weight: how many, the first, and whether that one is their sum already.
+struct Weighted { int n, first; bool plain; };
+Weighted weighted(const Run &r) {
+  Weighted w{0, 0, false};
+  for (int i = r.cnt - 1; i >= 0; --i)
+    if (r.wt[i] != 0.f) { ++w.n; w.first = i; }
+  w.plain = w.n == 1 && r.wt[w.first] == 1.f;
+  return w;
+}
 // the part-th range that carries weighted streams, nullptr beyond the last
 const Run *weighted_run(const std::vector<Run> &runs, int part) {
-  for (const Run &r : runs) {
-    bool any = false;
-    for (int i = 0; i < r.cnt; ++i) any = any || r.wt[i] != 0.f;
-    if (any && part-- == 0) return &r;
-  }
+  for (const Run &r : runs)
+    if (weighted(r).n && part-- == 0) return &r;
   return nullptr;
 }
 
@@ -202,6 +215,7 @@ struct il_ctx {
   float *G;                        // stream slots [nslots][N,d]
   RingEntry ring[kRing];
   int pos = 0;                     // ring entry of the next block
+  Summed above = {};               // what was left with the next block's Ga
   char *DH; float *dsum, *skws; size_t skws_floats;
   Tail tails[kGroup]; int ntails = 0;
   float *partials[kGroup][4];      // bias partials of the queued tails
@@ -295,6 +309,9 @@ size_t layout_workspace(il_ctx *c, void *base) {
   // (one more stream slot carries a head's gradient through its own blocks)
   const size_t ns = c->plan.nslots + (c->Lh ? 1 : 0), S = (size_t)std::max(c->plan.maxcnt, 1) * N;
   const size_t live = (size_t)std::max(c->plan.maxlive, 1) * N;
+  bool sums = false;  // some component's streams are not their sum as they are
+  for (const CompPlan &k : c->plan.comp)
+    for (const Run &r : k.runs) sums = sums || (weighted(r).n && !weighted(r).plain);
   c->G = (float *)cv.take(ns * N * d * 4);
   for (RingEntry &r : c->ring) {
     r.Ga = (char *)cv.take(ns * N * d * eb);
@@ -302,6 +319,8 @@ size_t layout_workspace(il_ctx *c, void *base) {
     r.DU = (char *)cv.take(live * m * eb);
     r.DQKV = (char *)cv.take(live * 3 * d * eb);
     for (float *&p : r.ln) p = (float *)cv.take((size_t)c->plan.maxruns * ln_backward_max_blocks() * 2 * d * 4);
+    for (char *&p : r.sum) p = (char *)cv.take(sums ? N * d * eb : 0);
+    for (float *&p : r.sum_cols) p = (float *)cv.take((size_t)ln_backward_max_blocks() * d * 4);
   }
   c->DH = (char *)cv.take(S * d * eb);
   c->dsum = (float *)cv.take(S * std::max(H, d / 32) * 4);
@@ -455,15 +474,22 @@ int attention_bwd(il_ctx *c, const BlockSave &s, const void *d_o, int cnt, void 
   return IL_OK;
 }
 
-// Gout: the range's rows of the updated stream as a GEMM operand
+// Gout: the range's rows of the updated stream as a GEMM operand.  left: where the streams' weighted sum and its
+// column sums may go (nullptr: not wanted); *made: what is there afterwards.
 int ln_bwd(il_ctx *c, const Run &run, const void *dy, const float *x, const float *stats, size_t g_off, void *Gout,
-           float *partials, int *nblk) {
+           float *partials, int *nblk, void *sum, float *sum_cols, Summed *made) {
   StreamWeights sw;
   memcpy(sw.w, run.wt, sizeof(sw.w));
   const int rows = run.cnt * c->N;
-  Scope sc(c, KC_LN_BWD, 0, (double)rows * c->d * (c->eb + 8 + c->eb) + (double)c->N * c->d * 4);
-  IL_TRY(ln_backward_residual(c->cfg.dtype, dy, x, stats, P(c, g_off), rows, c->N, c->d,
-                              c->G + (size_t)run.s0 * c->N * c->d, Gout, sw, partials, nblk, c->stream));
+  const Weighted w = weighted(run);
+  void *ysum = sum_cols && !w.plain ? sum : nullptr;
+  Scope sc(c, KC_LN_BWD, 0, (double)rows * c->d * (c->eb + 8 + c->eb) + (double)c->N * c->d * (4 + (ysum ? c->eb : 0)));
+  bool summed = false;
+  IL_TRY(ln_backward_residual(c->cfg.dtype, dy, x, stats, P(c, g_off), run.cnt, c->N, c->d,
+                              c->G + (size_t)run.s0 * c->N * c->d, Gout, sw, partials, nblk, ysum, sum_cols, &summed,
+                              c->stream));
+  if (summed)
+    *made = Summed{ysum ? ysum : (const char *)Gout + (size_t)w.first * c->N * c->d * c->eb, sum_cols, *nblk};
   return IL_OK;
 }
 
@@ -540,16 +566,22 @@ int launch_tails(il_ctx *c) {
       const size_t w_off[4] = {b.w_fc2, b.w_fc1, b.w_o, b.w_qkv}, b_off[4] = {b.b_fc2, b.b_fc1, b.b_o, b.b_qkv};
       const int in[4] = {c->m, c->d, c->d, c->d};
       for (int j = 0; j < 4; ++j) {
-        SumColsumJob &q = sums.job[sums.count++];
-        q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j > 0);
-        char *first = dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb;
-        q.ysum = plain ? nullptr : first;
-        q.partials = c->partials[i][j];
-        sum_bytes += (double)(plain ? 1 : ns + 1) * c->N * wide[j] * c->eb;
-        finals.job[finals.count++] = ColsumJob{q.partials, 0, q.cols, Gr(c, b_off[j]), acc};
+        const void *y = t.done[j].y;
+        if (t.done[j].cols) {
+          finals.job[finals.count++] = ColsumJob{t.done[j].cols, t.done[j].nblk, (int)wide[j], Gr(c, b_off[j]), acc};
+        } else {
+          SumColsumJob &q = sums.job[sums.count++];
+          q.Y = dy[j]; q.cols = (int)wide[j]; q.table = 2 * i + (j > 0);
+          char *first = dy[j] + (size_t)sums.table[q.table].row[0] * c->N * wide[j] * c->eb;
+          q.ysum = plain ? nullptr : first;
+          q.partials = c->partials[i][j];
+          y = first;
+          sum_bytes += (double)(plain ? 1 : ns + 1) * c->N * wide[j] * c->eb;
+          finals.job[finals.count++] = ColsumJob{q.partials, 0, q.cols, Gr(c, b_off[j]), acc};
+        }
         GemmArgs g = base_args();
         g.A = x[j]; g.lda = in[j]; g.a_kmajor = 1;
-        g.B = first; g.ldb = (int)wide[j]; g.b_kmajor = 1;
+        g.B = y; g.ldb = (int)wide[j]; g.b_kmajor = 1;
         g.M = in[j]; g.N = (int)wide[j]; g.K = c->N;
         g.epi = EPI_WGRAD; g.C = Gr(c, w_off[j]); g.ldc = (int)wide[j]; g.beta = acc;
         wg[nw++] = g;
@@ -559,8 +591,9 @@ int launch_tails(il_ctx *c) {
     {
       Scope sc(c, KC_COLSUM, 0, sum_bytes);
       int nblk = 0;
-      IL_TRY(sum_colsum_multi(c->cfg.dtype, sums, &nblk, c->stream));
-      for (int i = 0; i < finals.count; ++i) finals.job[i].nblk = nblk;
+      if (sums.count > 0) IL_TRY(sum_colsum_multi(c->cfg.dtype, sums, &nblk, c->stream));
+      for (int i = 0; i < finals.count; ++i)
+        if (finals.job[i].nblk == 0) finals.job[i].nblk = nblk;
       for (int i = 0; part == 0 && i < c->ntails; ++i) {  // (every range's LayerNorm sums at once)
         const Tail &t = c->tails[i];
         finals.job[finals.count++] = ColsumJob{t.r->ln[0], t.ln_blocks, 2 * c->d, Gr(c, t.b->ln2_g), c->accumulate};
@@ -581,13 +614,18 @@ int launch_tails(il_ctx *c) {
   return IL_OK;
 }
 
-// Backward of one block for all live streams: data gradients now, its tail queued.
-int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, const BlockSave &s) {
+// Backward of one block for all live streams: data gradients now, its tail queued.  lowest: the streams that
+// leave it are not the next block's (another component's, or nobody's).
+int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, const BlockSave &s, bool lowest) {
   const int N = c->N, d = c->d, m = c->m;
   const size_t eb = c->eb;
   const RingEntry &r = c->ring[c->pos];
   const int next = (c->pos + 1) % kRing;
   int rc, ln_blocks = 0;
+  const bool one = runs.size() == 1;  // (several ranges' sums only meet in the gradients)
+  Tail tail{&b, &s, &r, &runs, 0, {}};
+  tail.done[0] = c->above;
+  c->above = Summed{};
   for (const Run &run : runs) {
     const int S = run.cnt * N;
     const size_t slot = (size_t)run.s0 * N, stack = (size_t)run.off * N;
@@ -598,7 +636,9 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
     // MLP
     if ((rc = linear_dgrad(c, Ga, b.w_fc2, S, m, d, EPI_GELU_BWD, DU, s.u, N))) return rc;
     if ((rc = linear_dgrad(c, DU, b.w_fc1, S, d, m, EPI_STORE, c->DH, nullptr, 0))) return rc;
-    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk))) return rc;
+    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk, r.sum[1], one ? r.sum_cols[1] : nullptr,
+                     &tail.done[2])))
+      return rc;
     // attention
     const bool dots = attention_dsum_given(c->cfg.dtype, c->dh);
     if ((rc = linear_dgrad(c, Gb, b.w_o, S, d, d, dots ? EPI_STORE_DOT : EPI_STORE, c->DH, dots ? s.o : nullptr, N,
@@ -611,10 +651,14 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
       IL_TRY(hipStreamWaitEvent(c->main_stream, c->ev_tail[next / kGroup], 0));
       c->tail_pending[next / kGroup] = 0;
     }
-    if ((rc = ln_bwd(c, run, c->DH, s.xs, s.st1, b.ln1_g, c->ring[next].Ga + slot * d * eb, ln[1], &nblk))) return rc;
+    const RingEntry &n = c->ring[next];
+    if ((rc = ln_bwd(c, run, c->DH, s.xs, s.st1, b.ln1_g, n.Ga + slot * d * eb, ln[1], &nblk, n.sum[0],
+                     one && !lowest ? n.sum_cols[0] : nullptr, &c->above)))
+      return rc;
     ln_blocks += nblk;
   }
-  c->tails[c->ntails++] = Tail{&b, &s, &r, &runs, ln_blocks};
+  tail.ln_blocks = ln_blocks;
+  c->tails[c->ntails++] = tail;
   if (c->tail_inline || next % kGroup == 0)
     if ((rc = launch_tails(c))) return rc;
   c->pos = next;
@@ -755,6 +799,7 @@ int il_stage_forward(il_ctx *c, int32_t k, const float *x_in, float *x_out) {
     { const int rc = join_tails(c); if (rc) return rc; }  // ... or weight gradients of its backward
     c->ntails = 0;
     c->pos = 0;
+    c->above = Summed{};
   } else if (!c->fwd_done[k - 1]) {
     return IL_E_STATE;
   }
@@ -880,7 +925,7 @@ static int head_xent_impl(il_ctx *c, int32_t k, const float *x_k, const int32_t 
     c->tail_inline = true;  // already off the caller's stream: the block tails run in line, block by block
     for (int l = c->Lh - 1; l >= 0; --l) {
       const size_t bi = (size_t)(k - 1) * c->Lh + l;
-      int rc = block_backward(c, runs, c->hboff[bi], c->hsave[bi]);
+      int rc = block_backward(c, runs, c->hboff[bi], c->hsave[bi], l == 0);
       if (rc) return rc;
     }
     StreamWeights one;
@@ -1001,7 +1046,7 @@ int il_stage_backward_nwise(il_ctx *c, int32_t k, float *dx0_out) {
   }
   for (int l = c->L - 1; l >= 0; --l) {
     const size_t bi = (size_t)(k - 1) * c->L + l;
-    const int rc = block_backward(c, cp.runs, c->boff[bi], c->save[bi]);
+    const int rc = block_backward(c, cp.runs, c->boff[bi], c->save[bi], l == 0);
     if (rc) return rc;
   }
   // a tail that waits for a partner does not wait beyond the call: a caller that synchronises the device after

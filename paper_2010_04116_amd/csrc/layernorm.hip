@@ -2,6 +2,7 @@
 // row; row reductions are wavefront shuffles (no LDS), statistics are fp32.  The
 // backward is fused with the residual-gradient add (the gradient stream G is updated in
 // place) and with the first stage of the gamma/beta column reductions.
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -18,6 +19,10 @@ __device__ inline float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+
+template <typename T> __device__ inline float round_to(float v);
+template <> __device__ inline float round_to<float>(float v) { return v; }
+template <> __device__ inline float round_to<bf16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
 
 // Vector access helpers: V consecutive elements per lane (V = 4 when d and every address divide by 4, else 1).
 template <typename T, int V> struct Vec;
@@ -58,7 +63,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
   const int row = blockIdx.x * kWaves + wave;
   if (row >= rows) return;
   const float *xr = x + (size_t)row * d;
-  float v[J][V];
+  float v[J][V], g[J][V], b[J][V];  // gain and bias are requested with the row: after the reductions their latency stands alone
   float s = 0.f;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -69,9 +74,19 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
 #pragma unroll
       for (int e = 0; e < V; ++e) v[j][e] = 0.f;
     }
+  }
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = (lane + 64 * j) * V;
+    if (c < d) {
+      Vec<T, V>::load(gamma + c, g[j]);
+      Vec<T, V>::load(beta + c, b[j]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int e = 0; e < V; ++e) s += v[j][e];
-  }
   const float invd = 1.f / d;
   const float mean = wave_sum(s) * invd;
   float q = 0.f;
@@ -87,11 +102,9 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
   for (int j = 0; j < J; ++j) {
     const int c = (lane + 64 * j) * V;
     if (c >= d) continue;
-    float g[V], b[V], o[V];
-    Vec<T, V>::load(gamma + c, g);
-    Vec<T, V>::load(beta + c, b);
+    float o[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) o[e] = (v[j][e] - mean) * rstd * g[e] + b[e];
+    for (int e = 0; e < V; ++e) o[e] = (v[j][e] - mean) * rstd * g[j][e] + b[j][e];
     Vec<T, V>::store(y + (size_t)row * d + c, o);
     if (xcopy) Vec<float, V>::store(xcopy + (size_t)row * d + c, v[j]);
   }
@@ -101,86 +114,120 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
   }
 }
 
-// Backward, d divisible by 4: GW wavefronts share a row (a lane owns columns 4 l + 0..3 for its lane
-// number l in the group, d <= 256 GW), a workgroup walks over rows with NG groups.  Bound by its bytes
-// (16 per element and stream; 25 us for 8192 x 1024).  One wavefront per row needed 130 registers at
-// d = 1024 and 235 at 2048; this form stays near 70, so that its workgroups start beside those of a
-// 256x256 GEMM tile of the other stream, which leaves 76 registers a lane.
-template <typename T, int GW>
+// Backward, d divisible by 4: GW wavefronts share a token (a lane owns columns 4 l + 0..3 for its lane number l
+// in the group, d <= 256 GW), a workgroup walks over tokens with NG groups, a token's streams NS at a time: x
+// and the statistics are read once for all of them, and their weighted sum - what the weight gradient of the linear
+// map in front of this LayerNorm multiplies with - and its column sums are left beside them instead of in a
+// pass of their own, which read every stream again.  Bound by its bytes.  One wavefront per row needed 130
+// registers at d = 1024 and 235 at 2048; this form stays under 76, so that its workgroups start beside those
+// of a 256x256 GEMM tile of the other stream, which leaves 76 registers a lane.
+template <typename T, int GW, int NS>
 __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const T *__restrict__ dy, const float *__restrict__ x,
                                                            const float *__restrict__ stats,
-                                                           const T *__restrict__ gamma, int rows, int N, int d, float *G,
-                                                           T *Gb, StreamWeights sw, float *__restrict__ partials) {
+                                                           const T *__restrict__ gamma, int ns, int N, int d, float *G,
+                                                           T *Gb, StreamWeights sw, float *__restrict__ partials, T *ysum,
+                                                           float *__restrict__ ypart) {
   constexpr int NG = GW > 4 ? 1 : 4 / GW, GL = 64 * GW;
-  __shared__ float red[2][NG][GW][2];
+  __shared__ float red[2][NG][GW][2 * NS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = wave / GW, wg = wave % GW, l = wg * 64 + lane;
-  float dg[4], db[4], gm[4];
+  float dg[4], db[4], dy1[4], gm[4];
   const int c = l * 4;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) { dg[e] = 0.f; db[e] = 0.f; gm[e] = 0.f; }
+  for (int e = 0; e < 4; ++e) { dg[e] = 0.f; db[e] = 0.f; dy1[e] = 0.f; gm[e] = 0.f; }
   if (c < d) Vec<T, 4>::load(gamma + c, gm);
   const float invd = 1.f / d;
   const int step = gridDim.x * NG;
-  const int trips = (rows + step - 1) / step;  // the same for every wavefront: the barrier below is theirs together
+  const int trips = (N + step - 1) / step;  // the same for every wavefront: the barrier below is theirs together
+  int turn = 0;
   for (int it = 0; it < trips; ++it) {
-    const int row = it * step + blockIdx.x * NG + grp;
-    const bool live = row < rows;
-    const int tok = live ? row % N : 0;
-    const float w = live ? sw.w[row / N] : 0.f;
-    const float mean = stats[2 * tok], rstd = stats[2 * tok + 1];
-    const float *xr = x + (size_t)tok * d;
-    const T *dyr = dy + (size_t)row * d;
-    float *gr = G + (size_t)row * d;
-    T *gbr = Gb + (size_t)row * d;
-    float xh[4], dv[4], gv[4];
-    float s1 = 0.f, s2 = 0.f;
-    const bool in = live && c < d;
-    if (in) {
-      Vec<T, 4>::load(dyr + c, dv);
-      Vec<float, 4>::load(xr + c, xh);
-      Vec<float, 4>::load(gr + c, gv);
-    }
+    const int tok = it * step + blockIdx.x * NG + grp;
+    const bool in = tok < N && c < d;
+    const int t0 = tok < N ? tok : 0;
+    const float mean = stats[2 * t0], rstd = stats[2 * t0 + 1];
+    float xh[4] = {0.f, 0.f, 0.f, 0.f}, y[4] = {0.f, 0.f, 0.f, 0.f};
+    if (in) Vec<float, 4>::load(x + (size_t)tok * d + c, xh);
+    for (int s0 = 0; s0 < ns; s0 += NS, turn ^= 1) {
+      float dv[NS][4], gv[NS][4], sum[2 * NS];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      dv[e] = in ? dv[e] : 0.f;
-      xh[e] = in ? (xh[e] - mean) * rstd : 0.f;
-      const float t = dv[e] * gm[e];
-      s1 += t;
-      s2 += t * xh[e];
-      dg[e] += w * dv[e] * xh[e];
-      db[e] += w * dv[e];
-    }
-    s1 = wave_sum(s1);
-    s2 = wave_sum(s2);
-    if constexpr (GW > 1) {
-      float *r = red[it & 1][grp][wg];
-      if (lane == 0) { r[0] = s1; r[1] = s2; }
-      __syncthreads();  // (the other half of `red` is written next, so one barrier a row is enough)
-      s1 = s2 = 0.f;
+      for (int k = 0; k < NS; ++k) {
+        const bool live = in && (NS == 1 || s0 + k < ns);
+        const size_t at = ((size_t)(s0 + k) * N + tok) * d + c;
+        if (live) {
+          Vec<T, 4>::load(dy + at, dv[k]);
+          Vec<float, 4>::load(G + at, gv[k]);
+        }
 #pragma unroll
-      for (int k = 0; k < GW; ++k) { s1 += red[it & 1][grp][k][0]; s2 += red[it & 1][grp][k][1]; }
-    }
-    const float m1 = s1 * invd, m2 = s2 * invd;
-    if (in) {
+        for (int e = 0; e < 4; ++e) dv[k][e] = live ? dv[k][e] : 0.f;
+      }
+      if (s0 == 0) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) gv[e] += rstd * (dv[e] * gm[e] - m1 - xh[e] * m2);
-      Vec<float, 4>::store(gr + c, gv);
-      Vec<T, 4>::store(gbr + c, gv);
+        for (int e = 0; e < 4; ++e) xh[e] = in ? (xh[e] - mean) * rstd : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const float w = NS == 1 || s0 + k < ns ? sw.w[s0 + k] : 0.f;
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float t = dv[k][e] * gm[e];
+          s1 += t;
+          s2 += t * xh[e];
+          dg[e] += w * dv[k][e] * xh[e];
+          db[e] += w * dv[k][e];
+        }
+        sum[2 * k] = wave_sum(s1);
+        sum[2 * k + 1] = wave_sum(s2);
+      }
+      if constexpr (GW > 1) {
+        float *r = red[turn][grp][wg];
+        if (lane == 0) {
+#pragma unroll
+          for (int k = 0; k < 2 * NS; ++k) r[k] = sum[k];
+        }
+        __syncthreads();  // (the other half of `red` is written next, so one barrier a turn is enough)
+#pragma unroll
+        for (int k = 0; k < 2 * NS; ++k) {
+          sum[k] = 0.f;
+#pragma unroll
+          for (int q = 0; q < GW; ++q) sum[k] += red[turn][grp][q][k];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        if (!in || (NS > 1 && s0 + k >= ns)) continue;
+        const float m1 = sum[2 * k] * invd, m2 = sum[2 * k + 1] * invd, w = sw.w[s0 + k];
+        const size_t at = ((size_t)(s0 + k) * N + tok) * d + c;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gv[k][e] += rstd * (dv[k][e] * gm[e] - m1 - xh[e] * m2);
+        Vec<float, 4>::store(G + at, gv[k]);
+        Vec<T, 4>::store(Gb + at, gv[k]);
+        if (ypart && w != 0.f) {  // (uniform) the sum is taken of the stored values
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] += w * round_to<T>(gv[k][e]);
+        }
+      }
+    }
+    if (ypart && in) {
+      if (ysum) Vec<T, 4>::store(ysum + (size_t)tok * d + c, y);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dy1[e] += y[e];
     }
   }
   // column sums of the workgroup: its groups combine through LDS, fixed order
-  float *pg = partials + (size_t)blockIdx.x * 2 * d;
+  float *pg = partials + (size_t)blockIdx.x * 2 * d, *py = ypart ? ypart + (size_t)blockIdx.x * d : nullptr;
   if constexpr (NG == 1) {
     if (c < d) {
       Vec<float, 4>::store(pg + c, dg);
       Vec<float, 4>::store(pg + d + c, db);
+      if (py) Vec<float, 4>::store(py + c, dy1);
     }
   } else {
-    __shared__ float4 cols[NG][2][GL];
+    __shared__ float4 cols[NG][3][GL];
     cols[grp][0][l] = make_float4(dg[0], dg[1], dg[2], dg[3]);
     cols[grp][1][l] = make_float4(db[0], db[1], db[2], db[3]);
+    cols[grp][2][l] = make_float4(dy1[0], dy1[1], dy1[2], dy1[3]);
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * GL; i += 256) {
+    for (int i = threadIdx.x; i < (py ? 3 : 2) * GL; i += 256) {
       const int which = i / GL, col = (i % GL) * 4;
       if (col >= d) continue;
       float4 a = cols[0][which][i % GL];
@@ -189,7 +236,7 @@ __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const 
         const float4 b = cols[k][which][i % GL];
         a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
       }
-      *reinterpret_cast<float4 *>(pg + which * d + col) = a;
+      *reinterpret_cast<float4 *>(which == 2 ? py + col : pg + which * d + col) = a;
     }
   }
 }
@@ -317,23 +364,34 @@ void launch_fwd(hipStream_t s, const float *x, const T *gamma, const T *beta, fl
   });
 }
 template <typename T>
-void launch_bwd(int blocks, hipStream_t s, const T *dy, const float *x, const float *stats, const T *gamma, int rows,
-                int N, int d, float *G, T *Gb, StreamWeights sw, float *partials) {
-  auto launch = [&](auto kernel, int threads) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, dy, x, stats, gamma, rows, N, d, G, Gb, sw, partials);
-  };
+void launch_bwd(hipStream_t s, const T *dy, const float *x, const float *stats, const T *gamma, int ns, int N, int d,
+                float *G, T *Gb, const StreamWeights &sw, float *partials, int *nblk, T *ysum, float *ypart, bool *summed) {
+  *summed = false;
   if (!vec4<T>(d, gamma, gamma, x, G)) {
-    if (d <= 256) launch(ln_bwd_kernel<T, 1, 4>, 256);
-    else launch(ln_bwd_kernel<T, 1, 32>, 256);
-  } else if (d <= 256) {
-    launch(ln_bwd_group_kernel<T, 1>, 256);
-  } else if (d <= 512) {
-    launch(ln_bwd_group_kernel<T, 2>, 256);
-  } else if (d <= 1024) {
-    launch(ln_bwd_group_kernel<T, 4>, 256);
-  } else {
-    launch(ln_bwd_group_kernel<T, 8>, 512);
+    const int rows = ns * N;
+    *nblk = std::min((rows + kWaves - 1) / kWaves, kLnBwdBlocks);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(256), 0, s, dy, x, stats, gamma, rows, N, d, G, Gb, sw, partials);
+    };
+    if (d <= 256) launch(ln_bwd_kernel<T, 1, 4>);
+    else launch(ln_bwd_kernel<T, 1, 32>);
+    return;
   }
+  *summed = ypart != nullptr;
+  auto launch = [&](auto gw) {
+    constexpr int GW = decltype(gw)::value, NG = GW > 4 ? 1 : 4 / GW;
+    *nblk = std::min((N + NG - 1) / NG, kLnBwdBlocks);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(GW > 4 ? 512 : 256), 0, s, dy, x, stats, gamma, ns, N, d, G, Gb, sw,
+                         partials, ysum, ypart);
+    };
+    if (ns == 1) go(ln_bwd_group_kernel<T, GW, 1>);
+    else go(ln_bwd_group_kernel<T, GW, 2>);
+  };
+  if (d <= 256) launch(std::integral_constant<int, 1>{});
+  else if (d <= 512) launch(std::integral_constant<int, 2>{});
+  else if (d <= 1024) launch(std::integral_constant<int, 4>{});
+  else launch(std::integral_constant<int, 8>{});
 }
 
 }  // namespace
@@ -349,18 +407,15 @@ hipError_t ln_forward(int dtype, const float *x, const void *gamma, const void *
   return hipGetLastError();
 }
 
-hipError_t ln_backward_residual(int dtype, const void *dy, const float *x, const float *stats,
-                                const void *gamma, int rows, int N, int d, float *G, void *Gb,
-                                StreamWeights sw, float *partials, int *nblk, hipStream_t s) {
-  int blocks = (rows + kWaves - 1) / kWaves;
-  if (blocks > kLnBwdBlocks) blocks = kLnBwdBlocks;
-  *nblk = blocks;
+hipError_t ln_backward_residual(int dtype, const void *dy, const float *x, const float *stats, const void *gamma,
+                                int ns, int N, int d, float *G, void *Gb, const StreamWeights &sw, float *partials,
+                                int *nblk, void *ysum, float *ypart, bool *summed, hipStream_t s) {
   if (dtype == 0)
-    launch_bwd<float>(blocks, s, (const float *)dy, x, stats, (const float *)gamma, rows, N, d, G, (float *)Gb, sw,
-                      partials);
+    launch_bwd<float>(s, (const float *)dy, x, stats, (const float *)gamma, ns, N, d, G, (float *)Gb, sw, partials, nblk,
+                      (float *)ysum, ypart, summed);
   else
-    launch_bwd<bf16_t>(blocks, s, (const bf16_t *)dy, x, stats, (const bf16_t *)gamma, rows, N, d, G, (bf16_t *)Gb, sw,
-                       partials);
+    launch_bwd<bf16_t>(s, (const bf16_t *)dy, x, stats, (const bf16_t *)gamma, ns, N, d, G, (bf16_t *)Gb, sw, partials,
+                       nblk, (bf16_t *)ysum, ypart, summed);
   return hipGetLastError();
 }
 

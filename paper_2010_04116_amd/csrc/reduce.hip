@@ -155,9 +155,16 @@ __global__ __launch_bounds__(256) void convert_kernel(const float *__restrict__ 
 
 __global__ __launch_bounds__(256) void sum_scalar_kernel(const float *__restrict__ v, int n, float scale,
                                                          float *__restrict__ out) {
+  constexpr int U = 8;  // loads in flight per thread
   __shared__ float red[256];
   float acc = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) acc += v[i];
+  for (int i0 = threadIdx.x; i0 < n; i0 += 256 * U) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = i0 + 256 * u < n ? v[i0 + 256 * u] : 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += x[u];
+  }
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
@@ -204,16 +211,26 @@ hipError_t sum_colsum_multi(int dtype, const SumColsumJobs &jobs, int *nblk, hip
 }
 
 // Several second stages in one launch: grid.y selects the job.  Block = 16 columns x 16 partial lanes;
-// fixed summation order.
+// fixed summation order.  A thread has up to 32 partials to add and nothing else to do: bound by the latency of
+// its loads, so eight are in flight.
 __global__ __launch_bounds__(256) void colsum_final_multi_kernel(ColsumJobs jobs) {
+  constexpr int U = 8;
   __shared__ float red[16][17];
   const ColsumJob &jb = jobs.job[blockIdx.y];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + tx;
   if (blockIdx.x * 16 >= jb.cols) return;  // uniform across the block
   float acc = 0.f;
-  if (c < jb.cols)
-    for (int p = ty; p < jb.nblk; p += 16) acc += jb.partials[(size_t)p * jb.cols + c];
+  if (c < jb.cols) {
+    const float *__restrict__ col = jb.partials + c;
+    for (int p0 = ty; p0 < jb.nblk; p0 += 16 * U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = p0 + 16 * u < jb.nblk ? col[(size_t)(p0 + 16 * u) * jb.cols] : 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v[u];
+    }
+  }
   red[ty][tx] = acc;
   __syncthreads();
   if (ty == 0 && c < jb.cols) {
