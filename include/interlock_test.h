@@ -44,7 +44,10 @@ int il_profile_read(il_ctx *ctx, int32_t cap, const char **names, int64_t *launc
  *      every group of 64 columns, followed by fp32 [M] target logits z[row, aux[row]] with aux = int32 [M]
  *      targets (rows whose target is outside [0, N) are left unwritten) |
  *      8 store (T) and, in C2 = fp32 [N / 32][M], the sums over 32 columns each of C as stored times
- *      aux[row % aux_wrap] (bf16 operands, N a multiple of 32, data-gradient layout only);
+ *      aux[row % aux_wrap] (bf16 operands, N a multiple of 32, data-gradient layout only) |
+ *      9 as 4 for `beta` (1 or 2) streams stacked over M / beta rows, a multiple of 64, aux with as many rows, ldc = N
+ *      (bf16, data-gradient layout only): C2 = bf16 [M / beta][N], scale * stream 0 + stream 1 of C as stored, followed
+ *      by fp32 [M / beta / 64][N], its column sums over runs of 64 rows before it was rounded;
  * tile: 0 = library's choice, else for fp32 2 = 128x128, 3 = 128x64, any other 64x64 (operands whose rows do not
  *       divide by four always take the last), and for bf16 ("+4" = four wavefronts that only load)
  *       1 = 256x256 / 8 wavefronts in two groups that take turns, 2 = 128x128 / 4+4, two K steps staged, 3 = 128x128 / 4+4, four staged,

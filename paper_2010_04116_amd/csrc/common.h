@@ -92,6 +92,10 @@ enum Epi {
   EPI_WGRAD = 6,      // Cf = scale*acc (+ Cf if beta)            (fp32 out)
   EPI_STORE_DOT = 8,  // C = acc (bf16 out), and row_stats [N / 32][M] fp32: sums over 32 columns of C * aux
                       // (aux as for EPI_GELU_BWD): the row sums dO * O of the attention backward
+  EPI_GELU_BWD_SUM = 10,  // EPI_GELU_BWD for `streams` (1 or 2) streams stacked over M / streams tokens, which also leaves
+                      // their sum, sum_w[0] C0 + sum_w[1] C1 of the values as stored, in C2 (T; unless NULL) and the
+                      // sum's column sums over runs of 64 tokens in row_stats [ceil(tokens / 64)][N] (fp32); bf16,
+                      // where gemm_gelu_sum() says so
   EPI_LOGITS = 7      // the head's logits tile (bf16 operands only): C = acc as IEEE half, clamped to +-65504 (the
                       // softmax wants the three extra mantissa bits and never the range); and, when row_stats is
                       // set, softmax statistics straight from the fp32 accumulators: for every row and every
@@ -126,6 +130,8 @@ struct GemmArgs {
   // EPI_STORE_DOT: row_stats.  EPI_LOGITS, all optional together: row_stats [M][ceil(N / kStatGroup)][2] fp32, row_targets [M] int32,
   // row_ztgt [M] fp32 (written for rows whose target lies in [0, N))
   float *row_stats;
+  int streams;        // EPI_GELU_BWD_SUM
+  float sum_w[2];
   const int32_t *row_targets;
   float *row_ztgt;
 };
@@ -144,6 +150,7 @@ hipError_t gemm_bf16(const GemmArgs &g, hipStream_t s);   // T = bf16, MFMA
 constexpr int kMaxBatch = 8;
 hipError_t gemm_f32_batch(const GemmArgs *list, int count, hipStream_t s);
 hipError_t gemm_bf16_batch(const GemmArgs *list, int count, hipStream_t s);
+bool gemm_gelu_sum(int streams, int tokens, int N);  // see EPI_GELU_BWD_SUM
 // Split-K for EPI_STORE_F32: `splits` partial products over disjoint K ranges go to ws ([splits][M][N] fp32)
 // in one launch with the given tile, then a reduction adds them up in a fixed order.
 struct SplitPlan { int splits, tile; };

@@ -32,6 +32,7 @@
 namespace il {
 namespace {
 
+constexpr long kPairTiles = 160;  // 256x256 tiles from which that tile is taken
 constexpr int EPI_WGRAD_ACC = 9;  // EPI_WGRAD where every problem of the launch accumulates
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -62,7 +63,7 @@ __device__ inline float dpp_f32(float v) {
 // What the epilogue reads at a row's eight consecutive output columns, besides bias: the pre-activation or
 // attention output (bf16), the residual or the accumulated-into output (fp32).
 struct Extra { u32x4 q[2]; };
-template <int EPI> constexpr bool kExtraBf16 = EPI == EPI_GELU_BWD || EPI == EPI_STORE_DOT;
+template <int EPI> constexpr bool kExtraBf16 = EPI == EPI_GELU_BWD || EPI == EPI_GELU_BWD_SUM || EPI == EPI_STORE_DOT;
 template <int EPI> constexpr bool kExtraF32 = EPI == EPI_BIAS_RES || EPI == EPI_WGRAD_ACC;
 template <int EPI>
 __device__ inline Extra load_extra(const GemmArgs &g, int grow, int gcol) {
@@ -249,6 +250,85 @@ __device__ inline void epilogue_strips(const GemmArgs &g, floatx16 (&acc)[MI][NI
       }
       emit8<EPI>(g, v0, v1, grow, gcol, bv, ex.x[EpiExtras<WTN, EPI, MI>::COUNT > 1 ? i * E::NSTRIP + p : 0]);
     }
+}
+
+// EPI_GELU_BWD_SUM on a wave's two 64 x 64 pieces: of two streams the same tokens (one pre-activation, one
+// derivative and one sum for both), of one stream two runs of 64 rows.  Column sums of the pieces' sum, as stored,
+// go to row (first row of the piece) / 64 of g.row_stats.  limit: rows beyond it do not exist.
+__device__ inline void epilogue_gelu_sum(const GemmArgs &g, floatx16 (&acc)[2][2][2], float *stg, int r0, int r1, int limit0,
+                                         int limit1, int col0, int lane, const EpiExtras<64, EPI_GELU_BWD_SUM, 2> (&ex)[2]) {
+  typedef EpiStrip<64> E;
+  constexpr int SP = E::SP;
+  const int hh = lane >> 5, lq = lane & 31, col_l = (lane & 7) * 8, row_in = lane >> 3, gcol = col0 + col_l;
+  const bool two = g.streams == 2, in = gcol < g.N;
+  float cols[2][8] = {};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) stg[h * E::FLOATS + (4 * hh + e) * SP + j * 32 + lq] = acc[h][i][j][4 * p + e];
+      asm volatile("" ::: "memory");
+      float v[2][8], d[8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 f = *reinterpret_cast<const float4 *>(stg + h * E::FLOATS + row_in * SP + col_l + 4 * q);
+          v[h][4 * q] = f.x; v[h][4 * q + 1] = f.y; v[h][4 * q + 2] = f.z; v[h][4 * q + 3] = f.w;
+        }
+      asm volatile("" ::: "memory");
+      const int row = i * 32 + p * 8 + row_in;
+      float sum[8] = {};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h == 0 || !two) {
+          unpack8(ex[h].x[i * 4 + p].q[0], d);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d[e] = gelu_grad_f(d[e]);
+        }
+        const int grow = (h ? r1 : r0) + row;
+        if (!in || grow >= (h ? limit1 : limit0)) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[h][e] *= d[e];
+        const u32x4 o = pack8(v[h]);
+        *reinterpret_cast<u32x4 *>((bf16_t *)g.C + (size_t)grow * g.ldc + gcol) = o;
+        float y[8];
+        unpack8(o, y);
+        const float w = g.sum_w[two ? h : 0];
+        if (w != 0.f) {  // (uniform)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sum[e] += w * y[e];
+        }
+        if (h == 1 || !two) {
+          if (g.C2) *reinterpret_cast<u32x4 *>((bf16_t *)g.C2 + (size_t)((two ? r0 : grow - row) + row) * g.ldc + gcol) = pack8(sum);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { cols[two ? 0 : h][e] += sum[e]; sum[e] = 0.f; }
+        }
+      }
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && two) break;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float c = cols[h][e];
+      c += __shfl_xor(c, 8, 64);
+      c += __shfl_xor(c, 16, 64);
+      c += __shfl_xor(c, 32, 64);
+      cols[h][e] = c;
+    }
+    const int row = h ? r1 : r0;
+    if (lane < 8 && in && row < (h ? limit1 : limit0)) {
+      float *o = g.row_stats + (size_t)(row >> 6) * g.N + gcol;
+      *reinterpret_cast<float4 *>(o) = make_float4(cols[h][0], cols[h][1], cols[h][2], cols[h][3]);
+      *reinterpret_cast<float4 *>(o + 4) = make_float4(cols[h][4], cols[h][5], cols[h][6], cols[h][7]);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -566,14 +646,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int i = 0; i < batch.count - 1; ++i)
     if ((int)blockIdx.x >= batch.tile_end[i]) { prob = i + 1; tile0 = batch.tile_end[i]; }
   GemmArgs g = batch.p[prob];
-  const int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
+  // The tile's two halves are 128 rows each: consecutive, or (EPI_GELU_BWD_SUM of two streams stacked over
+  // M / 2 tokens) the same tokens of either stream.
+  const int half = EPI == EPI_GELU_BWD_SUM && g.streams == 2 ? g.M >> 1 : 0;
+  const int tiles_m = half ? (half + 127) / 128 : (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
   int kb0, ke;
   int pid = my_tile(g, blockIdx.x - tile0, tiles_m * tiles_n, kb0, ke);
   constexpr int GM = 8;
   const int per_group = GM * tiles_n;
   const int group = pid / per_group, first_m = group * GM;
   const int gsize = min(tiles_m - first_m, GM);
-  const int m0 = (first_m + (pid % per_group) % gsize) * 256, n0 = ((pid % per_group) / gsize) * 256;
+  const int tm = first_m + (pid % per_group) % gsize, n0 = ((pid % per_group) / gsize) * 256;
+  const int m0 = tm * (half ? 128 : 256), m1 = half ? half + m0 : m0 + 128;
+  const int limit0 = half ? half : g.M;
   const int nk = (ke - kb0 + 63) / 64;
 
   const BufRsrc ra = make_rsrc(g.A, g.a_bytes), rb = make_rsrc(g.B, g.b_bytes);
@@ -581,7 +666,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   TB lb[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    la[i].init(m0 + 128 * i, g.M, g.lda, t);
+    la[i].init(i ? m1 : m0, i ? g.M : limit0, g.lda, t);
     lb[i].init(n0 + 128 * i, g.N, g.ldb, t);
   }
   // LDS slot s & 1: A half 0, A half 1, B half 0, B half 1.  A step past the last one loads zeros (every lane
@@ -664,16 +749,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     products(std::integral_constant<int, 1>{});
   }
   wait_vmcnt<0>();           // (the zeros of the steps past the end have landed: the epilogue reuses the slots)
-  const int r0 = m0 + wm * 64, c0 = n0 + wn * 64;
+  const int r0 = m0 + wm * 64, r1 = m1 + wm * 64, c0 = n0 + wn * 64;
   EpiExtras<64, EPI, 2> ex[2];  // bf16 reads of both halves fit the registers the fragments leave, fp32 reads of one
   ex[0].load(g, r0, c0, lane);
-  if constexpr (!kExtraF32<EPI>) ex[1].load(g, r0 + 128, c0, lane);
+  if constexpr (!kExtraF32<EPI>) {
+    if (!half) ex[1].load(g, r1, c0, lane);
+  }
   if (wm == 0) hand_over();
   hand_over();
-  float *stg = reinterpret_cast<float *>(smem) + wave * EpiStrip<64>::FLOATS;
-  epilogue_strips<64, EPI>(g, acc[0], stg, r0, c0, lane, ex[0]);
-  if constexpr (kExtraF32<EPI>) ex[1].load(g, r0 + 128, c0, lane);
-  epilogue_strips<64, EPI>(g, acc[1], stg, r0 + 128, c0, lane, ex[1]);
+  if constexpr (EPI == EPI_GELU_BWD_SUM) {
+    float *stg = reinterpret_cast<float *>(smem) + 2 * wave * EpiStrip<64>::FLOATS;
+    epilogue_gelu_sum(g, acc, stg, r0, r1, limit0, g.M, c0, lane, ex);
+  } else {
+    float *stg = reinterpret_cast<float *>(smem) + wave * EpiStrip<64>::FLOATS;
+    epilogue_strips<64, EPI>(g, acc[0], stg, r0, c0, lane, ex[0]);
+    if constexpr (kExtraF32<EPI>) ex[1].load(g, r1, c0, lane);
+    epilogue_strips<64, EPI>(g, acc[1], stg, r1, c0, lane, ex[1]);
+  }
 }
 
 thread_local const KernelTimer *tl_timer = nullptr;  // armed by gemm_time_next()
@@ -701,7 +793,8 @@ template <bool AKM, bool BKM, int EPI>
 hipError_t launch_pair(GemmBatch &b, hipStream_t s) {
   int tiles = 0;
   for (int i = 0; i < b.count; ++i) {
-    tiles += ((b.p[i].M + 255) / 256) * ((b.p[i].N + 255) / 256) * std::max(b.p[i].splits, 1);
+    const int rows = EPI == EPI_GELU_BWD_SUM && b.p[i].streams == 2 ? (b.p[i].M / 2 + 127) / 128 : (b.p[i].M + 255) / 256;
+    tiles += rows * ((b.p[i].N + 255) / 256) * std::max(b.p[i].splits, 1);
     b.tile_end[i] = tiles;
   }
   if (const KernelTimer *t = tl_timer) {
@@ -747,7 +840,7 @@ hipError_t pick_tile(GemmBatch &b, hipStream_t s) {
   // workgroup's K loop, which is what bounds such a launch: loader wavefronts and four stages while at
   // most two workgroups land on a CU (the deeper ring covers the trip to HBM), beyond that up to five
   // plain small workgroups per CU that cover for each other.
-  if (t256 >= 160) return launch_pair<AKM, BKM, EPI>(b, s);
+  if (t256 >= kPairTiles) return launch_pair<AKM, BKM, EPI>(b, s);
   if (t128 >= 192 && t128 <= 256) return launch_dma<128, 128, 2, 2, 4, AKM, BKM, EPI, true>(b, s);
   // about one 256x128 (or 128x256) tile per CU, three stages: as good as the 128x128 tile on cached
   // operands and 15-20 % better on operands from HBM (fewer bytes per flop, deeper ring)
@@ -774,6 +867,9 @@ hipError_t prepare(GemmArgs &g) {
   if (!g.b_kmajor && (g.K & 7)) return hipErrorInvalidValue;
   if (!split_ok(g)) return hipErrorInvalidValue;
   if (g.epi == EPI_STORE_DOT && (!g.row_stats || !g.aux || g.aux_wrap < 1 || (g.N & 31))) return hipErrorInvalidValue;
+  if (g.epi == EPI_GELU_BWD_SUM && (!g.row_stats || !g.aux || (g.streams != 1 && (g.streams != 2 || (g.M & 127) || g.aux_wrap != g.M / 2)) ||
+                                    ((uintptr_t)g.row_stats & 15) || ((uintptr_t)g.C2 & 15) || g.aux_wrap < 1 || g.splits > 1))
+    return hipErrorInvalidValue;
   if (g.epi == EPI_LOGITS && g.row_stats && (!g.row_targets || !g.row_ztgt)) return hipErrorInvalidValue;
   const size_t arows = g.a_kmajor ? (size_t)g.K : (size_t)g.M;
   const size_t brows = g.b_kmajor ? (size_t)g.K : (size_t)g.N;
@@ -843,6 +939,7 @@ hipError_t gemm_bf16_batch(const GemmArgs *list, int count, hipStream_t s) {
         case EPI_STORE: return pick_tile<false, false, EPI_STORE>(b, s);
         case EPI_STORE_DOT: return pick_tile<false, false, EPI_STORE_DOT>(b, s);
         case EPI_GELU_BWD: return pick_tile<false, false, EPI_GELU_BWD>(b, s);
+        case EPI_GELU_BWD_SUM: return launch_pair<false, false, EPI_GELU_BWD_SUM>(b, s);
         case EPI_STORE_F32: return pick_tile<false, false, EPI_STORE_F32>(b, s);
         default: return hipErrorInvalidValue;
       }
@@ -856,6 +953,12 @@ hipError_t gemm_bf16_batch(const GemmArgs *list, int count, hipStream_t s) {
 }
 
 hipError_t gemm_bf16(const GemmArgs &g, hipStream_t s) { return gemm_bf16_batch(&g, 1, s); }
+
+// The 256x256 tile has both streams' halves of a token in one lane; it is taken where it is the choice anyway.
+bool gemm_gelu_sum(int streams, int tokens, int N) {
+  const long rows = streams == 2 ? (tokens + 127) / 128 : (tokens + 255) / 256;
+  return (streams == 1 || streams == 2) && rows * ((N + 255) / 256) >= kPairTiles;
+}
 
 // Prices every number of parts with every tile (measured microseconds per 64-deep K step of a workgroup:
 // the 128x128 tile alone on its CU 0.47 with four stages, two of them with two stages 0.96; 256x256 1.35;

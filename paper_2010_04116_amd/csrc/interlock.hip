@@ -170,6 +170,7 @@ struct RingEntry {
   // What the LayerNorm that makes Ga (Gb) leaves with it: the weighted sum over the streams [N, d] (where there
   // are several) and the first stage of its column sums.
   char *sum[2]; float *sum_cols[2];
+  char *sum_du; float *sum_du_cols;  // the same of DU, left by the product that makes it
 };
 // A block's linear outputs in the order FC2, FC1, attention output projection, QKV: the streams' weighted sum as
 // an operand, and its column sums' first stage, where the kernel that made the streams has left them.
@@ -286,6 +287,11 @@ size_t head_split_floats(const il_ctx *c, int rows, size_t floats) {
   return sp > 1 ? (size_t)sp * rows * c->d : 0;
 }
 
+// The FC2 data gradient of these ranges leaves DU's sum of streams beside it.
+bool gelu_sums(const il_ctx *c, const std::vector<Run> &runs) {
+  return c->eb == 2 && runs.size() == 1 && gemm_gelu_sum(runs[0].cnt, c->N, c->m);
+}
+
 size_t layout_workspace(il_ctx *c, void *base) {
   Carver cv(base);
   const size_t N = c->N, d = c->d, m = c->m, eb = c->eb, H = c->H;
@@ -309,9 +315,15 @@ size_t layout_workspace(il_ctx *c, void *base) {
   // (one more stream slot carries a head's gradient through its own blocks)
   const size_t ns = c->plan.nslots + (c->Lh ? 1 : 0), S = (size_t)std::max(c->plan.maxcnt, 1) * N;
   const size_t live = (size_t)std::max(c->plan.maxlive, 1) * N;
-  bool sums = false;  // some component's streams are not their sum as they are
+  bool sums = false, du_sums = false, du_cols = false;  // some component's streams are not their sum as they are; ... and DU's is made with it; ...
   for (const CompPlan &k : c->plan.comp)
-    for (const Run &r : k.runs) sums = sums || (weighted(r).n && !weighted(r).plain);
+    for (const Run &r : k.runs) {
+      const bool plain = !weighted(r).n || weighted(r).plain, gelu = gelu_sums(c, k.runs);
+      sums = sums || !plain;
+      du_sums = du_sums || (gelu && !plain);
+      du_cols = du_cols || gelu;
+    }
+  du_cols = du_cols || (c->Lh && c->eb == 2 && gemm_gelu_sum(1, c->N, c->m));  // (a head's own blocks: one stream)
   c->G = (float *)cv.take(ns * N * d * 4);
   for (RingEntry &r : c->ring) {
     r.Ga = (char *)cv.take(ns * N * d * eb);
@@ -321,6 +333,8 @@ size_t layout_workspace(il_ctx *c, void *base) {
     for (float *&p : r.ln) p = (float *)cv.take((size_t)c->plan.maxruns * ln_backward_max_blocks() * 2 * d * 4);
     for (char *&p : r.sum) p = (char *)cv.take(sums ? N * d * eb : 0);
     for (float *&p : r.sum_cols) p = (float *)cv.take((size_t)ln_backward_max_blocks() * d * 4);
+    r.sum_du = (char *)cv.take(du_sums ? N * m * eb : 0);
+    r.sum_du_cols = (float *)cv.take(du_cols ? (N + 63) / 64 * m * 4 : 0);
   }
   c->DH = (char *)cv.take(S * d * eb);
   c->dsum = (float *)cv.take(S * std::max(H, d / 32) * 4);
@@ -388,6 +402,7 @@ double gemm_bytes(il_ctx *c, const GemmArgs &g) {
     case EPI_BIAS_RES: b += 2 * mn * 4; break;
     case EPI_GELU_BWD:
     case EPI_STORE_DOT: b += 2 * mn * eb; break;
+    case EPI_GELU_BWD_SUM: b += (1.0 + 1.0 / g.streams + (g.C2 ? 1.0 / g.streams : 0.0)) * mn * eb; break;
     case EPI_STORE_F32: b += mn * 4; break;
     case EPI_WGRAD: b += mn * 4 * (g.beta ? 2 : 1); break;
     default: b += mn * eb; break;
@@ -417,9 +432,13 @@ int linear_fwd(il_ctx *c, const void *x, size_t w_off, size_t b_off, int M, int 
 
 // dx[M,Kin] = dy[M,Nout] W[Kin,Nout]^T
 int linear_dgrad(il_ctx *c, const void *dy, size_t w_off, int M, int Kin, int Nout, int epi, void *out,
-                 const void *aux, int aux_wrap, float *dots = nullptr) {
+                 const void *aux, int aux_wrap, float *stats = nullptr, void *sum = nullptr, const Run *run = nullptr) {
   GemmArgs g = base_args();
-  g.row_stats = dots;
+  g.row_stats = stats; g.C2 = sum;
+  if (run) {
+    g.streams = run->cnt;
+    for (int i = 0; i < run->cnt; ++i) g.sum_w[i] = run->wt[i];
+  }
   g.A = dy; g.lda = Nout; g.a_kmajor = 0;
   g.B = P(c, w_off); g.ldb = Nout; g.b_kmajor = 0;
   g.M = M; g.N = Kin; g.K = Nout; g.epi = epi; g.C = out; g.ldc = Kin; g.aux = aux; g.aux_wrap = aux_wrap;
@@ -634,7 +653,14 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
     float *ln[2] = {r.ln[0] + (size_t)ln_blocks * 2 * d, r.ln[1] + (size_t)ln_blocks * 2 * d};
     int nblk = 0;
     // MLP
-    if ((rc = linear_dgrad(c, Ga, b.w_fc2, S, m, d, EPI_GELU_BWD, DU, s.u, N))) return rc;
+    if (gelu_sums(c, runs)) {
+      const Weighted w = weighted(run);
+      void *sum = w.plain ? nullptr : r.sum_du;
+      if ((rc = linear_dgrad(c, Ga, b.w_fc2, S, m, d, EPI_GELU_BWD_SUM, DU, s.u, N, r.sum_du_cols, sum, &run))) return rc;
+      tail.done[1] = Summed{sum ? sum : DU + (size_t)w.first * N * m * eb, r.sum_du_cols, (N + 63) / 64};
+    } else if ((rc = linear_dgrad(c, Ga, b.w_fc2, S, m, d, EPI_GELU_BWD, DU, s.u, N))) {
+      return rc;
+    }
     if ((rc = linear_dgrad(c, DU, b.w_fc1, S, d, m, EPI_STORE, c->DH, nullptr, 0))) return rc;
     if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk, r.sum[1], one ? r.sum_cols[1] : nullptr,
                      &tail.done[2])))
@@ -1111,7 +1137,9 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
                  int32_t beta, int32_t tile, void *stream) {
   if (!A || !B || !C || M < 1 || N < 1 || K < 1) return IL_E_ARG;
   if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
-  if (epi < EPI_STORE || epi > EPI_STORE_DOT || tile < 0 || tile > 8) return IL_E_ARG;
+  if (epi < EPI_STORE || epi > EPI_STORE_DOT + 1 || tile < 0 || tile > 8) return IL_E_ARG;
+  const bool gelu_sum = epi == EPI_STORE_DOT + 1;
+  if (gelu_sum && (dtype != IL_BF16 || !aux || !C2 || (beta != 1 && beta != 2) || M % (64 * beta) || ldc != N)) return IL_E_ARG;
   if (epi == EPI_STORE_DOT && (dtype != IL_BF16 || !aux || !C2 || aux_wrap < 1)) return IL_E_ARG;
   if (epi == EPI_LOGITS && (dtype != IL_BF16 || (C2 && !aux))) return IL_E_ARG;
   if ((epi == EPI_BIAS || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RES) && !bias) return IL_E_ARG;
@@ -1131,6 +1159,12 @@ int il_test_gemm(int32_t dtype, const void *A, const void *B, int32_t M, int32_t
   if (epi == EPI_STORE_DOT) {
     g.row_stats = (float *)C2;
     g.C2 = nullptr;
+  }
+  if (gelu_sum) {
+    g.epi = EPI_GELU_BWD_SUM;
+    g.streams = beta; g.aux_wrap = M / beta;
+    g.sum_w[0] = scale; g.sum_w[1] = 1.f;
+    g.row_stats = (float *)C2 + (size_t)(M / beta) * N / 2;
   }
   const hipError_t e = dtype == IL_F32 ? gemm_f32(g, (hipStream_t)stream) : gemm_bf16(g, (hipStream_t)stream);
   return e == hipSuccess ? IL_OK : (e == hipErrorInvalidValue ? IL_E_SHAPE : IL_E_HIP);

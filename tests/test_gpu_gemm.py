@@ -345,6 +345,42 @@ def test_row_sums_epilogue(M, N, K, wrap, tile):
     assert np.all(s[M * (N // 32):] == -7.0)
 
 
+@pytest.mark.parametrize("streams,scale", [(1, 1.0), (2, 1.0), (2, 0.5), (2, 0.0)])
+@pytest.mark.parametrize("tokens,N,K", [(64, 8, 64), (64, 264, 72), (192, 256, 128), (320, 520, 200)])
+def test_gelu_gradient_with_sum_of_streams(tokens, N, K, streams, scale):
+    """The FC2 data gradient of one stream, or of two whose tokens share a tile, with their weighted sum and its
+    column sums; halves of the tile that end inside the operand; a stream of weight zero may hold anything."""
+    import torch
+    M = tokens * streams
+    rng = np.random.default_rng(tokens + N + K + streams)
+    x, y, aux = (_bf16(rng.standard_normal(s)) for s in ((M, K), (N, K), (tokens, N)))
+    if scale == 0.0:
+        x[3] = np.nan
+    to = lambda v: torch.from_numpy(v).to(torch.bfloat16).to("cuda:0")  # noqa: E731
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    C2 = torch.full((tokens * N // 2 + tokens // 64 * N + 64,), -7.0, device="cuda:0")
+    print("case gelu sum", tokens, N, K, streams, scale, flush=True)
+    b.il_test_gemm(b.IL_BF16, to(x), to(y), M, N, K, K, K, 0, 0, 9, C, C2=C2, aux=to(aux), scale=scale, beta=streams)
+    torch.cuda.synchronize()
+    c = C.float().cpu().numpy().astype(np.float64).reshape(streams, tokens, N)
+    f = _gelu_grad(aux.astype(np.float64))
+    mag = (np.abs(x).astype(np.float64) @ np.abs(y).T.astype(np.float64)).reshape(streams, tokens, N)
+    want = (x.astype(np.float64) @ y.T.astype(np.float64)).reshape(streams, tokens, N) * f
+    ok = ~np.isnan(want)
+    # one rounding to bf16, K fp32 additions, 1e-6 of the derivative's terms
+    bound = 2.0 ** -8 * np.abs(want) + (K * 2.0 ** -24 * np.abs(f) + 4e-6) * mag
+    assert np.all(np.abs(c - want)[ok] <= bound[ok]) and np.array_equal(np.isnan(c), np.isnan(want))
+    w = [scale, 1.0][:streams]
+    exact = sum(w[i] * c[i] if w[i] else 0 * aux.astype(np.float64) for i in range(streams))
+    size = sum(abs(w[i]) * np.abs(c[i]) if w[i] else 0 * aux.astype(np.float64) for i in range(streams))
+    flat = C2.cpu().numpy()
+    s = C2[:tokens * N // 2].view(torch.bfloat16).float().cpu().numpy().reshape(tokens, N).astype(np.float64)
+    assert np.all(np.abs(s - exact) <= 2.0 ** -8 * np.abs(exact) + 2.0 ** -23 * size)
+    cols = flat[tokens * N // 2:][:tokens // 64 * N].reshape(tokens // 64, N)
+    assert np.all(np.abs(cols - exact.reshape(-1, 64, N).sum(1)) <= 66 * 2.0 ** -24 * size.reshape(-1, 64, N).sum(1))
+    assert np.all(flat[tokens * N // 2 + tokens // 64 * N:] == -7.0)
+
+
 def _split_case(dtype, M, N, K, splits, tile, ldc):
     import torch
     rng = np.random.default_rng(M + N + K + splits)
