@@ -106,6 +106,29 @@ struct TokTile {
         lds + (row + 8) * RB + (((dcol >> 3) ^ h(row + 8)) << 4) + sub));
     return f.v;
   }
+  // The same two with one byte offset per lane for all fragments, where registers are short: a dh slice, a dh block
+  // and the 8 rows between a fragment's halves are constants exclusive-or'd into the swizzled chunk, and tiles,
+  // stages and row blocks constants added (they and RB are multiples of the span the exclusive-or reaches).
+  __device__ static inline uint32_t row_offset(int lane) {
+    const int row = lane & 31;
+    return row * RB + (((lane >> 5) ^ h(row)) << 4);
+  }
+  __device__ static inline bf16x8 rowfrag_at(const char *lds, uint32_t off, int ks, int add) {
+    return *reinterpret_cast<const bf16x8 *>(lds + (off ^ (uint32_t)(ks << 5)) + add);
+  }
+  __device__ static inline uint32_t tr_offset(int lane) {
+    const int g16 = lane >> 4, i = lane & 15, row = 4 * (g16 >> 1) + (i >> 2), dcol = 16 * (g16 & 1) + 4 * (i & 3);
+    return row * RB + (((dcol >> 3) ^ h(row)) << 4) + ((dcol >> 2) & 1) * 8;
+  }
+  __device__ static inline bf16x8 trfrag_at(const char *lds, uint32_t off, int dt, int add) {
+    constexpr uint32_t kHalf = (uint32_t)(DH >= 128 ? 2 : 1) << 4;  // h(row) ^ h(row + 8), row < 8
+    Frag f;
+    f.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) short4v *)(lds + (off ^ (uint32_t)(dt << 6)) + add));
+    f.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) short4v *)(lds + (off ^ (uint32_t)(dt << 6) ^ kHalf) + add + 8 * RB));
+    return f.v;
+  }
 };
 
 
@@ -293,9 +316,21 @@ __device__ inline float dsum_of(const float *pieces, size_t rows, size_t row, in
   return s;
 }
 
-// ------------------------------------------------------------------ backward: dQ --------
-// Same walk as the forward.
+// The same value, which the compiler takes for a new one: what is derived from it in a loop is not kept across it.
+__device__ inline uint32_t here(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+  return v;
+}
+
+// The bytes a stage of the dK / dV part holds: Q and each stream's dO as stored, lse and each stream's dsum.
 template <int DH>
+constexpr int dkv_stage(int streams) { return (1 + streams) * (64 * DH * 2 + 64 * 4); }
+
+// ------------------------------------------------------------------ backward: dQ --------
+// Same walk as the forward, for NS streams from sidx on: they share K, V, the scores and the probabilities.
+template <int DH, int NS>
 __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
                                                  const float *__restrict__ lse, const float *__restrict__ dsum, int B,
                                                  int T, int H, int ns, int sidx, bf16_t *__restrict__ dqkv, char *smem) {
@@ -328,26 +363,32 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
 #pragma unroll
   for (int s = 0; s < kStages - 1; ++s) issue(s);
 
-  Frag qf[DH / 16], gf[DH / 16];
+  Frag qf[DH / 16], gf[NS][DH / 16];
 #pragma unroll
   for (int ks = 0; ks < DH / 16; ++ks) {
     if (q < T) {
       qf[ks].q = ldg16(qbase + (size_t)q * ld3 + 16 * ks + 8 * hh);
-      gf[ks].q = ldg16(d_o + (sidx * N + tok) * d + h * DH + 16 * ks + 8 * hh);
+#pragma unroll
+      for (int st = 0; st < NS; ++st)
+        gf[st][ks].q = ldg16(d_o + ((sidx + st) * N + tok) * d + h * DH + 16 * ks + 8 * hh);
     } else {
       qf[ks].q = make_uint4(0, 0, 0, 0);
-      gf[ks].q = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int st = 0; st < NS; ++st) gf[st][ks].q = make_uint4(0, 0, 0, 0);
     }
   }
   const float sc = rsqrtf((float)DH), sc2 = sc * kLog2e;
   const float l2 = (q < T) ? lse[((size_t)b * H + h) * T + q] : 0.f;
-  const float dsv = (q < T) ? dsum_of<DH>(dsum, ns * N, sidx * N + tok, h) : 0.f;
-
-  floatx16 dq[DH / 32];
+  float dsv[NS];
+  floatx16 dq[NS][DH / 32];
 #pragma unroll
-  for (int i = 0; i < DH / 32; ++i)
+  for (int st = 0; st < NS; ++st) {
+    dsv[st] = (q < T) ? dsum_of<DH>(dsum, ns * N, (sidx + st) * N + tok, h) : 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dq[i][r] = 0.f;
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq[st][i][r] = 0.f;
+  }
 
   for (int kt = 0; kt < nkv; ++kt) {
     const char *sk = smem + (kt % kStages) * STAGE, *sv = sk + KT;
@@ -357,15 +398,19 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
     issue(kt + kStages - 1);
     if (kv0 <= qw0 + 31) {
       const bool diag = kv0 + BKV - 1 > qw0 || kv0 + BKV > T;
-#pragma unroll(DH > 64 ? 1 : 2)
+#pragma unroll(DH > 64 || NS > 1 ? 1 : 2)
       for (int a = 0; a < 2; ++a) {
-        floatx16 s = kZero16, dp = kZero16;  // a constant accumulator input costs no registers to clear
+        floatx16 s = kZero16, dp[NS];  // a constant accumulator input costs no registers to clear
+#pragma unroll
+        for (int st = 0; st < NS; ++st) dp[st] = kZero16;
 #pragma unroll
         for (int ks = 0; ks < DH / 16; ++ks) {
           const bf16x8 kf = Tile::rowfrag(sk, 32 * a, ks, lane);
           const bf16x8 vf = Tile::rowfrag(sv, 32 * a, ks, lane);
           s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks].v, s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, gf[ks].v, dp, 0, 0, 0);
+#pragma unroll
+          for (int st = 0; st < NS; ++st)
+            dp[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, gf[st][ks].v, dp[st], 0, 0, 0);
         }
         auto probs = [&](auto masked) {
 #pragma unroll
@@ -375,7 +420,8 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
               const int kv = kv0 + 32 * a + 8 * (r >> 2) + 4 * hh + (r & 3);
               p = ((kv > q) | (kv >= T)) ? 0.f : p;
             }
-            s[r] = p * (dp[r] - dsv);  // dS^T, without the scale
+#pragma unroll
+            for (int st = 0; st < NS; ++st) dp[st][r] = p * (dp[st][r] - dsv[st]);  // dS^T, without the scale
           }
         };
         if (DH > 128 || diag)
@@ -384,13 +430,17 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
           probs(std::false_type{});
 #pragma unroll
         for (int bq = 0; bq < 2; ++bq) {
-          Frag pf;
+          Frag pf[NS];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pf.u[e] = pack2(s[8 * bq + 2 * e], s[8 * bq + 2 * e + 1]);
+          for (int st = 0; st < NS; ++st)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pf[st].u[e] = pack2(dp[st][8 * bq + 2 * e], dp[st][8 * bq + 2 * e + 1]);
 #pragma unroll
           for (int dt = 0; dt < DH / 32; ++dt) {
             const bf16x8 kf = Tile::trfrag(sk, 32 * a + 16 * bq, dt, lane);
-            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, pf.v, dq[dt], 0, 0, 0);
+#pragma unroll
+            for (int st = 0; st < NS; ++st)
+              dq[st][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, pf[st].v, dq[st][dt], 0, 0, 0);
           }
         }
       }
@@ -398,16 +448,19 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
   }
   wait_vmcnt<0>();
   if (q < T) {
-    bf16_t *op = dqkv + (sidx * N + tok) * ld3 + h * DH;
 #pragma unroll
-    for (int dt = 0; dt < DH / 32; ++dt)
+    for (int st = 0; st < NS; ++st) {
+      bf16_t *op = dqkv + ((sidx + st) * N + tok) * ld3 + h * DH;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint2 v;
-        v.x = pack2(dq[dt][4 * g] * sc, dq[dt][4 * g + 1] * sc);
-        v.y = pack2(dq[dt][4 * g + 2] * sc, dq[dt][4 * g + 3] * sc);
-        *reinterpret_cast<uint2 *>(op + dt * 32 + 8 * g + 4 * hh) = v;
-      }
+      for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          uint2 v;
+          v.x = pack2(dq[st][dt][4 * g] * sc, dq[st][dt][4 * g + 1] * sc);
+          v.y = pack2(dq[st][dt][4 * g + 2] * sc, dq[st][dt][4 * g + 3] * sc);
+          *reinterpret_cast<uint2 *>(op + dt * 32 + 8 * g + 4 * hh) = v;
+        }
+    }
   }
 }
 
@@ -422,8 +475,9 @@ __device__ __forceinline__ void attn_bwd_dq_body(const bf16_t *__restrict__ qkv,
 // into a dV pass (K fragments, 64 accumulator registers) and a dK pass (K and V fragments, 64
 // accumulator registers), both fit with two wavefronts per SIMD; the score product is computed in
 // both (40 matrix instructions per 32x32 sub-tile instead of 32), which the kernel - bound by
-// latency, not by the matrix unit - more than wins back.
-template <int DH, int WHAT>
+// latency, not by the matrix unit - more than wins back.  NS streams from sidx on share Q, the scores and
+// the probabilities.
+template <int DH, int WHAT, int NS>
 __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
                                                   const float *__restrict__ lse, const float *__restrict__ dsum, int B,
                                                   int T, int H, int ns, int sidx, bf16_t *__restrict__ dqkv,
@@ -431,7 +485,7 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
   constexpr bool DO_DV = WHAT != 2, DO_DK = WHAT != 1;
   constexpr int BKV = 128, BQ = 64;
   constexpr int QT = BQ * DH * 2;                 // one staged tile
-  constexpr int STAGE = 2 * QT + 2 * BQ * 4;      // Q, dO as stored, lse, dsum
+  constexpr int STAGE = dkv_stage<DH>(NS);
   typedef TokTile<BQ, DH> Tile;
   const int t = threadIdx.x, lane = t & 63, hh = lane >> 5, lk_ = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -441,7 +495,6 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
   const size_t ld3 = 3 * (size_t)d, N = (size_t)B * T;
   const bf16_t *qbase = qkv + (size_t)b * T * ld3 + h * DH;
   const bf16_t *kbase = qbase + d, *vbase = qbase + 2 * d;
-  const bf16_t *gbase = d_o + (sidx * N + (size_t)b * T) * d + h * DH;
   const float *lrow = lse + ((size_t)b * H + h) * T;
   const int kv0 = ct.rank * BKV, kvw0 = kv0 + 32 * wave, kv = kvw0 + lk_;
   const int qt0 = kv0 / BQ, nqt = (T + BQ - 1) / BQ;
@@ -457,42 +510,50 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
       if constexpr (DO_DK) vf[ks].q = make_uint4(0, 0, 0, 0);
     }
   }
-  floatx16 dk[DO_DK ? DH / 32 : 1], dv[DO_DV ? DH / 32 : 1];
+  floatx16 dk[NS][DO_DK ? DH / 32 : 1], dv[NS][DO_DV ? DH / 32 : 1];
 #pragma unroll
-  for (int i = 0; i < DH / 32; ++i)
+  for (int st = 0; st < NS; ++st)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if constexpr (DO_DK) dk[i][r] = 0.f;
-      if constexpr (DO_DV) dv[i][r] = 0.f;
-    }
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (DO_DK) dk[st][i][r] = 0.f;
+        if constexpr (DO_DV) dv[st][i][r] = 0.f;
+      }
   const float sc = rsqrtf((float)DH);
   const float sc2 = sc * kLog2e;
 
   const BufRsrc rq = make_rsrc(qbase, (size_t)T * ld3 * 2 - (size_t)h * DH * 2);
-  const BufRsrc rg = make_rsrc(gbase, (size_t)T * d * 2 - (size_t)h * DH * 2);
+  BufRsrc rg[NS];
+#pragma unroll
+  for (int st = 0; st < NS; ++st)
+    rg[st] = make_rsrc(d_o + ((sidx + st) * N + (size_t)b * T) * d + h * DH, (size_t)T * d * 2 - (size_t)h * DH * 2);
   Tile lq, lg;
   lq.init(0, (int)ld3, t);
   lg.init(0, d, t);
   // Direct loads of the Q and dO tiles, kStages - 1 tiles ahead (past the last tile: zeros); the 64 lse and
-  // dsum values of a tile go through registers, one tile ahead: wavefront 0 fetches lse, wavefront 1 dsum.
+  // dsum values of a tile go through registers, one tile ahead: wavefront 0 fetches lse, wavefront 1 + st dsum.
   auto issue = [&](int it) {
     char *base = smem + (it % kStages) * STAGE;
     const int r0 = (qt0 + it) * BQ, end = qt0 + it < nqt ? T : 0;
     lq.issue(rq, base, wave, r0, end);
-    lg.issue(rg, base + QT, wave, r0, end);
+#pragma unroll
+    for (int st = 0; st < NS; ++st) lg.issue(rg[st], base + (1 + st) * QT, wave, r0, end);
   };
   float row_val = 0.f;
   auto fetch_rows = [&](int it) {
     const int r = (qt0 + it) * BQ + lane;
     row_val = 0.f;
     if (r < T && wave == 0) row_val = lrow[r];
-    if (DO_DK && r < T && wave == 1) row_val = dsum_of<DH>(dsum, ns * N, sidx * N + (size_t)b * T + r, h);
+    if (DO_DK && r < T && wave >= 1 && wave <= NS)
+      row_val = dsum_of<DH>(dsum, ns * N, (sidx + wave - 1) * N + (size_t)b * T + r, h);
   };
   auto put_rows = [&](int it) {
-    float *row = reinterpret_cast<float *>(smem + (it % kStages) * STAGE + 2 * QT);
-    if (wave < 2) row[wave * BQ + lane] = row_val;
+    float *row = reinterpret_cast<float *>(smem + (it % kStages) * STAGE + (1 + NS) * QT);
+    if (wave < 1 + NS) row[wave * BQ + lane] = row_val;
   };
   const int nit = nqt - qt0;
+  const uint32_t row_off = Tile::row_offset(lane), tr_off = Tile::tr_offset(lane);
   fetch_rows(0);
 #pragma unroll
   for (int s = 0; s < kStages - 1; ++s) issue(s);
@@ -500,40 +561,56 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
 
   for (int it = 0; it < nit; ++it) {
     const int qt = qt0 + it;
-    const char *sq = smem + (it % kStages) * STAGE, *sg = sq + QT;
-    const float *sl = reinterpret_cast<const float *>(sq + 2 * QT), *sd = sl + BQ;
+    const char *sq = smem + (it % kStages) * STAGE;
+    const float *sl = reinterpret_cast<const float *>(sq + (1 + NS) * QT), *sd = sl + BQ;
     const int qb0 = qt * BQ;
     wait_vmcnt<0>();
     __syncthreads();
     fetch_rows(it + 1);
     issue(it + kStages - 1);
-#pragma unroll(DH > 64 ? 1 : 2)
+#pragma unroll(DH > 64 || NS > 1 ? 1 : 2)
     for (int a = 0; a < BQ / 32; ++a) {
       const int qa0 = qb0 + 32 * a;
       if (qa0 + 31 < kvw0 || qa0 >= T) continue;  // every query of the sub-tile precedes every key
+      // (two streams' accumulators leave room for two of the fragments' addresses, and not for the eight that would
+      // be kept across the loop: those came back from scratch, each behind a wait for the direct loads in flight)
+      uint32_t ro = 0, to = 0;
+      if constexpr (NS > 1) {
+        ro = here(row_off + (it % kStages) * STAGE + 32 * a * Tile::RB);
+        to = here(tr_off + (it % kStages) * STAGE + 32 * a * Tile::RB);
+      }
+      auto rows = [&](int tile, int ks) {
+        if constexpr (NS > 1) return Tile::rowfrag_at(smem, ro, ks, tile * QT);
+        return Tile::rowfrag(sq + tile * QT, 32 * a, ks, lane);
+      };
+      auto trans = [&](int tile, int bq, int dt) {
+        if constexpr (NS > 1) return Tile::trfrag_at(smem, to, dt, tile * QT + 16 * bq * Tile::RB);
+        return Tile::trfrag(sq + tile * QT, 32 * a + 16 * bq, dt, lane);
+      };
       floatx16 s = kZero16, dp = kZero16;
 #pragma unroll
       for (int ks = 0; ks < DH / 16; ++ks) {
-        const bf16x8 qf = Tile::rowfrag(sq, 32 * a, ks, lane);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[ks].v, s, 0, 0, 0);
-        if constexpr (DO_DK) {
-          const bf16x8 gf = Tile::rowfrag(sg, 32 * a, ks, lane);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf, vf[ks].v, dp, 0, 0, 0);
-        }
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(0, ks), kf[ks].v, s, 0, 0, 0);
+        if constexpr (DO_DK)
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(1, ks), vf[ks].v, dp, 0, 0, 0);
       }
       const bool diag = qa0 < kvw0 + 31 || qa0 + 32 > T;
       Frag pf[2], sf[2];  // P and dS of the sub-tile, packed to bf16 as they are produced
+      auto grads = [&](int st, int g, const float (&p4)[4]) {  // dS of stream st from its dO V^T, four rows
+        const float4 d4 = *reinterpret_cast<const float4 *>(sd + st * BQ + 32 * a + 8 * g + 4 * hh);
+        const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+        float s4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s4[e] = p4[e] * (dp[4 * g + e] - dv4[e]);  // without the scale
+        sf[g >> 1].u[2 * (g & 1)] = pack2(s4[0], s4[1]);
+        sf[g >> 1].u[2 * (g & 1) + 1] = pack2(s4[2], s4[3]);
+      };
       auto probs = [&](auto masked) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 l4 = *reinterpret_cast<const float4 *>(sl + 32 * a + 8 * g + 4 * hh);
           const float lv4[4] = {l4.x, l4.y, l4.z, l4.w};
-          float dv4[4] = {0.f, 0.f, 0.f, 0.f};
-          if constexpr (DO_DK) {
-            const float4 d4 = *reinterpret_cast<const float4 *>(sd + 32 * a + 8 * g + 4 * hh);
-            dv4[0] = d4.x; dv4[1] = d4.y; dv4[2] = d4.z; dv4[3] = d4.w;
-          }
-          float p4[4], s4[4];
+          float p4[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int r = 4 * g + e;
@@ -543,16 +620,13 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
               p = ((kv > qq) | (qq >= T)) ? 0.f : p;
             }
             p4[e] = p;
-            s4[e] = p * (dp[r] - dv4[e]);  // dS, without the scale
+            if constexpr (NS > 1) s[r] = p;
           }
           if constexpr (DO_DV) {
             pf[g >> 1].u[2 * (g & 1)] = pack2(p4[0], p4[1]);
             pf[g >> 1].u[2 * (g & 1) + 1] = pack2(p4[2], p4[3]);
           }
-          if constexpr (DO_DK) {
-            sf[g >> 1].u[2 * (g & 1)] = pack2(s4[0], s4[1]);
-            sf[g >> 1].u[2 * (g & 1) + 1] = pack2(s4[2], s4[3]);
-          }
+          if constexpr (DO_DK) grads(0, g, p4);
         }
       };
       if (DH > 128 || diag)
@@ -560,16 +634,26 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
       else
         probs(std::false_type{});
 #pragma unroll
-      for (int bq = 0; bq < 2; ++bq) {
+      for (int st = 0; st < NS; ++st) {
+        if (DO_DK && st > 0) {
+          dp = kZero16;
 #pragma unroll
-        for (int dt = 0; dt < DH / 32; ++dt) {
-          if constexpr (DO_DV) {
-            const bf16x8 gt = Tile::trfrag(sg, 32 * a + 16 * bq, dt, lane);
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt, pf[bq].v, dv[dt], 0, 0, 0);
-          }
-          if constexpr (DO_DK) {
-            const bf16x8 qtf = Tile::trfrag(sq, 32 * a + 16 * bq, dt, lane);
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtf, sf[bq].v, dk[dt], 0, 0, 0);
+          for (int ks = 0; ks < DH / 16; ++ks)
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(1 + st, ks),
+                                                         vf[DO_DK ? ks : 0].v, dp, 0, 0, 0);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) grads(st, g, {s[4 * g], s[4 * g + 1], s[4 * g + 2], s[4 * g + 3]});
+        }
+#pragma unroll
+        for (int bq = 0; bq < 2; ++bq) {
+#pragma unroll
+          for (int dt = 0; dt < DH / 32; ++dt) {
+            if constexpr (DO_DV)
+              dv[st][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  trans(1 + st, bq, dt), pf[bq].v, dv[st][dt], 0, 0, 0);
+            if constexpr (DO_DK)
+              dk[st][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trans(0, bq, dt),
+                                                                   sf[bq].v, dk[st][dt], 0, 0, 0);
           }
         }
       }
@@ -578,27 +662,30 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
   }
   wait_vmcnt<0>();
   if (kv < T) {
-    bf16_t *kp = dqkv + (sidx * N + (size_t)b * T + kv) * ld3 + d + h * DH;
 #pragma unroll
-    for (int dt = 0; dt < DH / 32; ++dt)
+    for (int st = 0; st < NS; ++st) {
+      bf16_t *kp = dqkv + ((sidx + st) * N + (size_t)b * T + kv) * ld3 + d + h * DH;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint2 v;
-        if constexpr (DO_DK) {
-          v.x = pack2(dk[dt][4 * g] * sc, dk[dt][4 * g + 1] * sc);
-          v.y = pack2(dk[dt][4 * g + 2] * sc, dk[dt][4 * g + 3] * sc);
-          *reinterpret_cast<uint2 *>(kp + dt * 32 + 8 * g + 4 * hh) = v;
+      for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          uint2 v;
+          if constexpr (DO_DK) {
+            v.x = pack2(dk[st][dt][4 * g] * sc, dk[st][dt][4 * g + 1] * sc);
+            v.y = pack2(dk[st][dt][4 * g + 2] * sc, dk[st][dt][4 * g + 3] * sc);
+            *reinterpret_cast<uint2 *>(kp + dt * 32 + 8 * g + 4 * hh) = v;
+          }
+          if constexpr (DO_DV) {
+            v.x = pack2(dv[st][dt][4 * g], dv[st][dt][4 * g + 1]);
+            v.y = pack2(dv[st][dt][4 * g + 2], dv[st][dt][4 * g + 3]);
+            *reinterpret_cast<uint2 *>(kp + d + dt * 32 + 8 * g + 4 * hh) = v;
+          }
         }
-        if constexpr (DO_DV) {
-          v.x = pack2(dv[dt][4 * g], dv[dt][4 * g + 1]);
-          v.y = pack2(dv[dt][4 * g + 2], dv[dt][4 * g + 3]);
-          *reinterpret_cast<uint2 *>(kp + d + dt * 32 + 8 * g + 4 * hh) = v;
-        }
-      }
+    }
   }
 }
 
-// The backward of all streams in one launch, grid (ceil(T/128), B*H, roles * streams): blockIdx.z % roles
+// The backward of all streams in one launch, grid (ceil(T/128), B*H, roles * groups of NS streams): blockIdx.z % roles
 // selects what a workgroup computes, the longest role first - dK and dV, dQ; or (head width 128) dK, dQ, dV.
 // With at least two wavefronts per SIMD demanded, the register budget is the 256 architectural VGPRs and the
 // compiler keeps the MFMA accumulators there; without, it places them in the accumulation registers and
@@ -607,19 +694,26 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const bf16_t *__restrict__ qkv
 // alone takes 232 + 160); two launches are slower all the same: 32 x 128 tokens, 4 heads 45.2 us against 26.8, two
 // streams 49.5 against 45.7, 4 x 512, 8 heads 100.6 against 60.4.
 constexpr int bwd_roles(int dh) { return dh == 128 ? 3 : 2; }
-template <int DH>
+template <int DH, int NS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 128 ? 1 : 2))) void attn_bwd_mfma(
     const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
     const float *__restrict__ dsum, int ns, int B, int T, int H, bf16_t *__restrict__ dqkv) {
-  __shared__ __attribute__((aligned(16))) char smem[kStages * (2 * 64 * DH * 2 + 2 * 64 * 4)];
+  __shared__ __attribute__((aligned(256))) char smem[kStages * dkv_stage<DH>(NS)];
   constexpr int R = bwd_roles(DH);
-  const int role = blockIdx.z % R, sidx = blockIdx.z / R;
-  if (role == 1)
-    attn_bwd_dq_body<DH>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
-  else if (role == 0)
-    attn_bwd_dkv_body<DH, R == 3 ? 2 : 0>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
-  else if constexpr (R == 3)
-    attn_bwd_dkv_body<DH, 1>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
+  const int role = blockIdx.z % R, sidx = blockIdx.z / R * NS;
+  auto walk = [&](auto streams) {
+    constexpr int n = decltype(streams)::value;
+    if (role == 1)
+      attn_bwd_dq_body<DH, n>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
+    else if (role == 0)
+      attn_bwd_dkv_body<DH, R == 3 ? 2 : 0, n>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
+    else if constexpr (R == 3)
+      attn_bwd_dkv_body<DH, 1, n>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
+  };
+  if (NS > 1 && sidx + NS > ns)
+    walk(std::integral_constant<int, 1>{});  // the last of an odd number
+  else
+    walk(std::integral_constant<int, NS>{});
 }
 
 }  // namespace
@@ -655,19 +749,37 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
   }
 }
 
+// At head width 64 a workgroup walks two streams together: one read of K, V and Q and one score product and
+// exponential serve both, 24 matrix instructions per sub-tile and stream instead of 28, half of the LDS reads for dQ;
+// the walk is bound by the latency of its products and reads.  250 registers, two wavefronts per SIMD as before.
+// That leaves half as many workgroups, so it is taken where there are more of them than the 512 that the chip holds at
+// a time.  Backward in us, one by one / in pairs (workgroups in pairs):
+//   8 x 512 tokens, 16 heads, two streams (1024) 65.0 / 53.0, three streams (2048) 91.6 / 79.3;  4 x 1024, 16 (1024) 91.0 / 76.1;
+//   64 x 64, 8 (1024) 22.4 / 20.5;  8 x 200, 12, three (768) 27.6 / 23.8;  3 x 640, 12, three (720) 45.1 / 39.1;
+//   8 x 256, 16 (512) 27.1 / 23.4;  4 x 512, 16 (512) 35.2 / 34.8;  2 x 1024, 16 (512) 51.8 / 54.0;  4 x 1024, 8 (512) 49.8 / 52.9;
+//   8 x 256, 12 (384) 20.0 / 21.4;  8 x 256, 8 (256) 17.1 / 19.1.
+// Wider heads have no registers for a second stream's accumulators.  The streams' weighted sum formed here as well, of
+// the rows just stored, cost 15 to 25 us a launch: more than the pass on the other stream that it replaces.
+constexpr long kPairedWgs = 640;
+template <int DH, int NS>
+hipError_t bwd(const bf16_t *qkv, const bf16_t *d_o, const float *lse, const float *dsum, int ns, int B, int T, int H,
+               bf16_t *dqkv, hipStream_t s) {
+  hipLaunchKernelGGL((attn_bwd_mfma<DH, NS>), dim3((T + 127) / 128, B * H, bwd_roles(DH) * ((ns + NS - 1) / NS)), dim3(256), 0,
+                     s, qkv, d_o, lse, dsum, ns, B, T, H, dqkv);
+  return hipGetLastError();
+}
 hipError_t attention_backward_mfma(const void *qkv, const void *d_o, const float *lse, const float *dsum, int ns,
                                    int B, int T, int H, int dh, void *dqkv, hipStream_t s) {
-#define IL_ATTN_BWD(DH)                                                                                          \
-  hipLaunchKernelGGL(attn_bwd_mfma<DH>, dim3((T + 127) / 128, B * H, bwd_roles(DH) * ns), dim3(256), 0, s,       \
-                     (const bf16_t *)qkv, (const bf16_t *)d_o, lse, dsum, ns, B, T, H, (bf16_t *)dqkv)
+  const bf16_t *x = (const bf16_t *)qkv, *g = (const bf16_t *)d_o;
+  bf16_t *out = (bf16_t *)dqkv;
+  const long wgs = (long)((T + 127) / 128) * B * H * bwd_roles(dh) * ((ns + 1) / 2);
+  const bool pairs = ns > 1 && wgs >= kPairedWgs;
   switch (dh) {
-    case 64: IL_ATTN_BWD(64); break;
-    case 128: IL_ATTN_BWD(128); break;
-    case 256: IL_ATTN_BWD(256); break;
+    case 64: return pairs ? bwd<64, 2>(x, g, lse, dsum, ns, B, T, H, out, s) : bwd<64, 1>(x, g, lse, dsum, ns, B, T, H, out, s);
+    case 128: return bwd<128, 1>(x, g, lse, dsum, ns, B, T, H, out, s);
+    case 256: return bwd<256, 1>(x, g, lse, dsum, ns, B, T, H, out, s);
     default: return hipErrorInvalidValue;
   }
-#undef IL_ATTN_BWD
-  return hipGetLastError();
 }
 
 }  // namespace il

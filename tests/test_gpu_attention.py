@@ -158,3 +158,33 @@ def test_bf16_products(dh, T, H):
         assert np.linalg.norm(got - want) <= 2 ** -7 * np.linalg.norm(want), "QKV"[i]
         rows = np.sqrt(((got - want) ** 2).sum(axis=1) / np.maximum((want ** 2).sum(axis=1), (want ** 2).sum() / len(want)))
         assert rows.max() <= 2 ** -5, ("QKV"[i], int(rows.argmax()))
+
+
+@pytest.mark.parametrize("dh,B,T,H,ns", [
+    (64, 5, 256, 16, 2), (64, 5, 256, 16, 3), (64, 10, 129, 16, 2), (64, 5, 1000, 8, 2), (64, 40, 33, 8, 2), (64, 160, 1, 2, 3),
+    (64, 27, 64, 4, 5), (64, 1, 64, 1, 2), (128, 4, 200, 11, 2), (256, 8, 65, 4, 3)])
+def test_streams_that_share_a_walk(dh, B, T, H, ns):
+    """Streams taken together give what each gives by itself, bit for bit: the same products and sums in the same order.
+    Both sides of the number of workgroups from which streams go in pairs, even and odd numbers of them."""
+    import torch
+    dev, d, N = torch.device("cuda:0"), H * dh, B * T
+    print("case streams", dh, B, T, H, ns, flush=True)
+    gen = torch.Generator().manual_seed(dh + T)
+    qkv = torch.randn(N, 3 * d, generator=gen).to(torch.bfloat16).to(dev)
+    g = torch.randn(ns * N, d, generator=gen).to(torch.bfloat16).to(dev)
+    g[(ns - 1) * N + N // 2, 0] = float("nan")   # one stream's alone
+    o, lse = torch.empty(N, d, dtype=torch.bfloat16, device=dev), torch.empty(B, H, T, device=dev)
+    stream = torch.cuda.current_stream().cuda_stream
+    b.il_test_attention(b.IL_BF16, qkv, B, T, H, dh, o, lse, stream=stream)
+
+    def backward(g, streams):
+        dsum = (g.float().reshape(streams, N, d) * o.float()).reshape(streams * N, d // 32, 32).sum(dim=2).t().contiguous()
+        out = torch.full((streams * N, 3 * d), 7.0, dtype=torch.bfloat16, device=dev)
+        b.il_test_attention(b.IL_BF16, qkv, B, T, H, dh, o, lse, g, streams, out, dsum, stream=stream)
+        return out
+
+    out = backward(g, ns)
+    for s in range(ns):
+        one = backward(g[s * N:(s + 1) * N].contiguous(), 1)
+        assert torch.equal(one.isnan(), out[s * N:(s + 1) * N].isnan()) and bool(one.isnan().any()) == (s == ns - 1), s
+        assert torch.equal(one.nan_to_num(), out[s * N:(s + 1) * N].nan_to_num()), s
