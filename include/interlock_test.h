@@ -84,6 +84,13 @@ int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq
                       void *o, float *lse, const void *d_o, int32_t streams, void *dqkv, float *dsum, void *stream);
 int il_attention_wants_dsum(int32_t dtype, int32_t width);
 
+/*
+ * Kernel-level test hook: one LayerNorm forward.  x: fp32 [rows, d]; gamma, beta: dtype [d]; y: dtype [rows, d]; stats:
+ * fp32 [rows, 2], mean and 1 / sqrt(variance + eps); xcopy: fp32 [rows, d], a copy of x, or NULL.  d <= 2048.
+ */
+int il_test_layernorm(int32_t dtype, const float *x, const void *gamma, const void *beta, float eps, int32_t rows, int32_t d,
+                      void *y, float *stats, float *xcopy, void *stream);
+
 /* ---- measured peaks of the board (reported beside the nominal 2.5 PFLOP/s and 8 TB/s) ------------- */
 
 /*

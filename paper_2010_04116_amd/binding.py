@@ -26,7 +26,7 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
            "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum",
-           "il_test_gemm_splitk", "il_gemm_split_plan")
+           "il_test_gemm_splitk", "il_gemm_split_plan", "il_test_layernorm")
 
 
 class il_config(C.Structure):
@@ -72,6 +72,7 @@ def load():
     lib.il_test_gemm_splitk.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
     lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
+    lib.il_test_layernorm.argtypes = [i32, vp, vp, vp, C.c_float, i32, i32, vp, vp, vp, vp]
     lib.il_lr_schedule.argtypes = [C.c_int64, i32, i32]
     lib.il_lr_schedule.restype = C.c_double
     lib.il_adam_step.argtypes = [i32, vp, vp, vp, vp, vp, C.c_size_t, C.c_int64, C.c_float, C.c_float, C.c_float,
@@ -204,6 +205,12 @@ def il_test_attention(dtype, qkv, batch, seq, heads, width, o, lse, d_o=None, st
 
 def il_attention_wants_dsum(dtype, width) -> bool:
     return bool(load().il_attention_wants_dsum(dtype, width))
+
+
+def il_test_layernorm(dtype, x, gamma, beta, eps, rows, d, y, stats, xcopy=None, stream=None):
+    """One LayerNorm forward of the library's kernels on torch device tensors (test hook)."""
+    _check(load().il_test_layernorm(dtype, _ptr(x), _ptr(gamma), _ptr(beta), eps, rows, d, _ptr(y), _ptr(stats), _ptr(xcopy),
+                                    stream), "il_test_layernorm")
 
 
 def il_profile_read(ctx) -> Dict[str, dict]:

@@ -1187,6 +1187,15 @@ int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws
   return p.splits;
 }
 
+int il_test_layernorm(int32_t dtype, const float *x, const void *gamma, const void *beta, float eps, int32_t rows, int32_t d,
+                      void *y, float *stats, float *xcopy, void *stream) {
+  if (!x || !gamma || !beta || !y || !stats || rows < 1 || d < 1) return IL_E_ARG;
+  if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
+  if (d > 2048 || rows > (1 << 24)) return IL_E_SHAPE;
+  IL_TRY(ln_forward(dtype, x, gamma, beta, eps, rows, d, y, stats, xcopy, (hipStream_t)stream));
+  return IL_OK;
+}
+
 int il_attention_wants_dsum(int32_t dtype, int32_t width) { return attention_dsum_given(dtype, width) ? 1 : 0; }
 
 int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq, int32_t heads, int32_t width,

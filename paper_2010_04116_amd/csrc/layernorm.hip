@@ -53,7 +53,10 @@ template <typename T> struct Vec<T, 1> {
   static __device__ inline void store(T *p, const float (&o)[1]) { st<T>(p, o[0]); }
 };
 
-// Forward: a lane owns columns (lane + 64 j) * V + (0..V-1), j < J, d <= 64 V J.
+// Forward: a lane owns columns (lane + 64 j) * V + (0..V-1), j < J, d <= 64 V J.  Gain and bias are requested with the row
+// where the registers they take leave enough wavefronts: after the reductions their latency stands alone.  bf16, us with
+// the row / after it: 4096 x 256 3.14 / 3.23, 512 x 1024 3.52 / 3.62, but 8192 x 1280 14.0 / 12.7, 4096 x 2048 12.1 / 10.5;
+// fp32, whose gain needs no conversion: 512 x 2048 4.2 / 4.6, 8192 x 2048 21.3 / 22.1, 4096 x 2048 12.9 / 12.4 (alone slower).
 template <typename T, int V, int J>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x, const T *__restrict__ gamma,
                                                      const T *__restrict__ beta, float eps, int rows, int d,
@@ -63,7 +66,12 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
   const int row = blockIdx.x * kWaves + wave;
   if (row >= rows) return;
   const float *xr = x + (size_t)row * d;
-  float v[J][V], g[J][V], b[J][V];  // gain and bias are requested with the row: after the reductions their latency stands alone
+  constexpr bool AHEAD = sizeof(T) == 4 || J <= 4;
+  float v[J][V], g[J][V], b[J][V];
+  auto gain = [&](int j, int c) {
+    Vec<T, V>::load(gamma + c, g[j]);
+    Vec<T, V>::load(beta + c, b[j]);
+  };
   float s = 0.f;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -78,38 +86,40 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int c = (lane + 64 * j) * V;
-    if (c < d) {
-      Vec<T, V>::load(gamma + c, g[j]);
-      Vec<T, V>::load(beta + c, b[j]);
-    }
+    if (AHEAD && c < d) gain(j, c);
   }
 #pragma unroll
   for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int e = 0; e < V; ++e) s += v[j][e];
-  const float invd = 1.f / d;
-  const float mean = wave_sum(s) * invd;
-  float q = 0.f;
+  // x - sum / d in one rounding, and the same value for the variance and the result: a mean rounded first costs
+  // the result another 2^-24 of the mean wherever 1 / d is not a power of two
+  const float invd = 1.f / d, total = wave_sum(s);
+  auto centred = [&](float x) { return __builtin_fmaf(-invd, total, x); };
+  float q = 0.f, first = 0.f;
 #pragma unroll
   for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int e = 0; e < V; ++e) {
-      const float t = (lane + 64 * j) * V < d ? v[j][e] - mean : 0.f;
-      q += t * t;
+      const float t = (lane + 64 * j) * V < d ? centred(v[j][e]) : 0.f;
+      if (V > 1 && j * V + e == 0) first = t;
+      else q = __builtin_fmaf(t, t, q);
+      if (V > 1 && j * V + e == 1) q = __builtin_fmaf(first, first, q);
     }
-  const float rstd = rsqrtf(wave_sum(q) * invd + eps);
+  const float rstd = rsqrtf(__builtin_fmaf(wave_sum(q), invd, eps));
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int c = (lane + 64 * j) * V;
     if (c >= d) continue;
+    if (!AHEAD) gain(j, c);
     float o[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) o[e] = (v[j][e] - mean) * rstd * g[j][e] + b[j][e];
+    for (int e = 0; e < V; ++e) o[e] = __builtin_fmaf(centred(v[j][e]) * rstd, g[j][e], b[j][e]);
     Vec<T, V>::store(y + (size_t)row * d + c, o);
     if (xcopy) Vec<float, V>::store(xcopy + (size_t)row * d + c, v[j]);
   }
   if (lane == 0) {
-    stats[2 * row] = mean;
+    stats[2 * row] = total * invd;
     stats[2 * row + 1] = rstd;
   }
 }
