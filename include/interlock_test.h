@@ -91,6 +91,18 @@ int il_attention_wants_dsum(int32_t dtype, int32_t width);
 int il_test_layernorm(int32_t dtype, const float *x, const void *gamma, const void *beta, float eps, int32_t rows, int32_t d,
                       void *y, float *stats, float *xcopy, void *stream);
 
+/*
+ * Kernel-level test hook: one LayerNorm backward of `streams` (1 to 16) gradient streams stacked over `tokens` rows.
+ * dy: dtype [streams * tokens, d]; x, stats, gamma: the forward's; G: fp32 [streams * tokens, d], to which the gradient at x
+ * is added; Gb: G as dtype; weights: streams floats (host); partials: fp32 [512][2 d], of which *blocks rows are written:
+ * partial column sums of weight * dy * xhat and of weight * dy.  If ypart (fp32 [512][d]) is given, *summed says
+ * whether the weighted sum of the streams' Gb was formed (d > 256, divisible by four, vectors aligned): its partial column sums, *blocks rows of ypart, and the sum
+ * itself, dtype [tokens, d], in ysum unless that is NULL.
+ */
+int il_test_layernorm_backward(int32_t dtype, const void *dy, const float *x, const float *stats, const void *gamma, int32_t streams,
+                               int32_t tokens, int32_t d, float *G, void *Gb, const float *weights, float *partials, void *ysum,
+                               float *ypart, int32_t *blocks, int32_t *summed, void *stream);
+
 /* ---- measured peaks of the board (reported beside the nominal 2.5 PFLOP/s and 8 TB/s) ------------- */
 
 /*

@@ -26,7 +26,8 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
            "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum",
-           "il_test_gemm_splitk", "il_gemm_split_plan", "il_test_layernorm")
+           "il_test_gemm_splitk", "il_gemm_split_plan", "il_test_layernorm",
+           "il_test_layernorm_backward")
 
 
 class il_config(C.Structure):
@@ -73,6 +74,8 @@ def load():
     lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
     lib.il_test_layernorm.argtypes = [i32, vp, vp, vp, C.c_float, i32, i32, vp, vp, vp, vp]
+    lib.il_test_layernorm_backward.argtypes = [i32, vp, vp, vp, vp, i32, i32, i32, vp, vp, C.POINTER(C.c_float), vp, vp, vp,
+                                               C.POINTER(i32), C.POINTER(i32), vp]
     lib.il_lr_schedule.argtypes = [C.c_int64, i32, i32]
     lib.il_lr_schedule.restype = C.c_double
     lib.il_adam_step.argtypes = [i32, vp, vp, vp, vp, vp, C.c_size_t, C.c_int64, C.c_float, C.c_float, C.c_float,
@@ -211,6 +214,16 @@ def il_test_layernorm(dtype, x, gamma, beta, eps, rows, d, y, stats, xcopy=None,
     """One LayerNorm forward of the library's kernels on torch device tensors (test hook)."""
     _check(load().il_test_layernorm(dtype, _ptr(x), _ptr(gamma), _ptr(beta), eps, rows, d, _ptr(y), _ptr(stats), _ptr(xcopy),
                                     stream), "il_test_layernorm")
+
+
+def il_test_layernorm_backward(dtype, dy, x, stats, gamma, streams, tokens, d, G, Gb, weights, partials, ysum=None, ypart=None,
+                               stream=None):
+    """One LayerNorm backward on torch device tensors (test hook): (rows of partials written, whether ypart / ysum were)."""
+    blocks, summed = C.c_int32(), C.c_int32()
+    _check(load().il_test_layernorm_backward(dtype, _ptr(dy), _ptr(x), _ptr(stats), _ptr(gamma), streams, tokens, d, _ptr(G),
+                                             _ptr(Gb), (C.c_float * streams)(*weights), _ptr(partials), _ptr(ysum), _ptr(ypart),
+                                             C.byref(blocks), C.byref(summed), stream), "il_test_layernorm_backward")
+    return blocks.value, bool(summed.value)
 
 
 def il_profile_read(ctx) -> Dict[str, dict]:

@@ -163,12 +163,13 @@ hipError_t ln_forward(int dtype, const float *x, const void *gamma, const void *
                       int rows, int d, void *y, float *stats, float *xcopy, hipStream_t s);
 // For each row r of ns streams stacked over N tokens (stream r / N, token r % N): G[r] += LN'(x)^T dy[r]; Gb[r] = T(G[r]);
 // partial column sums of w*dy*xhat and w*dy go to `partials` ([nblk][2*d]); returns nblk.  If ypart is given (and
-// *summed returns true, which takes vectors of four): partial column sums [nblk][d] of the streams' weighted sum
-// sum_s w[s] Gb[s], and the sum itself to ysum [N][d] unless that is NULL.
+// *summed returns true, which takes vectors of four and d > 256): partial column sums [nblk][d] of the streams' weighted
+// sum sum_s w[s] Gb[s], and the sum itself to ysum [N][d] unless that is NULL.
 hipError_t ln_backward_residual(int dtype, const void *dy, const float *x, const float *stats, const void *gamma,
                                 int ns, int N, int d, float *G, void *Gb, const StreamWeights &sw, float *partials,
                                 int *nblk, void *ysum, float *ypart, bool *summed, hipStream_t s);
 int ln_backward_max_blocks();
+bool ln_backward_sums(int N, int d);  // whether the sums are worth asking for
 
 // ---- reductions / elementwise (reduce.hip) --------------------------------------------
 // second stage: out[c] = sum over blocks p of partials[p][c], c < cols (fp32 out, deterministic order)

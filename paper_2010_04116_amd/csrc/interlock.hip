@@ -315,15 +315,18 @@ size_t layout_workspace(il_ctx *c, void *base) {
   // (one more stream slot carries a head's gradient through its own blocks)
   const size_t ns = c->plan.nslots + (c->Lh ? 1 : 0), S = (size_t)std::max(c->plan.maxcnt, 1) * N;
   const size_t live = (size_t)std::max(c->plan.maxlive, 1) * N;
-  bool sums = false, du_sums = false, du_cols = false;  // some component's streams are not their sum as they are; ... and DU's is made with it; ...
-  for (const CompPlan &k : c->plan.comp)
-    for (const Run &r : k.runs) {
-      const bool plain = !weighted(r).n || weighted(r).plain, gelu = gelu_sums(c, k.runs);
-      sums = sums || !plain;
-      du_sums = du_sums || (gelu && !plain);
-      du_cols = du_cols || gelu;
-    }
-  du_cols = du_cols || (c->Lh && c->eb == 2 && gemm_gelu_sum(1, c->N, c->m));  // (a head's own blocks: one stream)
+  // What LayerNorm backward (ln_) and the FC2 data gradient (du_) leave beside the streams, by the components' ranges: column
+  // sums of their sum, and the sum itself where the streams are not it already.  (A head's own blocks: one stream.)
+  const bool ln = ln_backward_sums(c->N, c->d);
+  bool ln_cols = ln && c->Lh, ln_sums = false, du_cols = c->Lh && c->eb == 2 && gemm_gelu_sum(1, c->N, c->m), du_sums = false;
+  for (const CompPlan &k : c->plan.comp) {
+    if (k.runs.size() != 1) continue;
+    const bool several = !weighted(k.runs[0]).plain, gelu = gelu_sums(c, k.runs);
+    ln_cols = ln_cols || ln;
+    ln_sums = ln_sums || (ln && several);
+    du_cols = du_cols || gelu;
+    du_sums = du_sums || (gelu && several);
+  }
   c->G = (float *)cv.take(ns * N * d * 4);
   for (RingEntry &r : c->ring) {
     r.Ga = (char *)cv.take(ns * N * d * eb);
@@ -331,8 +334,11 @@ size_t layout_workspace(il_ctx *c, void *base) {
     r.DU = (char *)cv.take(live * m * eb);
     r.DQKV = (char *)cv.take(live * 3 * d * eb);
     for (float *&p : r.ln) p = (float *)cv.take((size_t)c->plan.maxruns * ln_backward_max_blocks() * 2 * d * 4);
-    for (char *&p : r.sum) p = (char *)cv.take(sums ? N * d * eb : 0);
-    for (float *&p : r.sum_cols) p = (float *)cv.take((size_t)ln_backward_max_blocks() * d * 4);
+    for (int i = 0; i < 2; ++i) {
+      const bool next = i || c->L > 1 || c->Lh > 1;  // (LayerNorm 1 leaves them for the next block down)
+      r.sum[i] = (char *)cv.take(ln_sums && next ? N * d * eb : 0);
+      r.sum_cols[i] = (float *)cv.take(ln_cols && next ? (size_t)ln_backward_max_blocks() * d * 4 : 0);
+    }
     r.sum_du = (char *)cv.take(du_sums ? N * m * eb : 0);
     r.sum_du_cols = (float *)cv.take(du_cols ? (N + 63) / 64 * m * 4 : 0);
   }
@@ -641,7 +647,7 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
   const RingEntry &r = c->ring[c->pos];
   const int next = (c->pos + 1) % kRing;
   int rc, ln_blocks = 0;
-  const bool one = runs.size() == 1;  // (several ranges' sums only meet in the gradients)
+  const bool sums = runs.size() == 1 && ln_backward_sums(N, d);  // (several ranges' sums only meet in the gradients)
   Tail tail{&b, &s, &r, &runs, 0, {}};
   tail.done[0] = c->above;
   c->above = Summed{};
@@ -662,7 +668,7 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
       return rc;
     }
     if ((rc = linear_dgrad(c, DU, b.w_fc1, S, d, m, EPI_STORE, c->DH, nullptr, 0))) return rc;
-    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk, r.sum[1], one ? r.sum_cols[1] : nullptr,
+    if ((rc = ln_bwd(c, run, c->DH, s.a, s.st2, b.ln2_g, Gb, ln[0], &nblk, r.sum[1], sums ? r.sum_cols[1] : nullptr,
                      &tail.done[2])))
       return rc;
     // attention
@@ -679,7 +685,7 @@ int block_backward(il_ctx *c, const std::vector<Run> &runs, const BlockOff &b, c
     }
     const RingEntry &n = c->ring[next];
     if ((rc = ln_bwd(c, run, c->DH, s.xs, s.st1, b.ln1_g, n.Ga + slot * d * eb, ln[1], &nblk, n.sum[0],
-                     one && !lowest ? n.sum_cols[0] : nullptr, &c->above)))
+                     sums && !lowest ? n.sum_cols[0] : nullptr, &c->above)))
       return rc;
     ln_blocks += nblk;
   }
@@ -1193,6 +1199,24 @@ int il_test_layernorm(int32_t dtype, const float *x, const void *gamma, const vo
   if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
   if (d > 2048 || rows > (1 << 24)) return IL_E_SHAPE;
   IL_TRY(ln_forward(dtype, x, gamma, beta, eps, rows, d, y, stats, xcopy, (hipStream_t)stream));
+  return IL_OK;
+}
+
+int il_test_layernorm_backward(int32_t dtype, const void *dy, const float *x, const float *stats, const void *gamma, int32_t streams,
+                               int32_t tokens, int32_t d, float *G, void *Gb, const float *weights, float *partials, void *ysum,
+                               float *ypart, int32_t *blocks, int32_t *summed, void *stream) {
+  if (!dy || !x || !stats || !gamma || !G || !Gb || !weights || !partials || !blocks || !summed || tokens < 1 || d < 1) return IL_E_ARG;
+  if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
+  if (d > 2048 || streams < 1 || streams > kMaxStreams || (long long)streams * tokens * d * 4 > 0xFFFFFFFFll) return IL_E_SHAPE;
+  StreamWeights sw;
+  memset(&sw, 0, sizeof(sw));
+  memcpy(sw.w, weights, streams * sizeof(float));
+  bool made = false;
+  int nblk = 0;
+  IL_TRY(ln_backward_residual(dtype, dy, x, stats, gamma, streams, tokens, d, G, Gb, sw, partials, &nblk, ysum, ypart, &made,
+                              (hipStream_t)stream));
+  *blocks = nblk;
+  *summed = made;
   return IL_OK;
 }
 

@@ -124,15 +124,111 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ x
   }
 }
 
-// Backward, d divisible by 4: GW wavefronts share a token (a lane owns columns 4 l + 0..3 for its lane number l
-// in the group, d <= 256 GW), a workgroup walks over tokens with NG groups, a token's streams NS at a time: x
-// and the statistics are read once for all of them, and their weighted sum - what the weight gradient of the linear
-// map in front of this LayerNorm multiplies with - and its column sums are left beside them instead of in a
-// pass of their own, which read every stream again.  Bound by its bytes.  One wavefront per row needed 130
-// registers at d = 1024 and 235 at 2048; this form stays under 76, so that its workgroups start beside those
-// of a 256x256 GEMM tile of the other stream, which leaves 76 registers a lane.
+// p[at], with the element's place as one 32-bit byte offset beside a uniform address (a stream is below 4 GiB)
+template <typename T>
+__device__ inline T *lane_at(T *p, uint32_t at) {
+  return reinterpret_cast<T *>(reinterpret_cast<char *>(const_cast<std::remove_const_t<T> *>(p)) + (uint32_t)(at * sizeof(T)));
+}
+
+// Backward, d divisible by 4: GW wavefronts share a row (a lane owns columns 4 l + 0..3 for its lane
+// number l in the group, d <= 256 GW), a workgroup walks over rows with NG groups.  Bound by its bytes
+// (16 per element and stream; 27 us for 8192 x 1024).  One wavefront per row needed 130 registers at
+// d = 1024 and 235 at 2048; this form takes 64 to 74.
+template <typename T, int GW>
+__global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_rows_kernel(const T *__restrict__ dy, const float *__restrict__ x,
+                                                           const float *__restrict__ stats,
+                                                           const T *__restrict__ gamma, int rows, int N, int d, float *G,
+                                                           T *Gb, StreamWeights sw, float *__restrict__ partials) {
+  constexpr int NG = GW > 4 ? 1 : 4 / GW, GL = 64 * GW;
+  __shared__ float red[2][NG][GW][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = wave / GW, wg = wave % GW, l = wg * 64 + lane;
+  float dg[4], db[4], gm[4];
+  const int c = l * 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { dg[e] = 0.f; db[e] = 0.f; gm[e] = 0.f; }
+  if (c < d) Vec<T, 4>::load(gamma + c, gm);
+  const float invd = 1.f / d;
+  const int step = gridDim.x * NG;
+  const int trips = (rows + step - 1) / step;  // the same for every wavefront: the barrier below is theirs together
+  for (int it = 0; it < trips; ++it) {
+    const int row = it * step + blockIdx.x * NG + grp;
+    const bool live = row < rows;
+    const int tok = live ? row % N : 0;
+    const float w = live ? sw.w[row / N] : 0.f;
+    const float mean = stats[2 * tok], rstd = stats[2 * tok + 1];
+    const float *xr = x + (size_t)tok * d;
+    const T *dyr = dy + (size_t)row * d;
+    float *gr = G + (size_t)row * d;
+    T *gbr = Gb + (size_t)row * d;
+    float xh[4], dv[4], gv[4];
+    float s1 = 0.f, s2 = 0.f;
+    const bool in = live && c < d;
+    if (in) {
+      Vec<T, 4>::load(dyr + c, dv);
+      Vec<float, 4>::load(xr + c, xh);
+      Vec<float, 4>::load(gr + c, gv);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      dv[e] = in ? dv[e] : 0.f;
+      xh[e] = in ? (xh[e] - mean) * rstd : 0.f;
+      const float t = dv[e] * gm[e];
+      s1 += t;
+      s2 += t * xh[e];
+      dg[e] += w * dv[e] * xh[e];
+      db[e] += w * dv[e];
+    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if constexpr (GW > 1) {
+      float *r = red[it & 1][grp][wg];
+      if (lane == 0) { r[0] = s1; r[1] = s2; }
+      __syncthreads();  // (the other half of `red` is written next, so one barrier a row is enough)
+      s1 = s2 = 0.f;
+#pragma unroll
+      for (int k = 0; k < GW; ++k) { s1 += red[it & 1][grp][k][0]; s2 += red[it & 1][grp][k][1]; }
+    }
+    const float m1 = s1 * invd, m2 = s2 * invd;
+    if (in) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) gv[e] += rstd * (dv[e] * gm[e] - m1 - xh[e] * m2);
+      Vec<float, 4>::store(gr + c, gv);
+      Vec<T, 4>::store(gbr + c, gv);
+    }
+  }
+  // column sums of the workgroup: its groups combine through LDS, fixed order
+  float *pg = partials + (size_t)blockIdx.x * 2 * d;
+  if constexpr (NG == 1) {
+    if (c < d) {
+      Vec<float, 4>::store(pg + c, dg);
+      Vec<float, 4>::store(pg + d + c, db);
+    }
+  } else {
+    __shared__ float4 cols[NG][2][GL];
+    cols[grp][0][l] = make_float4(dg[0], dg[1], dg[2], dg[3]);
+    cols[grp][1][l] = make_float4(db[0], db[1], db[2], db[3]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * GL; i += 256) {
+      const int which = i / GL, col = (i % GL) * 4;
+      if (col >= d) continue;
+      float4 a = cols[0][which][i % GL];
+#pragma unroll
+      for (int k = 1; k < NG; ++k) {
+        const float4 b = cols[k][which][i % GL];
+        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+      }
+      *reinterpret_cast<float4 *>(pg + which * d + col) = a;
+    }
+  }
+}
+
+// The same, a workgroup walking over tokens, a token's streams NS at a time: x and the statistics are read once for all of
+// them, and their weighted sum - what the weight gradient of the linear map in front of this LayerNorm multiplies
+// with - and its column sums are left beside them instead of in a pass of their own, which reads every stream again.
+// 72 to 98 registers.  Two streams at a time against one, us: 4096 x 1024, two streams 24.1 / 24.8, 1024 x 768 7.4 / 8.0; at
+// GW = 8 it takes 110 registers and 2048 x 2048, three streams 32.2 / 30.1: one at a time there.
 template <typename T, int GW, int NS>
-__global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const T *__restrict__ dy, const float *__restrict__ x,
+__global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_sum_kernel(const T *__restrict__ dy, const float *__restrict__ x,
                                                            const float *__restrict__ stats,
                                                            const T *__restrict__ gamma, int ns, int N, int d, float *G,
                                                            T *Gb, StreamWeights sw, float *__restrict__ partials, T *ysum,
@@ -146,6 +242,7 @@ __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const 
   for (int e = 0; e < 4; ++e) { dg[e] = 0.f; db[e] = 0.f; dy1[e] = 0.f; gm[e] = 0.f; }
   if (c < d) Vec<T, 4>::load(gamma + c, gm);
   const float invd = 1.f / d;
+  const size_t nd = (size_t)N * d;
   const int step = gridDim.x * NG;
   const int trips = (N + step - 1) / step;  // the same for every wavefront: the barrier below is theirs together
   int turn = 0;
@@ -155,16 +252,16 @@ __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const 
     const int t0 = tok < N ? tok : 0;
     const float mean = stats[2 * t0], rstd = stats[2 * t0 + 1];
     float xh[4] = {0.f, 0.f, 0.f, 0.f}, y[4] = {0.f, 0.f, 0.f, 0.f};
-    if (in) Vec<float, 4>::load(x + (size_t)tok * d + c, xh);
+    const uint32_t at = (uint32_t)tok * d + c;
+    if (in) Vec<float, 4>::load(lane_at(x, at), xh);
     for (int s0 = 0; s0 < ns; s0 += NS, turn ^= 1) {
       float dv[NS][4], gv[NS][4], sum[2 * NS];
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const bool live = in && (NS == 1 || s0 + k < ns);
-        const size_t at = ((size_t)(s0 + k) * N + tok) * d + c;
         if (live) {
-          Vec<T, 4>::load(dy + at, dv[k]);
-          Vec<float, 4>::load(G + at, gv[k]);
+          Vec<T, 4>::load(lane_at(dy + (s0 + k) * nd, at), dv[k]);
+          Vec<float, 4>::load(lane_at(G + (s0 + k) * nd, at), gv[k]);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) dv[k][e] = live ? dv[k][e] : 0.f;
@@ -206,30 +303,29 @@ __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const 
       for (int k = 0; k < NS; ++k) {
         if (!in || (NS > 1 && s0 + k >= ns)) continue;
         const float m1 = sum[2 * k] * invd, m2 = sum[2 * k + 1] * invd, w = sw.w[s0 + k];
-        const size_t at = ((size_t)(s0 + k) * N + tok) * d + c;
 #pragma unroll
         for (int e = 0; e < 4; ++e) gv[k][e] += rstd * (dv[k][e] * gm[e] - m1 - xh[e] * m2);
-        Vec<float, 4>::store(G + at, gv[k]);
-        Vec<T, 4>::store(Gb + at, gv[k]);
-        if (ypart && w != 0.f) {  // (uniform) the sum is taken of the stored values
+        Vec<float, 4>::store(lane_at(G + (s0 + k) * nd, at), gv[k]);
+        Vec<T, 4>::store(lane_at(Gb + (s0 + k) * nd, at), gv[k]);
+        if (w != 0.f) {  // (uniform) the sum is taken of the stored values
 #pragma unroll
           for (int e = 0; e < 4; ++e) y[e] += w * round_to<T>(gv[k][e]);
         }
       }
     }
-    if (ypart && in) {
-      if (ysum) Vec<T, 4>::store(ysum + (size_t)tok * d + c, y);
+    if (in) {
+      if (ysum) Vec<T, 4>::store(lane_at(ysum, at), y);
 #pragma unroll
       for (int e = 0; e < 4; ++e) dy1[e] += y[e];
     }
   }
   // column sums of the workgroup: its groups combine through LDS, fixed order
-  float *pg = partials + (size_t)blockIdx.x * 2 * d, *py = ypart ? ypart + (size_t)blockIdx.x * d : nullptr;
+  float *pg = partials + (size_t)blockIdx.x * 2 * d, *py = ypart + (size_t)blockIdx.x * d;
   if constexpr (NG == 1) {
     if (c < d) {
       Vec<float, 4>::store(pg + c, dg);
       Vec<float, 4>::store(pg + d + c, db);
-      if (py) Vec<float, 4>::store(py + c, dy1);
+      Vec<float, 4>::store(py + c, dy1);
     }
   } else {
     __shared__ float4 cols[NG][3][GL];
@@ -237,7 +333,7 @@ __global__ __launch_bounds__(GW > 4 ? 512 : 256) void ln_bwd_group_kernel(const 
     cols[grp][1][l] = make_float4(db[0], db[1], db[2], db[3]);
     cols[grp][2][l] = make_float4(dy1[0], dy1[1], dy1[2], dy1[3]);
     __syncthreads();
-    for (int i = threadIdx.x; i < (py ? 3 : 2) * GL; i += 256) {
+    for (int i = threadIdx.x; i < 3 * GL; i += 256) {
       const int which = i / GL, col = (i % GL) * 4;
       if (col >= d) continue;
       float4 a = cols[0][which][i % GL];
@@ -377,26 +473,29 @@ template <typename T>
 void launch_bwd(hipStream_t s, const T *dy, const float *x, const float *stats, const T *gamma, int ns, int N, int d,
                 float *G, T *Gb, const StreamWeights &sw, float *partials, int *nblk, T *ysum, float *ypart, bool *summed) {
   *summed = false;
+  const int rows = ns * N;
+  auto by_rows = [&](auto kernel, int threads, int at_once) {
+    *nblk = std::min((rows + at_once - 1) / at_once, kLnBwdBlocks);
+    hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(threads), 0, s, dy, x, stats, gamma, rows, N, d, G, Gb, sw, partials);
+  };
   if (!vec4<T>(d, gamma, gamma, x, G)) {
-    const int rows = ns * N;
-    *nblk = std::min((rows + kWaves - 1) / kWaves, kLnBwdBlocks);
-    auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(256), 0, s, dy, x, stats, gamma, rows, N, d, G, Gb, sw, partials);
-    };
-    if (d <= 256) launch(ln_bwd_kernel<T, 1, 4>);
-    else launch(ln_bwd_kernel<T, 1, 32>);
+    if (d <= 256) by_rows(ln_bwd_kernel<T, 1, 4>, 256, kWaves);
+    else by_rows(ln_bwd_kernel<T, 1, 32>, 256, kWaves);
     return;
   }
-  *summed = ypart != nullptr;
+  *summed = ypart != nullptr && d > 256;
   auto launch = [&](auto gw) {
-    constexpr int GW = decltype(gw)::value, NG = GW > 4 ? 1 : 4 / GW;
-    *nblk = std::min((N + NG - 1) / NG, kLnBwdBlocks);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(GW > 4 ? 512 : 256), 0, s, dy, x, stats, gamma, ns, N, d, G, Gb, sw,
-                         partials, ysum, ypart);
-    };
-    if (ns == 1) go(ln_bwd_group_kernel<T, GW, 1>);
-    else go(ln_bwd_group_kernel<T, GW, 2>);
+    constexpr int GW = decltype(gw)::value, NG = GW > 4 ? 1 : 4 / GW, threads = GW > 4 ? 512 : 256;
+    if (!*summed) return by_rows(ln_bwd_rows_kernel<T, GW>, threads, NG);
+    if constexpr (GW > 1) {
+      *nblk = std::min((N + NG - 1) / NG, kLnBwdBlocks);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(*nblk), dim3(threads), 0, s, dy, x, stats, gamma, ns, N, d, G, Gb, sw,
+                           partials, ysum, ypart);
+      };
+      if (ns == 1 || GW == 8) go(ln_bwd_sum_kernel<T, GW, 1>);
+      else go(ln_bwd_sum_kernel<T, GW, GW == 8 ? 1 : 2>);
+    }
   };
   if (d <= 256) launch(std::integral_constant<int, 1>{});
   else if (d <= 512) launch(std::integral_constant<int, 2>{});
@@ -407,6 +506,17 @@ void launch_bwd(hipStream_t s, const T *dy, const float *x, const float *stats, 
 }  // namespace
 
 int ln_backward_max_blocks() { return kLnBwdBlocks; }
+
+// Forming the sums makes the launch 0.2 to 1.5 us longer, and in a backward it stands in the chain of data gradients that
+// the step waits for, where the pass it replaces runs beside them.  It pays where the chain's products fill the
+// chip, so that the pass takes time from them.  Steps in us, without / with the sums (bf16, tokens x d, n):
+//   4096 x 1024 2 16858 / 16707, 3 (8 components) 23763 / 23383;  2752 x 576 3 11022 / 10903;  3776 x 768 1 16055 / 15986;
+//   4096 x 2048 2 73610 / 73170;  2752 x 1984 2 33041 / 32875;  4096 x 512 1 3438 / 3423;  2048 x 1024 2, 2304 x 768 2 equal;
+//   2048 x 512 1 1720 / 1732;  4096 x 256 1 2346 / 2364;  1600 x 768 3 4828 / 4844;  960 x 1920 2 25278 / 25385;
+//   576 x 256 2 3024 / 3097;  1024 x 2048 2 7486 / 7504;  704 x 448 2 5806 / 5843.
+bool ln_backward_sums(int N, int d) {
+  return d > 256 && (d & 3) == 0 && N >= 1536 && (long)N * d >= 3l << 19;
+}
 
 hipError_t ln_forward(int dtype, const float *x, const void *gamma, const void *beta, float eps, int rows,
                       int d, void *y, float *stats, float *xcopy, hipStream_t s) {
