@@ -2,17 +2,22 @@
 // three bf16 and a product of two elements the sum of six bf16 products, accumulated in fp32.  Arbitrary M, N, K,
 // both operand layouts, the library's fused epilogues.
 //
-// Precision.  hi + mid + lo holds all 24 bits; the three products left out are below 2^-26 of the largest.  What
-// remains are the roundings of the accumulation, and there are fewer of them than with the fp32 instruction
-// (v_mfma_f32_32x32x2_f32: two k at a time): against 64 bits the relative error (2-norm) at 2048 x 512 x 2048 is
-// 3.5e-7 where that instruction gave 8.1e-7, at 256 x 256 x 31992 1.6e-6 and 3.2e-6, at K = 16 3.3e-8 and 7.3e-8;
-// no shape, layout or distribution tried (normal, with an offset, over ten decades, probabilities) was worse.
-// What comes out not finite is computed again with the fp32 instruction: an infinity splits into NaN parts.
+// Precision.  hi + mid + lo holds all 24 bits of every normal operand (taken times 2^24, see split8).  Of the nine partial
+// products three are left out, mid lo, lo mid and lo lo: each at most 2^-25 of the whole product, together less than
+// 2^-24, and of one sign where the operands are equal.  What remains are the roundings of the accumulation, and
+// there are fewer of them than with the fp32 instruction (v_mfma_f32_32x32x2_f32: two k at a time): against 64 bits the
+// relative error (2-norm) at 2048 x 512 x 2048 is 3.5e-7 where that instruction gave 8.1e-7, at 256 x 256 x 31992 1.6e-6
+// and 3.2e-6, at K = 64 5.5e-8 and 1.4e-7; from K = 64 on no shape, layout or distribution tried (normal, with an offset,
+// over ten decades, probabilities) was worse; below, where accumulation hardly rounds, at most 1.4 times as large (K = 1
+// 3.6e-8 and 2.6e-8).
+// What comes out not finite - an infinity splits into NaN parts, sums from 2^80 on overflow - is computed again with the
+// fp32 instruction, 64 x 64 outputs at a time: 2048 x 512 x 2048 33 -> 136 us if every block is,
+// whatever the number of values.
 //
 // Bound: 6 x 32 matrix cycles for 32 x 32 x 16, where the fp32 instruction takes 8 x 64: 2.7 times its rate at equal
-// clock.  4096 x 4096 x 2048 558 -> 328 us (210 TFLOP/s, 1.26 PFLOP/s of bf16 products: the clock the power limit
-// allows); 2048 x 2048 x 512 with GELU 47 -> 31, 4096 x 512 x 2048 74 -> 51, 2048 x 512 x 2048 45 -> 33 us: small
-// outputs are bound by what a CU is delivered (64 KB and four products of 64 x 64 x 64 every 0.9 us), not by the
+// clock.  4096 x 4096 x 2048 558 -> 336 us (205 TFLOP/s, 1.23 PFLOP/s of bf16 products: the clock the power limit
+// allows); 2048 x 2048 x 512 with GELU 47 -> 30.5, 4096 x 512 x 2048 74 -> 52, 2048 x 512 x 2048 45 -> 32 us: small
+// outputs are bound by what a CU is delivered and converts (64 KB and four products of 64 x 64 x 64 every 0.9 us), not by the
 // matrix units.
 #include <algorithm>
 #include <cstring>
@@ -121,12 +126,20 @@ struct Tile {
 };
 
 // A float as the sum of three bf16, hi + mid + lo, each the rounded rest of the one before: 8 + 8 + 8 bits and
-// two signs hold all 24 (operands below 2^-110, whose lo leaves bf16's range, keep fewer).  Eight values become
-// a chunk of each plane.
+// two signs hold all 24.  It is taken times 2^24, so that lo of the smallest normal operand is a normal number too, and
+// the sums of products times 2^-48 at the end: exact both, at 0 to 3 % of the time (2048 x 512 x 2048 31.2 -> 32.1 us).
+// Without it operands below 2^-110 lost lo, 1e-36 times 1e36 ten of its bits.  Eight values become a chunk of each plane.
+// (Plain multiplies and subtractions of four bytes: fused ones of eight with a literal made the loop 2 % slower.)
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
 __device__ inline void split8(const float (&x)[8], u32x4 (&f)[3]) {
+#pragma clang fp contract(off)
+  float up = kUp;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+s"(up));
+#endif
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float a = x[2 * i], b = x[2 * i + 1];
+    float a = x[2 * i] * up, b = x[2 * i + 1] * up;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       uint32_t u = pack_bf16x2(a, b);
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))
       return o;
     };
     auto products = [&](const Operands &o) {
-      // all but the products below 2^-26 of the largest, the small ones first
+      // all but mid lo, lo mid and lo lo, the small ones first
       constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
       for (int q = 0; q < 6; ++q)
@@ -326,9 +339,9 @@ __global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))
     }
     products(cur);
 
-    // Infinities and values that round to one split into NaN parts, and parts of a product can overflow to both
-    // signs: what comes out not finite is done again in fp32 products, straight from memory.
-    float bad = 0.f;
+    // Infinities and values from 2^104 on split into NaN parts, and sums from 2^80 on overflow: what comes out not finite
+    // is done again in fp32 products, straight from memory.
+    float bad = 0.f, down = kDown;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -336,6 +349,7 @@ __global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))
 #pragma unroll
         for (int r = 0; r < 16; ++r) bad = __builtin_fmaf(acc[i][j][r], 0.f, bad);
     if (__any(!(bad == 0.f))) {
+      down = 1.f;
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -367,7 +381,7 @@ __global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(32 * i + 8 * (r >> 2) + (r & 3)) * S::PITCH + 32 * j] = acc[i][j][r];
+        for (int r = 0; r < 16; ++r) mine[(32 * i + 8 * (r >> 2) + (r & 3)) * S::PITCH + 32 * j] = acc[i][j][r] * down;
   }
 
   // What the epilogue reads is requested for all of a thread's rows before the sums are there.

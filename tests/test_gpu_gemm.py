@@ -255,6 +255,50 @@ def test_f32_tiles(M, N, K, akm, bkm, epi, tile):
     assert np.all(np.abs(C.cpu().numpy() - want) <= (K + 2) * 2.0 ** -24 * mag)
 
 
+@pytest.mark.parametrize("tile", [0, 2, 3, 4])
+@pytest.mark.parametrize("akm,bkm", [(0, 1), (0, 0), (1, 1)])
+@pytest.mark.parametrize("small,large", [(-125, 124), (-118, 60), (-112, 0), (-100, 100)])
+def test_f32_small_operands(small, large, akm, bkm, tile):
+    """Operands down to the smallest normal numbers keep all their bits: 2^small times 2^large, either way round."""
+    import torch
+    M, N, K = 68, 132, 100
+    rng = np.random.default_rng(7)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")  # noqa: E731
+    for p, q in ((small, large), (large, small)):
+        x, y = (np.ldexp(rng.uniform(1, 2, size=s) * rng.choice([-1, 1], size=s), e).astype(np.float32) for s, e in (((M, K), p), ((K, N), q)))
+        A, B = dev(x.T if akm else x), dev(y if bkm else y.T)
+        C = torch.zeros((M, N), device="cuda:0")
+        print("case f32 small", p, q, akm, bkm, tile, flush=True)
+        b.il_test_gemm(0, A, B, M, N, K, A.shape[1], B.shape[1], akm, bkm, 6 if akm else 0, C, tile=tile)
+        torch.cuda.synchronize()
+        want, mag = x.astype(np.float64) @ y, np.abs(x).astype(np.float64) @ np.abs(y)
+        # 2^-149: half of it per rounding to a number below 2^-126, which the smallest pair's sums come near to
+        assert np.all(np.abs(C.cpu().numpy() - want) <= (K + 2) * 2.0 ** -24 * mag + 2.0 ** -149), (p, q)
+        err = np.linalg.norm(C.cpu().numpy() - want) / np.linalg.norm(want)
+        assert err <= 2.0 ** -21, (p, q, err)
+
+
+@pytest.mark.parametrize("tile,K", [(2, 4096), (3, 4096), (4, 4096), (0, 16384), (4, 16)])
+@pytest.mark.parametrize("value", [1.0 + 2.0 ** -8 - 2.0 ** -17, 1.0038986, 1.0 - 2.0 ** -9 + 2.0 ** -18])
+def test_f32_worst_split(value, tile, K):
+    """Equal operands whose parts left out are the largest and of one sign: of the three products left out none is above
+    2^-25 of the whole, and together they are below 2^-24.  That is the first term of the bound; the others are the
+    roundings of the sum, one per product kept and addition of a K step of 16."""
+    import torch
+    M, N = 132, 68
+    x = np.full((M, K), value, np.float32)
+    y = np.full((K, N), value, np.float32)
+    C = torch.zeros((M, N), device="cuda:0")
+    print("case f32 worst split", value, tile, K, flush=True)
+    A, B = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(y).to("cuda:0")
+    b.il_test_gemm(0, A, B, M, N, K, K, N, 0, 1, 0, C, tile=tile)
+    torch.cuda.synchronize()
+    want = K * np.float64(np.float32(value)) ** 2
+    got = C.cpu().numpy()
+    assert np.all(got == got[0, 0])
+    assert abs(got[0, 0] / want - 1) <= 2.0 ** -24 * (1 + 6 * -(-K // 16) + 4), got[0, 0] / want - 1
+
+
 @pytest.mark.parametrize("tile,M,N,K", [(2, 130, 130, 40), (3, 130, 66, 72), (4, 68, 68, 136), (0, 67, 65, 33)])
 @pytest.mark.parametrize("akm,bkm", [(0, 1), (0, 0), (1, 1)])
 def test_f32_not_finite(tile, M, N, K, akm, bkm):
