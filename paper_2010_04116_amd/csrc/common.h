@@ -150,6 +150,7 @@ hipError_t gemm_bf16(const GemmArgs &g, hipStream_t s);   // T = bf16, MFMA
 constexpr int kMaxBatch = 8;
 hipError_t gemm_f32_batch(const GemmArgs *list, int count, hipStream_t s);
 hipError_t gemm_bf16_batch(const GemmArgs *list, int count, hipStream_t s);
+double gemm_f32_us(int tile, long workgroups, long steps);  // estimate for `workgroups` tiles over steps x 64 of K each
 bool gemm_gelu_sum(int streams, int tokens, int N);  // see EPI_GELU_BWD_SUM
 // Split-K for EPI_STORE_F32: `splits` partial products over disjoint K ranges go to ws ([splits][M][N] fp32)
 // in one launch with the given tile, then a reduction adds them up in a fixed order.

@@ -431,9 +431,6 @@ hipError_t launch(GemmBatch &b, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Rounds of workgroups, times what one takes: microseconds per 64 of K with the chip full, and about five for start
-// and epilogue.  Measured (128x128 / 128x64 / 64x64): 2048x1536x512 24 / 30 / 31 us, 4096x512x2048 64 / 51 / 65,
-// 2048x512x2048 - / 43 / 33, 1600x768x3072 87 / 62 / 85, 4096x2048x512 57 / 71 / 91.
 template <bool AKM, bool BKM>
 hipError_t pick(GemmBatch &b, bool aligned, hipStream_t s) {
   if (!aligned) return launch<64, 64, AKM, BKM, 1>(b, s);
@@ -445,8 +442,8 @@ hipError_t pick(GemmBatch &b, bool aligned, hipStream_t s) {
     t128 += tiles_of<128, 128>(b.p[i]);
     k = std::max(k, b.p[i].splits > 1 ? b.p[i].k_per : b.p[i].K);
   }
-  auto price = [&](long tiles, double step_us) { return (double)((tiles + 255) / 256) * (5.0 + (k + 63) / 64 * step_us); };
-  const double us64 = price(t64, 0.9), us128x64 = price(t128x64, 1.45), us128 = price(t128, 2.6);
+  const long steps = (k + 63) / 64;
+  const double us64 = gemm_f32_us(4, t64, steps), us128x64 = gemm_f32_us(3, t128x64, steps), us128 = gemm_f32_us(2, t128, steps);
   int tile = b.p[0].tile;
   if (!tile) tile = us128 <= std::min(us128x64, us64) ? 2 : us128x64 <= us64 ? 3 : 4;
   switch (tile) {
@@ -457,6 +454,14 @@ hipError_t pick(GemmBatch &b, bool aligned, hipStream_t s) {
 }
 
 }  // namespace
+
+// Rounds of workgroups, times what one takes: microseconds per 64 of K with the chip full, and about five for start
+// and epilogue.  Measured (128x128 / 128x64 / 64x64): 2048x1536x512 24 / 30 / 31 us, 4096x512x2048 64 / 51 / 65,
+// 2048x512x2048 - / 43 / 33, 1600x768x3072 87 / 62 / 85, 4096x2048x512 57 / 71 / 91.
+double gemm_f32_us(int tile, long workgroups, long steps) {
+  const double step_us = tile == 2 ? 2.6 : tile == 3 ? 1.45 : 0.9;
+  return (double)((workgroups + 255) / 256) * (5.0 + steps * step_us);
+}
 
 hipError_t gemm_f32_batch(const GemmArgs *list, int count, hipStream_t s) {
   if (count < 1 || count > kMaxBatch) return hipErrorInvalidValue;

@@ -962,8 +962,8 @@ bool gemm_gelu_sum(int streams, int tokens, int N) {
 
 // Prices every number of parts with every tile (measured microseconds per 64-deep K step of a workgroup:
 // the 128x128 tile alone on its CU 0.47 with four stages, two of them with two stages 0.96; 256x256 1.35;
-// 64x64 up to two per CU 0.42; fp32 0.9 for 64x64, 1.45 for 128x64, 2.6 for 128x128), the rounds its workgroups need, and
-// the traffic of writing and adding up the parts at 4 bytes per picosecond.
+// 64x64 up to two per CU 0.42; fp32 as gemm_f32_us), the rounds its workgroups need, and the traffic of writing and
+// adding up the parts at 4 bytes per picosecond.
 SplitPlan gemm_split_plan(int dtype, int M, int N, int K, size_t ws_floats) {
   const long steps = (K + 63) / 64, cap = std::min<long>({32, (long)(ws_floats / ((size_t)M * N)), steps / 4});
   auto tiles = [&](int t) { return (long)((M + t - 1) / t) * ((N + t - 1) / t); };
@@ -973,14 +973,14 @@ SplitPlan gemm_split_plan(int dtype, int M, int N, int K, size_t ws_floats) {
   for (long sp = 1; sp <= std::max<long>(cap, 1); ++sp) {
     const double add_us = sp < 2 ? 0.0 : 4.0 + 2.0 * sp * M * N * 4.0 / 4e6;
     const long per = up(steps, sp);
-    auto price = [&](int tile, long wgs, long per_round, double step_us) {
-      const double us = up(wgs, per_round) * per * step_us + add_us;
-      if (us < best_us) { best_us = us; best = SplitPlan{(int)sp, tile}; }
+    auto take = [&](int tile, double us) {
+      if (us + add_us < best_us) { best_us = us + add_us; best = SplitPlan{(int)sp, tile}; }
     };
+    auto price = [&](int tile, long wgs, long per_round, double step_us) { take(tile, up(wgs, per_round) * per * step_us); };
     if (dtype == 0) {
-      price(4, tiles(64) * sp, 256, 0.9);
-      price(3, up(M, 128) * up(N, 64) * sp, 256, 1.45);
-      price(2, tiles(128) * sp, 256, 2.6);
+      take(2, gemm_f32_us(2, tiles(128) * sp, per));
+      take(3, gemm_f32_us(3, up(M, 128) * up(N, 64) * sp, per));
+      take(4, gemm_f32_us(4, tiles(64) * sp, per));
     } else {
       price(3, tiles(128) * sp, 256, 0.47);
       price(2, tiles(128) * sp, 512, 0.96);

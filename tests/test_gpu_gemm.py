@@ -212,8 +212,8 @@ def test_long_reduction_and_thin_outputs():
     run_case(72, 8, 520, 0, 1, 3, 0, seed=79)
 
 
-# fp32: tile edges and remainders in every direction, both load widths (16-byte rows or not), both tiles
-# (the last shape fills the chip twice with 128x128 tiles), one K step and many
+# fp32: tile edges and remainders in every direction, both load widths (16-byte rows or not), the tile the library
+# chooses (the last shape fills the chip twice with 128x128 tiles), one K step and many
 @pytest.mark.parametrize("M,N,K", [(64, 64, 32), (1, 3, 5), (65, 68, 36), (67, 129, 33), (128, 200, 260),
                                    (2816, 3000, 100)])
 @pytest.mark.parametrize("akm,bkm", [(0, 0), (0, 1), (1, 0), (1, 1)])
@@ -333,7 +333,7 @@ def test_f32_not_finite(tile, M, N, K, akm, bkm):
                                               (1, 1, 6, 0), (1, 1, 6, 1)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 32), (37, 3, 5), (67, 132, 33), (300, 200, 260), (2816, 3000, 40)])
 def test_f32_epilogues(M, N, K, akm, bkm, epi, beta):
-    """Every epilogue the step has in fp32, over both tiles and both load widths, with rows that wrap."""
+    """Every epilogue the step has in fp32, over the tiles the library chooses and both load widths, with rows that wrap."""
     import torch
     rng = np.random.default_rng(M + 7 * N + K + epi)
     x, y = (rng.normal(size=s).astype(np.float32) for s in ((M, K), (K, N)))

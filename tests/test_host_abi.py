@@ -187,3 +187,14 @@ def test_workspace_grows_by_what_is_kept_and_nothing_twice(n, dtype):
     assert size(m=m + 64) - size() == 64 * (blocks * 2 * N * eb + 4 * live * N * eb + 2 * 64 * 4)
     saved = N * (2 * d * 4 + (6 * d + 2 * m) * eb + w.H * 4 + 2 * 2 * 4)   # a block's activations
     assert size(K=w.K + 1) - size() == w.L * saved + N * d * 4 + 4 * N * d * eb + N * d * 4   # stream, operand, dx of the head
+
+
+def test_fp32_parts_are_priced_as_the_tiles_are():
+    """A head's dx in fp32: every round of workgroups costs its start and epilogue, so many short parts do not pay (each
+    plan was the fastest of those timed: 4016 x 272 x 20008 in three parts 339 us, eight 343; 1552 x 1744 x 12488 in
+    four 383 us, seven 401), and without room for parts the tile is the one a product by itself takes."""
+    for (M, N, K), plan in {(2720, 1024, 18464): (7, 2), (4016, 272, 20008): (3, 3), (1552, 1744, 12488): (4, 2),
+                            (192, 1168, 28144): (4, 4), (2048, 512, 8192): (4, 2)}.items():
+        assert binding.il_gemm_split_plan(0, M, N, K, 1 << 40) == plan, (M, N, K)
+    for (M, N, K), tile in {(2048, 512, 2048): 4, (4096, 512, 2048): 3, (4096, 2048, 512): 2}.items():
+        assert binding.il_gemm_split_plan(0, M, N, K, 0) == (1, tile), (M, N, K)
