@@ -1041,7 +1041,9 @@ int il_head_xent_static(il_ctx *c, int32_t k, const float *x_k, const int32_t *t
       carve(rows, (size_t)8 * rows * c->d);
     }
   }
-  if (need > kStaticScratchBytes) {  // fewer parts, whatever is left for them
+  // fp32 likes more parts than it did when its products were slower: fewer of them, whatever is left for them, so that no
+  // size that fitted then is refused
+  if (need > kStaticScratchBytes && c->cfg.dtype == IL_F32) {
     const size_t rest = need - ((skws_floats * 4 + 255) & ~(size_t)255);
     carve(rows, rest < kStaticScratchBytes ? (kStaticScratchBytes - rest) / 4 : 0);
   }

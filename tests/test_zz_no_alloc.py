@@ -74,3 +74,29 @@ def test_static_scratch_head_rejects_what_does_not_fit():
     assert e.value.status == binding.IL_E_SHAPE
     st.close()
     torch.cuda.synchronize()
+
+
+def test_static_scratch_head_takes_fewer_parts_where_those_it_would_like_do_not_fit():
+    """1024 x 12288 fp32 logits, x and the parts of dx the planner would choose are 71 MB: the head runs with the parts that
+    fit.  Losses and the head's gradient are the workspace head's bit for bit; dx, sums over the vocabulary in another
+    order, and the component's gradients behind it to fp32 rounding (5e-7 to 7e-7 of norm over three
+    inputs; the bound is about six times that).
+    bf16 of 1024 x 24576, which needs as much, is refused."""
+    w = synth.Workload("na_parts", "f32", K=1, L=1, d=512, H=8, m=512, V=12288, B=4, T=512, n=1)
+    print("case static head, parts that do not fit", flush=True)
+    parts, _ = binding.il_gemm_split_plan(0, 1024, w.d, w.V, 1 << 40)
+    tile = 1024 * w.V * 4 + w.N * w.d * 4
+    assert tile + min(parts, 8) * 1024 * w.d * 4 > 64 << 20 > tile
+    a, b = _both(w, 23)
+    assert np.array_equal(a["losses"], b["losses"]) and np.array_equal(a["head_grads"][0], b["head_grads"][0])
+    for name in synth.BLOCK_TENSORS:
+        p, q = a["comp_grads"][0][0][name].astype(np.float64), b["comp_grads"][0][0][name]
+        assert np.linalg.norm(p - q) <= 4e-6 * np.linalg.norm(p), (name, np.linalg.norm(p - q) / np.linalg.norm(p))
+    w = w.with_(dtype="bf16", V=24576)
+    st = binding.Step(w, np.zeros(binding.param_count(w), np.float32))
+    st.set_inputs(np.zeros((w.N, w.d), np.float32), np.zeros((w.B, w.T), np.int32))
+    binding.il_stage_forward(st.ctx, 1, st.x[0], st.x[1])
+    with pytest.raises(binding.InterlockError) as e:
+        binding.il_head_xent_static(st.ctx, 1, st.x[1], st.targets, st.losses)
+    assert e.value.status == binding.IL_E_WORKSPACE
+    st.close()
