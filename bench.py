@@ -23,7 +23,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3       # its fp32 matrix instructions
+PEAK_F32_TFLOPS = 157.3       # its fp32 matrix instructions (attention in fp32)
+PEAK_F32_GEMM_TFLOPS = PEAK_BF16_TFLOPS / 6   # fp32 GEMMs: six bf16 products each
 PEAK_HBM_GBS = 8000.0
 
 # HBM-side bytes per GEMM kernel launch (average over the GEMM launches of one step), from two
@@ -33,9 +34,9 @@ PEAK_HBM_GBS = 8000.0
 # carried here for the workloads they were measured on and are null for any other.
 MEASURED_TRAFFIC = {
     "small_bf16_n2": 37.89e6,   # 27.66 MB read + 10.23 MB written per launch, 1104 launches (1.58 x algorithmic)
-    "large_bf16_n2": 462.79e6,  # 369.64 + 93.15 MB, 4104 launches (1.95 x)
-    "medium_bf16_n2": 172.80e6,  # 132.79 + 40.02 MB, 2736 launches (1.69 x)
-    "many_head_bf16_n3": 209.19e6,  # 158.61 + 50.59 MB, 3072 launches (1.65 x)
+    "large_bf16_n2": 463.60e6,  # 365.51 + 98.10 MB, 4104 launches (1.95 x)
+    "medium_bf16_n2": 173.07e6,  # 131.17 + 41.90 MB, 2736 launches (1.70 x)
+    "many_head_bf16_n3": 209.33e6,  # 157.91 + 51.43 MB, 3072 launches (1.65 x)
 }
 
 # which roofline bounds a kernel class, and the peak its fraction is taken against
@@ -207,7 +208,7 @@ def measure(w, steps, warmup, peaks):
     g_fl = sum(prof[k]["flops_per_step"] for k in gemm)
     g_by = sum(prof[k]["bytes_per_step"] for k in gemm)
     g_n = sum(prof[k]["launches_per_step"] for k in gemm)
-    peak = PEAK_BF16_TFLOPS if bf else PEAK_F32_TFLOPS
+    peak = PEAK_BF16_TFLOPS if bf else PEAK_F32_GEMM_TFLOPS
     if bf:
         # events attached to each MFMA GEMM dispatch: the kernel's own execution time
         iso_ms = sum(prof[k]["kernel_ms_per_step"] for k in gemm)
@@ -246,7 +247,8 @@ def measure(w, steps, warmup, peaks):
         e = {"ms_per_step": round(v["ms_per_step"], 4), "launches": v["launches_per_step"], "bound": bound}
         if bound == "mfma":
             e["tflops"] = v["flops_per_step"] / t / 1e12 if t > 0 and v["flops_per_step"] else None
-            e["frac"] = e["tflops"] / peak if e["tflops"] else None
+            top = peak if bf or k in gemm else PEAK_F32_TFLOPS
+            e["frac"] = e["tflops"] / top if e["tflops"] else None
             if bf and k in gemm:                       # the kernel alone, and inside the two-stream step
                 tk, ti = v["kernel_ms_per_step"] * 1e-3, instep[k]["kernel_ms_per_step"] * 1e-3
                 e["kernel_tflops"] = v["flops_per_step"] / tk / 1e12 if tk > 0 else None

@@ -751,9 +751,9 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
 
 // At head width 64 a workgroup walks two streams together: one read of K, V and Q and one score product and
 // exponential serve both, 24 matrix instructions per sub-tile and stream instead of 28, half of the LDS reads for dQ;
-// the walk is bound by the latency of its products and reads.  250 registers, two wavefronts per SIMD as before.
-// That leaves half as many workgroups, so it is taken where there are more of them than the 512 that the chip holds at
-// a time.  Backward in us, one by one / in pairs (workgroups in pairs):
+// the walk is bound by the latency of its products and reads.  256 registers, the most two wavefronts per SIMD have, none
+// spilled.  That leaves half as many workgroups, so it is taken where there are more of them than the 512 that the chip
+// holds at a time; at 512 short sequences would gain and long ones lose.  Backward in us, one by one / in pairs (workgroups in pairs):
 //   8 x 512 tokens, 16 heads, two streams (1024) 65.0 / 53.0, three streams (2048) 91.6 / 79.3;  4 x 1024, 16 (1024) 91.0 / 76.1;
 //   64 x 64, 8 (1024) 22.4 / 20.5;  8 x 200, 12, three (768) 27.6 / 23.8;  3 x 640, 12, three (720) 45.1 / 39.1;
 //   8 x 256, 16 (512) 27.1 / 23.4;  4 x 512, 16 (512) 35.2 / 34.8;  2 x 1024, 16 (512) 51.8 / 54.0;  4 x 1024, 8 (512) 49.8 / 52.9;

@@ -7,9 +7,10 @@
 // 2^-24, and of one sign where the operands are equal.  What remains are the roundings of the accumulation, and
 // there are fewer of them than with the fp32 instruction (v_mfma_f32_32x32x2_f32: two k at a time): against 64 bits the
 // relative error (2-norm) at 2048 x 512 x 2048 is 3.5e-7 where that instruction gave 8.1e-7, at 256 x 256 x 31992 1.6e-6
-// and 3.2e-6, at K = 64 5.5e-8 and 1.4e-7; from K = 64 on no shape, layout or distribution tried (normal, with an offset,
-// over ten decades, probabilities) was worse; below, where accumulation hardly rounds, at most 1.4 times as large (K = 1
-// 3.6e-8 and 2.6e-8).
+// and 3.2e-6, at K = 64 5.5e-8 and 1.4e-7; from K = 64 on no shape, layout or distribution of random operands tried
+// (normal, with an offset, over ten decades, probabilities) was worse; below, where accumulation hardly rounds, at most
+// 1.4 times as large (K = 1 3.6e-8 and 2.6e-8).  Sums of equal products, whose roundings have one sign, come out either
+// way: 512 times 0.998^2 1.5e-8 and 5.2e-6, 512 times 1.732^2 5.1e-7 and 3.6e-8.
 // What comes out not finite - an infinity splits into NaN parts, sums from 2^80 on overflow - is computed again with the
 // fp32 instruction, 64 x 64 outputs at a time: 2048 x 512 x 2048 33 -> 136 us if every block is,
 // whatever the number of values.

@@ -499,8 +499,8 @@ int attention_bwd(il_ctx *c, const BlockSave &s, const void *d_o, int cnt, void 
   return IL_OK;
 }
 
-// Gout: the range's rows of the updated stream as a GEMM operand.  left: where the streams' weighted sum and its
-// column sums may go (nullptr: not wanted); *made: what is there afterwards.
+// Gout: the range's rows of the updated stream as a GEMM operand.  sum, sum_cols: where the streams' weighted sum and its
+// column sums may go (sum_cols nullptr: not wanted); *made: what is there afterwards.
 int ln_bwd(il_ctx *c, const Run &run, const void *dy, const float *x, const float *stats, size_t g_off, void *Gout,
            float *partials, int *nblk, void *sum, float *sum_cols, Summed *made) {
   StreamWeights sw;

@@ -20,7 +20,7 @@ A completely wrong row scores about 1 (or more) on `rows`, a zeroed tile 1 on bo
 garbage or dropped element 0.5 or more on `elem`; rounding noise scores a small multiple of the tensor
 tolerance (the bounds are ROW_FACTOR and ELEM_FACTOR times it).  Measured worst over all cases, the
 full-size runs included: bf16 tensor 9.3e-3, rows 1.4e-2, cols 6.4e-2, elem 0.11 (one column of a head matrix; 0.05 to
-0.11 as x_0 changes in its last bits); fp32 2e-6, 3e-6, 4e-6, 9e-6.
+0.11 as x_0 changes in its last bits); fp32 9e-7, 1.4e-6, 3.3e-6, 4.1e-6.
 """
 import json
 import os
