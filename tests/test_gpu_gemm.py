@@ -111,6 +111,14 @@ def test_multi_tile_shapes(tile):
     run_case(512, 1024, 2048, 1, 1, 6, tile, seed=42)
 
 
+@pytest.mark.parametrize("tile,edge", [(1, 256), (3, 128), (5, 64)])
+@pytest.mark.parametrize("tiles", [1, 7, 8, 9, 11, 23])
+def test_tile_counts_on_either_side_of_eight(tiles, tile, edge):
+    """Workgroups are dealt out over eight XCDs: every tile is taken once whatever the remainder."""
+    run_case(edge * tiles - 8, 40, 64, 0, 1, 1, tile, seed=50 + tiles)
+    run_case(edge + 8, edge * tiles, 64, 0, 0, 0, tile, seed=60 + tiles)
+
+
 def test_library_choice_at_the_benchmark_shapes():
     """tile = 0 at output shapes of the benchmark workloads, one per branch of the tile choice
     (256x256; 128x128 four-stage; 128x256 / 256x128; 128x128 two-stage; 64x64 four-stage; 64x64),
