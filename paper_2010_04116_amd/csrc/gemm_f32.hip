@@ -54,9 +54,8 @@ __device__ inline float load_f32(Rsrc r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
-struct GemmBatch {
+struct GemmBatch {  // the prepared problems of one call
   int count;
-  int tile_end[kMaxBatch];  // exclusive prefix of tile counts
   GemmArgs p[kMaxBatch];
 };
 
@@ -214,8 +213,8 @@ struct Shape {
   static constexpr int STAGE = (BM + BN) * BK * 6, PITCH = BN + 8;
   static constexpr int RING = 2 * STAGE, SUMS = KG * BM * PITCH * 4, LDS = RING > SUMS ? RING : SUMS;
 };
-template <int BM, int BN, bool AKM, bool BKM, int LB>
-__global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_f32_kernel(GemmBatch batch) {
+template <int BM, int BN, bool AKM, bool BKM, int LB, int MAX>
+__global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_f32_kernel(Problems<MAX> batch) {
   typedef Shape<BM, BN> S;
   constexpr int WM = S::WM, WN = S::WN, KG = S::KG, SL = S::SL, BK = S::BK;
   typedef Tile<BM, AKM, BK, LB> TA;
@@ -225,16 +224,11 @@ __global__ __launch_bounds__(256 + NL) __attribute__((amdgpu_waves_per_eu(3, 3))
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-  int prob = 0, tile0 = 0;
-  for (int i = 0; i < batch.count - 1; ++i)
-    if ((int)blockIdx.x >= batch.tile_end[i]) { prob = i + 1; tile0 = batch.tile_end[i]; }
-  GemmArgs g = batch.p[prob];
+  int tile0;
+  GemmArgs g = my_problem(batch, tile0);
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  int kb0, ke;
-  const int pid = my_tile(g, blockIdx.x - tile0, tiles_m * tiles_n, kb0, ke);
-  constexpr int GM = 8;
-  const int per_group = GM * tiles_n, first_m = pid / per_group * GM, gsize = min(tiles_m - first_m, GM);
-  const int m0 = (first_m + (pid % per_group) % gsize) * BM, n0 = ((pid % per_group) / gsize) * BN;
+  const MyTile mt = my_tile(g, blockIdx.x - tile0, tiles_m, tiles_n);
+  const int m0 = mt.m * BM, n0 = mt.n * BN, kb0 = mt.k0, ke = mt.k1;
   const int nk = (ke - kb0 + BK - 1) / BK;
 
   float *sums = reinterpret_cast<float *>(smem);
@@ -426,10 +420,13 @@ long tiles_of(const GemmArgs &g) {
 }
 template <int BM, int BN, bool AKM, bool BKM, int LB>
 hipError_t launch(GemmBatch &b, hipStream_t s) {
-  int tiles = 0;
-  for (int i = 0; i < b.count; ++i) b.tile_end[i] = tiles += (int)tiles_of<BM, BN>(b.p[i]);
-  hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, AKM, BKM, LB>), dim3(tiles), dim3(256 + NL), 0, s, b);
-  return hipGetLastError();
+  return with_problems<AKM && BKM>(
+      b.p, b.count, [](const GemmArgs &g) { return (int)tiles_of<BM, BN>(g); },
+      [&](const auto &problems, int tiles) {
+        hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, AKM, BKM, LB, std::decay_t<decltype(problems)>::kRoom>), dim3(tiles), dim3(256 + NL),
+                           0, s, problems);
+        return hipGetLastError();
+      });
 }
 
 template <bool AKM, bool BKM>

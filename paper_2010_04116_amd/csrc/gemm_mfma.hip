@@ -434,9 +434,9 @@ __device__ inline void static_for(F &&f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// The prepared problems of one call, as the launchers take them.
 struct GemmBatch {
   int count;
-  int tile_end[kMaxBatch];  // exclusive prefix of tile counts
   GemmArgs p[kMaxBatch];
 };
 
@@ -448,8 +448,8 @@ struct GemmBatch {
 // arrangement when many small workgroups share a CU and cover for each other).
 // The multiply loop is hand-pipelined where it has the wavefront's LDS queue to itself.
 constexpr int kLoaderWaves = 4;
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS>
-__global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) void gemm_dma_kernel(GemmBatch batch) {
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS, int MAX>
+__global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) void gemm_dma_kernel(Problems<MAX> batch) {
   constexpr int NC = 64 * WGM * WGN;                // multiplying threads
   constexpr int NL = LOADERS ? 64 * kLoaderWaves : NC;  // threads that share the loading of one tile
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -462,20 +462,11 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  // which problem of the batch this workgroup belongs to (uniform)
-  int prob = 0, tile0 = 0;
-  for (int i = 0; i < batch.count - 1; ++i)
-    if ((int)blockIdx.x >= batch.tile_end[i]) { prob = i + 1; tile0 = batch.tile_end[i]; }
-  GemmArgs g = batch.p[prob];
+  int tile0;
+  GemmArgs g = my_problem(batch, tile0);
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  int kb0, ke;
-  int pid = my_tile(g, blockIdx.x - tile0, tiles_m * tiles_n, kb0, ke);
-  constexpr int GM = 8;
-  const int per_group = GM * tiles_n;
-  const int group = pid / per_group, first_m = group * GM;
-  const int gsize = min(tiles_m - first_m, GM);
-  const int tm = first_m + (pid % per_group) % gsize, tn = (pid % per_group) / gsize;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const MyTile mt = my_tile(g, blockIdx.x - tile0, tiles_m, tiles_n);
+  const int m0 = mt.m * BM, n0 = mt.n * BN, kb0 = mt.k0, ke = mt.k1;
 
   const BufRsrc ra = make_rsrc(g.A, g.a_bytes), rb = make_rsrc(g.B, g.b_bytes);
   typedef DmaTile<BM, AKM, NL> TA;
@@ -632,8 +623,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
     asm volatile("" ::: "memory");         \
     __builtin_amdgcn_sched_barrier(0);     \
   } while (0)
-template <bool AKM, bool BKM, int EPI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pair_kernel(GemmBatch batch) {
+template <bool AKM, bool BKM, int EPI, int MAX>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pair_kernel(Problems<MAX> batch) {
   constexpr int HB = 128 * 64 * 2;  // bytes of half an operand tile
   __shared__ __attribute__((aligned(1024))) char smem[8 * HB];
   const int t = threadIdx.x, lane = t & 63;
@@ -642,21 +633,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   typedef DmaTile<128, BKM, 512> TB;
   static_assert(TA::NLD == 2 && TB::NLD == 2, "the load counts below");
 
-  int prob = 0, tile0 = 0;
-  for (int i = 0; i < batch.count - 1; ++i)
-    if ((int)blockIdx.x >= batch.tile_end[i]) { prob = i + 1; tile0 = batch.tile_end[i]; }
-  GemmArgs g = batch.p[prob];
+  int tile0;
+  GemmArgs g = my_problem(batch, tile0);
   // The tile's two halves are 128 rows each: consecutive, or (EPI_GELU_BWD_SUM of two streams stacked over
   // M / 2 tokens) the same tokens of either stream.
   const int half = EPI == EPI_GELU_BWD_SUM && g.streams == 2 ? g.M >> 1 : 0;
   const int tiles_m = half ? (half + 127) / 128 : (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
-  int kb0, ke;
-  int pid = my_tile(g, blockIdx.x - tile0, tiles_m * tiles_n, kb0, ke);
-  constexpr int GM = 8;
-  const int per_group = GM * tiles_n;
-  const int group = pid / per_group, first_m = group * GM;
-  const int gsize = min(tiles_m - first_m, GM);
-  const int tm = first_m + (pid % per_group) % gsize, n0 = ((pid % per_group) / gsize) * 256;
+  const MyTile mt = my_tile(g, blockIdx.x - tile0, tiles_m, tiles_n);
+  const int tm = mt.m, n0 = mt.n * 256, kb0 = mt.k0, ke = mt.k1;
   const int m0 = tm * (half ? 128 : 256), m1 = half ? half + m0 : m0 + 128;
   const int limit0 = half ? half : g.M;
   const int nk = (ke - kb0 + 63) / 64;
@@ -770,40 +754,40 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 thread_local const KernelTimer *tl_timer = nullptr;  // armed by gemm_time_next()
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS>
-hipError_t launch_dma(GemmBatch &b, hipStream_t s) {
-  int tiles = 0;
-  for (int i = 0; i < b.count; ++i) {
-    tiles += ((b.p[i].M + BM - 1) / BM) * ((b.p[i].N + BN - 1) / BN) * std::max(b.p[i].splits, 1);
-    b.tile_end[i] = tiles;
-  }
-  constexpr int nthreads = 64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0));
+// The launch, with the armed timer's events on it if there is one.
+template <typename P>
+hipError_t launch_one(void (*kernel)(P), const P &problems, int workgroups, int threads, hipStream_t s) {
   if (const KernelTimer *t = tl_timer) {
     tl_timer = nullptr;
-    hipExtLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
-                          dim3(nthreads), 0, s, t->start, t->stop, 0, b);
+    hipExtLaunchKernelGGL(kernel, dim3(workgroups), dim3(threads), 0, s, t->start, t->stop, 0, problems);
   } else {
-    hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS>), dim3(tiles),
-                       dim3(nthreads), 0, s, b);
+    hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(threads), 0, s, problems);
   }
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int EPI, bool LOADERS>
+hipError_t launch_dma(GemmBatch &b, hipStream_t s) {
+  return with_problems<AKM && BKM>(
+      b.p, b.count,
+      [](const GemmArgs &g) { return ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * std::max(g.splits, 1); },
+      [&](const auto &problems, int tiles) {
+        return launch_one(gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS, std::decay_t<decltype(problems)>::kRoom>, problems,
+                          tiles, 64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0)), s);
+      });
+}
+
 template <bool AKM, bool BKM, int EPI>
 hipError_t launch_pair(GemmBatch &b, hipStream_t s) {
-  int tiles = 0;
-  for (int i = 0; i < b.count; ++i) {
-    const int rows = EPI == EPI_GELU_BWD_SUM && b.p[i].streams == 2 ? (b.p[i].M / 2 + 127) / 128 : (b.p[i].M + 255) / 256;
-    tiles += rows * ((b.p[i].N + 255) / 256) * std::max(b.p[i].splits, 1);
-    b.tile_end[i] = tiles;
-  }
-  if (const KernelTimer *t = tl_timer) {
-    tl_timer = nullptr;
-    hipExtLaunchKernelGGL((gemm_pair_kernel<AKM, BKM, EPI>), dim3(tiles), dim3(512), 0, s, t->start, t->stop, 0, b);
-  } else {
-    hipLaunchKernelGGL((gemm_pair_kernel<AKM, BKM, EPI>), dim3(tiles), dim3(512), 0, s, b);
-  }
-  return hipGetLastError();
+  return with_problems<AKM && BKM>(
+      b.p, b.count,
+      [](const GemmArgs &g) {
+        const int rows = EPI == EPI_GELU_BWD_SUM && g.streams == 2 ? (g.M / 2 + 127) / 128 : (g.M + 255) / 256;
+        return rows * ((g.N + 255) / 256) * std::max(g.splits, 1);
+      },
+      [&](const auto &problems, int tiles) {
+        return launch_one(gemm_pair_kernel<AKM, BKM, EPI, std::decay_t<decltype(problems)>::kRoom>, problems, tiles, 512, s);
+      });
 }
 
 template <bool AKM, bool BKM, int EPI>
