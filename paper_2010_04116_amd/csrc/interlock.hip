@@ -454,15 +454,19 @@ int linear_dgrad(il_ctx *c, const void *dy, size_t w_off, int M, int Kin, int No
 }
 
 // The context's second stream (non-blocking, default priority) and the events that tie it to the
-// caller's stream; created on first use.
+// caller's stream; created on first use.  The events order two streams of one device and nobody else looks at them,
+// so they leave out the write-back to the host that a recorded event makes (a record 4.6 -> 3.5 us of its stream's time;
+// steps 0.3 % faster at d = 1024, 1.2 % at 512, 0.7 to 2.3 % below); what the caller reads on the host is written back where the
+// caller waits for its own stream.
+constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 int ensure_side(il_ctx *c) {
   if (c->side) return IL_OK;
   IL_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-  IL_TRY(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
+  IL_TRY(hipEventCreateWithFlags(&c->ev_fork, kEventFlags));
   c->ev_head.assign(c->K + 1, nullptr);
-  for (int j = 1; j <= c->K; ++j) IL_TRY(hipEventCreateWithFlags(&c->ev_head[j], hipEventDisableTiming));
-  IL_TRY(hipEventCreateWithFlags(&c->ev_ready, hipEventDisableTiming));
-  for (int p = 0; p < 2; ++p) IL_TRY(hipEventCreateWithFlags(&c->ev_tail[p], hipEventDisableTiming));
+  for (int j = 1; j <= c->K; ++j) IL_TRY(hipEventCreateWithFlags(&c->ev_head[j], kEventFlags));
+  IL_TRY(hipEventCreateWithFlags(&c->ev_ready, kEventFlags));
+  for (int p = 0; p < 2; ++p) IL_TRY(hipEventCreateWithFlags(&c->ev_tail[p], kEventFlags));
   return IL_OK;
 }
 
