@@ -3,10 +3,11 @@
 // LDS (bf16 inputs are widened on the way in), fp32 softmax; nothing is rounded below the inputs' and
 // outputs' own type.
 //
-// A wavefront owns 16 queries (forward, dQ) or 16 keys (dK, dV), a workgroup four such neighbours, which
-// share tiles of the other axis in LDS: a T = 256, 64-head problem then is one wavefront per SIMD, and
-// the longest one 16 k matrix cycles.  (One thread per row, as this file's predecessor had it, left most
-// lanes' loads serial: forward + backward of a block took 1.5 ms at 8 x 256 tokens, 8 heads of 64.)
+// A wavefront owns 16 queries (forward, dQ) or 16 keys (dK, dV).  Where there are enough of them a workgroup is four
+// such neighbours, which share tiles of the other axis in LDS: a T = 256, 64-head problem then is one wavefront per
+// SIMD, and the longest one 16 k matrix cycles.  In small grids it is four or eight wavefronts that share 16 queries
+// (keys) and divide up the other axis (the second half of this file).  (One thread per row, as this file's predecessor
+// had it, left most lanes' loads serial: forward + backward of a block took 1.5 ms at 8 x 256 tokens, 8 heads of 64.)
 //
 // Layout of a product: lane l holds matrix row (A) or column (B) l & 15 and k = l >> 4; of the result
 // column l & 15, rows 4 (l >> 4) + 0..3.  Scores are computed with the streamed axis as rows, so a lane
@@ -20,6 +21,8 @@
 // not finite reaches columns it is masked for (0 x NaN).  A wavefront whose sums come out other than finite
 // therefore adds them up again pair by pair, over the visible pairs only: nothing in the loop pays for it (a
 // check of that block's operands cost 5 % at widths up to 64 and 25 % at 128, by its registers).
+#include <type_traits>
+
 #include "common.h"
 
 namespace il {
@@ -387,16 +390,395 @@ __global__ __launch_bounds__(256) void attn_dkv_f32(const T *__restrict__ qkv, c
   }
 }
 
+// ---- the same with a workgroup's wavefronts on different parts of the streamed axis ------------------------------
+// A wavefront's chain over a long row is what a small grid waits for.  Here a workgroup owns 16 queries (keys), its W wavefronts take
+// every W-th 16-row block of the streamed axis each, straight from memory - no row is read by two of them - and add up
+// what they have through LDS.
+
+// N consecutive elements as fp32, zero where the row does not exist
+template <int N, typename T>
+__device__ inline void get_row(float (&v)[N], const T *p, bool in) {
+  if constexpr (N >= 4) {
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+      const f4 x = in ? get4(p + 4 * i) : f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * i + e] = x[e];
+    }
+  } else if constexpr (N == 2) {
+    if constexpr (sizeof(T) == 4) {
+      const float2 x = in ? *reinterpret_cast<const float2 *>(p) : make_float2(0.f, 0.f);
+      v[0] = x.x;
+      v[1] = x.y;
+    } else {
+      const uint32_t x = in ? *reinterpret_cast<const uint32_t *>(p) : 0;
+      v[0] = bf16_to_f32((bf16_t)(x & 0xFFFF));
+      v[1] = bf16_to_f32((bf16_t)(x >> 16));
+    }
+  } else {
+    v[0] = in ? ld<T>(p) : 0.f;
+  }
+}
+template <int N, typename T>
+__device__ inline void put_row(T *p, const float (&v)[N]) {
+  if constexpr (N >= 4) {
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) put4(p + 4 * i, f4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]});
+  } else if constexpr (N == 2) {
+    if constexpr (sizeof(T) == 4) *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    else *reinterpret_cast<uint32_t *>(p) = pack_bf16x2(v[0], v[1]);
+  } else {
+    st<T>(p, v[0]);
+  }
+}
+
+// A 16-row block of the streamed axis as A operand, rows [row0, row0 + 16) of X below `end`: with the rows as matrix rows
+// (ByRow: lane's row l & 15, columns 16 s + 4 (l >> 4) + 0..3) and with the columns as matrix rows (ByCol: the lane's rows are
+// 4 (l >> 4) + r, and matrix row i of tile dt is column i DH / 16 + dt, so that a lane reads DH / 16 neighbours).
+template <typename T, int DH>
+struct ByRow {
+  f4 v[DH / 16];
+  __device__ inline void load(const T *X, size_t ld, int row0, int end, int lane) {
+    const int r = row0 + (lane & 15);
+    load_own<T, DH>(v, X + (size_t)r * ld, r < end, lane);
+  }
+};
+template <typename T, int DH>
+struct ByCol {
+  float v[4][DH / 16];
+  __device__ inline void load(const T *X, size_t ld, int row0, int end, int lane) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = row0 + 4 * (lane >> 4) + r;
+      get_row(v[r], X + (size_t)row * ld + (lane & 15) * (DH / 16), row < end);
+    }
+  }
+};
+template <typename T, int DH>
+__device__ inline f4 scores(const ByRow<T, DH> &x, const f4 (&own)[DH / 16]) {
+  f4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e4 = 0; e4 < DH / 16; ++e4)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = mma(x.v[e4][e], own[e4][e], s);
+  return s;
+}
+template <typename T, int DH>
+__device__ inline void add_cols(f4 (&acc)[DH / 16], const ByCol<T, DH> &x, const f4 &w) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) acc[dt] = mma(x.v[r][dt], w[r], acc[dt]);
+}
+// A lane's sums are columns (4 (l >> 4) + e) DH / 16 + dt of its query (key): DH / 4 neighbours from DH / 4 (l >> 4) on.
+template <typename T, int DH>
+__device__ inline void add_row_cols(f4 (&acc)[DH / 16], float w, const T *X, int lane) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float x[DH / 16];
+    get_row(x, X + (4 * (lane >> 4) + e) * (DH / 16), true);
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) acc[dt][e] += x[dt] * w;
+  }
+}
+// The wavefronts' sums meet in LDS: after park() and a barrier, thread t < 256 of the workgroup takes columns
+// (t & 15) DH / 16 + 0.. of row t >> 4 from each.
+template <int DH, int W>
+struct Meet {
+  static constexpr int P = DH + 4;
+  float sum[W][16][P];
+  __device__ inline void park(const f4 (&acc)[DH / 16], int wave, int lane) {
+    float *p = sum[wave][lane & 15] + (lane >> 4) * (DH / 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int dt = 0; dt < DH / 16; ++dt) p[e * (DH / 16) + dt] = acc[dt][e];
+  }
+  __device__ inline void take(float (&v)[DH / 16], const float (&weight)[W], int t) const {
+#pragma unroll
+    for (int i = 0; i < DH / 16; ++i) v[i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+#pragma unroll
+      for (int i = 0; i < DH / 16; ++i) v[i] = fmaf(sum[w][t >> 4][(t & 15) * (DH / 16) + i], weight[w], v[i]);
+  }
+};
+
+// grid (ceil(T/16), B*H); the longest rows start first
+template <typename T, int DH, int W>
+__global__ __launch_bounds__(64 * W) void attn_fwd_split_f32(const T *__restrict__ qkv, int Tn, int H, T *__restrict__ o,
+                                                             float *__restrict__ lse) {
+  __shared__ __attribute__((aligned(16))) Meet<DH, W> meet;
+  __shared__ float ms[W][16], ls[W][16];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), kk = lane >> 4;
+  const int b = blockIdx.y / H, h = blockIdx.y % H, d = H * DH;
+  const size_t ld = 3 * (size_t)d;
+  const T *base = qkv + (size_t)b * Tn * ld + h * DH;
+  const int last = gridDim.x - 1 - blockIdx.x, q0 = 16 * last, q = q0 + (lane & 15);  // key blocks 0 .. last
+  f4 qf[DH / 16], acc[DH / 16];
+  load_own<T, DH>(qf, base + (size_t)q * ld, q < Tn, lane);
+  zero<DH>(acc);
+  float m = -INFINITY, l = 0.f;
+  const float sc = rsqrtf((float)DH) * kLog2e;
+  ByRow<T, DH> kf;  // (a block's rows are requested while the block before it is summed up, its columns ahead of its scores)
+  if (wave <= last) kf.load(base + d, ld, 16 * wave, Tn, lane);
+  for (int a = wave; a <= last; a += W) {
+    ByCol<T, DH> vf;
+    vf.load(base + 2 * d, ld, 16 * a, Tn, lane);
+    f4 s = scores<T, DH>(kf, qf);
+    if (a + W <= last) kf.load(base + d, ld, 16 * (a + W), Tn, lane);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int kv = 16 * a + 4 * kk + r;
+      s[r] = kv > q || kv >= Tn ? -INFINITY : s[r] * sc;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m, mx), at = base_of(mn), alpha = __builtin_amdgcn_exp2f(m - at);
+    m = mn;
+    l *= alpha;
+#pragma unroll
+    for (int i = 0; i < DH / 16; ++i) acc[i] *= alpha;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(s[r] - at);
+      l += s[r];
+    }
+    add_cols<T, DH>(acc, vf, s);
+  }
+  if (!all_finite<DH>(acc)) {
+    zero<DH>(acc);
+    for (int a = wave; a <= last; a += W)
+      for (int u = 16 * a; u < min(Tn, 16 * a + 16); ++u) {
+        const T *row = base + u * ld;
+        const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(qf, row + d, lane) * sc - base_of(m));
+        if (u <= q) add_row_cols<T, DH>(acc, p, row + 2 * d, lane);
+      }
+  }
+  l = sum_groups(l);
+  meet.park(acc, wave, lane);
+  if (kk == 0) {
+    ms[wave][lane] = m;
+    ls[wave][lane] = l;
+  }
+  __syncthreads();
+  if (t < 256) {
+    const int qi = t >> 4;
+    float mm = -INFINITY, ll = 0.f, w[W], v[DH / 16];
+#pragma unroll
+    for (int i = 0; i < W; ++i) mm = fmaxf(mm, ms[i][qi]);
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      w[i] = __builtin_amdgcn_exp2f(ms[i][qi] - base_of(mm));
+      ll = fmaf(ls[i][qi], w[i], ll);
+    }
+    const float inv = 1.f / ll;
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] *= inv;
+    meet.take(v, w, t);
+    if (q0 + qi < Tn) {
+      put_row(o + ((size_t)b * Tn + q0 + qi) * d + h * DH + (t & 15) * (DH / 16), v);
+      if ((t & 15) == 0) lse[((size_t)b * H + h) * Tn + q0 + qi] = (mm + log2f(ll)) * kLn2;
+    }
+  }
+}
+
+// dQ and dsum; grid (ceil(T/16), B*H, streams)
+template <typename T, int DH, int W>
+__global__ __launch_bounds__(64 * W) void attn_dq_split_f32(const T *__restrict__ qkv, const T *__restrict__ o,
+                                                            const T *__restrict__ d_o, const float *__restrict__ lse,
+                                                            int Tn, int H, int B, T *__restrict__ dqkv,
+                                                            float *__restrict__ dsum) {
+  __shared__ __attribute__((aligned(16))) Meet<DH, W> meet;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), kk = lane >> 4;
+  const int b = blockIdx.y / H, h = blockIdx.y % H, d = H * DH, sidx = blockIdx.z;
+  const size_t ld = 3 * (size_t)d, N = (size_t)B * Tn;
+  const T *base = qkv + (size_t)b * Tn * ld + h * DH;
+  const int last = gridDim.x - 1 - blockIdx.x, q0 = 16 * last, q = q0 + (lane & 15);
+  const size_t tok = (size_t)b * Tn + q;
+  f4 qf[DH / 16], gf[DH / 16], dq[DH / 16];
+  load_own<T, DH>(qf, base + (size_t)q * ld, q < Tn, lane);
+  load_own<T, DH>(gf, d_o + (sidx * N + tok) * d + h * DH, q < Tn, lane);
+  load_own<T, DH>(dq, o + tok * d + h * DH, q < Tn, lane);
+  float D = 0.f;
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) D = fmaf(gf[s][e], dq[s][e], D);
+  D = sum_groups(D);
+  if (q < Tn && lane < 16 && wave == 0) dsum[(sidx * (size_t)B * H + blockIdx.y) * Tn + q] = D;
+  zero<DH>(dq);
+  const float sc = rsqrtf((float)DH), sc2 = sc * kLog2e;
+  const float L2 = q < Tn ? lse[((size_t)b * H + h) * Tn + q] * kLog2e : 0.f;
+  ByRow<T, DH> kf, vf;
+  auto rows = [&](int a) {
+    kf.load(base + d, ld, 16 * a, Tn, lane);
+    vf.load(base + 2 * d, ld, 16 * a, Tn, lane);
+  };
+  if (wave <= last) rows(wave);
+  for (int a = wave; a <= last; a += W) {
+    ByCol<T, DH> kc;
+    kc.load(base + d, ld, 16 * a, Tn, lane);
+    f4 s = scores<T, DH>(kf, qf);
+    const f4 dp = scores<T, DH>(vf, gf);
+    if (a + W <= last) rows(a + W);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int kv = 16 * a + 4 * kk + r;
+      const float ds = __builtin_amdgcn_exp2f(s[r] * sc2 - L2) * (dp[r] - D);
+      s[r] = kv > q || kv >= Tn ? 0.f : ds;
+    }
+    add_cols<T, DH>(dq, kc, s);
+  }
+  if (!all_finite<DH>(dq)) {
+    zero<DH>(dq);
+    for (int a = wave; a <= last; a += W)
+      for (int u = 16 * a; u < min(Tn, 16 * a + 16); ++u) {
+        const T *row = base + u * ld;
+        const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(qf, row + d, lane) * sc2 - L2);
+        const float ds = p * (dot_row<T, DH>(gf, row + 2 * d, lane) - D);
+        if (u <= q) add_row_cols<T, DH>(dq, ds, row + d, lane);
+      }
+  }
+  meet.park(dq, wave, lane);
+  __syncthreads();
+  if (t < 256 && q0 + (t >> 4) < Tn) {
+    float w[W], v[DH / 16];
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = sc;
+    meet.take(v, w, t);
+    put_row(dqkv + (sidx * N + (size_t)b * Tn + q0 + (t >> 4)) * ld + h * DH + (t & 15) * (DH / 16), v);
+  }
+}
+
+// dK, dV; grid (ceil(T/16), B*H, streams); the first keys have the most queries
+template <typename T, int DH, int W>
+__global__ __launch_bounds__(64 * W) void attn_dkv_split_f32(const T *__restrict__ qkv, const T *__restrict__ d_o,
+                                                             const float *__restrict__ lse, const float *__restrict__ dsum,
+                                                             int Tn, int H, int B, T *__restrict__ dqkv) {
+  __shared__ __attribute__((aligned(16))) Meet<DH, W> meet;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), kk = lane >> 4;
+  const int b = blockIdx.y / H, h = blockIdx.y % H, d = H * DH, sidx = blockIdx.z;
+  const size_t ld = 3 * (size_t)d, N = (size_t)B * Tn;
+  const T *base = qkv + (size_t)b * Tn * ld + h * DH, *gbase = d_o + (sidx * N + (size_t)b * Tn) * d + h * DH;
+  const float *lrow = lse + ((size_t)b * H + h) * Tn, *drow = dsum + (sidx * (size_t)B * H + blockIdx.y) * Tn;
+  const int first = blockIdx.x, kv0 = 16 * first, kv = kv0 + (lane & 15), nb = (Tn + 15) / 16;  // query blocks first .. nb - 1
+  f4 kf[DH / 16], vf[DH / 16], dk[DH / 16], dv[DH / 16];
+  load_own<T, DH>(kf, base + (size_t)kv * ld + d, kv < Tn, lane);
+  load_own<T, DH>(vf, base + (size_t)kv * ld + 2 * d, kv < Tn, lane);
+  zero<DH>(dk);
+  zero<DH>(dv);
+  const float sc = rsqrtf((float)DH), sc2 = sc * kLog2e;
+  ByRow<T, DH> qf, gf;
+  auto rows = [&](int a) {
+    qf.load(base, ld, 16 * a, Tn, lane);
+    gf.load(gbase, (size_t)d, 16 * a, Tn, lane);
+  };
+  if (first + wave < nb) rows(first + wave);
+  for (int a = first + wave; a < nb; a += W) {
+    ByCol<T, DH> qc, gc;
+    float l4[4], d4[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = 16 * a + 4 * kk + r;
+      l4[r] = q < Tn ? lrow[q] * kLog2e : 0.f;
+      d4[r] = q < Tn ? drow[q] : 0.f;
+    }
+    qc.load(base, ld, 16 * a, Tn, lane);
+    gc.load(gbase, (size_t)d, 16 * a, Tn, lane);
+    f4 s = scores<T, DH>(qf, kf), dp = scores<T, DH>(gf, vf);
+    if (a + W < nb) rows(a + W);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = 16 * a + 4 * kk + r;
+      const bool seen = kv <= q && q < Tn;
+      const float p = seen ? __builtin_amdgcn_exp2f(s[r] * sc2 - l4[r]) : 0.f;
+      dp[r] = seen ? p * (dp[r] - d4[r]) : 0.f;
+      s[r] = p;
+    }
+    add_cols<T, DH>(dv, gc, s);
+    add_cols<T, DH>(dk, qc, dp);
+  }
+  if (!all_finite<DH>(dv) || !all_finite<DH>(dk)) {
+    zero<DH>(dv);
+    zero<DH>(dk);
+    for (int a = first + wave; a < nb; a += W)
+      for (int u = 16 * a; u < min(Tn, 16 * a + 16); ++u) {
+        const T *qr = base + u * ld, *gr = gbase + (size_t)u * d;
+        const float p = __builtin_amdgcn_exp2f(dot_row<T, DH>(kf, qr, lane) * sc2 - lrow[u] * kLog2e);
+        const float ds = p * (dot_row<T, DH>(vf, gr, lane) - drow[u]);
+        if (u < kv) continue;
+        add_row_cols<T, DH>(dv, p, gr, lane);
+        add_row_cols<T, DH>(dk, ds, qr, lane);
+      }
+  }
+  float w[W], v[DH / 16];
+  T *out = dqkv + (sidx * N + (size_t)b * Tn + kv0 + (t >> 4)) * ld + d + h * DH + (t & 15) * (DH / 16);
+  const bool mine = t < 256 && kv0 + (t >> 4) < Tn;
+  meet.park(dk, wave, lane);
+  __syncthreads();
+  if (mine) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = sc;
+    meet.take(v, w, t);
+    put_row(out, v);
+  }
+  __syncthreads();
+  meet.park(dv, wave, lane);
+  __syncthreads();
+  if (mine) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = 1.f;
+    meet.take(v, w, t);
+    put_row(out + d, v);
+  }
+}
+
+// Which form: by the workgroups of 64 rows that there would be.  Up to about half the CUs' number of them the chain of the
+// longest wavefront is what a launch waits for; beyond, a tile that four wavefronts share costs less than each
+// reading its own.  Forward / backward, us, of 64 rows and split: 1 x 896 tokens, a head of 128, two streams 93 / 270 and 27 / 100;
+// 4 x 1024, two of 128 (128 workgroups) 110 / 310 and 60 / 229; 2 x 640, four of 64, two streams (160) 35 / 112 and 18 / 87; but 8 x 256, eight of 64 (256) 18 / 56
+// and 20 / 78, 8 x 512, sixteen of 64 (1024) 94 / 290 and 107 / 446.  A single tile of 64 rows has no chain to cut:
+// 4 x 64, sixteen of 32, two streams (128) 12.1 and 12.7.
+bool split_rows(long workgroups, int Tn) { return workgroups <= (Tn <= 64 ? 64 : 160); }
+// Eight wavefronts for long rows of narrow heads, whose blocks take less time than their loads: backward of 2 x 1000 tokens, four heads
+// of 16, 71 -> 62 us with four and 45 with eight; 1 x 576, seven of 32, forward 25 -> 10 -> 7.9.  (At 64 and 128 four are as fast or faster.)
+template <int DH, typename F>
+void with_waves(int Tn, F &&f) {
+  if constexpr (DH <= 32) {
+    if (Tn >= 512) return f(std::integral_constant<int, 8>{});
+  }
+  f(std::integral_constant<int, 4>{});
+}
+
 template <typename T, int DH>
 hipError_t fwd_t(const void *qkv, int B, int Tn, int H, void *o, float *lse, hipStream_t s) {
-  hipLaunchKernelGGL((attn_fwd_f32<T, DH>), dim3((Tn + kOwn - 1) / kOwn, B * H), dim3(256), 0, s, (const T *)qkv, Tn, H,
-                     (T *)o, lse);
+  const dim3 grid((Tn + kOwn - 1) / kOwn, B * H), split((Tn + 15) / 16, B * H);
+  if (split_rows((long)grid.x * grid.y, Tn))
+    with_waves<DH>(Tn, [&](auto w) {
+      constexpr int W = decltype(w)::value;
+      hipLaunchKernelGGL((attn_fwd_split_f32<T, DH, W>), split, dim3(64 * W), 0, s, (const T *)qkv, Tn, H, (T *)o, lse);
+    });
+  else
+    hipLaunchKernelGGL((attn_fwd_f32<T, DH>), grid, dim3(256), 0, s, (const T *)qkv, Tn, H, (T *)o, lse);
   return hipGetLastError();
 }
 template <typename T, int DH>
 hipError_t bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, int ns, int B, int Tn, int H,
                  void *dqkv, float *dsum, hipStream_t s) {
-  const dim3 grid((Tn + kOwn - 1) / kOwn, B * H, ns);
+  const dim3 grid((Tn + kOwn - 1) / kOwn, B * H, ns), split((Tn + 15) / 16, B * H, ns);
+  if (split_rows((long)grid.x * grid.y * ns, Tn)) {
+    with_waves<DH>(Tn, [&](auto w) {
+      constexpr int W = decltype(w)::value;
+      hipLaunchKernelGGL((attn_dq_split_f32<T, DH, W>), split, dim3(64 * W), 0, s, (const T *)qkv, (const T *)o, (const T *)d_o,
+                         lse, Tn, H, B, (T *)dqkv, dsum);
+      hipLaunchKernelGGL((attn_dkv_split_f32<T, DH, W>), split, dim3(64 * W), 0, s, (const T *)qkv, (const T *)d_o, lse, dsum,
+                         Tn, H, B, (T *)dqkv);
+    });
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((attn_dq_f32<T, DH>), grid, dim3(256), 0, s, (const T *)qkv, (const T *)o, (const T *)d_o, lse, Tn,
                      H, B, (T *)dqkv, dsum);
   hipLaunchKernelGGL((attn_dkv_f32<T, DH>), grid, dim3(256), 0, s, (const T *)qkv, (const T *)d_o, lse, dsum, Tn, H, B,

@@ -115,6 +115,37 @@ def test_what_is_not_finite_stays_with_the_rows_that_see_it(dtype, dh, T, token,
 
 
 @pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("B,T", [(1, 15), (1, 16), (3, 33), (64, 64), (65, 64), (53, 150), (54, 150), (1, 511), (1, 512), (1, 530)])
+def test_either_form_of_the_fp32_products(dtype, dh, B, T):
+    """Both sides of the number of workgroups from which tiles are shared, and of the length from which narrow heads take
+    eight wavefronts; the same bounds as above."""
+    qkv, g = draw(B + T, B, T, 1, dh)
+    print("case", dtype, dh, B, T, flush=True)
+    o, dqkv = run(dtype, qkv, g, B, T, 1, dh)
+    wo, wd = reference(qkv, g, B, T, 1, dh, stored_o=o)
+    held(o, wo, dtype, "o")
+    held(dqkv, wd, dtype, "dqkv")
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("part,value", [("q", np.nan), ("k", np.nan), ("v", np.inf), ("g", -np.inf)])
+def test_what_is_not_finite_where_tiles_are_shared(dtype, dh, part, value):
+    B, T, H, token = 81, 90, 1, 64 * 90 + 31
+    qkv, g = draw(7, B, T, H, dh)
+    if part == "g":
+        g[token, 3] = value
+    else:
+        qkv[token, {"q": 0, "k": dh, "v": 2 * dh}[part] + 3] = value
+    print("case", dtype, dh, part, value, flush=True)
+    o, dqkv = run(dtype, qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh)
+    held(o, wo, dtype, "o")
+    assert np.array_equal(np.isfinite(dqkv), np.isfinite(wd))
+    if dtype == "f32":
+        held(np.where(np.isfinite(dqkv), dqkv, 0), np.where(np.isfinite(wd), wd, 0), dtype, "dqkv")
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
 @pytest.mark.parametrize("low", [-1e31, -1e37, -np.inf])
 def test_scores_below_any_mask_value(dtype, dh, low):
     """The first tokens' scores are all equal and lie far below -1e30; a later block's are -inf for every other key.
