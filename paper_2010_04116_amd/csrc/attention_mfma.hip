@@ -716,7 +716,419 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 128 ? 
     walk(std::integral_constant<int, NS>{});
 }
 
+// ------------------------------------------------------------------ small grids ---------
+// With few batches and heads a launch waits for the chain of its longest workgroup, tile after tile behind a barrier.
+// Here a workgroup owns 32 queries (keys) and its W wavefronts take every W-th 32-row block of the other axis each, staged
+// in LDS of their own: no barrier until they add up what they have.  A block's last fragments are requested before
+// the next block's loads are issued (a read behind them in a wavefront's queue waits for their data).
+
+// Two 32 x DH tiles of one wavefront, two stages.
+template <int DH>
+struct Private {
+  static constexpr int KT = 32 * DH * 2, STAGE = 2 * KT, BYTES = kStages * STAGE;
+  typedef TokTile<32, DH, 64> Tile;
+};
+// What W wavefronts hold of a 32 x DH result meets in LDS: row = the lane's own query (key).
+template <int DH, int W>
+struct Meet {
+  static constexpr int P = DH + 4, PER = DH / (2 * W);  // columns a thread of the workgroup takes of one row
+  float *at;                                            // [W][32][P]
+  __device__ inline void park(const floatx16 (&acc)[DH / 32], int wave, int lane) const {
+    float *p = at + (wave * 32 + (lane & 31)) * P + 4 * (lane >> 5);
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4 *>(p + 32 * dt + 8 * g) =
+            make_float4(acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]);
+  }
+  __device__ static inline int row(int t) { return t / (2 * W); }
+  __device__ static inline int col(int t) { return t % (2 * W) * PER; }
+  __device__ inline void store(bf16_t *out, const float (&weight)[W], int t) const {  // out: the row's first column
+#pragma unroll
+    for (int c = 0; c < PER; c += 4) {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float4 x = *reinterpret_cast<const float4 *>(at + (w * 32 + row(t)) * P + col(t) + c);
+        v.x = __builtin_fmaf(x.x, weight[w], v.x);
+        v.y = __builtin_fmaf(x.y, weight[w], v.y);
+        v.z = __builtin_fmaf(x.z, weight[w], v.z);
+        v.w = __builtin_fmaf(x.w, weight[w], v.w);
+      }
+      *reinterpret_cast<uint2 *>(out + col(t) + c) = make_uint2(pack2(v.x, v.y), pack2(v.z, v.w));
+    }
+  }
+};
+template <int DH, int W>
+constexpr int split_lds() {
+  return W * Private<DH>::BYTES > W * 32 * (DH + 4) * 4 ? W * Private<DH>::BYTES : W * 32 * (DH + 4) * 4;
+}
+
+// grid (ceil(T / 32), B*H)
+template <int DH, int W>
+__global__ __launch_bounds__(64 * W) void attn_fwd_split(const bf16_t *__restrict__ qkv, int T, int H, bf16_t *__restrict__ o,
+                                                         float *__restrict__ lse) {
+  typedef Private<DH> L;
+  typedef typename L::Tile Tile;
+  __shared__ __attribute__((aligned(256))) char smem[split_lds<DH, W>()];
+  __shared__ float ms[W][32], ls[W][32];
+  const int t = threadIdx.x, lane = t & 63, hh = lane >> 5, lq = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const CausalTile ct = causal_tile();
+  const int qt = gridDim.x - 1 - ct.rank, b = ct.y / H, h = ct.y % H, d = H * DH;  // key blocks 0 .. qt
+  const size_t ld3 = 3 * (size_t)d;
+  const bf16_t *qbase = qkv + (size_t)b * T * ld3 + h * DH;
+  const int q = 32 * qt + lq;
+  char *const mine = smem + wave * L::BYTES;
+
+  const BufRsrc rs = make_rsrc(qbase, (size_t)T * ld3 * 2 - (size_t)h * DH * 2);
+  Tile lk, lv;
+  lk.init(d, (int)ld3, lane);
+  lv.init(2 * d, (int)ld3, lane);
+  auto issue = [&](int kt, int stage) {
+    lk.issue(rs, mine + stage * L::STAGE, 0, 32 * kt, T);
+    lv.issue(rs, mine + stage * L::STAGE + L::KT, 0, 32 * kt, T);
+  };
+  if (wave <= qt) issue(wave, 0);
+  Frag qf[DH / 16];
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks)
+    qf[ks].q = (q < T) ? ldg16(qbase + (size_t)q * ld3 + 16 * ks + 8 * hh) : make_uint4(0, 0, 0, 0);
+  floatx16 oacc[DH / 32];
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i) oacc[i] = kZero16;
+  float m = kNegBig, l = 0.f;
+  const float sc = rsqrtf((float)DH) * kLog2e;
+
+  int stage = 0;
+  for (int kt = wave; kt <= qt; kt += W, stage ^= 1) {
+    const char *sk = mine + stage * L::STAGE, *sv = sk + L::KT;
+    wait_vmcnt<0>();
+    floatx16 s = kZero16;
+#pragma unroll
+    for (int ks = 0; ks < DH / 16; ++ks)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::rowfrag(sk, 0, ks, lane), qf[ks].v, s, 0, 0, 0);
+    bf16x8 vf[2][DH / 32];
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq)
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt) vf[bq][dt] = Tile::trfrag(sv, 16 * bq, dt, lane);
+    if (kt + W <= qt) issue(kt + W, stage ^ 1);
+    float mx = kNegBig;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (kt == qt) {  // (uniform)
+        const int kv = 32 * kt + 8 * (r >> 2) + 4 * hh + (r & 3);
+        s[r] = ((kv > q) | (kv >= T)) ? kNegBig : s[r];
+      }
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mnew = fmaxf(m, mx * sc), alpha = __builtin_amdgcn_exp2f(m - mnew);
+    float rsum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc, -mnew));
+      rsum += s[r];
+    }
+    l = l * alpha + rsum;
+    m = mnew;
+#pragma unroll
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq) {
+      Frag pf;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pf.u[e] = pack2(s[8 * bq + 2 * e], s[8 * bq + 2 * e + 1]);
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt)
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[bq][dt], pf.v, oacc[dt], 0, 0, 0);
+    }
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (hh == 0) {
+    ms[wave][lq] = m;
+    ls[wave][lq] = l;
+  }
+  __syncthreads();  // every wavefront is done with its tiles
+  const Meet<DH, W> meet{reinterpret_cast<float *>(smem)};
+  meet.park(oacc, wave, lane);
+  __syncthreads();
+  const int r = meet.row(t), qr = 32 * qt + r;
+  if (qr >= T) return;
+  float mm = kNegBig, ll = 0.f, w[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) mm = fmaxf(mm, ms[i][r]);
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    w[i] = __builtin_amdgcn_exp2f(ms[i][r] - mm);
+    ll = __builtin_fmaf(ls[i][r], w[i], ll);
+  }
+  const float inv = 1.f / ll;
+#pragma unroll
+  for (int i = 0; i < W; ++i) w[i] *= inv;
+  meet.store(o + ((size_t)b * T + qr) * d + h * DH, w, t);
+  if (meet.col(t) == 0) lse[((size_t)b * H + h) * T + qr] = mm + log2f(ll);
+}
+
+// The backward's roles in one launch, grid (ceil(T / 32), B*H, roles * streams): dK and dV first, then dQ.
+template <int DH, int W>
+__device__ __forceinline__ void split_dq(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+                                         const float *__restrict__ lse, const float *__restrict__ dsum, int B, int T, int H, int ns,
+                                         int sidx, bf16_t *__restrict__ dqkv, char *smem) {
+  typedef Private<DH> L;
+  typedef typename L::Tile Tile;
+  const int t = threadIdx.x, lane = t & 63, hh = lane >> 5, lq = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const CausalTile ct = causal_tile();
+  const int qt = gridDim.x - 1 - ct.rank, b = ct.y / H, h = ct.y % H, d = H * DH;
+  const size_t ld3 = 3 * (size_t)d, N = (size_t)B * T;
+  const bf16_t *qbase = qkv + (size_t)b * T * ld3 + h * DH;
+  const int q = 32 * qt + lq;
+  const size_t tok = (size_t)b * T + q;
+  char *const mine = smem + wave * L::BYTES;
+  const BufRsrc rs = make_rsrc(qbase, (size_t)T * ld3 * 2 - (size_t)h * DH * 2);
+  Tile lk, lv;
+  lk.init(d, (int)ld3, lane);
+  lv.init(2 * d, (int)ld3, lane);
+  auto issue = [&](int kt, int stage) {
+    lk.issue(rs, mine + stage * L::STAGE, 0, 32 * kt, T);
+    lv.issue(rs, mine + stage * L::STAGE + L::KT, 0, 32 * kt, T);
+  };
+  if (wave <= qt) issue(wave, 0);
+  Frag qf[DH / 16], gf[DH / 16];
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    qf[ks].q = q < T ? ldg16(qbase + (size_t)q * ld3 + 16 * ks + 8 * hh) : make_uint4(0, 0, 0, 0);
+    gf[ks].q = q < T ? ldg16(d_o + (sidx * N + tok) * d + h * DH + 16 * ks + 8 * hh) : make_uint4(0, 0, 0, 0);
+  }
+  const float sc = rsqrtf((float)DH), sc2 = sc * kLog2e;
+  const float l2 = (q < T) ? lse[((size_t)b * H + h) * T + q] : 0.f;
+  const float dsv = (q < T) ? dsum_of<DH>(dsum, ns * N, sidx * N + tok, h) : 0.f;
+  floatx16 dq[DH / 32];
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i) dq[i] = kZero16;
+  int stage = 0;
+  for (int kt = wave; kt <= qt; kt += W, stage ^= 1) {
+    const char *sk = mine + stage * L::STAGE, *sv = sk + L::KT;
+    wait_vmcnt<0>();
+    floatx16 s = kZero16, dp = kZero16;
+#pragma unroll
+    for (int ks = 0; ks < DH / 16; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::rowfrag(sk, 0, ks, lane), qf[ks].v, s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::rowfrag(sv, 0, ks, lane), gf[ks].v, dp, 0, 0, 0);
+    }
+    bf16x8 kc[2][DH / 32];
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq)
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt) kc[bq][dt] = Tile::trfrag(sk, 16 * bq, dt, lane);
+    if (kt + W <= qt) issue(kt + W, stage ^ 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc2, -l2));
+      if (kt == qt) {  // (uniform)
+        const int kv = 32 * kt + 8 * (r >> 2) + 4 * hh + (r & 3);
+        p = ((kv > q) | (kv >= T)) ? 0.f : p;
+      }
+      dp[r] = p * (dp[r] - dsv);  // dS^T, without the scale
+    }
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq) {
+      Frag pf;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pf.u[e] = pack2(dp[8 * bq + 2 * e], dp[8 * bq + 2 * e + 1]);
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt)
+        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc[bq][dt], pf.v, dq[dt], 0, 0, 0);
+    }
+  }
+  __syncthreads();
+  const Meet<DH, W> meet{reinterpret_cast<float *>(smem)};
+  meet.park(dq, wave, lane);
+  __syncthreads();
+  const int qr = 32 * qt + meet.row(t);
+  if (qr >= T) return;
+  float w[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) w[i] = sc;
+  meet.store(dqkv + (sidx * N + (size_t)b * T + qr) * ld3 + h * DH, w, t);
+}
+
+// WHAT as for attn_bwd_dkv_body: 0 = dK and dV, 1 = dV only, 2 = dK only.
+template <int DH, int W, int WHAT>
+__device__ __forceinline__ void split_dkv(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+                                          const float *__restrict__ lse, const float *__restrict__ dsum, int B, int T, int H, int ns,
+                                          int sidx, bf16_t *__restrict__ dqkv, char *smem, float (*rows)[2][2][32]) {
+  constexpr bool DO_DV = WHAT != 2, DO_DK = WHAT != 1;
+  typedef Private<DH> L;
+  typedef typename L::Tile Tile;
+  const int t = threadIdx.x, lane = t & 63, hh = lane >> 5, lk_ = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const CausalTile ct = causal_tile();  // the first keys have the most queries
+  const int own = ct.rank, b = ct.y / H, h = ct.y % H, d = H * DH, nqt = (T + 31) / 32;  // query blocks own .. nqt - 1
+  const size_t ld3 = 3 * (size_t)d, N = (size_t)B * T;
+  const bf16_t *qbase = qkv + (size_t)b * T * ld3 + h * DH;
+  const bf16_t *kbase = qbase + d, *vbase = qbase + 2 * d;
+  const float *lrow = lse + ((size_t)b * H + h) * T;
+  const int kv = 32 * own + lk_;
+  char *const mine = smem + wave * L::BYTES;
+  Frag kf[DH / 16], vf[DO_DK ? DH / 16 : 1];
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    kf[ks].q = kv < T ? ldg16(kbase + (size_t)kv * ld3 + 16 * ks + 8 * hh) : make_uint4(0, 0, 0, 0);
+    if constexpr (DO_DK) vf[ks].q = kv < T ? ldg16(vbase + (size_t)kv * ld3 + 16 * ks + 8 * hh) : make_uint4(0, 0, 0, 0);
+  }
+  floatx16 dk[DH / 32], dv[DH / 32];  // (the one that is not asked for is never used)
+#pragma unroll
+  for (int i = 0; i < DH / 32; ++i) {
+    dk[i] = kZero16;
+    dv[i] = kZero16;
+  }
+  const float sc = rsqrtf((float)DH), sc2 = sc * kLog2e;
+  const BufRsrc rq = make_rsrc(qbase, (size_t)T * ld3 * 2 - (size_t)h * DH * 2);
+  const BufRsrc rg = make_rsrc(d_o + (sidx * N + (size_t)b * T) * d + h * DH, (size_t)T * d * 2 - (size_t)h * DH * 2);
+  Tile lq, lg;
+  lq.init(0, (int)ld3, lane);
+  lg.init(0, d, lane);
+  auto issue = [&](int qt, int stage) {
+    lq.issue(rq, mine + stage * L::STAGE, 0, 32 * qt, T);
+    lg.issue(rg, mine + stage * L::STAGE + L::KT, 0, 32 * qt, T);
+  };
+  // lse (lanes 0..31) and dsum of a block's rows go through a register, one block ahead
+  auto row_value = [&](int qt) {
+    const int r = 32 * qt + (lane & 31);
+    return r >= T ? 0.f : hh == 0 ? lrow[r] : !DO_DK ? 0.f : dsum_of<DH>(dsum, ns * N, sidx * N + (size_t)b * T + r, h);
+  };
+  float ahead = 0.f;
+  if (own + wave < nqt) {
+    ahead = row_value(own + wave);
+    issue(own + wave, 0);
+  }
+  int stage = 0;
+  for (int qt = own + wave; qt < nqt; qt += W, stage ^= 1) {
+    const char *sq = mine + stage * L::STAGE, *sg = sq + L::KT;
+    float(*row)[32] = rows[wave][stage];
+    row[hh][lane & 31] = ahead;
+    wait_vmcnt<0>();
+    floatx16 s = kZero16, dp = kZero16;
+#pragma unroll
+    for (int ks = 0; ks < DH / 16; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::rowfrag(sq, 0, ks, lane), kf[ks].v, s, 0, 0, 0);
+      if constexpr (DO_DK)
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::rowfrag(sg, 0, ks, lane), vf[ks].v, dp, 0, 0, 0);
+    }
+    bf16x8 gc[2][DO_DV ? DH / 32 : 1], qc[2][DO_DK ? DH / 32 : 1];
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq)
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt) {
+        if constexpr (DO_DV) gc[bq][dt] = Tile::trfrag(sg, 16 * bq, dt, lane);
+        if constexpr (DO_DK) qc[bq][dt] = Tile::trfrag(sq, 16 * bq, dt, lane);
+      }
+    float4 l4[4], d4[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      l4[g] = *reinterpret_cast<const float4 *>(&row[0][8 * g + 4 * hh]);
+      d4[g] = *reinterpret_cast<const float4 *>(&row[1][8 * g + 4 * hh]);
+    }
+    if (qt + W < nqt) {
+      ahead = row_value(qt + W);
+      issue(qt + W, stage ^ 1);
+    }
+    Frag pf[2], sf[2];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float lv4[4] = {l4[g].x, l4[g].y, l4[g].z, l4[g].w}, dv4[4] = {d4[g].x, d4[g].y, d4[g].z, d4[g].w};
+      float p4[4], s4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * g + e;
+        p4[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], sc2, -lv4[e]));
+        if (qt == own || qt == nqt - 1) {  // (uniform)
+          const int qq = 32 * qt + 8 * g + 4 * hh + e;
+          p4[e] = ((kv > qq) | (qq >= T)) ? 0.f : p4[e];
+        }
+        s4[e] = p4[e] * (dp[r] - dv4[e]);  // without the scale
+      }
+      pf[g >> 1].u[2 * (g & 1)] = pack2(p4[0], p4[1]);
+      pf[g >> 1].u[2 * (g & 1) + 1] = pack2(p4[2], p4[3]);
+      sf[g >> 1].u[2 * (g & 1)] = pack2(s4[0], s4[1]);
+      sf[g >> 1].u[2 * (g & 1) + 1] = pack2(s4[2], s4[3]);
+    }
+#pragma unroll
+    for (int bq = 0; bq < 2; ++bq)
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt) {
+        if constexpr (DO_DV) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gc[bq][dt], pf[bq].v, dv[dt], 0, 0, 0);
+        if constexpr (DO_DK) dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qc[bq][dt], sf[bq].v, dk[dt], 0, 0, 0);
+      }
+  }
+  const Meet<DH, W> meet{reinterpret_cast<float *>(smem)};
+  const int kr = 32 * own + meet.row(t);
+  bf16_t *out = dqkv + (sidx * N + (size_t)b * T + kr) * ld3 + d + h * DH;
+  auto hand_in = [&](const floatx16 (&acc)[DH / 32], float scale, bf16_t *to) {
+    float w[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = scale;
+    __syncthreads();  // every wavefront is done with what lies there
+    meet.park(acc, wave, lane);
+    __syncthreads();
+    if (kr < T) meet.store(to, w, t);
+  };
+  if constexpr (DO_DK) hand_in(dk, sc, out);
+  if constexpr (DO_DV) hand_in(dv, 1.f, out + d);
+}
+
+// (dK and dV of heads of 256 have registers of their own each: 512 and 310 on the stack together)
+constexpr int split_roles(int dh) { return dh > 128 ? 3 : 2; }
+template <int DH, int W>
+__global__ __launch_bounds__(64 * W) void attn_bwd_split(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+                                                         const float *__restrict__ lse, const float *__restrict__ dsum, int ns, int B,
+                                                         int T, int H, bf16_t *__restrict__ dqkv) {
+  __shared__ __attribute__((aligned(256))) char smem[split_lds<DH, W>()];
+  __shared__ __attribute__((aligned(16))) float rows[W][2][2][32];
+  constexpr int R = split_roles(DH);
+  const int role = blockIdx.z % R, sidx = blockIdx.z / R;
+  if (role == 1)
+    split_dq<DH, W>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem);
+  else if (role == 0)
+    split_dkv<DH, W, R == 3 ? 2 : 0>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem, rows);
+  else if constexpr (R == 3)
+    split_dkv<DH, W, 1>(qkv, d_o, lse, dsum, B, T, H, ns, sidx, dqkv, smem, rows);
+}
+
 }  // namespace
+
+// Where the other axis is divided up.  The split forms' workgroups are short, but every wavefront loads its own blocks and holds 16 KB
+// (width 64) to 64 KB (256) of LDS, so they gain while one round holds them all, and a little beyond where rows are
+// long; up to 64 tokens there is no chain to cut (at 256 there is: its shared tiles hold 32 keys).  In us, shared / split (workgroups of the split form):
+//   forward 64   1 x 576 tokens, 2 heads (36) 11.4 / 7.1;  1 x 1000, 3 (96) 18.2 / 9.7;  2 x 400, 8 (208) 9.7 / 6.5;  8 x 256, 8 (512)
+//                7.3 / 6.0;  8 x 200, 12 (672) 7.1 / 9.5;  32 x 64, 6 (384) 4.4 / 5.3
+//   forward 128  1 x 672, 6 (126) 19.9 / 11.8;  12 x 208, 3 (252) 10.1 / 6.9;  2 x 1024, 4 (256) 29.2 / 16.0;  4 x 656, 5 (420) 20.1 / 20.6
+//   forward 256  1 x 928, 2 (58) 62.0 / 33.6;  16 x 128, 2 (128) 13.5 / 8.9;  4 x 928, 4 (464) 63.7 / 39.9;  32 x 128, 4 (512) 15.0 / 16.3;
+//                8 x 32, 2 (16) 6.5 / 6.7
+//   backward 64  1 x 576, 2 (72) 18.4 / 9.9;  4 x 96, 8 (192) 6.9 / 5.0;  2 x 400, 8 (416) 15.4 / 10.7;  2 x 256, 14 (448) 11.4 / 11.2;
+//                2 x 128, 12, two streams (384) 8.0 / 8.4;  2 x 640, 5, two (800) 20.9 / 25.0;  4 x 64, 9, two (288) 5.1 / 7.5
+//   backward 128 1 x 672, 6 (252) 25.3 / 17.9;  2 x 256, 8 (256) 13.8 / 9.5;  2 x 1024, 4 (512) 35.1 / 27.4;  4 x 128, 8, two (512) 10.4 / 13.0;
+//                8 x 40, 4, two (256) 6.0 / 7.2
+//   backward 256 1 x 928, 2 (174) 98 / 45;  1 x 64, 1 (6) 12.2 / 7.1;  16 x 128, 2 (384) 24.3 / 15.0;  8 x 128, 3, two (576) 25.1 / 20.4;
+//                8 x 104, 4, two (768) 25.0 / 24.2;  4 x 928, 4 (1392) 102 / 118;  16 x 64, 2, two (384) 13.7 / 13.4;
+//                8 x 65, 4, three (864) 20.2 / 25.7
+constexpr int split_waves(int dh) { return dh > 128 ? 2 : 4; }  // (four at 256: 256 KB of tiles)
+template <int DH>
+bool fwd_splits(long workgroups, int T) {
+  if (DH == 256) return T > 32 && workgroups <= (T >= 512 ? 512 : 256);
+  return T > 64 && workgroups <= (DH == 64 ? 512 : 256);
+}
+template <int DH>
+bool bwd_splits(long workgroups, int T) {
+  if (DH == 256) return workgroups <= (T > 96 ? 640 : 256);
+  return T > 64 && workgroups <= (DH == 64 ? (T >= 256 ? 448 : 256) : (T >= 512 ? 512 : 256));
+}
 
 // A workgroup of four wavefronts takes 128 queries; where that leaves CUs without a workgroup, two wavefronts take
 // 64, but each of them reads the keys for half as many queries and has more of them to load.  Forward in us, four /
@@ -728,6 +1140,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 128 ? 
 //   width 256  16 x 64, 4 heads 8.62 / 9.01;  8 x 128, 4: 14.39 / 13.33;  4 x 256, 4: 22.14 / 21.93;  2 x 512, 8: 39.0 / 40.0
 template <int DH>
 hipError_t fwd(const bf16_t *qkv, int B, int T, int H, bf16_t *o, float *lse, hipStream_t s) {
+  const long split = (long)((T + 31) / 32) * B * H;
+  if (fwd_splits<DH>(split, T)) {
+    constexpr int W = split_waves(DH);
+    hipLaunchKernelGGL((attn_fwd_split<DH, W>), dim3((T + 31) / 32, B * H), dim3(64 * W), 0, s, qkv, T, H, o, lse);
+    return hipGetLastError();
+  }
   if constexpr (DH != 128) {
     const int tiles = (T + 127) / 128 * B * H;
     if (tiles < 256 && (DH == 64 ? T <= 512 : T > 64 && T <= 256)) {
@@ -764,6 +1182,13 @@ constexpr long kPairedWgs = 640;
 template <int DH, int NS>
 hipError_t bwd(const bf16_t *qkv, const bf16_t *d_o, const float *lse, const float *dsum, int ns, int B, int T, int H,
                bf16_t *dqkv, hipStream_t s) {
+  const long split = (long)((T + 31) / 32) * B * H * ns * split_roles(DH);
+  if (bwd_splits<DH>(split, T)) {
+    constexpr int W = split_waves(DH);
+    hipLaunchKernelGGL((attn_bwd_split<DH, W>), dim3((T + 31) / 32, B * H, split_roles(DH) * ns), dim3(64 * W), 0, s, qkv, d_o,
+                       lse, dsum, ns, B, T, H, dqkv);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((attn_bwd_mfma<DH, NS>), dim3((T + 127) / 128, B * H, bwd_roles(DH) * ((ns + NS - 1) / NS)), dim3(256), 0,
                      s, qkv, d_o, lse, dsum, ns, B, T, H, dqkv);
   return hipGetLastError();

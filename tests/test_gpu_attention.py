@@ -192,6 +192,49 @@ def test_bf16_products(dh, T, H):
 
 
 @pytest.mark.parametrize("dh,B,T,H,ns", [
+    (64, 1, 65, 1, 1), (64, 2, 300, 3, 2), (64, 8, 256, 8, 1), (64, 8, 257, 8, 1), (64, 16, 255, 2, 1), (64, 2, 416, 8, 1), (64, 2, 450, 8, 1),
+    (128, 1, 65, 2, 2), (128, 2, 97, 16, 1), (128, 16, 257, 1, 1), (128, 1, 512, 16, 1), (128, 2, 1023, 4, 1),
+    (256, 1, 2, 1, 1), (256, 1, 33, 2, 3), (256, 32, 64, 2, 1), (256, 33, 64, 2, 1), (256, 20, 64, 2, 1), (256, 1, 96, 8, 3), (256, 5, 128, 8, 1), (256, 7, 128, 8, 1), (256, 1, 512, 7, 2)])
+def test_bf16_products_split_over_wavefronts(dh, B, T, H, ns):
+    """Both sides of every line from which a row's keys are divided up, several streams; the bounds of the test above."""
+    import torch
+    dev, d, N = torch.device("cuda:0"), H * dh, B * T
+    print("case split", dh, B, T, H, ns, flush=True)
+    gen = torch.Generator(device=dev).manual_seed(dh + T)
+    qkv = torch.randn(N, 3 * d, generator=gen, device=dev).to(torch.bfloat16)
+    g = torch.randn(ns * N, d, generator=gen, device=dev).to(torch.bfloat16)
+    o, lse = torch.full((N, d), 7.0, dtype=torch.bfloat16, device=dev), torch.full((B, H, T), 7.0, device=dev)
+    out = torch.full((ns * N, 3 * d), 7.0, dtype=torch.bfloat16, device=dev)
+    stream = torch.cuda.current_stream().cuda_stream
+    b.il_test_attention(b.IL_BF16, qkv, B, T, H, dh, o, lse, stream=stream)
+    dsum = (g.float().reshape(ns, N, d) * o.float()).reshape(ns * N, d // 32, 32).sum(dim=2).t().contiguous()
+    b.il_test_attention(b.IL_BF16, qkv, B, T, H, dh, o, lse, g, ns, out, dsum, stream=stream)
+    q, k, v = (x.reshape(B, T, H, dh).transpose(1, 2).float().contiguous() for x in qkv.reshape(N, 3, d).unbind(1))
+    S = (q.double() @ k.double().transpose(2, 3).contiguous()) * dh ** -0.5
+    S = S.masked_fill(torch.ones(T, T, dtype=torch.bool, device=dev).triu(1), float("-inf"))
+    P = torch.softmax(S, dim=3)
+    rows = lambda a: a.transpose(1, 2).reshape(N, d)  # noqa: E731
+
+    def near(got, want, tol, what):
+        got = got.double()
+        assert (got - want).norm() <= tol * want.norm(), what
+        assert (got - want).abs().max() <= 2 * tol * want.abs().max(), what
+        e = (got - want).square().sum(1) / want.square().sum(1).clamp_min(want.square().sum() / len(want))
+        assert e.max().sqrt() <= 4 * tol, (what, int(e.argmax()))
+
+    near(o, rows(P @ v.double()), 2 ** -8, "o")
+    got_lse, want_lse = lse.double() / np.log2(np.e), torch.logsumexp(S, dim=3)    # (powers of two)
+    assert (got_lse - want_lse).abs().max() <= 1e-5 * want_lse.abs().max()
+    for s in range(ns):
+        go = g[s * N:(s + 1) * N].reshape(B, T, H, dh).transpose(1, 2).double().contiguous()
+        D = (go * o.reshape(B, T, H, dh).transpose(1, 2).double()).sum(3, keepdim=True)
+        dS = P * (go @ v.double().transpose(2, 3).contiguous() - D) * dh ** -0.5
+        want = (dS @ k.double(), dS.transpose(2, 3).contiguous() @ q.double(), P.transpose(2, 3).contiguous() @ go)
+        for i in range(3):
+            near(out[s * N:(s + 1) * N, i * d:(i + 1) * d], rows(want[i]), 2 ** -7, (s, "QKV"[i]))
+
+
+@pytest.mark.parametrize("dh,B,T,H,ns", [
     (64, 5, 256, 16, 2), (64, 5, 256, 16, 3), (64, 10, 129, 16, 2), (64, 5, 1000, 8, 2), (64, 40, 33, 8, 2), (64, 160, 1, 2, 3),
     (64, 27, 64, 4, 5), (64, 1, 64, 1, 2), (128, 4, 200, 11, 2), (256, 8, 65, 4, 3)])
 def test_streams_that_share_a_walk(dh, B, T, H, ns):
