@@ -41,8 +41,8 @@ __device__ inline uint32_t pack_f16x2(float a, float b) {  // a in the low half;
   const float lim = 65504.f;
   typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 f16x2_t;
   f16x2_t v;
-  v[0] = (_Float16)fminf(fmaxf(a, -lim), lim);
-  v[1] = (_Float16)fminf(fmaxf(b, -lim), lim);
+  v[0] = (_Float16)__builtin_amdgcn_fmed3f(a, -lim, lim);
+  v[1] = (_Float16)__builtin_amdgcn_fmed3f(b, -lim, lim);
   return __builtin_bit_cast(uint32_t, v);
 }
 
@@ -58,11 +58,11 @@ template <> __device__ inline void st<bf16_t>(bf16_t *p, float v) { *p = f32_to_
 //   gelu(u)  = u s,      gelu'(u) = s + s (1 - s) * 2 sqrt(2/pi) u (1 + 3 * 0.044715 u^2).
 // exp and the reciprocal are the hardware instructions (relative error ~1e-6, far inside the fp32
 // tolerance; both ends saturate correctly: s -> 0 or 1).  These sit in the epilogue of every MLP GEMM,
-// where the two wavefronts of a SIMD share one vector ALU: the derivative costs eight plain and two
-// transcendental instructions per element in this form.
+// where the two wavefronts of a SIMD share one vector ALU: the derivative costs seven plain and
+// two transcendental instructions per element in this form.
 __device__ inline float gelu_sigmoid(float u, float u2) {
-  const float y = u * __builtin_fmaf(0.044715f, u2, 1.0f);
-  const float e = __builtin_amdgcn_exp2f(y * -2.3022081715f);  // exp(-2 sqrt(2/pi) y'), -2 * 0.79788456 * log2(e)
+  // exp(-2y) as a power of two: -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
+  const float e = __builtin_amdgcn_exp2f(u * __builtin_fmaf(-0.10294323839f, u2, -2.3022081715f));
   return __builtin_amdgcn_rcpf(e + 1.0f);
 }
 __device__ inline float gelu_f(float u) { return u * gelu_sigmoid(u, u * u); }

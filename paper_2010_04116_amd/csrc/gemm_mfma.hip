@@ -60,6 +60,16 @@ __device__ inline float dpp_f32(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
 
+// The largest of three in one instruction.  (fmaxf on values fresh from memory spends another on each to quiet
+// signalling NaNs, which no product leaves.)
+__device__ inline float max3(float a, float b, float c) {
+  float r = a;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+#endif
+  return r;
+}
+
 // What the epilogue reads at a row's eight consecutive output columns, besides bias: the pre-activation or
 // attention output (bf16), the residual or the accumulated-into output (fp32).
 struct Extra { u32x4 q[2]; };
@@ -213,23 +223,24 @@ __device__ inline void epilogue_strips(const GemmArgs &g, floatx16 (&acc)[MI][NI
       if constexpr (EPI == EPI_LOGITS) {
         // Softmax statistics of this row's 64 columns from the fp32 accumulators (before any rounding):
         // the row's eight lanes (consecutive lane ids) each hold eight columns; N is a multiple of 8, so a
-        // lane's columns are all inside the matrix or all outside.
+        // lane's columns are all inside the matrix or all outside.  These are vector instructions that nothing hides
+        // (two wavefronts to a SIMD, both in the epilogue), so they are counted: one selection per lane, not one per
+        // column, and the target's logit from the strip in LDS, not by eight comparisons.  2048 x 32000 x 256:
+        // 89.8 us with 1943 vector instructions per lane of a 256x256 tile, 85.4 with 1384.
         static_assert((WTN == kStatGroup && E::LPR == 8) || EPI != EPI_LOGITS, "one statistics group per wave-tile row");
         if (g.row_stats) {
           const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
           const bool in = gcol < g.N;
-          float m = -INFINITY;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) m = fmaxf(m, in ? v[e] : -INFINITY);
+          float m = max3(max3(v[0], v[1], v[2]), max3(v[3], v[4], v[5]), max3(v[6], v[7], v[7]));
+          m = in ? m : -INFINITY;
           m = fmaxf(m, dpp_f32<0xB1>(m));   // lane ^ 1
           m = fmaxf(m, dpp_f32<0x4E>(m));   // lane ^ 2
           m = fmaxf(m, dpp_f32<0x141>(m));  // the other quad of the eight lanes
+          const float m2 = m * 1.4426950408889634f;
           float se = 0.f;
-          if (in) {
-            const float m2 = m * 1.4426950408889634f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) se += __builtin_amdgcn_exp2f(v[e] * 1.4426950408889634f - m2);
-          }
+          for (int e = 0; e < 8; ++e) se += __builtin_amdgcn_exp2f(__builtin_fmaf(v[e], 1.4426950408889634f, -m2));
+          se = in ? se : 0.f;
           se += dpp_f32<0xB1>(se);
           se += dpp_f32<0x4E>(se);
           se += dpp_f32<0x141>(se);
@@ -240,11 +251,7 @@ __device__ inline void epilogue_strips(const GemmArgs &g, floatx16 (&acc)[MI][NI
               st[1] = se;
             }
             const int tgt = ex.tgt[i * E::NSTRIP + p];
-            if (in && tgt >= gcol && tgt < gcol + 8) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (gcol + e == tgt) g.row_ztgt[grow] = v[e];
-            }
+            if (in && (unsigned)(tgt - gcol) < 8) g.row_ztgt[grow] = stg[row_in * SP + tgt - col0];
           }
         }
       }
