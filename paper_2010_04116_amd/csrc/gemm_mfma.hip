@@ -546,6 +546,13 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
     return;
   }
 
+  // What the epilogue reads: before the first step, under which its latency passes, where the registers that it then
+  // holds through the loop cost no resident workgroup (one 128x128 ring of two steps less on a CU) and do not spill
+  // (fp32 reads beside the accumulators of twelve wavefronts).  GELU' of 4096 x 1024 x 256: 8.6 us, now 7.9; FC2 with its
+  // residual, 4096 x 256 x 1024: 7.0 us, now 6.6.
+  constexpr bool EARLY = LOADERS && (MI * NI == 1 || NSTAGE == 4 || (NSTAGE == 3 && !kExtraF32<EPI>));
+  EpiExtras<WTN, EPI, MI> ex;
+  if constexpr (EARLY) ex.load(g, m0 + wm * WTM, n0 + wn * WTN, lane);
   for (int kt = 0; kt < nk; ++kt) {
     if constexpr (!LOADERS) {
       if (nk - 1 - kt >= NSTAGE - 2)
@@ -618,8 +625,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0))) vo
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
     }
   }
-  EpiExtras<WTN, EPI, MI> ex;
-  ex.load(g, m0 + wm * WTM, n0 + wn * WTN, lane);
+  if constexpr (!EARLY) ex.load(g, m0 + wm * WTM, n0 + wn * WTN, lane);
   __syncthreads();  // every wavefront is done with the ring
   epilogue_strips<WTN, EPI>(g, acc, reinterpret_cast<float *>(smem) + wave * EpiStrip<WTN>::FLOATS, m0 + wm * WTM,
                             n0 + wn * WTN, lane, ex);
