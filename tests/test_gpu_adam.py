@@ -66,6 +66,18 @@ def test_bf16_parity(count):
     assert np.all(np.abs(got["p"] - ref["w"]) <= bound + 1e-30)
 
 
+# where buffers of 18 (fp32 mode: 16) bytes a parameter start to go past the Infinity Cache: the last and the first size,
+# a whole number of workgroups and a ragged tail
+@pytest.mark.parametrize("dtype,count", [("bf16", 19_444_444), ("bf16", 19_444_447), ("f32", 21_876_736), ("f32", 21_875_003)])
+def test_parity_about_the_size_of_the_cache(dtype, count):
+    print("case adam", dtype, "count", count, flush=True)
+    got, ref = run_steps(dtype, count, 1, seed=7)
+    for k in ("m", "v", "w"):
+        assert rel(got[k], ref[k]) <= TOL, k                             # as above; one step
+    assert np.abs(ref["w"] - got["w"]).max() <= 1e-6
+    assert np.array_equal(got["p"], synth.round_to_bf16(got["w"]) if dtype == "bf16" else got["w"])
+
+
 def test_moves_against_the_gradient_and_is_restartable():
     count = 4096
     g = torch.ones(count, device=DEV)
