@@ -30,7 +30,12 @@ __device__ inline void load4(const bf16_t *p, float (&o)[4]) {
 }
 
 constexpr int kSegment = 4096;   // positions listed at a time (one LDS list entry each)
-constexpr int kMaxGroups = 4096;  // vocabulary row groups = workgroups of the token-gradient kernel
+// Vocabulary row groups = workgroups of the token-gradient kernel: where dwte exceeds the L2s' 32 MB, kMostGroups (each
+// writes fewer rows one after the other); otherwise kMaxGroups, as each group scans all positions.  us with
+// kMaxGroups and kMostGroups: 33 MB (vocabulary 32000, d = 256) 24.6 and 30.2, 51 MB (50304, 256) 18.9 and 18.6,
+// (20000, 640) 25.1 and 23.1, 134 MB (32768, 1024) 32.4 and 26.3, 412 MB (50304, 2048) 150 and 133.
+constexpr int kMaxGroups = 4096, kMostGroups = 8192;
+constexpr size_t kManyBytes = 40u * 1000 * 1000;
 
 // Four consecutive columns per lane, two row passes apart in flight by occupancy: bound by the fp32
 // rows it writes.  VEC: rows of wte / wpe / x0 take 8- or 16-byte accesses.
@@ -90,9 +95,11 @@ __device__ inline void store_cols(float *p, const Cols<VEC> &r) {
 // positions of a word-like distribution to add up, one after the other through memory (1.26 ms at
 // 4096 positions, d = 1024, vocabulary 32768, where the launch is now bound by writing the 134 MB of
 // dwte).  The four wavefronts scan a quarter of a segment of positions each, 16 bytes per lane, and
-// append their hits in ascending order to a list each; then every row is summed from the lists by `nw`
-// wavefronts, one column group of VEC per lane, eight rows of dx0 in flight.  Rows are stored once per
-// segment; a later segment (N > kSegment) adds to the rows it hits only.
+// append their hits in ascending order to a list each, the next tokens under way; then every row is summed
+// from the lists by `nw` wavefronts, one column group of VEC per lane, eight rows of dx0 in flight.  Rows are
+// stored once per segment; a later segment (N > kSegment) adds to the rows it hits only.  The hits of a group are
+// few (one on average at 4096 positions): held in registers, a row costs one comparison and ballot instead of
+// four trips to the LDS (4096 positions, d = 1536, vocabulary 50304: 77 -> 71 us).
 //
 // The remaining workgroups: dwpe[t, c] = sum_b dx0[b*T + t, c], b ascending.
 template <int VEC>
@@ -128,11 +135,15 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const float *__restrict_
     {  // this wavefront's quarter of the segment
       const int base = seg + wave * QUARTER, end = min(N, base + QUARTER);
       int len = 0;
+      const auto whole = [&](int i) { return aligned && i + 3 < end; };
+      int4 next = {};
+      if (whole(base + lane * 4)) next = *reinterpret_cast<const int4 *>(tokens + base + lane * 4);
       for (int i0 = base; i0 < end; i0 += 256) {
         const int i = i0 + lane * 4;
         int tok[4];
-        if (aligned && i + 3 < end) {
-          const int4 q = *reinterpret_cast<const int4 *>(tokens + i);
+        const int4 q = next;
+        if (whole(i + 256)) next = *reinterpret_cast<const int4 *>(tokens + i + 256);
+        if (whole(i)) {
           tok[0] = q.x; tok[1] = q.y; tok[2] = q.z; tok[3] = q.w;
         } else {
 #pragma unroll
@@ -163,7 +174,18 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const float *__restrict_
       if (lane == 0) list_len[wave] = len;
     }
     __syncthreads();
-    const int all = list_len[0] + list_len[1] + list_len[2] + list_len[3];
+    // the four lists, one after the other, are ascending: entry l of all goes to lane l, once for all rows where they fit
+    const int o1 = list_len[0], o2 = o1 + list_len[1], o3 = o2 + list_len[2], all = o3 + list_len[3];
+    int my_row = -1, my_pos = 0;
+    auto fetch = [&](int l) {
+      my_row = -1;
+      if (l < all) {
+        const int q = (l >= o1) + (l >= o2) + (l >= o3), at = l - (q == 0 ? 0 : q == 1 ? o1 : q == 2 ? o2 : o3);
+        my_row = list_row[q][at];
+        my_pos = q * QUARTER + list_pos[q][at];
+      }
+    };
+    if (all <= 64) fetch(lane);
     for (int r = wave / nw; r < nrows; r += 4 / nw) {
       float *dst = dwte + ((size_t)r * groups + w) * d;
       for (int cg = (wave % nw) * 64 + lane; cg - lane < ncg; cg += nw * 64) {  // (uniform trip count)
@@ -171,39 +193,35 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const float *__restrict_
         const int c = cg * VEC;
         Cols<VEC> acc = {};
         bool touched = seg == 0;
-        if (all)
-          for (int q = 0; q < 4; ++q)
-            for (int l0 = 0; l0 < list_len[q]; l0 += 64) {
-              const int l = l0 + lane;
-              const bool is = l < list_len[q] && list_row[q][l] == r;
-              unsigned long long m = __ballot(is);
-              if (m == 0) continue;
-              if (!touched) {
-                if (in) acc = load_cols<VEC>(dst + c);
-                touched = true;
+        for (int l0 = 0; l0 < all; l0 += 64) {
+          if (all > 64) fetch(l0 + lane);
+          unsigned long long m = __ballot(my_row == r);
+          if (m == 0) continue;
+          if (!touched) {
+            if (in) acc = load_cols<VEC>(dst + c);
+            touched = true;
+          }
+          const float *src = dx0 + (size_t)seg * d + c;
+          while (m) {  // eight rows requested before the first is added; added in ascending order
+            Cols<VEC> x[8];
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (m) {
+                const int b = __builtin_ctzll(m);
+                m &= m - 1;
+                const int p = __builtin_amdgcn_readlane(my_pos, b);
+                x[u] = in ? load_cols<VEC>(src + (size_t)p * d) : Cols<VEC>{};
+                n = u + 1;
               }
-              const int pos = is ? list_pos[q][l] : 0;
-              const float *src = dx0 + (size_t)(seg + q * QUARTER) * d + c;
-              while (m) {  // eight rows requested before the first is added; added in ascending order
-                Cols<VEC> x[8];
-                int n = 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                  if (m) {
-                    const int b = __builtin_ctzll(m);
-                    m &= m - 1;
-                    const int p = __builtin_amdgcn_readlane(pos, b);
-                    x[u] = in ? load_cols<VEC>(src + (size_t)p * d) : Cols<VEC>{};
-                    n = u + 1;
-                  }
+            for (int u = 0; u < 8; ++u)
+              if (u < n) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                  if (u < n) {
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc.v[e] += x[u].v[e];
-                  }
+                for (int e = 0; e < VEC; ++e) acc.v[e] += x[u].v[e];
               }
-            }
+          }
+        }
         if (in && touched) store_cols<VEC>(dst + c, acc);
       }
     }
@@ -247,9 +265,10 @@ int il_embed_backward(const float *dx0, const int32_t *tokens, int32_t batch, in
   const long long N = (long long)batch * seq;
   if (N > (1 << 24) || vocab > (1 << 24)) return IL_E_SHAPE;
   hipStream_t s = (hipStream_t)stream;
-  // the smallest power of two that gives every workgroup one row, up to kMaxGroups
+  // the smallest power of two that gives every workgroup one row, up to the most
+  const int most = (size_t)vocab * d_model * sizeof(float) > kManyBytes ? kMostGroups : kMaxGroups;
   int groups = 1;
-  while (groups < vocab && groups < kMaxGroups) groups *= 2;
+  while (groups < vocab && groups < most) groups *= 2;
   const bool vec = (d_model & 3) == 0 && (((uintptr_t)dx0 | (uintptr_t)dwte | (uintptr_t)dwpe) & 15) == 0;
   const size_t pos = ((size_t)seq * d_model / (vec ? 4 : 1) + 255) / 256;
   const int pblocks = (int)(pos < 1024 ? pos : 1024);

@@ -102,8 +102,10 @@ def test_misuse():
 
 
 # two segments of the position list, one row group and many, one / two / four wavefronts per row, scalar columns;
+# as many groups as there are (dwte of more than 40 MB: one row or two to a group, long and empty lists side by side);
 # word-like token frequencies: the first ids take most positions, so lists are long and unevenly filled
-@pytest.mark.parametrize("B,T,d,V", [(5, 1000, 36, 3), (41, 100, 520, 4097), (2, 2048, 260, 9001), (3, 1400, 129, 300)])
+@pytest.mark.parametrize("B,T,d,V", [(5, 1000, 36, 3), (41, 100, 520, 4097), (2, 2048, 260, 9001), (3, 1400, 129, 300),
+                                     (41, 100, 1028, 9803), (1, 70, 1251, 8191)])
 def test_frequent_tokens(B, T, d, V):
     u = np.random.default_rng(9).random((B, T))
     tokens = np.minimum(np.floor((V + 1.0) ** u) - 1.0, V - 1).astype(np.int32)
