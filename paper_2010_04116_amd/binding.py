@@ -26,7 +26,7 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
            "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum",
-           "il_test_gemm_splitk", "il_gemm_split_plan", "il_test_layernorm",
+           "il_test_gemm_splitk", "il_gemm_split_plan", "il_gemm_tile_of", "il_test_layernorm",
            "il_test_layernorm_backward")
 
 
@@ -71,6 +71,7 @@ def load():
                                  i32, C.c_float, i32, i32, vp]
     lib.il_test_attention.argtypes = [i32, vp, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp]
     lib.il_test_gemm_splitk.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
+    lib.il_gemm_tile_of.argtypes = [i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
     lib.il_test_layernorm.argtypes = [i32, vp, vp, vp, C.c_float, i32, i32, vp, vp, vp, vp]
@@ -198,6 +199,13 @@ def il_gemm_split_plan(dtype, M, N, K, ws_floats):
     if parts < 0:
         raise InterlockError(parts, "il_gemm_split_plan")
     return parts, tile.value
+
+
+def il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, workgroup):
+    """(row, column) of the output tile that a GEMM launch gives this workgroup."""
+    m, n = C.c_int32(), C.c_int32()
+    _check(load().il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, workgroup, C.byref(m), C.byref(n)), "il_gemm_tile_of")
+    return m.value, n.value
 
 
 def il_test_attention(dtype, qkv, batch, seq, heads, width, o, lse, d_o=None, streams=1, dqkv=None, dsum=None, stream=None):

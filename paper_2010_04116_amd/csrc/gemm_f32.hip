@@ -421,7 +421,7 @@ long tiles_of(const GemmArgs &g) {
 template <int BM, int BN, bool AKM, bool BKM, int LB>
 hipError_t launch(GemmBatch &b, hipStream_t s) {
   return with_problems<AKM && BKM>(
-      b.p, b.count, [](const GemmArgs &g) { return (int)tiles_of<BM, BN>(g); },
+      b.p, b.count, [](const GemmArgs &g) { return TileGrid{(g.M + BM - 1) / BM, (g.N + BN - 1) / BN, BM, BN}; },
       [&](const auto &problems, int tiles) {
         hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, AKM, BKM, LB, std::decay_t<decltype(problems)>::kRoom>), dim3(tiles), dim3(256 + NL),
                            0, s, problems);

@@ -805,7 +805,7 @@ template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool AKM, bool BKM, int 
 hipError_t launch_dma(GemmBatch &b, hipStream_t s) {
   return with_problems<AKM && BKM>(
       b.p, b.count,
-      [](const GemmArgs &g) { return ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * std::max(g.splits, 1); },
+      [](const GemmArgs &g) { return TileGrid{(g.M + BM - 1) / BM, (g.N + BN - 1) / BN, BM, BN}; },
       [&](const auto &problems, int tiles) {
         return launch_one(gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, AKM, BKM, EPI, LOADERS, std::decay_t<decltype(problems)>::kRoom>, problems,
                           tiles, 64 * (WGM * WGN + (LOADERS ? kLoaderWaves : 0)), s);
@@ -818,7 +818,7 @@ hipError_t launch_pair(GemmBatch &b, hipStream_t s) {
       b.p, b.count,
       [](const GemmArgs &g) {
         const int rows = EPI == EPI_GELU_BWD_SUM && g.streams == 2 ? (g.M / 2 + 127) / 128 : (g.M + 255) / 256;
-        return rows * ((g.N + 255) / 256) * std::max(g.splits, 1);
+        return TileGrid{rows, (g.N + 255) / 256, 256, 256};
       },
       [&](const auto &problems, int tiles) {
         return launch_one(gemm_pair_kernel<AKM, BKM, EPI, std::decay_t<decltype(problems)>::kRoom>, problems, tiles, 512, s);

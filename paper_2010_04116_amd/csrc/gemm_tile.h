@@ -1,5 +1,6 @@
 // Which problem, which output tile and which part of the reduction a workgroup of a GEMM launch takes.
 #pragma once
+#include <algorithm>
 #include <cstring>
 
 #include "common.h"
@@ -34,40 +35,85 @@ __device__ inline GemmArgs my_problem(const Problems<MAX> &b, int &first) {
     return b.p[prob];
   }
 }
-// go(the launch's problems, its workgroups); tiles(p): the workgroups of problem p.
+// Output tiles of a problem (m x n of them) and their edges.
+struct TileGrid { int m, n, bm, bn; };
+
+// Where the `at`-th of a problem's tiles lies.
+struct TilePlace { int m, n; };
+__host__ __device__ inline TilePlace tile_place(int at, int tiles_m, int tiles_n) {
+  constexpr int GM = 8;  // rows of tiles that are taken column by column
+  const int per_group = GM * tiles_n, first_m = at / per_group * GM, left = tiles_m - first_m, rows = left < GM ? left : GM;
+  return {first_m + at % per_group % rows, at % per_group / rows};
+}
+// The place in that order of the workgroup `local` of `total`.  Workgroups land on XCD `local` mod 8.  in_turn: in launch
+// order; otherwise XCD x gets as many consecutive places as it has workgroups, also where eight does not divide the count.
+__host__ __device__ inline int tile_turn(int local, int total, bool in_turn) {
+  if (in_turn) return local;
+  const int xcd = local & 7, rest = total & 7;
+  return xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (local >> 3);
+}
+// Which of the two, where eight does not divide the number of tiles: the one for which the XCDs' L2s fetch fewer operand
+// rows and columns.  In launch order XCD x has every eighth row of tiles and all columns; with consecutive places it has
+// neighbouring rows and columns, but two neighbours on both sides of a group of eight rows' end.  So launch order is for tall
+// outputs of few columns, us, in turn and consecutive: 1768 x 296 x 3064 12.8 and 16.6, 5168 x 280 x 4872 40.0 and 47.5, 3112 x 728 x 4104
+// 46.0 and 54.1, 2136 x 280 x 1872 9.2 and 11.5; but 272 x 1184 x 2968 17.6 and 11.4, 832 x 1960 x 1920 21.4 and 16.8, 832 x 31992 x 768
+// 79.6 and 71.9, 1600 x 2304 x 768 13.5 and 12.2, 3984 x 184 x 2568 (each XCD one group) 15.3 and 11.5.  Of 890 products whose tiles
+// eight does not divide, consecutive places alone took up to 31 % longer than launch order; by this count the worst takes 15 %.
+// (Counts that eight divides and parts along K: consecutive, which was within 5 % of the other everywhere.)
+inline bool tiles_in_turn(const TileGrid &t, int splits) {
+  const int total = t.m * t.n;
+  if (splits > 1 || (total & 7) == 0) return false;
+  const int groups = t.m >> 3, left = t.m & 7, of_left = (left * t.n + 7) / 8;
+  // rows of the last, incomplete group that every eighth of its tiles meets, no more than these are
+  const int left_rows = std::min(left == 0 ? 0 : left == 4 ? 1 : (left & 1) ? left : left / 2, of_left);
+  const long turn = 8l * ((groups + left_rows) * t.bm + (groups ? t.n : std::min(t.n, of_left)) * t.bn);
+  long run = 0;
+  for (int x = 0, at = 0; x < 8; ++x) {
+    const int end = at + (total >> 3) + (x < (total & 7));
+    if (end == at) continue;
+    const int group = 8 * t.n, g0 = at / group, g1 = (end - 1) / group, rows0 = std::min(8, t.m - 8 * g0), rows1 = std::min(8, t.m - 8 * g1);
+    const int c0 = at % group / rows0, c1 = (end - 1) % group / rows1;  // first column of the first group, last of the last
+    const int cols = g1 == g0 ? c1 - c0 + 1 : g1 == g0 + 1 ? std::min(t.n, t.n - c0 + c1 + 1) : t.n;
+    const int rows = g1 == g0 ? std::min(rows0, end - at)
+                              : std::min(rows0, group * (g0 + 1) - at) + 8 * (g1 - g0 - 1) + std::min(rows1, end - group * g1);
+    run += rows * t.bm + cols * t.bn;
+    at = end;
+  }
+  return turn < run;
+}
+
+// go(the launch's problems, its workgroups); grid(p): the tiles of problem p.
 template <bool SEVERAL, typename T, typename F>
-hipError_t with_problems(const GemmArgs *list, int count, T &&tiles, F &&go) {
+hipError_t with_problems(const GemmArgs *list, int count, T &&grid, F &&go) {
+  auto take = [&](GemmArgs &p, const GemmArgs &from) {
+    p = from;
+    const TileGrid t = grid(from);
+    p.in_turn = tiles_in_turn(t, from.splits);
+    return t.m * t.n * std::max(from.splits, 1);
+  };
   if (count == 1) {
     Problems<1> one;
-    one.p[0] = list[0];
-    return go(one, tiles(list[0]));
+    const int tiles = take(one.p[0], list[0]);
+    return go(one, tiles);
   }
   if constexpr (SEVERAL) {
     Problems<kMaxBatch> b;
     memset(&b, 0, sizeof(b));
     b.count = count;
     int end = 0;
-    for (int i = 0; i < count; ++i) {
-      b.p[i] = list[i];
-      b.tile_end[i] = end += tiles(list[i]);
-    }
+    for (int i = 0; i < count; ++i) b.tile_end[i] = end += take(b.p[i], list[i]);
     return go(b, end);
   } else {
     return hipErrorInvalidValue;
   }
 }
 
-// The tile of a workgroup: `local` is its index within its problem, tiles_m x tiles_n the problem's output tiles.
-// Workgroups that land on one XCD (index mod 8) take neighbouring tiles of the same part: XCD x gets as many consecutive
-// places as it has workgroups, also where eight does not divide the count.  (Left in launch order, such a count had eight
-// neighbours fetch their operand panels into eight L2s: 832 x 31992 x 768, 500 tiles of 256 x 256, 79.6 -> 71.9 us,
-// 1600 x 2304 x 768, 234 of 128 x 128, 13.5 -> 12.2 us; the bf16 step of 1600 tokens at d = 768 4.80 -> 4.50 ms.)  Sets the
+// The tile of a workgroup: `local` is its index within its problem, tiles_m x tiles_n the problem's output tiles.  Sets the
 // reduction range [k0, k1) and points g.C at the part's output.
 struct MyTile { int m, n, k0, k1; };
 __device__ inline MyTile my_tile(GemmArgs &g, int local, int tiles_m, int tiles_n) {
-  const int tiles = tiles_m * tiles_n, splits = g.splits > 1 ? g.splits : 1, total = tiles * splits;
-  const int xcd = local & 7;
-  local = xcd * (total >> 3) + min(xcd, total & 7) + (local >> 3);
+  const int tiles = tiles_m * tiles_n, splits = g.splits > 1 ? g.splits : 1;
+  local = tile_turn(local, tiles * splits, g.in_turn);
   MyTile t{0, 0, 0, g.K};
   if (splits > 1) {
     const int part = local / tiles;
@@ -76,10 +122,9 @@ __device__ inline MyTile my_tile(GemmArgs &g, int local, int tiles_m, int tiles_
     t.k1 = min(g.K, t.k0 + g.k_per);
     g.C = (float *)g.C + (size_t)part * g.M * g.N;
   }
-  constexpr int GM = 8;  // rows of tiles that are taken column by column
-  const int per_group = GM * tiles_n, first_m = local / per_group * GM, rows = min(tiles_m - first_m, GM);
-  t.m = first_m + local % per_group % rows;
-  t.n = local % per_group / rows;
+  const TilePlace at = tile_place(local, tiles_m, tiles_n);
+  t.m = at.m;
+  t.n = at.n;
   return t;
 }
 // every part starts inside K, on a multiple of the K step

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "common.h"
+#include "gemm_tile.h"
 
 using namespace il;
 
@@ -1197,6 +1198,17 @@ int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws
   const SplitPlan p = gemm_split_plan(dtype, M, N, K, ws_floats);
   if (tile) *tile = p.tile;
   return p.splits;
+}
+
+int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t edge_n, int32_t workgroup, int32_t *tile_m,
+                    int32_t *tile_n) {
+  if (tiles_m < 1 || tiles_n < 1 || edge_m < 1 || edge_n < 1 || !tile_m || !tile_n) return IL_E_ARG;
+  if ((long long)tiles_m * tiles_n > 0x7FFFFFFF || workgroup < 0 || workgroup >= tiles_m * tiles_n) return IL_E_ARG;
+  const bool in_turn = tiles_in_turn({tiles_m, tiles_n, edge_m, edge_n}, 1);
+  const TilePlace at = tile_place(tile_turn(workgroup, tiles_m * tiles_n, in_turn), tiles_m, tiles_n);
+  *tile_m = at.m;
+  *tile_n = at.n;
+  return IL_OK;
 }
 
 int il_test_layernorm(int32_t dtype, const float *x, const void *gamma, const void *beta, float eps, int32_t rows, int32_t d,

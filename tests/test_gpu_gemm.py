@@ -119,6 +119,16 @@ def test_tile_counts_on_either_side_of_eight(tiles, tile, edge):
     run_case(edge + 8, edge * tiles, 64, 0, 0, 0, tile, seed=60 + tiles)
 
 
+@pytest.mark.parametrize("M,N,tile", [(1768, 296, 5), (1768, 296, 4), (2104, 136, 3), (8200, 520, 1), (8264, 520, 7), (2104, 296, 6)])
+def test_tall_outputs_whose_tiles_eight_does_not_divide(M, N, tile):
+    """Their tiles are dealt in launch order: every one is taken once."""
+    edge = {1: (256, 256), 3: (128, 128), 4: (64, 64), 5: (64, 64), 6: (256, 128), 7: (128, 256)}[tile]
+    tm, tn = -(-M // edge[0]), -(-N // edge[1])
+    assert tm * tn % 8 and b.il_gemm_tile_of(tm, tn, *edge, 9) == (1, 1)
+    run_case(M, N, 64, 0, 1, 1, tile, seed=60)
+    run_case(M, N, 64, 1, 1, 6, tile, seed=61, beta=1)
+
+
 def test_library_choice_at_the_benchmark_shapes():
     """tile = 0 at output shapes of the benchmark workloads, one per branch of the tile choice
     (256x256; 128x128 four-stage; 128x256 / 256x128; 128x128 two-stage; 64x64 four-stage; 64x64),

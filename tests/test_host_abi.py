@@ -198,3 +198,40 @@ def test_fp32_parts_are_priced_as_the_tiles_are():
         assert binding.il_gemm_split_plan(0, M, N, K, 1 << 40) == plan, (M, N, K)
     for (M, N, K), tile in {(2048, 512, 2048): 4, (4096, 512, 2048): 3, (4096, 2048, 512): 2}.items():
         assert binding.il_gemm_split_plan(0, M, N, K, 0) == (1, tile), (M, N, K)
+
+
+@pytest.mark.parametrize("edge", [(64, 64), (128, 128), (256, 128), (128, 256), (256, 256)])
+def test_gemm_tiles_are_dealt_once_and_to_the_xcd_that_has_their_operands(edge):
+    """Every tile goes to one workgroup, and where eight does not divide their number the XCDs (workgroup mod 8) fetch no
+    more operand rows and columns than in launch order or in consecutive places, whichever fetches fewer (a twentieth more
+    at most, the library counts parts of a group of rows, not tiles)."""
+    def fetched(place, total):
+        rows, cols = [set() for _ in range(8)], [set() for _ in range(8)]
+        for w in range(total):
+            m, n = place(w)
+            rows[w % 8].add(m)
+            cols[w % 8].add(n)
+        return sum(len(r) * edge[0] + len(c) * edge[1] for r, c in zip(rows, cols))
+
+    for tm, tn in [(1, 1), (1, 9), (9, 1), (3, 5), (5, 20), (7, 43), (12, 5), (13, 37), (17, 5), (20, 13), (25, 18), (28, 5), (34, 5), (44, 3),
+                   (49, 12), (62, 11), (63, 3), (81, 7), (117, 5), (13, 18), (4, 125), (8, 8), (16, 3), (11, 1), (63, 9)]:
+        total = tm * tn
+
+        def at(i):
+            first = i // (8 * tn) * 8
+            rows = min(8, tm - first)
+            return first + i % (8 * tn) % rows, i % (8 * tn) // rows
+
+        def consecutive(w):
+            return at(w % 8 * (total // 8) + min(w % 8, total % 8) + w // 8)
+
+        got = [binding.il_gemm_tile_of(tm, tn, *edge, w) for w in range(total)]
+        assert sorted(got) == [(m, n) for m in range(tm) for n in range(tn)], (tm, tn)
+        if total % 8 == 0:
+            assert got == [consecutive(w) for w in range(total)], (tm, tn)
+        else:
+            best = min(fetched(at, total), fetched(consecutive, total))
+            assert fetched(lambda w: got[w], total) <= 1.05 * best, (tm, tn)
+    for bad in [(0, 1, 64, 64, 0), (2, 2, 64, 64, 4), (2, 2, 64, 64, -1), (2, 2, 0, 64, 0)]:
+        with pytest.raises(binding.InterlockError):
+            binding.il_gemm_tile_of(*bad)
