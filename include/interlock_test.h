@@ -90,6 +90,12 @@ int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t ed
 int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq, int32_t heads, int32_t width,
                       void *o, float *lse, const void *d_o, int32_t streams, void *dqkv, float *dsum, void *stream);
 int il_attention_wants_dsum(int32_t dtype, int32_t width);
+/*
+ * Host function: the kernels that such a call takes, the forward (streams = 0) or the backward.  *form receives 0: a
+ * workgroup's four wavefronts share tiles of the other axis; 2, 4 or 8: that many wavefronts divide it up; -1: two wavefronts
+ * share tiles (forward); -2: as 0, two streams to a workgroup (backward).  Same errors as il_test_attention.
+ */
+int il_attention_form(int32_t dtype, int32_t width, int32_t batch, int32_t seq, int32_t heads, int32_t streams, int32_t *form);
 
 /*
  * Kernel-level test hook: one LayerNorm forward.  x: fp32 [rows, d]; gamma, beta: dtype [d]; y: dtype [rows, d]; stats:

@@ -25,7 +25,7 @@ SYMBOLS = ("il_init", "il_stage_forward", "il_head_xent", "il_stage_backward_nwi
            "il_routing_plan", "il_profile_read", "il_status_string", "il_test_gemm", "il_lr_schedule",
            "il_adam_step", "il_embed_forward", "il_embed_backward", "il_set_accumulation",
            "il_time_per_batch", "il_optimal_microbatches", "il_measure_mfma_peak", "il_measure_copy_peak",
-           "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum",
+           "il_head_xent_static", "il_test_attention", "il_attention_wants_dsum", "il_attention_form",
            "il_test_gemm_splitk", "il_gemm_split_plan", "il_gemm_tile_of", "il_test_layernorm",
            "il_test_layernorm_backward")
 
@@ -71,6 +71,7 @@ def load():
                                  i32, C.c_float, i32, i32, vp]
     lib.il_test_attention.argtypes = [i32, vp, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp]
     lib.il_test_gemm_splitk.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
+    lib.il_attention_form.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32)]
     lib.il_gemm_tile_of.argtypes = [i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
@@ -216,6 +217,13 @@ def il_test_attention(dtype, qkv, batch, seq, heads, width, o, lse, d_o=None, st
 
 def il_attention_wants_dsum(dtype, width) -> bool:
     return bool(load().il_attention_wants_dsum(dtype, width))
+
+
+def il_attention_form(dtype, width, batch, seq, heads, streams=0):
+    """Which attention kernels such a call takes (streams = 0: the forward), by the codes of interlock_test.h."""
+    form = C.c_int32()
+    _check(load().il_attention_form(dtype, width, batch, seq, heads, streams, C.byref(form)), "il_attention_form")
+    return form.value
 
 
 def il_test_layernorm(dtype, x, gamma, beta, eps, rows, d, y, stats, xcopy=None, stream=None):

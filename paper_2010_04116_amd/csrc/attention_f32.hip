@@ -736,19 +736,33 @@ __global__ __launch_bounds__(64 * W) void attn_dkv_split_f32(const T *__restrict
   }
 }
 
-// Which form: by the workgroups of 64 rows that there would be.  Up to about half the CUs' number of them the chain of the
-// longest wavefront is what a launch waits for; beyond, a tile that four wavefronts share costs less than each
-// reading its own.  Forward / backward, us, of 64 rows and split: 1 x 896 tokens, a head of 128, two streams 93 / 270 and 27 / 100;
-// 4 x 1024, two of 128 (128 workgroups) 110 / 310 and 60 / 229; 2 x 640, four of 64, two streams (160) 35 / 112 and 18 / 87; but 8 x 256, eight of 64 (256) 18 / 56
-// and 20 / 78, 8 x 512, sixteen of 64 (1024) 94 / 290 and 107 / 446.  A single tile of 64 rows has no chain to cut:
-// 4 x 64, sixteen of 32, two streams (128) 12.1 and 12.7.
-bool split_rows(long workgroups, int Tn) { return workgroups <= (Tn <= 64 ? 64 : 160); }
-// Eight wavefronts for long rows of narrow heads, whose blocks take less time than their loads: backward of 2 x 1000 tokens, four heads
-// of 16, 71 -> 62 us with four and 45 with eight; 1 x 576, seven of 32, forward 25 -> 10 -> 7.9.  (At 64 and 128 four are as fast or faster.)
+// Which form.  The chain of the longest wavefront is what a launch waits for up to about half the CUs' number of workgroups of
+// 64 rows; beyond, a tile that four wavefronts share costs less than each reading its own.  Forward / backward, us, of 64 rows
+// and split: 1 x 896 tokens, a head of 128, two streams 93 / 270 and 27 / 100; 4 x 1024, two of 128 (128 workgroups) 110 / 310 and
+// 60 / 229; 2 x 640, four of 64, two streams (160) 35 / 112 and 18 / 87; but 8 x 256, eight of 64 (256) 18 / 56 and 20 / 78, 8 x 512,
+// sixteen of 64 (1024) 94 / 290 and 107 / 446.  A single tile of 64 rows has no chain to cut: 4 x 64, sixteen of 32, two streams
+// (128) 12.1 and 12.7.  Up to 256 tokens the chain is short enough that the split form's workgroups also have to go into two
+// rounds or so (shared / split, in us, of that many split workgroups): forward, 128 tokens, heads of 128 16.9 / 14.0 (512), 17.2 / 20.8 (576);
+// 256 tokens, of 64 16.3 / 15.4 (576), of 128 30.2 / 29.8 (576), 30.1 / 33.1 (640); backward, 128 tokens, of 64 28.6 / 26.4 (512),
+// 28.7 / 36.3 (576); 256 tokens, of 64 49.8 / 39.2 (512), 50.3 / 55.5 (576), of 128 88.7 / 74.7 (512), 89.5 / 106.4 (576).  Between 128 and 224
+// tokens the shared tiles' last one is short or missing half, and the backward gains a little beyond.  Up to 96 tokens the backward of heads
+// of 128 has to go into one round: 96 tokens 38.6 / 25.6 (252), 40.2 / 43.2 (444).
+int split_parts(int dh, bool backward, long heads, int Tn) {  // heads: of all batches and streams; 0: tiles of 64 rows
+  const long tiles = (Tn + 63) / 64 * heads, split = (Tn + 15) / 16 * heads;
+  if (tiles > (Tn <= 64 ? 64 : 160)) return 0;
+  const int most = Tn > 256               ? 640
+                   : !backward            ? (Tn <= 128 ? 512 : dh == 128 ? 576 : 640)
+                   : dh == 128 && Tn < 97 ? 256
+                                          : (Tn > 128 && Tn <= 224 ? 560 : 512);
+  if (split > most) return 0;
+  // Eight wavefronts for long rows of narrow heads, whose blocks take less time than their loads: backward of 2 x 1000 tokens, four heads
+  // of 16, 71 -> 62 us with four and 45 with eight; 1 x 576, seven of 32, forward 25 -> 10 -> 7.9.  (At 64 and 128 four are as fast or faster.)
+  return dh <= 32 && Tn >= 512 ? 8 : 4;
+}
 template <int DH, typename F>
-void with_waves(int Tn, F &&f) {
+void with_waves(int parts, F &&f) {
   if constexpr (DH <= 32) {
-    if (Tn >= 512) return f(std::integral_constant<int, 8>{});
+    if (parts == 8) return f(std::integral_constant<int, 8>{});
   }
   f(std::integral_constant<int, 4>{});
 }
@@ -756,8 +770,8 @@ void with_waves(int Tn, F &&f) {
 template <typename T, int DH>
 hipError_t fwd_t(const void *qkv, int B, int Tn, int H, void *o, float *lse, hipStream_t s) {
   const dim3 grid((Tn + kOwn - 1) / kOwn, B * H), split((Tn + 15) / 16, B * H);
-  if (split_rows((long)grid.x * grid.y, Tn))
-    with_waves<DH>(Tn, [&](auto w) {
+  if (const int parts = split_parts(DH, false, (long)B * H, Tn))
+    with_waves<DH>(parts, [&](auto w) {
       constexpr int W = decltype(w)::value;
       hipLaunchKernelGGL((attn_fwd_split_f32<T, DH, W>), split, dim3(64 * W), 0, s, (const T *)qkv, Tn, H, (T *)o, lse);
     });
@@ -769,8 +783,8 @@ template <typename T, int DH>
 hipError_t bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, int ns, int B, int Tn, int H,
                  void *dqkv, float *dsum, hipStream_t s) {
   const dim3 grid((Tn + kOwn - 1) / kOwn, B * H, ns), split((Tn + 15) / 16, B * H, ns);
-  if (split_rows((long)grid.x * grid.y * ns, Tn)) {
-    with_waves<DH>(Tn, [&](auto w) {
+  if (const int parts = split_parts(DH, true, (long)B * H * ns, Tn)) {
+    with_waves<DH>(parts, [&](auto w) {
       constexpr int W = decltype(w)::value;
       hipLaunchKernelGGL((attn_dq_split_f32<T, DH, W>), split, dim3(64 * W), 0, s, (const T *)qkv, (const T *)o, (const T *)d_o,
                          lse, Tn, H, B, (T *)dqkv, dsum);
@@ -792,6 +806,13 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
                                   hipStream_t s);
 hipError_t attention_backward_mfma(const void *qkv, const void *d_o, const float *lse, const float *dsum, int ns,
                                    int B, int T, int H, int dh, void *dqkv, hipStream_t s);
+
+int attention_form_mfma(int dh, int ns, int B, int T, int H);
+
+int attention_form(int dtype, int dh, int ns, int B, int T, int H) {
+  if (dtype == 1 && dh >= 64) return attention_form_mfma(dh, ns, B, T, H);
+  return split_parts(dh, ns > 0, (long)B * H * (ns > 0 ? ns : 1), T);
+}
 
 // Front ends used by the step: bf16 with head widths 64 to 256 runs on the bf16 matrix instructions, fp32
 // and bf16 with head widths 16 and 32 on the kernels above.

@@ -1119,15 +1119,15 @@ __global__ __launch_bounds__(64 * W) void attn_bwd_split(const bf16_t *__restric
 //                8 x 104, 4, two (768) 25.0 / 24.2;  4 x 928, 4 (1392) 102 / 118;  16 x 64, 2, two (384) 13.7 / 13.4;
 //                8 x 65, 4, three (864) 20.2 / 25.7
 constexpr int split_waves(int dh) { return dh > 128 ? 2 : 4; }  // (four at 256: 256 KB of tiles)
-template <int DH>
-bool fwd_splits(long workgroups, int T) {
-  if (DH == 256) return T > 32 && workgroups <= (T >= 512 ? 512 : 256);
-  return T > 64 && workgroups <= (DH == 64 ? 512 : 256);
+bool fwd_splits(int dh, long heads, int T) {
+  const long workgroups = (T + 31) / 32 * heads;
+  if (dh == 256) return T > 32 && workgroups <= (T >= 512 ? 512 : 256);
+  return T > 64 && workgroups <= (dh == 64 ? 512 : 256);
 }
-template <int DH>
-bool bwd_splits(long workgroups, int T) {
-  if (DH == 256) return workgroups <= (T > 96 ? 640 : 256);
-  return T > 64 && workgroups <= (DH == 64 ? (T >= 256 ? 448 : 256) : (T >= 512 ? 512 : 256));
+bool bwd_splits(int dh, long heads, int ns, int T) {
+  const long workgroups = (T + 31) / 32 * heads * ns * split_roles(dh);
+  if (dh == 256) return workgroups <= (T > 96 ? 640 : 256);
+  return T > 64 && workgroups <= (dh == 64 ? (T >= 256 ? 448 : 256) : (T >= 512 ? 512 : 256));
 }
 
 // A workgroup of four wavefronts takes 128 queries; where that leaves CUs without a workgroup, two wavefronts take
@@ -1138,17 +1138,18 @@ bool bwd_splits(long workgroups, int T) {
 //   width 128  4 x 64, 16 heads 5.33 / 6.00;  8 x 256, 4: 10.72 / 11.13;  2 x 512, 16: 16.94 / 18.23  (the two-wavefront
 //              form gets 230 + 134 registers from the compiler, one wavefront per SIMD, where four get 256 + 0 and two)
 //   width 256  16 x 64, 4 heads 8.62 / 9.01;  8 x 128, 4: 14.39 / 13.33;  4 x 256, 4: 22.14 / 21.93;  2 x 512, 8: 39.0 / 40.0
+bool fwd_by_two(int dh, long heads, int T) {
+  return dh != 128 && (T + 127) / 128 * heads < 256 && (dh == 64 ? T <= 512 : T > 64 && T <= 256);
+}
 template <int DH>
 hipError_t fwd(const bf16_t *qkv, int B, int T, int H, bf16_t *o, float *lse, hipStream_t s) {
-  const long split = (long)((T + 31) / 32) * B * H;
-  if (fwd_splits<DH>(split, T)) {
+  if (fwd_splits(DH, (long)B * H, T)) {
     constexpr int W = split_waves(DH);
     hipLaunchKernelGGL((attn_fwd_split<DH, W>), dim3((T + 31) / 32, B * H), dim3(64 * W), 0, s, qkv, T, H, o, lse);
     return hipGetLastError();
   }
   if constexpr (DH != 128) {
-    const int tiles = (T + 127) / 128 * B * H;
-    if (tiles < 256 && (DH == 64 ? T <= 512 : T > 64 && T <= 256)) {
+    if (fwd_by_two(DH, (long)B * H, T)) {
       hipLaunchKernelGGL((attn_fwd_mfma<DH, 2>), dim3((T + 63) / 64, B * H), dim3(128), 0, s, qkv, T, H, o, lse);
       return hipGetLastError();
     }
@@ -1179,11 +1180,13 @@ hipError_t attention_forward_mfma(const void *qkv, int B, int T, int H, int dh, 
 // Wider heads have no registers for a second stream's accumulators.  The streams' weighted sum formed here as well, of
 // the rows just stored, cost 15 to 25 us a launch: more than the pass on the other stream that it replaces.
 constexpr long kPairedWgs = 640;
+bool bwd_pairs(int dh, long heads, int ns, int T) {
+  return dh == 64 && ns > 1 && (T + 127) / 128 * heads * bwd_roles(dh) * ((ns + 1) / 2) >= kPairedWgs;
+}
 template <int DH, int NS>
 hipError_t bwd(const bf16_t *qkv, const bf16_t *d_o, const float *lse, const float *dsum, int ns, int B, int T, int H,
                bf16_t *dqkv, hipStream_t s) {
-  const long split = (long)((T + 31) / 32) * B * H * ns * split_roles(DH);
-  if (bwd_splits<DH>(split, T)) {
+  if (bwd_splits(DH, (long)B * H, ns, T)) {
     constexpr int W = split_waves(DH);
     hipLaunchKernelGGL((attn_bwd_split<DH, W>), dim3((T + 31) / 32, B * H, split_roles(DH) * ns), dim3(64 * W), 0, s, qkv, d_o,
                        lse, dsum, ns, B, T, H, dqkv);
@@ -1193,12 +1196,16 @@ hipError_t bwd(const bf16_t *qkv, const bf16_t *d_o, const float *lse, const flo
                      s, qkv, d_o, lse, dsum, ns, B, T, H, dqkv);
   return hipGetLastError();
 }
+int attention_form_mfma(int dh, int ns, int B, int T, int H) {
+  const long heads = (long)B * H;
+  if (ns > 0) return bwd_splits(dh, heads, ns, T) ? split_waves(dh) : bwd_pairs(dh, heads, ns, T) ? -2 : 0;
+  return fwd_splits(dh, heads, T) ? split_waves(dh) : fwd_by_two(dh, heads, T) ? -1 : 0;
+}
 hipError_t attention_backward_mfma(const void *qkv, const void *d_o, const float *lse, const float *dsum, int ns,
                                    int B, int T, int H, int dh, void *dqkv, hipStream_t s) {
   const bf16_t *x = (const bf16_t *)qkv, *g = (const bf16_t *)d_o;
   bf16_t *out = (bf16_t *)dqkv;
-  const long wgs = (long)((T + 127) / 128) * B * H * bwd_roles(dh) * ((ns + 1) / 2);
-  const bool pairs = ns > 1 && wgs >= kPairedWgs;
+  const bool pairs = bwd_pairs(dh, (long)B * H, ns, T);
   switch (dh) {
     case 64: return pairs ? bwd<64, 2>(x, g, lse, dsum, ns, B, T, H, out, s) : bwd<64, 1>(x, g, lse, dsum, ns, B, T, H, out, s);
     case 128: return bwd<128, 1>(x, g, lse, dsum, ns, B, T, H, out, s);

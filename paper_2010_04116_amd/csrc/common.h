@@ -208,6 +208,8 @@ hipError_t attention_forward(int dtype, const void *qkv, int B, int T, int H, in
 // dO * O per 32 columns, fp32 [d / 32][nstreams*N], left by EPI_STORE_DOT; else fp32 scratch [nstreams*N*H].
 // lse is what attention_forward of the same type and head width wrote (its unit is theirs).
 inline bool attention_dsum_given(int dtype, int dh) { return dtype == 1 && dh >= 64; }
+// Which kernels a call takes (ns = 0: the forward), as il_attention_form() has it.
+int attention_form(int dtype, int dh, int ns, int B, int T, int H);
 hipError_t attention_backward(int dtype, const void *qkv, const void *o, const void *d_o, const float *lse,
                               int nstreams, int B, int T, int H, int dh, void *dqkv, float *dsum,
                               hipStream_t s);

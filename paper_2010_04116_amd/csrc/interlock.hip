@@ -1240,15 +1240,26 @@ int il_test_layernorm_backward(int32_t dtype, const void *dy, const float *x, co
 
 int il_attention_wants_dsum(int32_t dtype, int32_t width) { return attention_dsum_given(dtype, width) ? 1 : 0; }
 
+static int attention_extents(int32_t dtype, int32_t width, int32_t batch, int32_t seq, int32_t heads, int32_t streams, bool backward) {
+  if (batch < 1 || seq < 1 || heads < 1 || width < 1 || (dtype != IL_F32 && dtype != IL_BF16)) return IL_E_ARG;
+  const long long N = (long long)batch * seq, rows = N * (backward ? streams : 1);
+  if (!head_width_ok(dtype, width) || (long long)heads * width > 2048 || (long long)batch * heads > 65535 || N > (1 << 24) ||
+      (backward && (streams < 1 || streams > kMaxStreams)) || rows * 3 * heads * width * (dtype == IL_F32 ? 4 : 2) >= 0x7FFFFFFFll)
+    return IL_E_SHAPE;
+  return IL_OK;
+}
+
+int il_attention_form(int32_t dtype, int32_t width, int32_t batch, int32_t seq, int32_t heads, int32_t streams, int32_t *form) {
+  if (!form) return IL_E_ARG;
+  const int rc = attention_extents(dtype, width, batch, seq, heads, streams, streams != 0);
+  if (rc == IL_OK) *form = attention_form(dtype, width, streams, batch, seq, heads);
+  return rc;
+}
+
 int il_test_attention(int32_t dtype, const void *qkv, int32_t batch, int32_t seq, int32_t heads, int32_t width,
                       void *o, float *lse, const void *d_o, int32_t streams, void *dqkv, float *dsum, void *stream) {
-  if (!qkv || !o || !lse || batch < 1 || seq < 1 || heads < 1 || width < 1) return IL_E_ARG;
-  if (dtype != IL_F32 && dtype != IL_BF16) return IL_E_ARG;
-  if (d_o && (!dqkv || !dsum)) return IL_E_ARG;
-  const long long N = (long long)batch * seq, rows = N * (d_o ? streams : 1);
-  if (!head_width_ok(dtype, width) || (long long)heads * width > 2048 || (long long)batch * heads > 65535 || N > (1 << 24) ||
-      (d_o && (streams < 1 || streams > kMaxStreams)) || rows * 3 * heads * width * (dtype == IL_F32 ? 4 : 2) >= 0x7FFFFFFFll)
-    return IL_E_SHAPE;
+  if (!qkv || !o || !lse || (d_o && (!dqkv || !dsum))) return IL_E_ARG;
+  if (const int rc = attention_extents(dtype, width, batch, seq, heads, streams, d_o != nullptr)) return rc;
   hipStream_t s = (hipStream_t)stream;
   IL_TRY(attention_forward(dtype, qkv, batch, seq, heads, width, o, lse, s));
   if (d_o) IL_TRY(attention_backward(dtype, qkv, o, d_o, lse, streams, batch, seq, heads, width, dqkv, dsum, s));

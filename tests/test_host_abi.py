@@ -235,3 +235,22 @@ def test_gemm_tiles_are_dealt_once_and_to_the_xcd_that_has_their_operands(edge):
     for bad in [(0, 1, 64, 64, 0), (2, 2, 64, 64, 4), (2, 2, 64, 64, -1), (2, 2, 0, 64, 0)]:
         with pytest.raises(binding.InterlockError):
             binding.il_gemm_tile_of(*bad)
+
+
+def test_attention_forms():
+    """Which attention kernels small grids take, on both sides of lines where the other form was timed as the faster one."""
+    F32, BF16 = binding.IL_F32, binding.IL_BF16
+    form = binding.il_attention_form
+    for dtype, width, batch, seq, heads, streams, want in [
+            # fp32 products: short rows in more than two rounds of workgroups
+            (F32, 128, 16, 128, 4, 0, 4), (F32, 128, 18, 128, 4, 0, 0), (F32, 128, 18, 128, 4, 1, 0), (F32, 64, 16, 128, 4, 1, 4),
+            (F32, 64, 18, 128, 4, 1, 0), (F32, 64, 6, 128, 4, 3, 0), (F32, 32, 18, 128, 4, 2, 0), (BF16, 16, 18, 128, 4, 1, 0),
+            (F32, 64, 9, 256, 4, 0, 4), (F32, 128, 10, 256, 4, 0, 0), (F32, 64, 8, 256, 4, 1, 4), (F32, 64, 9, 256, 4, 1, 0),
+            (F32, 128, 21, 96, 2, 1, 4), (F32, 128, 37, 96, 2, 1, 0), (F32, 128, 37, 96, 2, 0, 4), (F32, 64, 10, 200, 4, 1, 4),
+            # tiles of 64 rows by number, and long rows of narrow heads
+            (F32, 128, 2, 1024, 5, 0, 4), (F32, 128, 2, 1024, 6, 0, 0), (F32, 16, 1, 511, 2, 1, 4), (F32, 16, 1, 512, 2, 1, 8),
+            (F32, 64, 8, 64, 8, 0, 4), (F32, 64, 8, 64, 9, 0, 0)]:
+        assert form(dtype, width, batch, seq, heads, streams) == want, (dtype, width, batch, seq, heads, streams)
+    for bad in [(7, 64, 1, 64, 1, 0), (F32, 64, 0, 64, 1, 0), (F32, 256, 1, 64, 1, 0), (BF16, 64, 1, 64, 1, 17), (BF16, 64, 1, 64, 1, -1)]:
+        with pytest.raises(binding.InterlockError):
+            form(*bad)
