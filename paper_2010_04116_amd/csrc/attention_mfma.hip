@@ -1114,7 +1114,10 @@ __global__ __launch_bounds__(64 * W) void attn_bwd_split(const bf16_t *__restric
 //   backward 64  1 x 576, 2 (72) 18.4 / 9.9;  4 x 96, 8 (192) 6.9 / 5.0;  2 x 400, 8 (416) 15.4 / 10.7;  2 x 256, 14 (448) 11.4 / 11.2;
 //                2 x 128, 12, two streams (384) 8.0 / 8.4;  2 x 640, 5, two (800) 20.9 / 25.0;  4 x 64, 9, two (288) 5.1 / 7.5
 //   backward 128 1 x 672, 6 (252) 25.3 / 17.9;  2 x 256, 8 (256) 13.8 / 9.5;  2 x 1024, 4 (512) 35.1 / 27.4;  4 x 128, 8, two (512) 10.4 / 13.0;
-//                8 x 40, 4, two (256) 6.0 / 7.2
+//                8 x 40, 4, two (256) 6.0 / 7.2;  beyond one round only where the XCDs get the same mix of lengths (causal_tile(): heads of all
+//                batches a multiple of eight) or rows are long: 1 x 512, 16 (512) 20.4 / 18.3, but 12 (384) 20.5 / 24.2, 5, three (480)
+//                21.1 / 25.3, 5, two (320) 20.3 / 19.0;  1 x 576, 11 (396) 23.3 / 21.7, 14 (504) 23.8 / 25.7;  1 x 1024, 8 (512) 34.0 / 25.6,
+//                2, four (512) 34.1 / 39.4;  1 x 2048, 4 (512) 65.8 / 59.9
 //   backward 256 1 x 928, 2 (174) 98 / 45;  1 x 64, 1 (6) 12.2 / 7.1;  16 x 128, 2 (384) 24.3 / 15.0;  8 x 128, 3, two (576) 25.1 / 20.4;
 //                8 x 104, 4, two (768) 25.0 / 24.2;  4 x 928, 4 (1392) 102 / 118;  16 x 64, 2, two (384) 13.7 / 13.4;
 //                8 x 65, 4, three (864) 20.2 / 25.7
@@ -1127,7 +1130,8 @@ bool fwd_splits(int dh, long heads, int T) {
 bool bwd_splits(int dh, long heads, int ns, int T) {
   const long workgroups = (T + 31) / 32 * heads * ns * split_roles(dh);
   if (dh == 256) return workgroups <= (T > 96 ? 640 : 256);
-  return T > 64 && workgroups <= (dh == 64 ? (T >= 256 ? 448 : 256) : (T >= 512 ? 512 : 256));
+  const int most = dh == 64 ? (T >= 256 ? 448 : 256) : T < 512 ? 256 : heads % 8 == 0 || T > 1024 ? 512 : T > 512 ? 400 : 288;
+  return T > 64 && workgroups <= most;
 }
 
 // A workgroup of four wavefronts takes 128 queries; where that leaves CUs without a workgroup, two wavefronts take

@@ -249,7 +249,11 @@ def test_attention_forms():
             (F32, 128, 21, 96, 2, 1, 4), (F32, 128, 37, 96, 2, 1, 0), (F32, 128, 37, 96, 2, 0, 4), (F32, 64, 10, 200, 4, 1, 4),
             # tiles of 64 rows by number, and long rows of narrow heads
             (F32, 128, 2, 1024, 5, 0, 4), (F32, 128, 2, 1024, 6, 0, 0), (F32, 16, 1, 511, 2, 1, 4), (F32, 16, 1, 512, 2, 1, 8),
-            (F32, 64, 8, 64, 8, 0, 4), (F32, 64, 8, 64, 9, 0, 0)]:
+            (F32, 64, 8, 64, 8, 0, 4), (F32, 64, 8, 64, 9, 0, 0),
+            # bf16 products at width 128: more than one round of workgroups that differ in length
+            (BF16, 128, 1, 512, 16, 1, 4), (BF16, 128, 1, 512, 12, 1, 0), (BF16, 128, 1, 512, 5, 3, 0), (BF16, 128, 1, 512, 4, 4, 0),
+            (BF16, 128, 1, 512, 9, 1, 4), (BF16, 128, 1, 576, 11, 1, 4), (BF16, 128, 1, 576, 14, 1, 0), (BF16, 128, 1, 1024, 8, 1, 4),
+            (BF16, 128, 1, 1024, 2, 4, 0), (BF16, 128, 1, 2048, 4, 1, 4), (BF16, 128, 1, 2048, 5, 1, 0), (BF16, 128, 2, 400, 8, 1, 0)]:
         assert form(dtype, width, batch, seq, heads, streams) == want, (dtype, width, batch, seq, heads, streams)
     for bad in [(7, 64, 1, 64, 1, 0), (F32, 64, 0, 64, 1, 0), (F32, 256, 1, 64, 1, 0), (BF16, 64, 1, 64, 1, 17), (BF16, 64, 1, 64, 1, -1)]:
         with pytest.raises(binding.InterlockError):
