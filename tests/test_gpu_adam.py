@@ -68,7 +68,8 @@ def test_bf16_parity(count):
 
 # where buffers of 18 (fp32 mode: 16) bytes a parameter start to go past the Infinity Cache: the last and the first size,
 # a whole number of workgroups and a ragged tail
-@pytest.mark.parametrize("dtype,count", [("bf16", 19_444_444), ("bf16", 19_444_447), ("f32", 21_876_736), ("f32", 21_875_003)])
+@pytest.mark.parametrize("dtype,count", [("bf16", 19_444_444), ("bf16", 19_444_447), ("f32", 21_875_000),
+                                         ("f32", 21_876_736), ("f32", 21_875_003)])
 def test_parity_about_the_size_of_the_cache(dtype, count):
     print("case adam", dtype, "count", count, flush=True)
     got, ref = run_steps(dtype, count, 1, seed=7)
