@@ -196,10 +196,28 @@ def test_bf16_products(dh, T, H):
     (128, 1, 65, 2, 2), (128, 2, 97, 16, 1), (128, 16, 257, 1, 1), (128, 1, 512, 16, 1), (128, 2, 1023, 4, 1),
     (256, 1, 2, 1, 1), (256, 1, 33, 2, 3), (256, 32, 64, 2, 1), (256, 33, 64, 2, 1), (256, 20, 64, 2, 1), (256, 1, 96, 8, 3), (256, 5, 128, 8, 1), (256, 7, 128, 8, 1), (256, 1, 512, 7, 2)])
 def test_bf16_products_split_over_wavefronts(dh, B, T, H, ns):
-    """Both sides of every line from which a row's keys are divided up, several streams; the bounds of the test above."""
+    """About the lines from which a row's keys are divided up, several streams; the bounds of the test above."""
+    print("case split", dh, B, T, H, ns, flush=True)
+    bf16_against_float64(dh, B, T, H, ns)
+
+
+# ragged lengths in grids that are large enough: the forward by four (0) and by two (-1) wavefronts, the backward (0) and
+# its pairs of streams (-2); beside the line for width 128 also the split forward (4) with a shared backward
+@pytest.mark.parametrize("dh,B,T,H,ns,forward,backward", [
+    (64, 9, 200, 12, 1, -1, 0), (64, 40, 33, 8, 1, 0, 0), (64, 3, 600, 13, 1, 0, 0), (64, 40, 129, 8, 2, 0, -2),
+    (128, 9, 100, 8, 1, 0, 0), (128, 5, 257, 8, 2, 0, 0), (128, 9, 33, 8, 3, 0, 0), (128, 3, 1000, 6, 1, 0, 0), (128, 1, 600, 14, 1, 0, 0),
+    (128, 1, 513, 5, 3, 4, 0),
+    (256, 9, 97, 8, 1, -1, 0), (256, 9, 257, 4, 2, 0, 0), (256, 17, 513, 2, 1, 0, 0), (256, 70, 31, 4, 3, 0, 0), (256, 40, 130, 8, 1, 0, 0)])
+def test_bf16_products_with_shared_tiles(dh, B, T, H, ns, forward, backward):
+    """What larger grids take, at lengths that no tile divides; the bounds of the tests above."""
+    print("case shared", dh, B, T, H, ns, flush=True)
+    assert (b.il_attention_form(b.IL_BF16, dh, B, T, H), b.il_attention_form(b.IL_BF16, dh, B, T, H, ns)) == (forward, backward)
+    bf16_against_float64(dh, B, T, H, ns)
+
+
+def bf16_against_float64(dh, B, T, H, ns):
     import torch
     dev, d, N = torch.device("cuda:0"), H * dh, B * T
-    print("case split", dh, B, T, H, ns, flush=True)
     gen = torch.Generator(device=dev).manual_seed(dh + T)
     qkv = torch.randn(N, 3 * d, generator=gen, device=dev).to(torch.bfloat16)
     g = torch.randn(ns * N, d, generator=gen, device=dev).to(torch.bfloat16)
@@ -232,6 +250,35 @@ def test_bf16_products_split_over_wavefronts(dh, B, T, H, ns):
         want = (dS @ k.double(), dS.transpose(2, 3).contiguous() @ q.double(), P.transpose(2, 3).contiguous() @ go)
         for i in range(3):
             near(out[s * N:(s + 1) * N, i * d:(i + 1) * d], rows(want[i]), 2 ** -7, (s, "QKV"[i]))
+
+
+@pytest.mark.parametrize("dh", [64, 128, 256])
+@pytest.mark.parametrize("part,value", [("q", np.nan), ("k", np.nan), ("v", np.nan), ("v", np.inf), ("g", np.nan), ("g", -np.inf)])
+def test_what_is_not_finite_where_bf16_products_are_split(dh, part, value):
+    """It reaches the rows that see it.  Rows of other 32-row blocks that do not are as they were; in its own block a
+    masked weight of zero meets it in a product, so nothing is asked of the rows there that do not see it."""
+    B, T, H, token = 1, 200, 2, 70
+    lo, hi = token // 32 * 32, token // 32 * 32 + 32
+    qkv, g = draw(dh, B, T, H, dh)
+    d = H * dh
+    clean = run("bf16", qkv, g, B, T, H, dh)
+    if part == "g":
+        g[token, 3] = value
+    else:
+        qkv[token, {"q": 0, "k": d, "v": 2 * d}[part] + 3] = value
+    print("case bf16 not finite", dh, part, value, flush=True)
+    form = b.il_attention_form(b.IL_BF16, dh, B, T, H)
+    assert form == b.il_attention_form(b.IL_BF16, dh, B, T, H, 1) == (2 if dh == 256 else 4)
+    o, dqkv = run("bf16", qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh)
+    rows = np.arange(T)
+    by_query, by_key = (rows < lo) | (rows >= token), (rows <= token) | (rows >= hi)
+    for got, want, was, asked, what in [(o, wo, clean[0], by_query, "o"), (dqkv[:, :d], wd[:, :d], clean[1][:, :d], by_query, "dq"),
+                                        (dqkv[:, d:2 * d], wd[:, d:2 * d], clean[1][:, d:2 * d], by_key, "dk"),
+                                        (dqkv[:, 2 * d:], wd[:, 2 * d:], clean[1][:, 2 * d:], by_key, "dv")]:
+        assert np.array_equal(np.isfinite(got)[asked], np.isfinite(want)[asked]), what
+        same = asked & ((rows < token) if what in ("o", "dq") else (rows > token))   # never meets the token
+        assert np.array_equal(got[same & np.isfinite(want).all(axis=1)], was[same & np.isfinite(want).all(axis=1)]), what
 
 
 @pytest.mark.parametrize("dh,B,T,H,ns", [
