@@ -146,6 +146,77 @@ def test_what_is_not_finite_where_tiles_are_shared(dtype, dh, part, value):
 
 
 @pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("B,T,H,ns,split", [(18, 150, 3, 2, False), (12, 72, 7, 3, False), (5, 150, 3, 3, True), (1, 520, 2, 2, True)])
+def test_streams_and_heads_in_either_form_of_the_fp32_products(dtype, dh, B, T, H, ns, split):
+    """Several heads and stacked streams, each with gradients of its own; the same bounds as above."""
+    import torch
+    dev, tt = torch.device("cuda:0"), torch.float32 if dtype == "f32" else torch.bfloat16
+    forms = b.il_attention_form(IL[dtype], dh, B, T, H), b.il_attention_form(IL[dtype], dh, B, T, H, ns)
+    wide = 8 if dh <= 32 and T >= 512 else 4
+    assert forms == ((wide, wide) if split else (0, 0)), forms
+    d, N = H * dh, B * T
+    qkv, _ = draw(B + T, B, T, H, dh)
+    g = np.concatenate([draw(B + T + s, B, T, H, dh)[1] for s in range(1, ns + 1)])
+    print("case streams", dtype, dh, B, T, H, ns, flush=True)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(tt).to(dev)  # noqa: E731
+    o, lse = torch.full((N, d), 7.0, dtype=tt, device=dev), torch.full((B, H, T), 7.0, device=dev)
+    out = torch.full((ns * N, 3 * d), 7.0, dtype=tt, device=dev)
+    b.il_test_attention(IL[dtype], to(qkv), B, T, H, dh, o, lse, to(g), ns, out, torch.zeros(ns * N * max(H, (d + 31) // 32), device=dev),
+                        stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    o, out = o.float().cpu().numpy(), out.float().cpu().numpy()
+    for s in range(ns):
+        wo, wd = reference(qkv, g[s * N:(s + 1) * N], B, T, H, dh, stored_o=o)
+        held(out[s * N:(s + 1) * N], wd, dtype, f"dqkv of stream {s}")
+    held(o, wo, dtype, "o")
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("B,T,H,at,token", [(27, 90, 3, 20, 31), (1, 520, 2, 0, 131), (1, 520, 2, 0, 519)])
+@pytest.mark.parametrize("part,value", [("q", np.nan), ("k", np.nan), ("v", np.inf), ("g", -np.inf)])
+def test_what_is_not_finite_with_several_heads_and_long_rows(dtype, dh, B, T, H, at, token, part, value):
+    """Tiles shared between the heads of a token, and rows that narrow heads divide over eight wavefronts."""
+    want_form = 0 if B > 1 else 8 if dh <= 32 else 4
+    assert b.il_attention_form(IL[dtype], dh, B, T, H) == b.il_attention_form(IL[dtype], dh, B, T, H, 1) == want_form
+    qkv, g = draw(T, B, T, H, dh)
+    d, row = H * dh, at * T + token
+    if part == "g":
+        g[row, dh + 3] = value
+    else:
+        qkv[row, {"q": 0, "k": d, "v": 2 * d}[part] + dh + 3] = value
+    print("case", dtype, dh, B, T, H, token, part, value, flush=True)
+    o, dqkv = run(dtype, qkv, g, B, T, H, dh)
+    wo, wd = reference(qkv, g, B, T, H, dh)
+    held(o, wo, dtype, "o")
+    assert np.array_equal(np.isfinite(dqkv), np.isfinite(wd))
+    if dtype == "f32":
+        held(np.where(np.isfinite(dqkv), dqkv, 0), np.where(np.isfinite(wd), wd, 0), dtype, "dqkv")
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
+@pytest.mark.parametrize("B,T,H", [(27, 90, 3), (1, 520, 2)])
+@pytest.mark.parametrize("low", [-1e31, -1e37, -np.inf])
+def test_scores_below_any_mask_value_with_several_heads_and_long_rows(dtype, dh, B, T, H, low):
+    """As test_scores_below_any_mask_value, with shared tiles and over eight wavefronts."""
+    qkv, g = draw(3, B, T, H, dh)
+    x = qkv.reshape(B, T, 3, H, dh)
+    x[:, :, 0] = 0
+    x[:, :, 0, :, 0] = 1e19
+    x[:, :, 1] = 0
+    if np.isinf(low):
+        x[:, 1::2, 1, :, 0] = -3e38
+    else:
+        x[:, :, 1, :, 0] = low * dh ** 0.5 / 1e19
+    t = np.arange(T)
+    x[:, :, 2] = (t % 128)[None, :, None, None]          # (whole numbers that bf16 holds)
+    print("case", dtype, dh, B, T, H, low, flush=True)
+    o, _ = run(dtype, bf16(qkv), g, B, T, H, dh)
+    seen = t % 2 == 0 if np.isinf(low) else t >= 0
+    want = np.cumsum(t % 128 * seen) / np.cumsum(seen)
+    held(o, np.tile(want[:, None], (B, H * dh)), dtype, "o")
+
+
+@pytest.mark.parametrize("dtype,dh", FP32_PRODUCTS)
 @pytest.mark.parametrize("low", [-1e31, -1e37, -np.inf])
 def test_scores_below_any_mask_value(dtype, dh, low):
     """The first tokens' scores are all equal and lie far below -1e30; a later block's are -inf for every other key.
