@@ -52,7 +52,7 @@ __device__ inline void store4(float *p, size_t i, const float4 &x) {
 // 4.0-4.9 TB/s from 42 M parameters on.  NT: the accesses pass the Infinity Cache by, which then keeps no
 // lines that the pass would evict before they are used again, and does not write them back in their own order.
 // us per pass with the bf16 image (42 M, 128 M, 437 M, 2.43 G parameters): strided 268, 958, 2773, 15068; window 245,
-// 731, 2473, 13860; NT in workgroups of 256 226, 657, 2387, 13707, of 1024 203, 614, 2349, 13315 (6.4 TB/s at 128 M).
+// 731, 2473, 13860; NT in workgroups of 256 226, 657, 2387, 13707, of 1024 203, 614, 2349, 13315 (6.3 TB/s at 128 M).
 template <bool BF, bool NT, int T>
 __global__ __launch_bounds__(T) void adam_step_kernel(float *__restrict__ w, bf16_t *__restrict__ p,
                                                       const float *__restrict__ g, float *__restrict__ m,

@@ -1103,8 +1103,9 @@ __global__ __launch_bounds__(64 * W) void attn_bwd_split(const bf16_t *__restric
 
 }  // namespace
 
-// Where the other axis is divided up.  The split forms' workgroups are short, but every wavefront loads its own blocks and holds 16 KB
-// (width 64) to 64 KB (256) of LDS, so they gain while one round holds them all, and a little beyond where rows are
+// Where the other axis is divided up.  The split forms' workgroups are short, but every wavefront loads its own blocks, and a CU holds few of
+// them: one at widths 128 and 256, whose wavefronts have 32 and 64 KB of LDS each; at width 64 (16 KB) two of the forward but one of
+// the backward, by its 276 registers.  So they gain while one round holds them all, and a little beyond where rows are
 // long; up to 64 tokens there is no chain to cut (at 256 there is: its shared tiles hold 32 keys).  In us, shared / split (workgroups of the split form):
 //   forward 64   1 x 576 tokens, 2 heads (36) 11.4 / 7.1;  1 x 1000, 3 (96) 18.2 / 9.7;  2 x 400, 8 (208) 9.7 / 6.5;  8 x 256, 8 (512)
 //                7.3 / 6.0;  8 x 200, 12 (672) 7.1 / 9.5;  32 x 64, 6 (384) 4.4 / 5.3

@@ -58,7 +58,7 @@ template <> __device__ inline void st<bf16_t>(bf16_t *p, float v) { *p = f32_to_
 //   gelu(u)  = u s,      gelu'(u) = s + s (1 - s) * 2 sqrt(2/pi) u (1 + 3 * 0.044715 u^2).
 // exp and the reciprocal are the hardware instructions (relative error ~1e-6, far inside the fp32
 // tolerance; both ends saturate correctly: s -> 0 or 1).  These sit in the epilogue of every MLP GEMM,
-// where the two wavefronts of a SIMD share one vector ALU: the derivative costs seven plain and
+// where the two wavefronts of a SIMD share one vector ALU: the derivative costs eight plain and
 // two transcendental instructions per element in this form.
 __device__ inline float gelu_sigmoid(float u, float u2) {
   // exp(-2y) as a power of two: -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
@@ -146,8 +146,8 @@ const KernelTimer *gemm_time_next(const KernelTimer *t);
 
 hipError_t gemm_f32(const GemmArgs &g, hipStream_t s);    // T = float, MFMA in fp32
 hipError_t gemm_bf16(const GemmArgs &g, hipStream_t s);   // T = bf16, MFMA
-// Up to kMaxBatch independent GEMMs with the same operand layouts and epilogue in ONE launch
-// (their tiles share the grid, so small problems fill the chip together).
+// Up to kMaxBatch independent weight gradients in ONE launch (their tiles share the grid, so small problems fill the
+// chip together); of the other layouts one problem.
 constexpr int kMaxBatch = 8;
 hipError_t gemm_f32_batch(const GemmArgs *list, int count, hipStream_t s);
 hipError_t gemm_bf16_batch(const GemmArgs *list, int count, hipStream_t s);
