@@ -33,10 +33,10 @@ PEAK_HBM_GBS = 8000.0
 # profiles/traffic_<workload>.md.  bench.py cannot run the profiler on itself, so the figures are
 # carried here for the workloads they were measured on and are null for any other.
 MEASURED_TRAFFIC = {
-    "small_bf16_n2": 37.89e6,   # 27.66 MB read + 10.23 MB written per launch, 1104 launches (1.58 x algorithmic)
-    "large_bf16_n2": 463.60e6,  # 365.51 + 98.10 MB, 4104 launches (1.95 x)
-    "medium_bf16_n2": 173.07e6,  # 131.17 + 41.90 MB, 2736 launches (1.70 x)
-    "many_head_bf16_n3": 209.33e6,  # 157.91 + 51.43 MB, 3072 launches (1.65 x)
+    "small_bf16_n2": 37.88e6,   # 27.65 MB read + 10.23 MB written per launch, 1104 launches (1.58 x algorithmic)
+    "large_bf16_n2": 464.26e6,  # 366.17 + 98.10 MB, 4104 launches (1.96 x)
+    "medium_bf16_n2": 172.99e6,  # 131.09 + 41.90 MB, 2736 launches (1.70 x)
+    "many_head_bf16_n3": 209.42e6,  # 157.99 + 51.44 MB, 3072 launches (1.65 x)
 }
 
 # which roofline bounds a kernel class, and the peak its fraction is taken against
