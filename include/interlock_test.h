@@ -72,10 +72,10 @@ int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws
 
 /*
  * Host function: the output tile (*tile_m, *tile_n) that a GEMM launch of tiles_m x tiles_n tiles of edge_m x edge_n
- * (K in one part) gives its workgroup number `workgroup`.
+ * over K (in one part) gives its workgroup number `workgroup`.
  */
-int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t edge_n, int32_t workgroup, int32_t *tile_m,
-                    int32_t *tile_n);
+int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t edge_n, int32_t K, int32_t workgroup,
+                    int32_t *tile_m, int32_t *tile_n);
 
 /*
  * Kernel-level test hook: the library's causal attention by itself.

@@ -72,7 +72,7 @@ def load():
     lib.il_test_attention.argtypes = [i32, vp, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp]
     lib.il_test_gemm_splitk.argtypes = [i32, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
     lib.il_attention_form.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32)]
-    lib.il_gemm_tile_of.argtypes = [i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
+    lib.il_gemm_tile_of.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     lib.il_gemm_split_plan.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.il_attention_wants_dsum.argtypes = [i32, i32]
     lib.il_test_layernorm.argtypes = [i32, vp, vp, vp, C.c_float, i32, i32, vp, vp, vp, vp]
@@ -202,10 +202,10 @@ def il_gemm_split_plan(dtype, M, N, K, ws_floats):
     return parts, tile.value
 
 
-def il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, workgroup):
+def il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, K, workgroup):
     """(row, column) of the output tile that a GEMM launch gives this workgroup."""
     m, n = C.c_int32(), C.c_int32()
-    _check(load().il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, workgroup, C.byref(m), C.byref(n)), "il_gemm_tile_of")
+    _check(load().il_gemm_tile_of(tiles_m, tiles_n, edge_m, edge_n, K, workgroup, C.byref(m), C.byref(n)), "il_gemm_tile_of")
     return m.value, n.value
 
 

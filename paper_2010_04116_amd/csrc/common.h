@@ -103,6 +103,8 @@ enum Epi {
 };
 constexpr int kStatGroup = 64;  // columns per statistics group of EPI_LOGITS
 
+constexpr int kInTurn = -1;
+
 struct GemmArgs {
   // C[M,N] = sum_k A(m,k) B(k,n); operand storage:
   //   a_kmajor == 0: A stored [M, K] row-major (lda);  1: A stored [K, M] row-major (lda)
@@ -123,8 +125,7 @@ struct GemmArgs {
   float scale;        // EPI_WGRAD
   uint32_t a_bytes, b_bytes;  // operand extents in bytes (filled by the front ends)
   int splits, k_per;  // split-K: part i of `splits` sums k in [i k_per, (i + 1) k_per) into C + i M N (fp32 outputs
-                      // with ldc = N); 0 = one part
-  int in_turn;        // tiles in launch order (filled by the launch, see tiles_in_turn())
+                      // with ldc = N); 0 = one part; kInTurn (set by the launch, see tiles_in_turn()): one, tiles in launch order
   int tile;           // 0 = choose by shape; fp32: 2 = 128x128, 3 = 128x64, 4 = 64x64; bf16: 1 = 256x256, 2 / 3 = 128x128 with 2 / 4 stages, 4 / 5 = 64x64 with 2 / 4,
                       // 6 = 256x128, 7 = 128x256 (three stages), 8 = 1
   int beta;           // EPI_WGRAD: accumulate into C

@@ -48,9 +48,8 @@ __host__ __device__ inline TilePlace tile_place(int at, int tiles_m, int tiles_n
 // The place in that order of the workgroup `local` of `total`.  Workgroups land on XCD `local` mod 8.  in_turn: in launch
 // order; otherwise XCD x gets as many consecutive places as it has workgroups, also where eight does not divide the count.
 __host__ __device__ inline int tile_turn(int local, int total, bool in_turn) {
-  if (in_turn) return local;
-  const int xcd = local & 7, rest = total & 7;
-  return xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (local >> 3);
+  const int xcd = local & 7, rest = total & 7, run = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (local >> 3);
+  return in_turn ? local : run;
 }
 // Which of the two, where eight does not divide the number of tiles: the one for which the XCDs' L2s fetch fewer operand
 // rows and columns.  In launch order XCD x has every eighth row of tiles and all columns; with consecutive places it has
@@ -59,14 +58,15 @@ __host__ __device__ inline int tile_turn(int local, int total, bool in_turn) {
 // 46.0 and 54.1, 2136 x 280 x 1872 9.2 and 11.5; but 272 x 1184 x 2968 17.6 and 11.4, 832 x 1960 x 1920 21.4 and 16.8, 832 x 31992 x 768
 // 79.6 and 71.9, 1600 x 2304 x 768 13.5 and 12.2, 3984 x 184 x 2568 (each XCD one group) 15.3 and 11.5.  Of 890 products whose tiles
 // eight does not divide, consecutive places alone took up to 31 % longer than launch order; by this count the worst takes 15 %.
-// (Counts that eight divides and parts along K: consecutive, which was within 5 % of the other everywhere.)
-inline bool tiles_in_turn(const TileGrid &t, int splits) {
+// Consecutive stay parts along K, which were within 5 % of launch order everywhere, sums of less than 1024, for which the two are
+// as fast (70 such products: median 0.995, 5 % either way), and what a twentieth of the operands would decide.
+inline bool tiles_in_turn(const TileGrid &t, int K, int splits) {
   const int total = t.m * t.n;
-  if (splits > 1 || (total & 7) == 0) return false;
+  if (splits > 1 || K < 1024 || t.m < 9 || (total & 7) == 0) return false;
   const int groups = t.m >> 3, left = t.m & 7, of_left = (left * t.n + 7) / 8;
   // rows of the last, incomplete group that every eighth of its tiles meets, no more than these are
   const int left_rows = std::min(left == 0 ? 0 : left == 4 ? 1 : (left & 1) ? left : left / 2, of_left);
-  const long turn = 8l * ((groups + left_rows) * t.bm + (groups ? t.n : std::min(t.n, of_left)) * t.bn);
+  const long turn = 8l * ((groups + left_rows) * t.bm + t.n * t.bn);
   long run = 0;
   for (int x = 0, at = 0; x < 8; ++x) {
     const int end = at + (total >> 3) + (x < (total & 7));
@@ -79,7 +79,7 @@ inline bool tiles_in_turn(const TileGrid &t, int splits) {
     run += rows * t.bm + cols * t.bn;
     at = end;
   }
-  return turn < run;
+  return turn + turn / 20 < run;
 }
 
 // go(the launch's problems, its workgroups); grid(p): the tiles of problem p.
@@ -88,7 +88,7 @@ hipError_t with_problems(const GemmArgs *list, int count, T &&grid, F &&go) {
   auto take = [&](GemmArgs &p, const GemmArgs &from) {
     p = from;
     const TileGrid t = grid(from);
-    p.in_turn = tiles_in_turn(t, from.splits);
+    if (tiles_in_turn(t, from.K, from.splits)) p.splits = kInTurn;
     return t.m * t.n * std::max(from.splits, 1);
   };
   if (count == 1) {
@@ -113,7 +113,7 @@ hipError_t with_problems(const GemmArgs *list, int count, T &&grid, F &&go) {
 struct MyTile { int m, n, k0, k1; };
 __device__ inline MyTile my_tile(GemmArgs &g, int local, int tiles_m, int tiles_n) {
   const int tiles = tiles_m * tiles_n, splits = g.splits > 1 ? g.splits : 1;
-  local = tile_turn(local, tiles * splits, g.in_turn);
+  local = tile_turn(local, tiles * splits, g.splits == kInTurn);
   MyTile t{0, 0, 0, g.K};
   if (splits > 1) {
     const int part = local / tiles;

@@ -1200,11 +1200,11 @@ int il_gemm_split_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, size_t ws
   return p.splits;
 }
 
-int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t edge_n, int32_t workgroup, int32_t *tile_m,
-                    int32_t *tile_n) {
-  if (tiles_m < 1 || tiles_n < 1 || edge_m < 1 || edge_n < 1 || !tile_m || !tile_n) return IL_E_ARG;
+int il_gemm_tile_of(int32_t tiles_m, int32_t tiles_n, int32_t edge_m, int32_t edge_n, int32_t K, int32_t workgroup,
+                    int32_t *tile_m, int32_t *tile_n) {
+  if (tiles_m < 1 || tiles_n < 1 || edge_m < 1 || edge_n < 1 || K < 1 || !tile_m || !tile_n) return IL_E_ARG;
   if ((long long)tiles_m * tiles_n > 0x7FFFFFFF || workgroup < 0 || workgroup >= tiles_m * tiles_n) return IL_E_ARG;
-  const bool in_turn = tiles_in_turn({tiles_m, tiles_n, edge_m, edge_n}, 1);
+  const bool in_turn = tiles_in_turn({tiles_m, tiles_n, edge_m, edge_n}, K, 1);
   const TilePlace at = tile_place(tile_turn(workgroup, tiles_m * tiles_n, in_turn), tiles_m, tiles_n);
   *tile_m = at.m;
   *tile_n = at.n;

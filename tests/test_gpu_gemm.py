@@ -124,9 +124,9 @@ def test_tall_outputs_whose_tiles_eight_does_not_divide(M, N, tile):
     """Their tiles are dealt in launch order: every one is taken once."""
     edge = {1: (256, 256), 3: (128, 128), 4: (64, 64), 5: (64, 64), 6: (256, 128), 7: (128, 256)}[tile]
     tm, tn = -(-M // edge[0]), -(-N // edge[1])
-    assert tm * tn % 8 and b.il_gemm_tile_of(tm, tn, *edge, 9) == (1, 1)
-    run_case(M, N, 64, 0, 1, 1, tile, seed=60)
-    run_case(M, N, 64, 1, 1, 6, tile, seed=61, beta=1)
+    assert tm * tn % 8 and b.il_gemm_tile_of(tm, tn, *edge, 1024, 9) == (1, 1)
+    run_case(M, N, 1024, 0, 1, 1, tile, seed=60)
+    run_case(M, N, 1024, 1, 1, 6, tile, seed=61, beta=1)
 
 
 def test_library_choice_at_the_benchmark_shapes():

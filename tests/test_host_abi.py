@@ -203,8 +203,8 @@ def test_fp32_parts_are_priced_as_the_tiles_are():
 @pytest.mark.parametrize("edge", [(64, 64), (128, 128), (256, 128), (128, 256), (256, 256)])
 def test_gemm_tiles_are_dealt_once_and_to_the_xcd_that_has_their_operands(edge):
     """Every tile goes to one workgroup, and where eight does not divide their number the XCDs (workgroup mod 8) fetch no
-    more operand rows and columns than in launch order or in consecutive places, whichever fetches fewer (a twentieth more
-    at most, the library counts parts of a group of rows, not tiles)."""
+    more operand rows and columns than in launch order or in consecutive places, whichever fetches fewer (a tenth more
+    at most: the library counts parts of a group of rows, not tiles, and takes launch order for more than a twentieth)."""
     def fetched(place, total):
         rows, cols = [set() for _ in range(8)], [set() for _ in range(8)]
         for w in range(total):
@@ -225,14 +225,15 @@ def test_gemm_tiles_are_dealt_once_and_to_the_xcd_that_has_their_operands(edge):
         def consecutive(w):
             return at(w % 8 * (total // 8) + min(w % 8, total % 8) + w // 8)
 
-        got = [binding.il_gemm_tile_of(tm, tn, *edge, w) for w in range(total)]
+        got = [binding.il_gemm_tile_of(tm, tn, *edge, 4096, w) for w in range(total)]
         assert sorted(got) == [(m, n) for m in range(tm) for n in range(tn)], (tm, tn)
+        assert [binding.il_gemm_tile_of(tm, tn, *edge, 1016, w) for w in range(total)] == [consecutive(w) for w in range(total)]
         if total % 8 == 0:
             assert got == [consecutive(w) for w in range(total)], (tm, tn)
         else:
             best = min(fetched(at, total), fetched(consecutive, total))
-            assert fetched(lambda w: got[w], total) <= 1.05 * best, (tm, tn)
-    for bad in [(0, 1, 64, 64, 0), (2, 2, 64, 64, 4), (2, 2, 64, 64, -1), (2, 2, 0, 64, 0)]:
+            assert fetched(lambda w: got[w], total) <= 1.1 * best, (tm, tn)
+    for bad in [(0, 1, 64, 64, 64, 0), (2, 2, 64, 64, 64, 4), (2, 2, 64, 64, 64, -1), (2, 2, 0, 64, 64, 0), (2, 2, 64, 64, 0, 0)]:
         with pytest.raises(binding.InterlockError):
             binding.il_gemm_tile_of(*bad)
 
