@@ -59,7 +59,7 @@ __host__ __device__ inline int tile_turn(int local, int total, bool in_turn) {
 // 79.6 and 71.9, 1600 x 2304 x 768 13.5 and 12.2, 3984 x 184 x 2568 (each XCD one group) 15.3 and 11.5.  Of 890 products whose tiles
 // eight does not divide, consecutive places alone took up to 31 % longer than launch order; by this count the worst takes 15 %.
 // Consecutive stay parts along K, which were within 5 % of launch order everywhere, sums of less than 1024, for which the two are
-// as fast (70 such products: median 0.995, 5 % either way), and what a twentieth of the operands would decide.
+// as fast (70 such products: median 0.995, 5 % either way, one 10 %), and what a twentieth of the operands would decide.
 inline bool tiles_in_turn(const TileGrid &t, int K, int splits) {
   const int total = t.m * t.n;
   if (splits > 1 || K < 1024 || t.m < 9 || (total & 7) == 0) return false;
